@@ -2,15 +2,22 @@
 // reductions such as a sum along one axis; end of Section 5) and the row softmax built from it.
 //
 // Both operations are memory bound: a row is read once and (softmax) written once.  The schedule is a
-// task mapping in the sense of Section 5.1 over the [rows, 16-byte chunks] grid of the input:
+// task mapping in the sense of Section 5.1 over the [rows, 16-byte chunks] grid of the input; as long as
+// a row fits, it sits in registers between the passes over it (max, exp and sum, write):
 //
-//   short rows   workgroup = 4 wavefronts; wavefront = spatial(64 / L, L) over (rows, chunks) composed
-//                with repeat(1, R): L lanes share one row, lane c of the group owns chunks c, c + L, ...
-//                The whole row sits in registers, so max, exp and sum need one pass over memory;
+//   wavefront    workgroup = 4 wavefronts; wavefront = spatial(64 / L, L) over (rows, chunks) composed
+//                with repeat(1, R): L lanes share one row, lane c of the group owns chunks c, c + L, ...;
 //                lanes combine with xor butterflies (L is a power of two).
-//   long rows    workgroup = spatial(1, 256) over chunks, repeat over the row; one row per workgroup;
-//                a running (max, sum) pair per thread, merged through LDS; softmax re-reads the row
-//                (from L2 when it fits) to write the result.
+//   workgroup    workgroup = spatial(1, NT) over the chunks of one row composed with repeat(1, R): rows too
+//                long for one wavefront's registers, and long rows of which there are too few to give
+//                every compute unit several wavefronts.  The wavefronts' results meet in LDS.
+//   streamed     rows of more than 16384 chunks: one workgroup per row, a running (max, sum) pair per
+//                thread, merged through LDS; softmax re-reads the row (from L2 when it fits).
+//
+// Chunks are accessed at element alignment (16-byte loads and stores take any element-aligned address
+// here), so rows of any length and leading dimension run the same way.  The last chunk of a row whose
+// length is no multiple of a chunk is loaded from the 16 bytes that end the row; its elements that
+// belong to the chunk before are masked out.
 //
 // Arithmetic is fp32 whatever the storage type.
 #include <hip/hip_runtime.h>
@@ -29,9 +36,8 @@ struct RowParams {
   long long rows;
   int cols;
   int op;       // reduce: hidet_reduce_op_t
-  int vec_in;   // rows of x allow 16-byte loads
-  int vec_out;  // softmax: rows of y allow 16-byte stores
   int out_f32;  // reduce: y is fp32 whatever T is
+  int shift;    // softmax: rows of y are not all 16-byte aligned (see row_shift)
 };
 
 constexpr float kNegInf = -__builtin_huge_valf();
@@ -39,40 +45,95 @@ constexpr float kNegInf = -__builtin_huge_valf();
 template <typename T>
 struct Chunk {
   static constexpr int VEC = 16 / (int)sizeof(T);
+  struct __attribute__((packed, aligned(sizeof(T)))) Raw {  // 16 bytes at element alignment
+    u32x4 v;
+  };
 };
 
-// One 16-byte chunk of a row -> VEC floats; elements at or beyond `cols` read as `fill`.
+// The 16 bytes that hold the elements of chunk [col0, col0 + VEC) of a row: the chunk itself, or, where it would stick
+// out of the row at either end, the first or last 16 bytes of the row.  Always a valid address, so that the loads of all
+// of a thread's chunks can be in flight together.  Rows shorter than one chunk are collected element by element.
 template <typename T>
-__device__ __forceinline__ void load_chunk(const T* row, int col0, int cols, bool vec_ok, float fill, float* v) {
+__device__ __forceinline__ int chunk_pos(int col0, int cols) {
+  const int last = cols - Chunk<T>::VEC;
+  const int pos = col0 < last ? col0 : last;
+  return pos > 0 ? pos : 0;
+}
+template <typename T, bool RAGGED>
+__device__ __forceinline__ u32x4 load_raw(const T* row, int col0, int cols) {
   constexpr int VEC = Chunk<T>::VEC;
-  if (col0 + VEC <= cols && vec_ok) {
-    T t[VEC];
-    *reinterpret_cast<u32x4*>(t) = *reinterpret_cast<const u32x4*>(row + col0);
+  if (!RAGGED || cols >= VEC)  // the same for the whole grid
+    return reinterpret_cast<const typename Chunk<T>::Raw*>(row + chunk_pos<T>(col0, cols))->v;
+  if (cols <= 0) return u32x4{0u, 0u, 0u, 0u};  // nothing may be read
+  T t[VEC];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) v[e] = to_f32(t[e]);
-  } else {
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const bool ok = col0 + e < cols;
-      const T t = row[ok ? col0 + e : 0];  // cols > 0 whenever a chunk is loaded
-      v[e] = ok ? to_f32(t) : fill;
-    }
-  }
+  for (int e = 0; e < VEC; ++e) t[e] = row[e < cols ? e : 0];
+  return __builtin_bit_cast(u32x4, t);
+}
+
+// Elements [lo, hi) of what load_raw returned belong to chunk [col0, col0 + VEC).
+template <typename T>
+__device__ __forceinline__ void chunk_range(int col0, int cols, int& lo, int& hi) {
+  const int pos = chunk_pos<T>(col0, cols), end = col0 + Chunk<T>::VEC;
+  lo = (col0 > 0 ? col0 : 0) - pos;
+  hi = (end < cols ? end : cols) - pos;
 }
 
 template <typename T>
-__device__ __forceinline__ void store_chunk(T* row, int col0, int cols, bool vec_ok, const float* v) {
+__device__ __forceinline__ void widen_chunk(u32x4 raw, float* v) {
+  constexpr int VEC = Chunk<T>::VEC;
+  T t[VEC];
+  __builtin_memcpy(t, &raw, 16);
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) v[e] = to_f32(t[e]);
+}
+
+// RAGGED: rows that are no whole number of chunks (or lie on a shifted grid); otherwise a chunk is inside or outside.
+// `whole`: the caller knows that no lane's chunk sticks out (uniform: it costs no vector instructions).
+template <typename T, bool RAGGED>
+__device__ __forceinline__ void widen_masked(u32x4 raw, int col0, int cols, bool whole, float fill, float* v) {
+  widen_chunk<T>(raw, v);
+  if (whole) return;
+  if constexpr (RAGGED) {
+    int lo, hi;
+    chunk_range<T>(col0, cols, lo, hi);
+#pragma unroll
+    for (int e = 0; e < Chunk<T>::VEC; ++e) v[e] = (e >= lo && e < hi) ? v[e] : fill;
+  } else {
+    const bool in = col0 < cols;
+#pragma unroll
+    for (int e = 0; e < Chunk<T>::VEC; ++e) v[e] = in ? v[e] : fill;
+  }
+}
+
+// (a chunk that lies wholly outside the row stores nothing)
+template <typename T, bool RAGGED>
+__device__ __forceinline__ void store_chunk(T* row, int col0, int cols, const float* v) {
   constexpr int VEC = Chunk<T>::VEC;
   T t[VEC];
 #pragma unroll
   for (int e = 0; e < VEC; ++e) t[e] = from_f32<T>(v[e]);
-  if (col0 + VEC <= cols && vec_ok) {
-    *reinterpret_cast<u32x4*>(row + col0) = *reinterpret_cast<const u32x4*>(t);
-  } else {
+  if (col0 >= 0 && col0 + VEC <= cols) {
+    typename Chunk<T>::Raw raw;
+    __builtin_memcpy(&raw.v, t, 16);
+    *reinterpret_cast<typename Chunk<T>::Raw*>(row + col0) = raw;
+  } else if constexpr (RAGGED) {
+    int lo, hi;
+    chunk_range<T>(col0, cols, lo, hi);
+    T* dst = row + chunk_pos<T>(col0, cols);
 #pragma unroll
     for (int e = 0; e < VEC; ++e)
-      if (col0 + e < cols) row[col0 + e] = t[e];
+      if (e >= lo && e < hi) dst[e] = t[e];
   }
+}
+
+// Chunks of a very long softmax row are laid on the 16-byte grid of the output row: the first one then begins `shift`
+// elements before the row.  Loads do not mind where a chunk lies, stores do (1024 x 50257 bf16: 53.4 us with chunks on
+// the row's own grid, 47.8 us with aligned stores), but both ends of a row are then stored element by element, which on
+// shorter rows costs as much or more (4096 x 8201: 33 us either way; 1000 x 4095: 6.5 -> 9.1 us).
+template <typename T>
+__device__ __forceinline__ int row_shift(const RowParams& p, const T* yr) {
+  return p.shift ? (int)((reinterpret_cast<uintptr_t>(yr) / sizeof(T)) % Chunk<T>::VEC) : 0;
 }
 
 template <int L>
@@ -104,8 +165,8 @@ struct Tag {
   static constexpr int value = sizeof(T) == 4 ? 0 : (std::is_same<T, f16>::value ? 1 : 2);
 };
 
-// ---- short rows: the row lives in the registers of L lanes ------------------------------------------
-template <typename T, int L, int R, bool SOFTMAX>
+// ---- the row lives in the registers of L lanes of a wavefront ----------------------------------------
+template <typename T, int L, int R, bool RAGGED, bool SOFTMAX>
 __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams p) {
   constexpr int VEC = Chunk<T>::VEC;
   constexpr int G = 64 / L;  // rows per wavefront
@@ -116,17 +177,13 @@ __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams 
   const long long stride = (long long)gridDim.x * 4 * G;
   for (long long row = ((long long)blockIdx.x * 4 + wave) * G + lane / L; row < p.rows; row += stride) {
     const T* xr = reinterpret_cast<const T*>(p.x) + row * p.ldx;
+    u32x4 raw[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) raw[r] = load_raw<T, RAGGED>(xr, (r * L + sub) * VEC, p.cols);
     float v[R][VEC];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int col0 = (r * L + sub) * VEC;
-      if (col0 < p.cols) {
-        load_chunk<T>(xr, col0, p.cols, p.vec_in != 0, fill, v[r]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) v[r][e] = fill;
-      }
-    }
+    for (int r = 0; r < R; ++r)
+      widen_masked<T, RAGGED>(raw[r], (r * L + sub) * VEC, p.cols, (r + 1) * L * VEC <= p.cols, fill, v[r]);
     float m = fill;
     if (is_max) {
 #pragma unroll
@@ -153,7 +210,7 @@ __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams 
         if (col0 < p.cols) {
 #pragma unroll
           for (int e = 0; e < VEC; ++e) v[r][e] *= inv;
-          store_chunk<T>(yr, col0, p.cols, p.vec_out != 0, v[r]);
+          store_chunk<T, RAGGED>(yr, col0, p.cols, v[r]);
         }
       }
     } else {
@@ -172,7 +229,99 @@ __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams 
   }
 }
 
-// ---- long rows: one workgroup per row, streamed ------------------------------------------------------
+// ---- the row lives in the registers of a workgroup ---------------------------------------------------------
+// Every thread holds R chunks as they were loaded (four registers each) and widens them again in each pass: with the
+// widened values kept instead, half as many bytes would be in flight per register (1024 x 50257 bf16: two workgroups of
+// 1024 threads per compute unit instead of one, 60 -> 53 us).  The row is read once.  Bound by memory, with the vector
+// instructions of the two exponentials per element (about 20 lane operations) not far below it: 1024 x 50257 bf16
+// 155 us (element-wise loads, row read twice) -> 48 us = 4.3 TB/s, 1024 x 50304 60 -> 46 us, 4096 x 8200 37 -> 28 us.
+template <typename T, int NT, int R, bool RAGGED, bool SOFTMAX>
+__global__ void __launch_bounds__(NT, R <= 8 ? 8 : 4) rows_in_workgroup_kernel(const RowParams p) {
+  constexpr int VEC = Chunk<T>::VEC, NW = NT / 64;
+  __shared__ float red[2][NW];
+  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+  const bool is_max = SOFTMAX || p.op == HIDET_REDUCE_MAX;
+  const float fill = is_max ? kNegInf : 0.0f;
+  const long long row = blockIdx.x;
+  const T* xr = reinterpret_cast<const T*>(p.x) + row * p.ldx;
+  T* yr = reinterpret_cast<T*>(p.y) + row * p.ldy;  // (softmax only)
+  const int shift = SOFTMAX ? row_shift(p, yr) : 0;
+  const int cols_end = p.cols + shift;  // (chunks r * NT .. of the threads are needed if they begin before it: uniform)
+  auto col_of = [&](int r) { return (r * NT + tid) * VEC - shift; };
+  auto needed = [&](int r) { return r * NT * VEC < cols_end; };
+  auto whole = [&](int r) { return (r > 0 || shift == 0) && (r + 1) * NT * VEC <= cols_end; };
+  u32x4 raw[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    raw[r] = u32x4{0u, 0u, 0u, 0u};
+    if (needed(r)) raw[r] = load_raw<T, RAGGED>(xr, col_of(r), p.cols);
+  }
+  // the passes below must not share widened values or exponentials: what is kept in registers would double
+  auto forget = [&]() {
+#pragma unroll
+    for (int r = 0; r < R; ++r) asm volatile("" : "+v"(raw[r]));
+  };
+  float m = fill, s = 0.0f;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (needed(r)) {
+      float v[VEC];
+      widen_masked<T, RAGGED>(raw[r], col_of(r), p.cols, whole(r), fill, v);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        if (is_max)
+          m = fmaxf(m, v[e]);
+        else
+          s += v[e];
+      }
+    }
+  }
+  // a value from every wavefront, combined in wavefront order
+  auto across = [&](int slot, float x, bool max) {
+    if (lane == 0) red[slot][wave] = x;
+    __syncthreads();
+    float t = red[slot][0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) t = max ? fmaxf(t, red[slot][w]) : t + red[slot][w];
+    return t;
+  };
+  if (is_max) m = across(0, group_max<64>(m), true);
+  if constexpr (SOFTMAX) {
+    forget();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (needed(r)) {
+        float v[VEC];
+        widen_masked<T, RAGGED>(raw[r], col_of(r), p.cols, whole(r), fill, v);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) s += __expf(v[e] - m);
+      }
+    }
+    forget();
+    s = across(1, group_sum<64>(s), false);
+    const float inv = 1.0f / s;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int col0 = col_of(r);
+      if (col0 < p.cols) {
+        float v[VEC];
+        widen_chunk<T>(raw[r], v);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[e] = __expf(v[e] - m) * inv;
+        store_chunk<T, RAGGED>(yr, col0, p.cols, v);
+      }
+    }
+  } else {
+    float out = m;
+    if (!is_max) {
+      s = across(1, group_sum<64>(s), false);
+      out = p.op == HIDET_REDUCE_MEAN ? s / (float)p.cols : s;
+    }
+    if (tid == 0) write_scalar(p, row, out, Tag<T>::value);
+  }
+}
+
+// ---- very long rows: one workgroup per row, streamed ---------------------------------------------------------
 // Merge of two (max, sum-of-exp-relative-to-max) pairs; pairs with max = -inf carry sum 0.
 __device__ __forceinline__ void merge(float& m, float& s, float m2, float s2) {
   const float mm = fmaxf(m, m2);
@@ -182,37 +331,49 @@ __device__ __forceinline__ void merge(float& m, float& s, float m2, float s2) {
   s = a + b;
 }
 
-template <typename T, bool SOFTMAX>
-__global__ void __launch_bounds__(256) long_rows_kernel(const RowParams p) {
-  constexpr int VEC = Chunk<T>::VEC;
-  __shared__ float red_m[4], red_s[4];
+// U chunks of a thread are requested together.
+template <typename T, int NT, int U, bool SOFTMAX>
+__global__ void __launch_bounds__(NT) long_rows_kernel(const RowParams p) {
+  constexpr int VEC = Chunk<T>::VEC, NW = NT / 64;
+  __shared__ float red_m[NW], red_s[NW];
   const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
   const bool is_max = SOFTMAX || p.op == HIDET_REDUCE_MAX;
   const float fill = is_max ? kNegInf : 0.0f;
-  const int chunks = (p.cols + VEC - 1) / VEC;
+  const int chunks = p.cols / VEC + (p.cols % VEC != 0);
   for (long long row = blockIdx.x; row < p.rows; row += gridDim.x) {
     const T* xr = reinterpret_cast<const T*>(p.x) + row * p.ldx;
     float m = fill, s = 0.0f;
-    for (int c = tid; c < chunks; c += 256) {
-      float v[VEC];
-      load_chunk<T>(xr, c * VEC, p.cols, p.vec_in != 0, fill, v);
-      if (is_max) {
-        float cm = v[0];
+    for (int c0 = 0; c0 < chunks; c0 += U * NT) {
+      u32x4 raw[U];
 #pragma unroll
-        for (int e = 1; e < VEC; ++e) cm = fmaxf(cm, v[e]);
-        if constexpr (SOFTMAX) {
-          if (cm != kNegInf) {
-            float cs = 0.0f;
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + u * NT + tid;
+        raw[u] = load_raw<T, true>(xr, (c < chunks ? c : 0) * VEC, p.cols);
+      }
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) cs += __expf(v[e] - cm);
-            merge(m, s, cm, cs);
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + u * NT + tid;
+        if (c >= chunks) continue;
+        float v[VEC];
+        widen_masked<T, true>(raw[u], c * VEC, p.cols, false, fill, v);
+        if (is_max) {
+          float cm = v[0];
+#pragma unroll
+          for (int e = 1; e < VEC; ++e) cm = fmaxf(cm, v[e]);
+          if constexpr (SOFTMAX) {
+            if (cm != kNegInf) {
+              float cs = 0.0f;
+#pragma unroll
+              for (int e = 0; e < VEC; ++e) cs += __expf(v[e] - cm);
+              merge(m, s, cm, cs);
+            }
+          } else {
+            m = fmaxf(m, cm);
           }
         } else {
-          m = fmaxf(m, cm);
-        }
-      } else {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) s += v[e];
+          for (int e = 0; e < VEC; ++e) s += v[e];
+        }
       }
     }
     // wavefront, then workgroup
@@ -235,7 +396,7 @@ __global__ void __launch_bounds__(256) long_rows_kernel(const RowParams p) {
     m = red_m[0];
     s = red_s[0];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) {
+    for (int w = 1; w < NW; ++w) {
       if constexpr (SOFTMAX)
         merge(m, s, red_m[w], red_s[w]);
       else {
@@ -246,12 +407,15 @@ __global__ void __launch_bounds__(256) long_rows_kernel(const RowParams p) {
     if constexpr (SOFTMAX) {
       const float inv = 1.0f / s;
       T* yr = reinterpret_cast<T*>(p.y) + row * p.ldy;
-      for (int c = tid; c < chunks; c += 256) {
+      // (in place: a chunk is written by the thread that reads it, but the last 16 bytes of the row hold elements of
+      // two chunks, and the thread that owns the one before may have written its own by then; elements of another
+      // chunk are not used)
+      for (int c = tid; c < chunks; c += NT) {
         float v[VEC];
-        load_chunk<T>(xr, c * VEC, p.cols, p.vec_in != 0, kNegInf, v);
+        widen_chunk<T>(load_raw<T, true>(xr, c * VEC, p.cols), v);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) v[e] = __expf(v[e] - m) * inv;
-        store_chunk<T>(yr, c * VEC, p.cols, p.vec_out != 0, v);
+        store_chunk<T, true>(yr, c * VEC, p.cols, v);
       }
     } else if (tid == 0) {
       const float out = is_max ? m : (p.op == HIDET_REDUCE_MEAN ? s / (float)p.cols : s);
@@ -262,31 +426,68 @@ __global__ void __launch_bounds__(256) long_rows_kernel(const RowParams p) {
 
 // ---- host side ------------------------------------------------------------------------------------------
 constexpr int kMaxBlocks = 256 * 8;  // 8 workgroups of 4 wavefronts fill a compute unit
+constexpr long long kMaxGrid = 1LL << 22;  // workgroups of one launch of the row-per-workgroup form (at most 1024 threads each)
 
 template <typename T, int L, int R, bool SOFTMAX>
-hipError_t launch_short(const RowParams& p, hipStream_t stream) {
+hipError_t launch_wavefront(const RowParams& p, hipStream_t stream) {
   constexpr int G = 64 / L;
   long long blocks = (p.rows + 4 * G - 1) / (4 * G);
   if (blocks > kMaxBlocks) blocks = kMaxBlocks;
-  hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, SOFTMAX>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  if (p.cols % Chunk<T>::VEC == 0 && p.cols > 0)
+    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, false, SOFTMAX>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  else
+    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, true, SOFTMAX>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  return hipGetLastError();
+}
+
+template <typename T, int NT, int R, bool SOFTMAX>
+hipError_t launch_workgroup(const RowParams& p, hipStream_t stream) {
+  if (p.cols % Chunk<T>::VEC == 0 && !p.shift)
+    hipLaunchKernelGGL((rows_in_workgroup_kernel<T, NT, R, false, SOFTMAX>), dim3((unsigned)p.rows), dim3(NT), 0, stream, p);
+  else
+    hipLaunchKernelGGL((rows_in_workgroup_kernel<T, NT, R, true, SOFTMAX>), dim3((unsigned)p.rows), dim3(NT), 0, stream, p);
+  return hipGetLastError();
+}
+
+template <typename T, int NT, int U, bool SOFTMAX>
+hipError_t launch_streamed(const RowParams& p, hipStream_t stream) {
+  const long long blocks = p.rows < kMaxBlocks ? p.rows : kMaxBlocks;
+  hipLaunchKernelGGL((long_rows_kernel<T, NT, U, SOFTMAX>), dim3((unsigned)blocks), dim3(NT), 0, stream, p);
   return hipGetLastError();
 }
 
 template <typename T, bool SOFTMAX>
-hipError_t dispatch(const RowParams& p, hipStream_t stream) {
+hipError_t dispatch(const RowParams& p_in, hipStream_t stream) {
   constexpr int VEC = Chunk<T>::VEC;
-  const int chunks = (p.cols + VEC - 1) / VEC;
-  if (chunks <= 8) return launch_short<T, 8, 1, SOFTMAX>(p, stream);
-  if (chunks <= 16) return launch_short<T, 16, 1, SOFTMAX>(p, stream);
-  if (chunks <= 32) return launch_short<T, 32, 1, SOFTMAX>(p, stream);
-  if (chunks <= 64) return launch_short<T, 64, 1, SOFTMAX>(p, stream);
-  if (chunks <= 128) return launch_short<T, 64, 2, SOFTMAX>(p, stream);
-  if (chunks <= 256) return launch_short<T, 64, 4, SOFTMAX>(p, stream);
-  if (chunks <= 512) return launch_short<T, 64, 8, SOFTMAX>(p, stream);
-  if (chunks <= 1024) return launch_short<T, 64, 16, SOFTMAX>(p, stream);
-  long long blocks = p.rows < kMaxBlocks ? p.rows : kMaxBlocks;
-  hipLaunchKernelGGL((long_rows_kernel<T, SOFTMAX>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
-  return hipGetLastError();
+  RowParams p = p_in;
+  const int chunks = p.cols / VEC + (p.cols % VEC != 0);
+  // the shifted grid needs room for one chunk more, and costs a few element-wise stores at both ends of a row
+  if (chunks <= 4096 || chunks >= 16384) p.shift = 0;
+  if (chunks <= 8) return launch_wavefront<T, 8, 1, SOFTMAX>(p, stream);
+  if (chunks <= 16) return launch_wavefront<T, 16, 1, SOFTMAX>(p, stream);
+  if (chunks <= 32) return launch_wavefront<T, 32, 1, SOFTMAX>(p, stream);
+  if (chunks <= 64) return launch_wavefront<T, 64, 1, SOFTMAX>(p, stream);
+  if (chunks <= 128) return launch_wavefront<T, 64, 2, SOFTMAX>(p, stream);
+  // From here on a workgroup per row.  Against a wavefront per row it gains 10-20 % at thousands of rows and up to 2x at
+  // few rows (8192 x 4096 bf16: 32.5 -> 25.5 us; 200 x 2048: 3.9 -> 2.9 us); with 128 chunks half of 256 threads would
+  // idle (98304 x 512 fp32: 107 us against 75 us).  More threads with fewer chunks each are the better split of longer
+  // rows (64 x 8192 bf16: 4.0 us on 256 threads, 3.6 us on 512), too many leave most of them idle (4096 x 8200: 28 us
+  // on 512 threads, 39 us on 1024).
+  if (p.rows <= kMaxGrid) {
+    if (chunks <= 256) return launch_workgroup<T, 256, 1, SOFTMAX>(p, stream);
+    if (chunks <= 512) return launch_workgroup<T, 256, 2, SOFTMAX>(p, stream);
+    if (chunks <= 1024) return launch_workgroup<T, 512, 2, SOFTMAX>(p, stream);
+    if (chunks <= 2048) return launch_workgroup<T, 512, 4, SOFTMAX>(p, stream);
+    if (chunks <= 4096) return launch_workgroup<T, 1024, 4, SOFTMAX>(p, stream);
+    if (chunks < 8192) return launch_workgroup<T, 1024, 8, SOFTMAX>(p, stream);
+    // A reduction has nothing to keep: where two or more such workgroups per compute unit are waiting and the registers
+    // leave room for one, short-lived ones that stream read faster (1024 x 50304 fp32: 31.6 against 33.7 us).
+    if constexpr (!SOFTMAX)
+      if (p.rows >= 512) return launch_streamed<T, 512, 2, SOFTMAX>(p, stream);
+    if (chunks <= 16384) return launch_workgroup<T, 1024, 16, SOFTMAX>(p, stream);
+  }
+  // (the most threads and bytes in flight for one row: 90 x 500000 bf16 94 us, 143 us on 512 threads)
+  return launch_streamed<T, 1024, 4, SOFTMAX>(p, stream);
 }
 
 template <bool SOFTMAX>
@@ -329,9 +530,8 @@ hidet_status_t hidet_reduce_rows(int32_t in, int32_t out, int32_t op, int64_t ro
   p.rows = rows;
   p.cols = (int)cols;
   p.op = op;
-  p.vec_in = (aligned_to(x, 16) && ldx % (16 / elem_bytes(in)) == 0) ? 1 : 0;
-  p.vec_out = 0;
   p.out_f32 = out == HIDET_F32 ? 1 : 0;
+  p.shift = 0;
   return dispatch_dtype<false>(in, p, (hipStream_t)stream) == hipSuccess ? HIDET_OK : HIDET_ERR_LAUNCH;
 }
 
@@ -353,9 +553,8 @@ hidet_status_t hidet_softmax_rows(int32_t dtype, int64_t rows, int64_t cols, con
   p.rows = rows;
   p.cols = (int)cols;
   p.op = HIDET_REDUCE_MAX;
-  p.vec_in = (aligned_to(x, 16) && ldx % (16 / (int)es) == 0) ? 1 : 0;
-  p.vec_out = (aligned_to(y, 16) && ldy % (16 / (int)es) == 0) ? 1 : 0;
   p.out_f32 = 0;
+  p.shift = (aligned_to(y, 16) && ldy % (16 / (int)es) == 0) ? 0 : 1;
   return dispatch_dtype<true>(dtype, p, (hipStream_t)stream) == hipSuccess ? HIDET_OK : HIDET_ERR_LAUNCH;
 }
 

@@ -178,3 +178,59 @@ def test_stream_bandwidth_probe_reports_plausible_rates():
         hb.hidet_probe_stream_bandwidth(ring, 3)
     with pytest.raises(hb.HidetError):
         hb.hidet_probe_stream_bandwidth(ring[: 100 << 20], 0)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_rows_at_the_edges_of_the_kernels(dtype):
+    """Row lengths on both sides of every boundary between the kernels (64, 128, 256, ... 16384 chunks of 16 bytes), with
+    whole and ragged last chunks, in and out of place, rows aligned and not.  Same bounds as the tests above."""
+    vec = 4 if dtype == "f32" else 8
+    g = wl.rng(9600)
+    for chunks in (8, 16, 32, 64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384):
+        for cols in (chunks * vec, chunks * vec - 1, chunks * vec + 1, (chunks - 1) * vec + 1):
+            for ld in (cols, cols + 3):
+                rows = 3
+                x = wl.to_storage((g.standard_normal((rows, ld)) * 3).astype(np.float32), dtype)
+                dx = to_gpu(x, dtype)
+                ref = red.softmax_rows(wl.widen(x, dtype)[:, :cols])
+                out = torch.full((rows, ld), 7.0, dtype=TORCH_DTYPE[dtype], device="cuda")
+                hb.hidet_softmax_rows(dx[:, :cols], out[:, :cols])
+                y32 = torch.full((rows,), float("nan"), dtype=torch.float32, device="cuda")
+                hb.hidet_reduce_rows(dx[:, :cols], y32, hb.HIDET_REDUCE_SUM)
+                ymax = torch.full_like(y32, float("nan"))
+                hb.hidet_reduce_rows(dx[:, :cols], ymax, hb.HIDET_REDUCE_MAX)
+                torch.cuda.synchronize()
+                x64 = wl.widen(x, dtype)[:, :cols]
+                assert within_bound(oracle.rel_frobenius(to_f64(out)[:, :cols], ref), ref, dtype), (cols, ld)
+                assert torch.all(out[:, cols:] == 7.0), (cols, ld)
+                # fp32 sums of signed values: the bound is relative to the sum of magnitudes
+                assert np.all(np.abs(to_f64(y32) - x64.sum(1)) <= 1e-6 * np.abs(x64).sum(1)), (cols, ld)
+                assert np.array_equal(to_f64(ymax), x64.max(1)), (cols, ld)
+                hb.hidet_softmax_rows(dx[:, :cols], dx[:, :cols])  # in place
+                torch.cuda.synchronize()
+                assert torch.equal(dx[:, :cols], out[:, :cols]), (cols, ld)
+
+
+@pytest.mark.parametrize("dtype,rows", [("f32", 600), ("bf16", 520)])
+def test_many_very_long_rows(dtype, rows):
+    """More than 8192 chunks in at least 512 rows: reductions take the streamed kernel on 512 threads."""
+    cols = 33003 if dtype == "f32" else 66001
+    x = (torch.arange(rows * cols, device="cuda") % 1021).view(rows, cols).to(torch.int32)
+    xf = (x % 3).to(TORCH_DTYPE[dtype])  # small integers: sums below 2^24 are exact in any order
+    y = torch.zeros(rows, dtype=torch.float32, device="cuda")
+    hb.hidet_reduce_rows(xf, y, hb.HIDET_REDUCE_SUM)
+    torch.cuda.synchronize()
+    assert torch.equal(y.to(torch.int64), (x % 3).sum(1))
+
+
+@pytest.mark.parametrize("cols", [33, 512, 5000, 60001])
+def test_softmax_of_the_most_negative_finite_values(cols):
+    """Masks made of the lowest finite value: an exponential of the difference, not a difference of scaled values."""
+    low = torch.finfo(torch.float32).min
+    x = torch.full((2, cols), low, device="cuda")
+    x[1, 3:5] = 1.0
+    y = torch.empty_like(x)
+    hb.hidet_softmax_rows(x, y)
+    torch.cuda.synchronize()
+    assert torch.allclose(y[0], torch.full((cols,), 1.0 / cols, device="cuda"), rtol=1e-5, atol=0.0)
+    assert y[1, 3] == 0.5 and y[1, 4] == 0.5 and y[1].sum() == 1.0
