@@ -134,27 +134,37 @@ def _check(status, where):
         raise HidetError(status, where)
 
 
+# A small call costs what its host path costs (the kernel of a 256^3 product runs 3 us), so the helpers below hand plain
+# integers to ctypes (argtypes converts them), read each shape and stride tuple once and take the current stream's
+# handle without building a Stream object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dtype(t):
-    if t.dtype not in _DTYPES:
+    d = _DTYPES.get(t.dtype)
+    if d is None:
         raise TypeError("unsupported dtype %s" % t.dtype)
-    return _DTYPES[t.dtype]
+    return d
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _ld(t):
     """Leading dimension of a 2-D (or the last two dims of a 3-D) row-major tensor, in elements."""
-    if t.stride(-1) != 1 and t.shape[-1] > 1:
+    n, s = t.shape, t.stride()
+    if s[-1] != 1 and n[-1] > 1:
         raise ValueError("innermost dimension must be contiguous")
-    return t.stride(-2) if t.shape[-2] > 1 else max(t.shape[-1], 1)
+    return s[-2] if n[-2] > 1 else max(n[-1], 1)
 
 
 def make_epilogue(alpha=1.0, bias=None, bias_axis=HIDET_BIAS_NONE, residual=None, relu=False, batched=False,
@@ -191,8 +201,9 @@ def _epi_ref(e):
 
 
 def _gemm_dims(A, B, transA, transB):
-    M, K = (A.shape[-1], A.shape[-2]) if transA else (A.shape[-2], A.shape[-1])
-    Kb, N = (B.shape[-1], B.shape[-2]) if transB else (B.shape[-2], B.shape[-1])
+    a, b = A.shape, B.shape
+    M, K = (a[-1], a[-2]) if transA else (a[-2], a[-1])
+    Kb, N = (b[-1], b[-2]) if transB else (b[-2], b[-1])
     if K != Kb:
         raise ValueError("inner dimensions differ: %d vs %d" % (K, Kb))
     return M, N, K
@@ -209,7 +220,7 @@ def hidet_gemm(A, B, C, transA=False, transB=False, epilogue=None, stream=None, 
                                   _ld(B), _ptr(C), N, _epi_ref(epilogue), _stream(stream))
         _check(st, "hidet_gemm")
         return
-    if tuple(C.shape) != (M, N):
+    if C.shape != (M, N):
         raise ValueError("C has shape %s, expected %s" % (tuple(C.shape), (M, N)))
     st = lib().hidet_gemm_cfg(config, _dtype(A), _dtype(C), int(transA), int(transB), M, N, K, _ptr(A), _ld(A), _ptr(B),
                               _ld(B), _ptr(C), _ld(C), _epi_ref(epilogue), _stream(stream))
@@ -217,14 +228,15 @@ def hidet_gemm(A, B, C, transA=False, transB=False, epilogue=None, stream=None, 
 
 
 def _bstride(t):
-    return t.stride(0) if t.shape[0] > 1 else t.shape[-2] * _ld(t)
+    n = t.shape
+    return t.stride(0) if n[0] > 1 else n[-2] * _ld(t)
 
 
 def hidet_batched_gemm(A, B, C, transA=False, transB=False, epilogue=None, stream=None, config=-1):
     """Batched form: A, B, C are 3-D GPU tensors [batch, rows, cols]."""
     M, N, K = _gemm_dims(A, B, transA, transB)
     batch = A.shape[0]
-    if B.shape[0] != batch or tuple(C.shape) != (batch, M, N):
+    if B.shape[0] != batch or C.shape != (batch, M, N):
         raise ValueError("batch/shape mismatch")
     st = lib().hidet_batched_gemm_cfg(config, _dtype(A), _dtype(C), int(transA), int(transB), batch, M, N, K, _ptr(A),
                                       _ld(A), _bstride(A), _ptr(B), _ld(B), _bstride(B), _ptr(C), _ld(C), _bstride(C),
@@ -251,7 +263,7 @@ def conv_out_shape(x_shape, w_shape, stride, pad):
 
 def hidet_conv2d_implicit_gemm(x, w, y, stride=(1, 1), pad=(0, 0), epilogue=None, stream=None, config=-1):
     """y = epilogue(conv2d(x, w)), NCHW / OIHW / NCHW dense GPU tensors; bias (if any) is per output channel."""
-    if tuple(y.shape) != conv_out_shape(x.shape, w.shape, stride, pad):
+    if y.shape != conv_out_shape(x.shape, w.shape, stride, pad):
         raise ValueError("y has the wrong shape")
     st = lib().hidet_conv2d_implicit_gemm_cfg(config, *_conv_args(x, w, y, stride, pad), _epi_ref(epilogue),
                                               _stream(stream))
@@ -300,7 +312,7 @@ def hidet_batched_gemm_splitk_static(A, B, C, k_slices=0, transA=False, transB=F
         A, B, C = A.unsqueeze(0), B.unsqueeze(0), C.unsqueeze(0)
     M, N, K = _gemm_dims(A, B, transA, transB)
     batch = A.shape[0]
-    if B.shape[0] != batch or tuple(C.shape) != (batch, M, N):
+    if B.shape[0] != batch or C.shape != (batch, M, N):
         raise ValueError("batch/shape mismatch")
     st = lib().hidet_batched_gemm_splitk_static(config, k_slices, _dtype(A), _dtype(C), int(transA), int(transB), batch, M, N,
                                                 K, _ptr(A), _ld(A), _bstride(A), _ptr(B), _ld(B), _bstride(B), _ptr(C),
@@ -322,7 +334,7 @@ def hidet_batched_gemm_splitk(A, B, C, workspace, k_slices=0, transA=False, tran
         A, B, C = A.unsqueeze(0), B.unsqueeze(0), C.unsqueeze(0)
     M, N, K = _gemm_dims(A, B, transA, transB)
     batch = A.shape[0]
-    if B.shape[0] != batch or tuple(C.shape) != (batch, M, N):
+    if B.shape[0] != batch or C.shape != (batch, M, N):
         raise ValueError("batch/shape mismatch")
     wp, wb = _ws(workspace)
     st = lib().hidet_batched_gemm_splitk(config, k_slices, _dtype(A), _dtype(C), int(transA), int(transB), batch, M, N, K,
@@ -334,7 +346,7 @@ def hidet_batched_gemm_splitk(A, B, C, workspace, k_slices=0, transA=False, tran
 def hidet_conv2d_implicit_gemm_splitk(x, w, y, workspace, k_slices=0, stride=(1, 1), pad=(0, 0), epilogue=None,
                                       stream=None, config=-1):
     """K-parallel form of hidet_conv2d_implicit_gemm; workspace is a GPU tensor."""
-    if tuple(y.shape) != conv_out_shape(x.shape, w.shape, stride, pad):
+    if y.shape != conv_out_shape(x.shape, w.shape, stride, pad):
         raise ValueError("y has the wrong shape")
     wp, wb = _ws(workspace)
     st = lib().hidet_conv2d_implicit_gemm_splitk(config, k_slices, *_conv_args(x, w, y, stride, pad), _epi_ref(epilogue),
@@ -364,7 +376,7 @@ def _packed_conv_args(x, w_packed, y, stride, pad):
     OC, KH, KW, IC2 = w_packed.shape
     if IC != IC2:
         raise ValueError("channel mismatch")
-    if tuple(y.shape) != conv_out_shape(x.shape, (OC, IC, KH, KW), stride, pad):
+    if y.shape != conv_out_shape(x.shape, (OC, IC, KH, KW), stride, pad):
         raise ValueError("y has the wrong shape")
     return [_dtype(x), _dtype(y), Nb, IC, H, W, OC, KH, KW, stride[0], stride[1], pad[0], pad[1], _ptr(x), _ptr(w_packed),
             _ptr(y)]

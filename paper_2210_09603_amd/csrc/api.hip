@@ -346,6 +346,8 @@ int default_config(const Problem& pr, int slices = 1) {
     return (long long)r.bm * r.bn * 8 + (r.sched == 1 ? 4 : 0) + (r.mfma == 16 ? 2 : 0) + ahead + ksplit;
   };
   const bool throughput = sat_mul(((M + 63) / 64) * ((N + 63) / 64), pr.batch) >= 384;
+  // (tile extents are powers of two, so that this choice, made on every call that names no configuration, shifts
+  // where it would divide)
   int best = -1, fewer = -1, most = -1;
   long long most_blocks = -1, best_key = -(1LL << 62), fewer_key = -(1LL << 62);
   for (int c = 0; c < kNumConfigs; ++c) {
@@ -354,8 +356,8 @@ int default_config(const Problem& pr, int slices = 1) {
     const ConfigRow& r = kConfigs[c];
     // the wave groups along K need at least one whole K tile to share, and are meant for latency-bound problems
     if (r.sched == 3 && (pr.p.K < r.bk || throughput)) continue;
-    const long long blocks =
-        sat_mul(((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn), pr.batch * (slices > 1 ? slices : 1));
+    const long long tiles = ((M + r.bm - 1) >> __builtin_ctz(r.bm)) * ((N + r.bn - 1) >> __builtin_ctz(r.bn));
+    const long long blocks = sat_mul(tiles, pr.batch * (slices > 1 ? slices : 1));
     // the ring schedule runs GEMMs only: by direct-to-LDS loads (at any element alignment), with its stages
     // staged through registers when an input prologue has to touch the values
     const bool ring_any = r.sched == 1 && pr.op == 0 && pr.p.out_map == 0;
@@ -369,11 +371,12 @@ int default_config(const Problem& pr, int slices = 1) {
 
     // useful outputs per workgroup, discounted by the share of the tile that is padding, decide; then the smaller
     // tile, then the schedule preferences
-    const long long useful = (M * N) / (((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn));
-    long long key = (useful * useful / area) * (1LL << 23) - area * 64 + (rank(r) & 63);
+    const long long useful = (M * N) / tiles;
+    const long long weight = (useful * useful) >> __builtin_ctzll(area);
+    long long key = weight * (1LL << 23) - area * 64 + (rank(r) & 63);
     // a K of at most two stages runs the two-slot ring: two workgroups of a 256x128 tile share a compute unit and
     // outrun one of a 256x256 tile
-    if (ring && pr.p.K <= 2 * r.bk && area == 256 * 128) key += (useful * useful / area) * (3LL << 22);
+    if (ring && pr.p.K <= 2 * r.bk && area == 256 * 128) key += weight * (3LL << 22);
     if (blocks >= enough && key > best_key) {
       best = c;
       best_key = key;
@@ -452,6 +455,11 @@ struct SplitK {  // how the caller wants K parallelised
   bool fixed = false;  // the workspace is the library's static scratch array: too small is HIDET_ERR_SCRATCH
 };
 
+// (g_mutex held.)  A process that has tuned nothing does not print keys: that took over a microsecond of each call.
+std::map<std::string, Tuned>::const_iterator find_tuned(const Problem& pr, const SplitK& sk) {
+  return g_cache.empty() ? g_cache.end() : g_cache.find(problem_key(pr, sk.workspace != nullptr));
+}
+
 template <int MAPPER>
 hipError_t reduce_dispatch(int dtype, const GemmParams& p, int batch, hipStream_t stream) {
   switch (dtype) {
@@ -503,7 +511,7 @@ hidet_status_t launch(const Problem& pr_in, int config, const SplitK& sk, hipStr
   if (config < 0) {
     {
       std::lock_guard<std::mutex> lock(g_mutex);
-      auto it = g_cache.find(problem_key(pr, sk.workspace != nullptr));
+      auto it = find_tuned(pr, sk);
       if (it != g_cache.end()) {
         config = it->second.config;
         if (slices < 0) slices = it->second.slices;
@@ -720,7 +728,7 @@ hidet_status_t launch_conv(const ConvCall& cc, int config, const SplitK& sk, hip
   Tuned t{-1, 1, 0};
   {
     std::lock_guard<std::mutex> lock(g_mutex);
-    auto it = g_cache.find(problem_key(cc.conv, sk.workspace != nullptr));
+    auto it = find_tuned(cc.conv, sk);
     if (it != g_cache.end()) t = it->second;
   }
   if (t.config < 0) return launch(cc.gemm, -1, sk, stream);
