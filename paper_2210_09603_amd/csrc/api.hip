@@ -326,6 +326,41 @@ LaunchFn find_partial_launcher(const Problem& pr, int config) {
   return registry().fn[config][pr.dtype][kPartialVariants + variant];
 }
 
+// Convolutions in 16-bit types on a long K.  A workgroup whose wave groups split K owns a compute unit, and its time
+// hardly depends on its tile's neighbours: one round of them costs K times a rate of the tile (3x3, 512 channels,
+// K = 4608: 16x16 11 us, 32x16 12, 32x32 18, 64x32 23, 64x64 36, 128x64 45, 128x128 67), a second round as much
+// again.  So the smallest such tile whose workgroups are all resident at once is taken; measured against the choice
+// below over batches 1 to 64 of 64x56x56, 128x28x28, 256x14x14 and 512x7x7, 3x3 and 5x5: 64 images of 512x7x7 69 -> 46 us,
+// 256x14x14 44 -> 38 us, 6 images of 256x14x14 20 -> 13.5 us, one of 512x7x7 16 -> 11 us.  Large tiles have to be
+// mostly output, not padding, and on a short K (fill and drain of the pipeline count) they need the round nearly full,
+// or lose to small tiles that share a compute unit (128x28x28, 7 images, K = 1152: 64x64 18 us, 128x64 17 us, two
+// 64x32 tiles of the two-stage form 15 us); the largest need half a round in any case (repacked weights allow only K tiles
+// that divide IC: 5 images of 128x27x27, 5x5: 68 tiles of 128x64 33 us, 270 of 64x32 28 us).  -1: none fits.
+int one_round_config(const Problem& pr) {
+  constexpr long long kComputeUnits = 256, kLongK = 2048;
+  const long long M = pr.p.M, N = pr.p.N;
+  int best = -1;
+  long long best_area = 0;
+  for (int c = 0; c < kNumConfigs; ++c) {
+    const ConfigRow& r = kConfigs[c];
+    if (r.sched != 3 || pr.p.K < r.bk || !find_launcher(pr, c)) continue;
+    const long long area = (long long)r.bm * r.bn;
+    const long long tiles = ((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
+    if (tiles > kComputeUnits || tiles < kComputeUnits / 4) continue;
+    if (area >= 64 * 64) {
+      if (4 * M * N < 3 * tiles * area) continue;
+      if (pr.p.K < kLongK && (area == 64 * 64 || tiles < kComputeUnits * 3 / 4)) continue;
+      if (area > 64 * 64 && tiles < kComputeUnits / 2) continue;
+    }
+    // (of two tiles of one size the taller one: it gathers fewer columns)
+    if (best < 0 || area < best_area || (area == best_area && r.bm > kConfigs[best].bm)) {
+      best = c;
+      best_area = area;
+    }
+  }
+  return best;
+}
+
 // Untuned choice: the largest tile that still gives (nearly) every compute unit a workgroup, else the largest
 // that gives a quarter of them one, else the tile with the most workgroups.  Outputs large enough to be bound by
 // throughput rather than by one workgroup's latency chain (at least 384 tiles of 64x64) ask for about two
@@ -337,6 +372,17 @@ LaunchFn find_partial_launcher(const Problem& pr, int config) {
 // and the output is small.  With slices > 1 only tiles that have a K-parallel form take part.
 int default_config(const Problem& pr, int slices = 1) {
   const long long M = pr.p.M, N = pr.p.N;
+  const bool conv16 = pr.op == 1 && pr.dtype != HIDET_F32 && slices <= 1;
+  if (conv16 && pr.p.K >= 512) {
+    const int c = one_round_config(pr);
+    if (c >= 0) return c;
+  }
+  // The gather of a convolution is paid per column of the tile, and fewer than 64 output channels fill one tile row
+  // anyway: there the 64x64 tile, more of which are resident together, beats the wider and the padded ones, with 32x32
+  // matrix-core tiles once it is bound by throughput (64 images of 64x56x56, 3x3: 66 us on 64x128, 54 us on 64x64 of
+  // 16x16, 50 us of 32x32).
+  // (Not measured for repacked weights, whose gather is cheaper.)
+  const bool conv_few_rows = conv16 && M <= 64 && !pr.packed;
   // (measured: equal to the two-stage tiles of their size at K = 1024, ahead beyond; the gather of the convolution
   // moves that point to about 512)
   const bool long_k = pr.p.K >= (pr.op == 1 ? 512 : 1024);
@@ -348,7 +394,7 @@ int default_config(const Problem& pr, int slices = 1) {
   const bool throughput = sat_mul(((M + 63) / 64) * ((N + 63) / 64), pr.batch) >= 384;
   // (tile extents are powers of two, so that this choice, made on every call that names no configuration, shifts
   // where it would divide)
-  int best = -1, fewer = -1, most = -1;
+  int best = -1, fewer = -1, most = -1, passed_over = -1;
   long long most_blocks = -1, best_key = -(1LL << 62), fewer_key = -(1LL << 62);
   for (int c = 0; c < kNumConfigs; ++c) {
     if (!find_launcher(pr, c)) continue;
@@ -356,8 +402,17 @@ int default_config(const Problem& pr, int slices = 1) {
     const ConfigRow& r = kConfigs[c];
     // the wave groups along K need at least one whole K tile to share, and are meant for latency-bound problems
     if (r.sched == 3 && (pr.p.K < r.bk || throughput)) continue;
+    if (conv_few_rows && (r.bm > 64 || r.bn > 64)) {
+      passed_over = c;
+      continue;
+    }
     const long long tiles = ((M + r.bm - 1) >> __builtin_ctz(r.bm)) * ((N + r.bn - 1) >> __builtin_ctz(r.bn));
     const long long blocks = sat_mul(tiles, pr.batch * (slices > 1 ? slices : 1));
+    // (a convolution: what one round of them can do has been decided above)
+    if (conv16 && r.sched == 3 && (blocks > 256 || (pr.p.K >= 512 && (long long)r.bm * r.bn >= 64 * 64))) {
+      passed_over = c;
+      continue;
+    }
     // the ring schedule runs GEMMs only: by direct-to-LDS loads (at any element alignment), with its stages
     // staged through registers when an input prologue has to touch the values
     const bool ring_any = r.sched == 1 && pr.op == 0 && pr.p.out_map == 0;
@@ -367,13 +422,17 @@ int default_config(const Problem& pr, int slices = 1) {
     // still the better choice; from 128 down the smaller tile fits into one round and wins.
     const long long area = (long long)r.bm * r.bn;
     const bool self_overlapping = ring_any && pr.p.K >= 128;
-    const long long enough = !throughput ? 192 : !self_overlapping ? 400 : 129;
+    // A convolution outside the rule above takes 64x64 tiles only where every compute unit gets more than one (7 images
+    // of 64x56x56, 5x5: 64x64 tiles 26.5 us, 64x32 21.8 us; 9 images of 128x28x28, 3x3: 18.3 us and 14.8 us).  From
+    // 64x32 down one round is enough (18 images of 128x28x28 repacked, stride 2: 64x32 13.5 us, 32x32 15.4 us).
+    const long long enough = throughput ? (self_overlapping ? 129 : 400) : (conv16 && area >= 64 * 64) ? 400 : 192;
 
     // useful outputs per workgroup, discounted by the share of the tile that is padding, decide; then the smaller
     // tile, then the schedule preferences
     const long long useful = (M * N) / tiles;
     const long long weight = (useful * useful) >> __builtin_ctzll(area);
-    long long key = weight * (1LL << 23) - area * 64 + (rank(r) & 63);
+    const long long preference = (conv_few_rows && throughput && r.mfma == 32) ? 8 : rank(r) & 63;
+    long long key = weight * (1LL << 23) - area * 64 + preference;
     // a K of at most two stages runs the two-slot ring: two workgroups of a 256x128 tile share a compute unit and
     // outrun one of a 256x256 tile
     if (ring && pr.p.K <= 2 * r.bk && area == 256 * 128) key += weight * (3LL << 22);
@@ -399,7 +458,7 @@ int default_config(const Problem& pr, int slices = 1) {
       most = c;
     }
   }
-  return best >= 0 ? best : (fewer >= 0 ? fewer : most);
+  return best >= 0 ? best : fewer >= 0 ? fewer : most >= 0 ? most : passed_over;
 }
 
 // ---- static scratch of the allocation-free K-parallel entry point --------------------------------------
