@@ -343,6 +343,20 @@ hidet_status_t hidet_reduce_rows(int32_t in, int32_t out, int32_t op, int64_t ro
                                  int64_t ldx, void* y, void* stream);
 hidet_status_t hidet_softmax_rows(int32_t dtype, int64_t rows, int64_t cols, const void* x, int64_t ldx, void* y,
                                   int64_t ldy, void* stream);
+/*
+ * Test aid: how the two entry points above cut `rows` rows of `cols` elements of `dtype` (softmax: 0 or 1), without
+ * running anything.  Every launch must stay below 2^32 work items (workgroups * workgroup_size).
+ * HIDET_ERR_INVALID_ARG for an unknown dtype, rows <= 0, cols < 0 or a NULL result.
+ */
+typedef struct {
+  int32_t form;              /* 0: several rows or one per wavefront, 1: one row per workgroup, held in registers, 2: streamed */
+  int32_t threads_per_row;   /* lanes or threads that share one row */
+  int32_t chunks_per_thread; /* 16-byte pieces of a row that each of them holds (streamed: has in flight) */
+  int32_t workgroup_size;    /* threads */
+  int64_t workgroups;        /* of the first, largest launch */
+  int64_t launches;
+} hidet_row_schedule_t;
+hidet_status_t hidet_row_schedule(int32_t dtype, int32_t softmax, int64_t rows, int64_t cols, hidet_row_schedule_t* out);
 
 /*
  * Task mappings (Section 5.1): the compile-time mappings the kernels are built from, plus the

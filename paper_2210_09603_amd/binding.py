@@ -47,6 +47,11 @@ class hidet_config_info_t(ctypes.Structure):
                                     "stages", "lds_bytes", "waves_k")]
 
 
+class hidet_row_schedule_t(ctypes.Structure):
+    _fields_ = [(n, _i32) for n in ("form", "threads_per_row", "chunks_per_thread", "workgroup_size")] + [
+        ("workgroups", _i64), ("launches", _i64)]
+
+
 class HidetError(RuntimeError):
     def __init__(self, status, where):
         self.status = status
@@ -63,7 +68,7 @@ EXPORTS = (
     "hidet_conv2d_implicit_gemm_splitk", "hidet_tune_gemm_splitk", "hidet_tune_conv2d_splitk", "hidet_reduce_rows",
     "hidet_softmax_rows", "hidet_host_div", "hidet_conv2d_splitk_workspace_bytes", "hidet_static_scratch_bytes",
     "hidet_batched_gemm_splitk_static", "hidet_conv2d_pack_weights", "hidet_conv2d_implicit_gemm_packed",
-    "hidet_tune_conv2d_packed",
+    "hidet_tune_conv2d_packed", "hidet_row_schedule",
 )
 
 _lib = None
@@ -108,6 +113,7 @@ def lib():
         L.hidet_host_div.argtypes = [_i64, _i32, ctypes.POINTER(_i32)]
         L.hidet_reduce_rows.argtypes = [_i32, _i32, _i32, _i64, _i64, _vp, _i64, _vp, _vp]
         L.hidet_softmax_rows.argtypes = [_i32, _i64, _i64, _vp, _i64, _vp, _i64, _vp]
+        L.hidet_row_schedule.argtypes = [_i32, _i32, _i64, _i64, ctypes.POINTER(hidet_row_schedule_t)]
         L.hidet_tune_last_times.argtypes = [ctypes.POINTER(ctypes.c_float), _i32]
         L.hidet_tune_clear.restype = None
         L.hidet_tune_save.argtypes = [ctypes.c_char_p]
@@ -454,6 +460,13 @@ def hidet_softmax_rows(x, y, stream=None):
     _, _, ldy = _rows_view(y)
     st = lib().hidet_softmax_rows(_dtype(x), rows, cols, _ptr(x), ldx, _ptr(y), ldy, _stream(stream))
     _check(st, "hidet_softmax_rows")
+
+
+def hidet_row_schedule(dtype, softmax, rows, cols):
+    """How a row softmax (or reduction) of this size is cut, as a dict; runs nothing."""
+    out = hidet_row_schedule_t()
+    _check(lib().hidet_row_schedule(dtype, int(softmax), rows, cols, ctypes.byref(out)), "hidet_row_schedule")
+    return {n: getattr(out, n) for n, _ in out._fields_}
 
 
 def hidet_tune_last_times():

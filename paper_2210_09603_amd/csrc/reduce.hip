@@ -426,7 +426,17 @@ __global__ void __launch_bounds__(NT) long_rows_kernel(const RowParams p) {
 
 // ---- host side ------------------------------------------------------------------------------------------
 constexpr int kMaxBlocks = 256 * 8;  // 8 workgroups of 4 wavefronts fill a compute unit
-constexpr long long kMaxGrid = 1LL << 22;  // workgroups of one launch of the row-per-workgroup form (at most 1024 threads each)
+// The kernel that a problem runs on: decided by its sizes and types, before anything is launched.
+enum RowForm { ROWS_PER_WAVEFRONT = 0, ROW_PER_WORKGROUP = 1, ROW_STREAMED = 2 };
+struct RowChoice {
+  int form;
+  int threads;  // that share one row
+  int chunks;   // each of them holds (streamed: requests together)
+};
+
+// Workgroups of `threads` threads that one launch may have: work items are counted in 32 bits (a larger launch is
+// refused).  The row-per-workgroup form runs more rows than that in several launches.
+constexpr long long max_workgroups(int threads) { return 0xffffffffLL / threads; }
 
 template <typename T, int L, int R, bool SOFTMAX>
 hipError_t launch_wavefront(const RowParams& p, hipStream_t stream) {
@@ -442,11 +452,19 @@ hipError_t launch_wavefront(const RowParams& p, hipStream_t stream) {
 
 template <typename T, int NT, int R, bool SOFTMAX>
 hipError_t launch_workgroup(const RowParams& p, hipStream_t stream) {
-  if (p.cols % Chunk<T>::VEC == 0 && !p.shift)
-    hipLaunchKernelGGL((rows_in_workgroup_kernel<T, NT, R, false, SOFTMAX>), dim3((unsigned)p.rows), dim3(NT), 0, stream, p);
-  else
-    hipLaunchKernelGGL((rows_in_workgroup_kernel<T, NT, R, true, SOFTMAX>), dim3((unsigned)p.rows), dim3(NT), 0, stream, p);
-  return hipGetLastError();
+  RowParams q = p;
+  for (long long row = 0; row < p.rows; row += max_workgroups(NT)) {
+    q.x = static_cast<const char*>(p.x) + row * p.ldx * (long long)sizeof(T);
+    q.y = static_cast<char*>(p.y) + (SOFTMAX ? row * p.ldy * (long long)sizeof(T) : row * (p.out_f32 ? 4 : (long long)sizeof(T)));
+    q.rows = p.rows - row < max_workgroups(NT) ? p.rows - row : max_workgroups(NT);
+    if (p.cols % Chunk<T>::VEC == 0 && !p.shift)
+      hipLaunchKernelGGL((rows_in_workgroup_kernel<T, NT, R, false, SOFTMAX>), dim3((unsigned)q.rows), dim3(NT), 0, stream, q);
+    else
+      hipLaunchKernelGGL((rows_in_workgroup_kernel<T, NT, R, true, SOFTMAX>), dim3((unsigned)q.rows), dim3(NT), 0, stream, q);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template <typename T, int NT, int U, bool SOFTMAX>
@@ -456,38 +474,66 @@ hipError_t launch_streamed(const RowParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <typename T, bool SOFTMAX>
-hipError_t dispatch(const RowParams& p_in, hipStream_t stream) {
-  constexpr int VEC = Chunk<T>::VEC;
-  RowParams p = p_in;
-  const int chunks = p.cols / VEC + (p.cols % VEC != 0);
-  // the shifted grid needs room for one chunk more, and costs a few element-wise stores at both ends of a row
-  if (chunks <= 4096 || chunks >= 16384) p.shift = 0;
-  if (chunks <= 8) return launch_wavefront<T, 8, 1, SOFTMAX>(p, stream);
-  if (chunks <= 16) return launch_wavefront<T, 16, 1, SOFTMAX>(p, stream);
-  if (chunks <= 32) return launch_wavefront<T, 32, 1, SOFTMAX>(p, stream);
-  if (chunks <= 64) return launch_wavefront<T, 64, 1, SOFTMAX>(p, stream);
-  if (chunks <= 128) return launch_wavefront<T, 64, 2, SOFTMAX>(p, stream);
+constexpr long long kManyRows = 1LL << 22;
+
+int chunks_of(int elem_size, int cols) { return cols / (16 / elem_size) + (cols % (16 / elem_size) != 0); }
+
+RowChoice choose_rows(int elem_size, bool softmax, long long rows, int cols) {
+  const int chunks = chunks_of(elem_size, cols);
+  if (chunks <= 8) return {ROWS_PER_WAVEFRONT, 8, 1};
+  if (chunks <= 16) return {ROWS_PER_WAVEFRONT, 16, 1};
+  if (chunks <= 32) return {ROWS_PER_WAVEFRONT, 32, 1};
+  if (chunks <= 64) return {ROWS_PER_WAVEFRONT, 64, 1};
+  if (chunks <= 128) return {ROWS_PER_WAVEFRONT, 64, 2};
   // From here on a workgroup per row.  Against a wavefront per row it gains 10-20 % at thousands of rows and up to 2x at
   // few rows (8192 x 4096 bf16: 32.5 -> 25.5 us; 200 x 2048: 3.9 -> 2.9 us); with 128 chunks half of 256 threads would
   // idle (98304 x 512 fp32: 107 us against 75 us).  More threads with fewer chunks each are the better split of longer
   // rows (64 x 8192 bf16: 4.0 us on 256 threads, 3.6 us on 512), too many leave most of them idle (4096 x 8200: 28 us
   // on 512 threads, 39 us on 1024).
-  if (p.rows <= kMaxGrid) {
-    if (chunks <= 256) return launch_workgroup<T, 256, 1, SOFTMAX>(p, stream);
-    if (chunks <= 512) return launch_workgroup<T, 256, 2, SOFTMAX>(p, stream);
-    if (chunks <= 1024) return launch_workgroup<T, 512, 2, SOFTMAX>(p, stream);
-    if (chunks <= 2048) return launch_workgroup<T, 512, 4, SOFTMAX>(p, stream);
-    if (chunks <= 4096) return launch_workgroup<T, 1024, 4, SOFTMAX>(p, stream);
-    if (chunks < 8192) return launch_workgroup<T, 1024, 8, SOFTMAX>(p, stream);
+  if (rows <= kManyRows) {
+    if (chunks <= 256) return {ROW_PER_WORKGROUP, 256, 1};
+    if (chunks <= 512) return {ROW_PER_WORKGROUP, 256, 2};
+    if (chunks <= 1024) return {ROW_PER_WORKGROUP, 512, 2};
+    if (chunks <= 2048) return {ROW_PER_WORKGROUP, 512, 4};
+    if (chunks <= 4096) return {ROW_PER_WORKGROUP, 1024, 4};
+    if (chunks < 8192) return {ROW_PER_WORKGROUP, 1024, 8};
     // A reduction has nothing to keep: where two or more such workgroups per compute unit are waiting and the registers
     // leave room for one, short-lived ones that stream read faster (1024 x 50304 fp32: 31.6 against 33.7 us).
-    if constexpr (!SOFTMAX)
-      if (p.rows >= 512) return launch_streamed<T, 512, 2, SOFTMAX>(p, stream);
-    if (chunks <= 16384) return launch_workgroup<T, 1024, 16, SOFTMAX>(p, stream);
+    if (!softmax && rows >= 512) return {ROW_STREAMED, 512, 2};
+    if (chunks <= 16384) return {ROW_PER_WORKGROUP, 1024, 16};
   }
   // (the most threads and bytes in flight for one row: 90 x 500000 bf16 94 us, 143 us on 512 threads)
-  return launch_streamed<T, 1024, 4, SOFTMAX>(p, stream);
+  return {ROW_STREAMED, 1024, 4};
+}
+
+constexpr int choice_key(int form, int threads, int chunks) { return (form * 2048 + threads) * 32 + chunks; }
+
+template <typename T, bool SOFTMAX>
+hipError_t dispatch(const RowParams& p_in, hipStream_t stream) {
+  RowParams p = p_in;
+  const int chunks = chunks_of(sizeof(T), p.cols);
+  // the shifted grid needs room for one chunk more, and costs a few element-wise stores at both ends of a row
+  if (chunks <= 4096 || chunks >= 16384) p.shift = 0;
+  const RowChoice c = choose_rows(sizeof(T), SOFTMAX, p.rows, p.cols);
+  switch (choice_key(c.form, c.threads, c.chunks)) {
+    case choice_key(ROWS_PER_WAVEFRONT, 8, 1): return launch_wavefront<T, 8, 1, SOFTMAX>(p, stream);
+    case choice_key(ROWS_PER_WAVEFRONT, 16, 1): return launch_wavefront<T, 16, 1, SOFTMAX>(p, stream);
+    case choice_key(ROWS_PER_WAVEFRONT, 32, 1): return launch_wavefront<T, 32, 1, SOFTMAX>(p, stream);
+    case choice_key(ROWS_PER_WAVEFRONT, 64, 1): return launch_wavefront<T, 64, 1, SOFTMAX>(p, stream);
+    case choice_key(ROWS_PER_WAVEFRONT, 64, 2): return launch_wavefront<T, 64, 2, SOFTMAX>(p, stream);
+    case choice_key(ROW_PER_WORKGROUP, 256, 1): return launch_workgroup<T, 256, 1, SOFTMAX>(p, stream);
+    case choice_key(ROW_PER_WORKGROUP, 256, 2): return launch_workgroup<T, 256, 2, SOFTMAX>(p, stream);
+    case choice_key(ROW_PER_WORKGROUP, 512, 2): return launch_workgroup<T, 512, 2, SOFTMAX>(p, stream);
+    case choice_key(ROW_PER_WORKGROUP, 512, 4): return launch_workgroup<T, 512, 4, SOFTMAX>(p, stream);
+    case choice_key(ROW_PER_WORKGROUP, 1024, 4): return launch_workgroup<T, 1024, 4, SOFTMAX>(p, stream);
+    case choice_key(ROW_PER_WORKGROUP, 1024, 8): return launch_workgroup<T, 1024, 8, SOFTMAX>(p, stream);
+    case choice_key(ROW_PER_WORKGROUP, 1024, 16): return launch_workgroup<T, 1024, 16, SOFTMAX>(p, stream);
+    case choice_key(ROW_STREAMED, 512, 2):
+      if constexpr (!SOFTMAX) return launch_streamed<T, 512, 2, SOFTMAX>(p, stream);
+      break;
+    case choice_key(ROW_STREAMED, 1024, 4): return launch_streamed<T, 1024, 4, SOFTMAX>(p, stream);
+  }
+  return hipErrorInvalidValue;  // (a choice that is not built)
 }
 
 template <bool SOFTMAX>
@@ -511,6 +557,22 @@ static bool span_ok(long long rows, long long ld) {
 }
 
 extern "C" {
+
+hidet_status_t hidet_row_schedule(int32_t dtype, int32_t softmax, int64_t rows, int64_t cols, hidet_row_schedule_t* out) {
+  if (dtype < 0 || dtype > 2 || rows <= 0 || cols < 0 || !out) return HIDET_ERR_INVALID_ARG;
+  if (cols > 0x7fffffffLL - 64) return HIDET_ERR_UNSUPPORTED;
+  const RowChoice c = choose_rows(elem_bytes(dtype), softmax != 0, rows, (int)cols);
+  out->form = c.form;
+  out->threads_per_row = c.threads;
+  out->chunks_per_thread = c.chunks;
+  out->workgroup_size = c.form == ROWS_PER_WAVEFRONT ? 256 : c.threads;
+  const long long rows_per_workgroup = out->workgroup_size / c.threads;
+  const long long limit = c.form == ROW_PER_WORKGROUP ? max_workgroups(c.threads) : kMaxBlocks;
+  const long long wanted = (rows - 1) / rows_per_workgroup + 1;
+  out->workgroups = wanted < limit ? wanted : limit;
+  out->launches = c.form == ROW_PER_WORKGROUP ? (wanted - 1) / limit + 1 : 1;
+  return HIDET_OK;
+}
 
 hidet_status_t hidet_reduce_rows(int32_t in, int32_t out, int32_t op, int64_t rows, int64_t cols, const void* x,
                                  int64_t ldx, void* y, void* stream) {

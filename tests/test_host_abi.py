@@ -267,6 +267,27 @@ def test_reduction_argument_validation():
     assert sm(rows=0, x=None, y=None) == 0 and sm(cols=0, ldx=0, ldy=0, x=None, y=None) == 0
 
 
+def _row_cols(dtype):
+    """Row lengths of every kernel form: 1, 8, ... 40000 chunks of 16 bytes, whole and ragged."""
+    vec = 4 if dtype == hb.HIDET_F32 else 8
+    return [c * vec - r for c in (1, 8, 64, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8191, 8192,
+                                  16384, 16385, 40000) for r in (0, 1)]
+
+
+@pytest.mark.parametrize("dtype", [hb.HIDET_F32, hb.HIDET_F16])
+@pytest.mark.parametrize("softmax", [0, 1])
+def test_row_launches_stay_below_the_limit_of_work_items(dtype, softmax):
+    """A launch of 2^32 work items is refused; 2^22 rows on workgroups of 1024 threads are exactly that many."""
+    for cols in _row_cols(dtype):
+        for rows in (1, 2 ** 22 - 1, 2 ** 22, 2 ** 22 + 1, 2 ** 23, 2 ** 24 - 1, 2 ** 24, 2 ** 24 + 1, 2 ** 30):
+            s = hb.hidet_row_schedule(dtype, softmax, rows, cols)
+            assert s["workgroups"] * s["workgroup_size"] < 2 ** 32, (rows, cols, s)
+            assert s["launches"] * s["workgroups"] >= (rows if s["form"] == 1 else 1), (rows, cols, s)
+    f = lambda *a: hb.lib().hidet_row_schedule(*a, ctypes.byref(hb.hidet_row_schedule_t()))
+    assert f(3, 0, 1, 1) == 1 and f(0, 0, 0, 1) == 1 and f(0, 0, 1, -1) == 1 and f(0, 0, 1, 2 ** 31) == 2
+    assert hb.lib().hidet_row_schedule(0, 0, 1, 1, None) == 1
+
+
 def test_probe_argument_validation():
     L = hb.lib()
     n = L.hidet_probe_scratch_bytes()
