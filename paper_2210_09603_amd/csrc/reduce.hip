@@ -474,8 +474,6 @@ hipError_t launch_streamed(const RowParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-constexpr long long kManyRows = 1LL << 22;
-
 int chunks_of(int elem_size, int cols) { return cols / (16 / elem_size) + (cols % (16 / elem_size) != 0); }
 
 RowChoice choose_rows(int elem_size, bool softmax, long long rows, int cols) {
@@ -490,18 +488,16 @@ RowChoice choose_rows(int elem_size, bool softmax, long long rows, int cols) {
   // idle (98304 x 512 fp32: 107 us against 75 us).  More threads with fewer chunks each are the better split of longer
   // rows (64 x 8192 bf16: 4.0 us on 256 threads, 3.6 us on 512), too many leave most of them idle (4096 x 8200: 28 us
   // on 512 threads, 39 us on 1024).
-  if (rows <= kManyRows) {
-    if (chunks <= 256) return {ROW_PER_WORKGROUP, 256, 1};
-    if (chunks <= 512) return {ROW_PER_WORKGROUP, 256, 2};
-    if (chunks <= 1024) return {ROW_PER_WORKGROUP, 512, 2};
-    if (chunks <= 2048) return {ROW_PER_WORKGROUP, 512, 4};
-    if (chunks <= 4096) return {ROW_PER_WORKGROUP, 1024, 4};
-    if (chunks < 8192) return {ROW_PER_WORKGROUP, 1024, 8};
-    // A reduction has nothing to keep: where two or more such workgroups per compute unit are waiting and the registers
-    // leave room for one, short-lived ones that stream read faster (1024 x 50304 fp32: 31.6 against 33.7 us).
-    if (!softmax && rows >= 512) return {ROW_STREAMED, 512, 2};
-    if (chunks <= 16384) return {ROW_PER_WORKGROUP, 1024, 16};
-  }
+  if (chunks <= 256) return {ROW_PER_WORKGROUP, 256, 1};
+  if (chunks <= 512) return {ROW_PER_WORKGROUP, 256, 2};
+  if (chunks <= 1024) return {ROW_PER_WORKGROUP, 512, 2};
+  if (chunks <= 2048) return {ROW_PER_WORKGROUP, 512, 4};
+  if (chunks <= 4096) return {ROW_PER_WORKGROUP, 1024, 4};
+  if (chunks < 8192) return {ROW_PER_WORKGROUP, 1024, 8};
+  // A reduction has nothing to keep: where two or more such workgroups per compute unit are waiting and the registers
+  // leave room for one, short-lived ones that stream read faster (1024 x 50304 fp32: 31.6 against 33.7 us).
+  if (!softmax && rows >= 512) return {ROW_STREAMED, 512, 2};
+  if (chunks <= 16384) return {ROW_PER_WORKGROUP, 1024, 16};
   // (the most threads and bytes in flight for one row: 90 x 500000 bf16 94 us, 143 us on 512 threads)
   return {ROW_STREAMED, 1024, 4};
 }

@@ -121,3 +121,38 @@ def test_conv_input_near_the_limit_and_output_beyond_2_31_elements():
     err = (num / den) ** 0.5
     print("  windows err %.3e" % err, flush=True)
     assert err <= TOL[dtype]
+
+
+def test_more_rows_than_one_launch_may_have():
+    """Row kernels with a workgroup per row: 2^32 work items are 16777216 workgroups of 256 threads, so more rows than
+    that run in two launches.  Rows on both sides of the cut (and elsewhere) hold one large element each."""
+    limit = (2 ** 32 - 1) // 256
+    rows, cols = limit + 6, 2051  # 257 chunks of 16 bytes, the last one ragged
+    for softmax in (0, 1):
+        s = hb.hidet_row_schedule(hb.HIDET_F16, softmax, rows, cols)
+        assert (s["form"], s["workgroup_size"], s["workgroups"], s["launches"]) == (1, 256, limit, 2), s
+    print("rows %d x %d" % (rows, cols), flush=True)
+    x = torch.zeros((rows, cols), dtype=torch.float16, device="cuda")  # 69 GB
+    marked = torch.cat([torch.arange(0, 3), torch.randint(3, limit - 8, (200,), generator=torch.Generator().manual_seed(7300)),
+                        torch.arange(limit - 5, rows, 2)]).unique().cuda()
+    x[marked, marked % cols] = 20.0
+    expected = torch.zeros(rows, dtype=torch.float32, device="cuda")
+    expected[marked] = 20.0
+    for op in (hb.HIDET_REDUCE_SUM, hb.HIDET_REDUCE_MAX):
+        y = torch.full((rows,), float("nan"), dtype=torch.float32, device="cuda")
+        hb.hidet_reduce_rows(x, y, op)
+        torch.cuda.synchronize()
+        assert torch.equal(y, expected), op
+    y16 = torch.full((rows,), float("nan"), dtype=torch.float16, device="cuda")
+    hb.hidet_reduce_rows(x, y16, hb.HIDET_REDUCE_SUM)
+    hb.hidet_softmax_rows(x, x)
+    torch.cuda.synchronize()
+    assert torch.equal(y16.float(), expected)
+    got = x[marked].float()
+    hit = torch.zeros_like(got)
+    hit[torch.arange(len(marked), device="cuda"), marked % cols] = 1.0
+    # (e^-20 is below half the smallest fp16 number)
+    assert torch.equal(got, hit)
+    plain = torch.cat([torch.arange(3, 6), torch.arange(limit - 6, rows, 2)]).cuda()
+    plain = plain[~torch.isin(plain, marked)]
+    assert len(plain) >= 4 and torch.allclose(x[plain].float(), torch.full((1, 1), 1.0 / cols, device="cuda"), rtol=1e-3, atol=0.0)

@@ -288,6 +288,17 @@ def test_row_launches_stay_below_the_limit_of_work_items(dtype, softmax):
     assert hb.lib().hidet_row_schedule(0, 0, 1, 1, None) == 1
 
 
+@pytest.mark.parametrize("dtype", [hb.HIDET_F32, hb.HIDET_F16])
+@pytest.mark.parametrize("softmax", [0, 1])
+def test_row_kernel_does_not_change_at_a_limit_of_the_launch(dtype, softmax):
+    """Millions of rows take the kernel that a million takes: only the number of launches grows."""
+    kernel = lambda s: (s["form"], s["threads_per_row"], s["chunks_per_thread"])
+    for cols in _row_cols(dtype):
+        million = kernel(hb.hidet_row_schedule(dtype, softmax, 2 ** 20, cols))
+        for rows in (2 ** 22, 2 ** 22 + 1, 2 ** 24 + 1, 2 ** 26):
+            assert kernel(hb.hidet_row_schedule(dtype, softmax, rows, cols)) == million, (rows, cols)
+
+
 def test_probe_argument_validation():
     L = hb.lib()
     n = L.hidet_probe_scratch_bytes()
