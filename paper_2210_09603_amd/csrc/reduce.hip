@@ -445,8 +445,10 @@ hipError_t launch_wavefront(const RowParams& p, hipStream_t stream) {
   if (blocks > kMaxBlocks) blocks = kMaxBlocks;
   if (p.cols % Chunk<T>::VEC == 0 && p.cols > 0)
     hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, false, SOFTMAX>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
-  else
+  else if constexpr (R <= 4)  // (longer ragged rows take a workgroup)
     hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, true, SOFTMAX>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -483,13 +485,28 @@ RowChoice choose_rows(int elem_size, bool softmax, long long rows, int cols) {
   if (chunks <= 32) return {ROWS_PER_WAVEFRONT, 32, 1};
   if (chunks <= 64) return {ROWS_PER_WAVEFRONT, 64, 1};
   if (chunks <= 128) return {ROWS_PER_WAVEFRONT, 64, 2};
-  // From here on a workgroup per row.  Against a wavefront per row it gains 10-20 % at thousands of rows and up to 2x at
-  // few rows (8192 x 4096 bf16: 32.5 -> 25.5 us; 200 x 2048: 3.9 -> 2.9 us); with 128 chunks half of 256 threads would
-  // idle (98304 x 512 fp32: 107 us against 75 us).  More threads with fewer chunks each are the better split of longer
-  // rows (64 x 8192 bf16: 4.0 us on 256 threads, 3.6 us on 512), too many leave most of them idle (4096 x 8200: 28 us
-  // on 512 threads, 39 us on 1024).
+  // Few rows: a workgroup per row has more loads in flight for each of them (200 x 2048 bf16: 3.9 -> 2.9 us).  With
+  // thousands of rows the compute units are full either way, and the threads that a row does not fill and the two
+  // barriers cost more than they give, so a wavefront per row is faster (65536 x 1152 fp16 softmax: 92 us on 256
+  // threads, 50 us on a wavefront; 16384 x 576 fp32 sum 10.8 and 6.7 us) -- up to 384 chunks, where the widened row begins
+  // to crowd the registers.  Reductions keep nothing after the sum and gain up to 512 chunks as long as the rows are not
+  // so many that memory alone decides (4096 x 1600 fp32: 5.2 and 3.9 us; 16384 x 2048 fp32: 21 us on either).
+  // Masks of a ragged length are paid by every lane: there it takes more rows and stops at 256 chunks (1024 x 1149 fp16
+  // softmax: 4.2 us on 256 threads, 4.7 us on a wavefront; 4096 rows 9.0 and 7.9 us).  An fp32 softmax beyond the
+  // Infinity Cache is bound by memory, which more threads use better (65536 x 1000: 90 us on 256 threads, 100 us on a
+  // wavefront), unless a quarter of them would have nothing to do (65536 x 768: 79 and 75 us).
+  const bool ragged = cols % (16 / elem_size) != 0;
+  int wavefront_chunks = ragged ? 256 : (!softmax && rows <= 8192) ? 512 : 384;
+  if (softmax && elem_size == 4 && rows >= 32768) wavefront_chunks = 192;
+  if (rows >= (ragged ? 2048 : 1024) && chunks <= wavefront_chunks)
+    return {ROWS_PER_WAVEFRONT, 64, chunks <= 256 ? 4 : 8};
   if (chunks <= 256) return {ROW_PER_WORKGROUP, 256, 1};
   if (chunks <= 512) return {ROW_PER_WORKGROUP, 256, 2};
+  // (513 chunks fill half of 512 threads with a second one: 4096 x 2052 fp32 softmax 14.2 us, 12.1 us on 256 threads
+  // with up to four each; below 512 rows the other way round, 3.5 and 3.7 us)
+  if (chunks <= 768 && rows >= 512) return {ROW_PER_WORKGROUP, 256, 4};
+  // More threads with fewer chunks each are the better split of longer rows (64 x 8192 bf16: 4.0 us on 256 threads, 3.6
+  // us on 512), too many leave most of them idle (4096 x 8200: 28 us on 512 threads, 39 us on 1024).
   if (chunks <= 1024) return {ROW_PER_WORKGROUP, 512, 2};
   if (chunks <= 2048) return {ROW_PER_WORKGROUP, 512, 4};
   if (chunks <= 4096) return {ROW_PER_WORKGROUP, 1024, 4};
@@ -517,8 +534,11 @@ hipError_t dispatch(const RowParams& p_in, hipStream_t stream) {
     case choice_key(ROWS_PER_WAVEFRONT, 32, 1): return launch_wavefront<T, 32, 1, SOFTMAX>(p, stream);
     case choice_key(ROWS_PER_WAVEFRONT, 64, 1): return launch_wavefront<T, 64, 1, SOFTMAX>(p, stream);
     case choice_key(ROWS_PER_WAVEFRONT, 64, 2): return launch_wavefront<T, 64, 2, SOFTMAX>(p, stream);
+    case choice_key(ROWS_PER_WAVEFRONT, 64, 4): return launch_wavefront<T, 64, 4, SOFTMAX>(p, stream);
+    case choice_key(ROWS_PER_WAVEFRONT, 64, 8): return launch_wavefront<T, 64, 8, SOFTMAX>(p, stream);
     case choice_key(ROW_PER_WORKGROUP, 256, 1): return launch_workgroup<T, 256, 1, SOFTMAX>(p, stream);
     case choice_key(ROW_PER_WORKGROUP, 256, 2): return launch_workgroup<T, 256, 2, SOFTMAX>(p, stream);
+    case choice_key(ROW_PER_WORKGROUP, 256, 4): return launch_workgroup<T, 256, 4, SOFTMAX>(p, stream);
     case choice_key(ROW_PER_WORKGROUP, 512, 2): return launch_workgroup<T, 512, 2, SOFTMAX>(p, stream);
     case choice_key(ROW_PER_WORKGROUP, 512, 4): return launch_workgroup<T, 512, 4, SOFTMAX>(p, stream);
     case choice_key(ROW_PER_WORKGROUP, 1024, 4): return launch_workgroup<T, 1024, 4, SOFTMAX>(p, stream);

@@ -234,3 +234,33 @@ def test_softmax_of_the_most_negative_finite_values(cols):
     torch.cuda.synchronize()
     assert torch.allclose(y[0], torch.full((cols,), 1.0 / cols, device="cuda"), rtol=1e-5, atol=0.0)
     assert y[1, 3] == 0.5 and y[1, 4] == 0.5 and y[1].sum() == 1.0
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_many_rows_of_medium_length(dtype):
+    """129 to 768 chunks with enough rows for a wavefront per row, and one row fewer (a workgroup per row): row count times
+    chunks at every boundary of the choice, whole and ragged, in and out of place."""
+    vec = 4 if dtype == "f32" else 8
+    g = wl.rng(9700)
+    for chunks, rows in ((129, 1023), (129, 1024), (192, 1025), (256, 1024), (257, 1024), (384, 1024), (385, 1024), (512, 1024),
+                         (513, 512), (768, 511), (768, 512)):
+        for cols in (chunks * vec, (chunks - 1) * vec + 1):
+            n = rows if cols % vec == 0 else 2 * rows
+            x = wl.to_storage((g.standard_normal((n, cols)) * 3).astype(np.float32), dtype)
+            x64 = wl.widen(x, dtype)
+            dx = to_gpu(x, dtype)
+            out = torch.full_like(dx, float("nan"))
+            hb.hidet_softmax_rows(dx, out)
+            y = {op: torch.full((n,), float("nan"), dtype=torch.float32, device="cuda")
+                 for op in (hb.HIDET_REDUCE_SUM, hb.HIDET_REDUCE_MEAN, hb.HIDET_REDUCE_MAX)}
+            for op in y:
+                hb.hidet_reduce_rows(dx, y[op], op)
+            hb.hidet_softmax_rows(dx, dx)
+            torch.cuda.synchronize()
+            ref = red.softmax_rows(x64)
+            assert within_bound(oracle.rel_frobenius(to_f64(out), ref), ref, dtype), (cols, n)
+            assert torch.equal(dx, out), (cols, n)
+            # fp32 sums of signed values: the bound is relative to the sum of magnitudes
+            assert np.all(np.abs(to_f64(y[hb.HIDET_REDUCE_SUM]) - x64.sum(1)) <= 1e-6 * np.abs(x64).sum(1)), (cols, n)
+            assert np.all(np.abs(to_f64(y[hb.HIDET_REDUCE_MEAN]) - x64.mean(1)) <= 1e-6 * np.abs(x64).mean(1)), (cols, n)
+            assert np.array_equal(to_f64(y[hb.HIDET_REDUCE_MAX]), x64.max(1)), (cols, n)

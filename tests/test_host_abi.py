@@ -299,6 +299,22 @@ def test_row_kernel_does_not_change_at_a_limit_of_the_launch(dtype, softmax):
             assert kernel(hb.hidet_row_schedule(dtype, softmax, rows, cols)) == million, (rows, cols)
 
 
+@pytest.mark.parametrize("dtype", [hb.HIDET_F32, hb.HIDET_F16])
+@pytest.mark.parametrize("softmax", [0, 1])
+def test_thousands_of_medium_rows_take_a_wavefront_each(dtype, softmax):
+    """129 to 384 chunks: a workgroup per row only where there are few of them (half of its threads have no chunk at 129)."""
+    vec = 4 if dtype == hb.HIDET_F32 else 8
+    form = lambda rows, cols: hb.hidet_row_schedule(dtype, softmax, rows, cols)["form"]
+    for chunks in (129, 150, 192, 250, 256, 257, 300, 384):
+        assert [form(r, chunks * vec) for r in (1, 64, 512, 1023)] == [1] * 4, chunks
+        assert [form(r, chunks * vec) for r in (1024, 8192, 32767)] == [0] * 3, chunks
+        # an fp32 softmax larger than the Infinity Cache keeps its 256 threads, unless a quarter of them would idle
+        assert form(2 ** 17, chunks * vec) == int(softmax and vec == 4 and chunks > 192), chunks
+        assert form(2047, chunks * vec - 1) == 1
+        assert form(2048, chunks * vec - 1) == int(chunks > 256), chunks
+    assert form(4096, 512 * vec) == softmax and form(8193, 512 * vec) == 1 and form(4096, 513 * vec) == 1
+
+
 def test_probe_argument_validation():
     L = hb.lib()
     n = L.hidet_probe_scratch_bytes()
