@@ -9,10 +9,11 @@
 //                with repeat(1, R): L lanes share one row, lane c of the group owns chunks c, c + L, ...;
 //                lanes combine with xor butterflies (L is a power of two).
 //   workgroup    workgroup = spatial(1, NT) over the chunks of one row composed with repeat(1, R): rows too
-//                long for one wavefront's registers, and long rows of which there are too few to give
+//                long for one wavefront's registers, and medium rows of which there are too few to give
 //                every compute unit several wavefronts.  The wavefronts' results meet in LDS.
-//   streamed     rows of more than 16384 chunks: one workgroup per row, a running (max, sum) pair per
-//                thread, merged through LDS; softmax re-reads the row (from L2 when it fits).
+//   streamed     rows of more than 16384 chunks, and reductions of many rows of more than 1024 whole (8192
+//                ragged) chunks: one workgroup per row, a running (max, sum) pair per thread, merged through
+//                LDS; softmax re-reads the row (from L2 when it fits).
 //
 // Chunks are accessed at element alignment (16-byte loads and stores take any element-aligned address
 // here), so rows of any length and leading dimension run the same way.  The last chunk of a row whose
@@ -332,7 +333,7 @@ __device__ __forceinline__ void merge(float& m, float& s, float m2, float s2) {
 }
 
 // U chunks of a thread are requested together.
-template <typename T, int NT, int U, bool SOFTMAX>
+template <typename T, int NT, int U, bool RAGGED, bool SOFTMAX>
 __global__ void __launch_bounds__(NT) long_rows_kernel(const RowParams p) {
   constexpr int VEC = Chunk<T>::VEC, NW = NT / 64;
   __shared__ float red_m[NW], red_s[NW];
@@ -348,14 +349,14 @@ __global__ void __launch_bounds__(NT) long_rows_kernel(const RowParams p) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int c = c0 + u * NT + tid;
-        raw[u] = load_raw<T, true>(xr, (c < chunks ? c : 0) * VEC, p.cols);
+        raw[u] = load_raw<T, RAGGED>(xr, (c < chunks ? c : 0) * VEC, p.cols);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int c = c0 + u * NT + tid;
         if (c >= chunks) continue;
         float v[VEC];
-        widen_masked<T, true>(raw[u], c * VEC, p.cols, false, fill, v);
+        widen_masked<T, RAGGED>(raw[u], c * VEC, p.cols, !RAGGED, fill, v);
         if (is_max) {
           float cm = v[0];
 #pragma unroll
@@ -412,10 +413,10 @@ __global__ void __launch_bounds__(NT) long_rows_kernel(const RowParams p) {
       // chunk are not used)
       for (int c = tid; c < chunks; c += NT) {
         float v[VEC];
-        widen_chunk<T>(load_raw<T, true>(xr, c * VEC, p.cols), v);
+        widen_chunk<T>(load_raw<T, RAGGED>(xr, c * VEC, p.cols), v);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) v[e] = __expf(v[e] - m) * inv;
-        store_chunk<T, true>(yr, c * VEC, p.cols, v);
+        store_chunk<T, RAGGED>(yr, c * VEC, p.cols, v);
       }
     } else if (tid == 0) {
       const float out = is_max ? m : (p.op == HIDET_REDUCE_MEAN ? s / (float)p.cols : s);
@@ -469,10 +470,10 @@ hipError_t launch_workgroup(const RowParams& p, hipStream_t stream) {
   return hipSuccess;
 }
 
-template <typename T, int NT, int U, bool SOFTMAX>
+template <typename T, int NT, int U, bool RAGGED, bool SOFTMAX>
 hipError_t launch_streamed(const RowParams& p, hipStream_t stream) {
   const long long blocks = p.rows < kMaxBlocks ? p.rows : kMaxBlocks;
-  hipLaunchKernelGGL((long_rows_kernel<T, NT, U, SOFTMAX>), dim3((unsigned)blocks), dim3(NT), 0, stream, p);
+  hipLaunchKernelGGL((long_rows_kernel<T, NT, U, RAGGED, SOFTMAX>), dim3((unsigned)blocks), dim3(NT), 0, stream, p);
   return hipGetLastError();
 }
 
@@ -505,14 +506,20 @@ RowChoice choose_rows(int elem_size, bool softmax, long long rows, int cols) {
   // (513 chunks fill half of 512 threads with a second one: 4096 x 2052 fp32 softmax 14.2 us, 12.1 us on 256 threads
   // with up to four each; below 512 rows the other way round, 3.5 and 3.7 us)
   if (chunks <= 768 && rows >= 512) return {ROW_PER_WORKGROUP, 256, 4};
+  // A reduction has nothing to keep after the sum.  From 512 rows on, two or more workgroups wait for every compute unit,
+  // and ones that stream whole chunks, with no register held for the row, read faster than those that hold it (16-bit
+  // rows of 2456 chunks: 1024 of them 8.9 us held by 1024 threads, 7.7 us streamed by 512; 8192 of them 54 and 50 us).
+  // Up to 2048 chunks this ends where memory alone decides (1024 rows of 1311 chunks: 4.9 and 4.1 us; 8192: 26.6 and
+  // 28.6 us).
+  if (!softmax && !ragged && rows >= 512 && chunks > 1024 && (chunks > 2048 || rows <= 2048)) return {ROW_STREAMED, 512, 4};
   // More threads with fewer chunks each are the better split of longer rows (64 x 8192 bf16: 4.0 us on 256 threads, 3.6
   // us on 512), too many leave most of them idle (4096 x 8200: 28 us on 512 threads, 39 us on 1024).
   if (chunks <= 1024) return {ROW_PER_WORKGROUP, 512, 2};
   if (chunks <= 2048) return {ROW_PER_WORKGROUP, 512, 4};
   if (chunks <= 4096) return {ROW_PER_WORKGROUP, 1024, 4};
   if (chunks < 8192) return {ROW_PER_WORKGROUP, 1024, 8};
-  // A reduction has nothing to keep: where two or more such workgroups per compute unit are waiting and the registers
-  // leave room for one, short-lived ones that stream read faster (1024 x 50304 fp32: 31.6 against 33.7 us).
+  // (ragged rows: the masks take registers, two chunks in flight are enough; 1024 rows of 10000 16-bit chunks 29 us, held
+  // 33 us)
   if (!softmax && rows >= 512) return {ROW_STREAMED, 512, 2};
   if (chunks <= 16384) return {ROW_PER_WORKGROUP, 1024, 16};
   // (the most threads and bytes in flight for one row: 90 x 500000 bf16 94 us, 143 us on 512 threads)
@@ -544,10 +551,13 @@ hipError_t dispatch(const RowParams& p_in, hipStream_t stream) {
     case choice_key(ROW_PER_WORKGROUP, 1024, 4): return launch_workgroup<T, 1024, 4, SOFTMAX>(p, stream);
     case choice_key(ROW_PER_WORKGROUP, 1024, 8): return launch_workgroup<T, 1024, 8, SOFTMAX>(p, stream);
     case choice_key(ROW_PER_WORKGROUP, 1024, 16): return launch_workgroup<T, 1024, 16, SOFTMAX>(p, stream);
-    case choice_key(ROW_STREAMED, 512, 2):
-      if constexpr (!SOFTMAX) return launch_streamed<T, 512, 2, SOFTMAX>(p, stream);
-      break;
-    case choice_key(ROW_STREAMED, 1024, 4): return launch_streamed<T, 1024, 4, SOFTMAX>(p, stream);
+    case choice_key(ROW_STREAMED, 1024, 4): return launch_streamed<T, 1024, 4, true, SOFTMAX>(p, stream);
+    default: break;
+  }
+  if constexpr (!SOFTMAX) switch (choice_key(c.form, c.threads, c.chunks)) {  // (without masks: chosen for whole rows only)
+    case choice_key(ROW_STREAMED, 512, 2): return launch_streamed<T, 512, 2, true, SOFTMAX>(p, stream);
+    case choice_key(ROW_STREAMED, 512, 4): return launch_streamed<T, 512, 4, false, SOFTMAX>(p, stream);
+    default: break;
   }
   return hipErrorInvalidValue;  // (a choice that is not built)
 }

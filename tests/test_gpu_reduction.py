@@ -223,6 +223,25 @@ def test_many_very_long_rows(dtype, rows):
     assert torch.equal(y.to(torch.int64), (x % 3).sum(1))
 
 
+@pytest.mark.parametrize("dtype,rows", [("f32", 512), ("f16", 520), ("bf16", 513)])
+def test_reductions_of_many_long_rows(dtype, rows):
+    """Streamed reductions: 1025 chunks to beyond 16384, whole and ragged, at every boundary of the choice of the threads."""
+    vec = 4 if dtype == "f32" else 8
+    buf = (torch.arange(rows * 16386 * vec, device="cuda", dtype=torch.int32) % 1021) % 3  # small integers: sums are exact
+    buf = buf.to(TORCH_DTYPE[dtype])
+    for chunks in (1025, 1500, 2048, 2049, 5000, 8191, 8192, 16384, 16385):
+        for cols in (chunks * vec, (chunks - 1) * vec + 1):
+            x = buf[: rows * cols].view(rows, cols)
+            x[rows - 1, cols - 1] = 5.0  # the last element, and an odd one out, are part of the row
+            total, top = x.to(torch.float64).sum(1), x.to(torch.float64).max(1).values
+            for op, ref in ((hb.HIDET_REDUCE_SUM, total), (hb.HIDET_REDUCE_MAX, top), (hb.HIDET_REDUCE_MEAN, total / cols)):
+                y = torch.full((rows,), float("nan"), dtype=torch.float32, device="cuda")
+                hb.hidet_reduce_rows(x, y, op)
+                torch.cuda.synchronize()
+                # (the mean is one fp32 division of an exact sum)
+                assert torch.allclose(y.double(), ref, rtol=2.0 ** -23 if op == hb.HIDET_REDUCE_MEAN else 0.0, atol=0.0), (cols, op)
+
+
 @pytest.mark.parametrize("cols", [33, 512, 5000, 60001])
 def test_softmax_of_the_most_negative_finite_values(cols):
     """Masks made of the lowest finite value: an exponential of the difference, not a difference of scaled values."""

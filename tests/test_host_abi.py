@@ -315,6 +315,17 @@ def test_thousands_of_medium_rows_take_a_wavefront_each(dtype, softmax):
     assert form(4096, 512 * vec) == softmax and form(8193, 512 * vec) == 1 and form(4096, 513 * vec) == 1
 
 
+def test_reductions_of_many_long_rows_are_streamed():
+    """Nothing of a row is needed after its sum: from 512 rows on, long rows of whole chunks are not held in registers."""
+    for dtype, vec in ((hb.HIDET_F32, 4), (hb.HIDET_F16, 8), (hb.HIDET_BF16, 8)):
+        form = lambda rows, chunks, r=0: hb.hidet_row_schedule(dtype, 0, rows, chunks * vec - r)["form"]
+        assert [form(r, 1311) for r in (511, 512, 2048, 2049)] == [1, 2, 2, 1]
+        for chunks in (2049, 2456, 4255, 8191, 8192, 15000, 16384):
+            assert [form(r, chunks) for r in (1, 511, 512, 2 ** 16)] == [1, 1, 2, 2], chunks
+            assert form(600, chunks, 1) == (2 if chunks >= 8192 else 1), chunks
+            assert hb.hidet_row_schedule(dtype, 1, 600, chunks * vec)["form"] == 1, chunks
+
+
 def test_probe_argument_validation():
     L = hb.lib()
     n = L.hidet_probe_scratch_bytes()
