@@ -351,7 +351,8 @@ hidet_status_t hidet_softmax_rows(int32_t dtype, int64_t rows, int64_t cols, con
 typedef struct {
   int32_t form;              /* 0: several rows or one per wavefront, 1: one row per workgroup, held in registers, 2: streamed */
   int32_t threads_per_row;   /* lanes or threads that share one row */
-  int32_t chunks_per_thread; /* 16-byte pieces of a row that each of them holds (streamed: has in flight) */
+  int32_t chunks_per_thread; /* 16-byte pieces of a row that each of them holds (streamed: has in flight); 0: the row is
+                                shorter than one, its first lane reads it element by element */
   int32_t workgroup_size;    /* threads */
   int64_t workgroups;        /* of the first, largest launch */
   int64_t launches;

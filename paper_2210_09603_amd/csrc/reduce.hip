@@ -53,23 +53,16 @@ struct Chunk {
 
 // The 16 bytes that hold the elements of chunk [col0, col0 + VEC) of a row: the chunk itself, or, where it would stick
 // out of the row at either end, the first or last 16 bytes of the row.  Always a valid address, so that the loads of all
-// of a thread's chunks can be in flight together.  Rows shorter than one chunk are collected element by element.
+// of a thread's chunks can be in flight together.  (Rows shorter than one chunk: load_short.)
 template <typename T>
 __device__ __forceinline__ int chunk_pos(int col0, int cols) {
   const int last = cols - Chunk<T>::VEC;
   const int pos = col0 < last ? col0 : last;
   return pos > 0 ? pos : 0;
 }
-template <typename T, bool RAGGED>
+template <typename T>
 __device__ __forceinline__ u32x4 load_raw(const T* row, int col0, int cols) {
-  constexpr int VEC = Chunk<T>::VEC;
-  if (!RAGGED || cols >= VEC)  // the same for the whole grid
-    return reinterpret_cast<const typename Chunk<T>::Raw*>(row + chunk_pos<T>(col0, cols))->v;
-  if (cols <= 0) return u32x4{0u, 0u, 0u, 0u};  // nothing may be read
-  T t[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) t[e] = row[e < cols ? e : 0];
-  return __builtin_bit_cast(u32x4, t);
+  return reinterpret_cast<const typename Chunk<T>::Raw*>(row + chunk_pos<T>(col0, cols))->v;
 }
 
 // Elements [lo, hi) of what load_raw returned belong to chunk [col0, col0 + VEC).
@@ -105,6 +98,28 @@ __device__ __forceinline__ void widen_masked(u32x4 raw, int col0, int cols, bool
 #pragma unroll
     for (int e = 0; e < Chunk<T>::VEC; ++e) v[e] = in ? v[e] : fill;
   }
+}
+
+// A row shorter than one chunk, element by element and by its first lane alone: with all lanes taking part, a sum over
+// 700000 rows of one fp16 element took 12.2 us, 8.0 us this way (softmax 20.5 and 14.0 us).
+template <typename T>
+__device__ __forceinline__ void load_short(const T* row, int sub, int cols, float fill, float* v) {
+#pragma unroll
+  for (int e = 0; e < Chunk<T>::VEC; ++e) v[e] = fill;
+  if (sub == 0 && cols > 0) {  // (cols == 0: nothing may be read)
+#pragma unroll
+    for (int e = 0; e < Chunk<T>::VEC; ++e) {
+      const bool in = e < cols;
+      const T t = row[in ? e : 0];
+      v[e] = in ? to_f32(t) : fill;
+    }
+  }
+}
+template <typename T>
+__device__ __forceinline__ void store_short(T* row, int cols, const float* v) {
+#pragma unroll
+  for (int e = 0; e < Chunk<T>::VEC; ++e)
+    if (e < cols) row[e] = from_f32<T>(v[e]);
 }
 
 // (a chunk that lies wholly outside the row stores nothing)
@@ -167,9 +182,12 @@ struct Tag {
 };
 
 // ---- the row lives in the registers of L lanes of a wavefront ----------------------------------------
-template <typename T, int L, int R, bool RAGGED, bool SOFTMAX>
+// SHAPE: WHOLE chunks, RAGGED rows of at least one chunk, SHORT ones of less.
+enum RowShape { WHOLE, RAGGED_END, SHORT };
+template <typename T, int L, int R, RowShape SHAPE, bool SOFTMAX>
 __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams p) {
   constexpr int VEC = Chunk<T>::VEC;
+  constexpr bool RAGGED = SHAPE != WHOLE;
   constexpr int G = 64 / L;  // rows per wavefront
   const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
   const int sub = lane % L;
@@ -178,13 +196,17 @@ __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams 
   const long long stride = (long long)gridDim.x * 4 * G;
   for (long long row = ((long long)blockIdx.x * 4 + wave) * G + lane / L; row < p.rows; row += stride) {
     const T* xr = reinterpret_cast<const T*>(p.x) + row * p.ldx;
-    u32x4 raw[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) raw[r] = load_raw<T, RAGGED>(xr, (r * L + sub) * VEC, p.cols);
     float v[R][VEC];
+    if constexpr (SHAPE == SHORT) {
+      load_short<T>(xr, sub, p.cols, fill, v[0]);
+    } else {
+      u32x4 raw[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-      widen_masked<T, RAGGED>(raw[r], (r * L + sub) * VEC, p.cols, (r + 1) * L * VEC <= p.cols, fill, v[r]);
+      for (int r = 0; r < R; ++r) raw[r] = load_raw<T>(xr, (r * L + sub) * VEC, p.cols);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        widen_masked<T, RAGGED>(raw[r], (r * L + sub) * VEC, p.cols, (r + 1) * L * VEC <= p.cols, fill, v[r]);
+    }
     float m = fill;
     if (is_max) {
 #pragma unroll
@@ -211,7 +233,10 @@ __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams 
         if (col0 < p.cols) {
 #pragma unroll
           for (int e = 0; e < VEC; ++e) v[r][e] *= inv;
-          store_chunk<T, RAGGED>(yr, col0, p.cols, v[r]);
+          if constexpr (SHAPE == SHORT)
+            store_short<T>(yr, p.cols, v[r]);
+          else
+            store_chunk<T, RAGGED>(yr, col0, p.cols, v[r]);
         }
       }
     } else {
@@ -255,7 +280,7 @@ __global__ void __launch_bounds__(NT, R <= 8 ? 8 : 4) rows_in_workgroup_kernel(c
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     raw[r] = u32x4{0u, 0u, 0u, 0u};
-    if (needed(r)) raw[r] = load_raw<T, RAGGED>(xr, col_of(r), p.cols);
+    if (needed(r)) raw[r] = load_raw<T>(xr, col_of(r), p.cols);
   }
   // the passes below must not share widened values or exponentials: what is kept in registers would double
   auto forget = [&]() {
@@ -349,7 +374,7 @@ __global__ void __launch_bounds__(NT) long_rows_kernel(const RowParams p) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int c = c0 + u * NT + tid;
-        raw[u] = load_raw<T, RAGGED>(xr, (c < chunks ? c : 0) * VEC, p.cols);
+        raw[u] = load_raw<T>(xr, (c < chunks ? c : 0) * VEC, p.cols);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -413,7 +438,7 @@ __global__ void __launch_bounds__(NT) long_rows_kernel(const RowParams p) {
       // chunk are not used)
       for (int c = tid; c < chunks; c += NT) {
         float v[VEC];
-        widen_chunk<T>(load_raw<T, RAGGED>(xr, c * VEC, p.cols), v);
+        widen_chunk<T>(load_raw<T>(xr, c * VEC, p.cols), v);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) v[e] = __expf(v[e] - m) * inv;
         store_chunk<T, RAGGED>(yr, c * VEC, p.cols, v);
@@ -432,7 +457,7 @@ enum RowForm { ROWS_PER_WAVEFRONT = 0, ROW_PER_WORKGROUP = 1, ROW_STREAMED = 2 }
 struct RowChoice {
   int form;
   int threads;  // that share one row
-  int chunks;   // each of them holds (streamed: requests together)
+  int chunks;   // each of them holds (streamed: requests together); 0: a row is shorter than one
 };
 
 // Workgroups of `threads` threads that one launch may have: work items are counted in 32 bits (a larger launch is
@@ -444,10 +469,12 @@ hipError_t launch_wavefront(const RowParams& p, hipStream_t stream) {
   constexpr int G = 64 / L;
   long long blocks = (p.rows + 4 * G - 1) / (4 * G);
   if (blocks > kMaxBlocks) blocks = kMaxBlocks;
-  if (p.cols % Chunk<T>::VEC == 0 && p.cols > 0)
-    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, false, SOFTMAX>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  if constexpr (R == 0)
+    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, 1, SHORT, SOFTMAX>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  else if (p.cols % Chunk<T>::VEC == 0)
+    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, WHOLE, SOFTMAX>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
   else if constexpr (R <= 4)  // (longer ragged rows take a workgroup)
-    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, true, SOFTMAX>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, RAGGED_END, SOFTMAX>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -481,6 +508,7 @@ int chunks_of(int elem_size, int cols) { return cols / (16 / elem_size) + (cols 
 
 RowChoice choose_rows(int elem_size, bool softmax, long long rows, int cols) {
   const int chunks = chunks_of(elem_size, cols);
+  if (cols < 16 / elem_size) return {ROWS_PER_WAVEFRONT, 8, 0};
   if (chunks <= 8) return {ROWS_PER_WAVEFRONT, 8, 1};
   if (chunks <= 16) return {ROWS_PER_WAVEFRONT, 16, 1};
   if (chunks <= 32) return {ROWS_PER_WAVEFRONT, 32, 1};
@@ -536,6 +564,7 @@ hipError_t dispatch(const RowParams& p_in, hipStream_t stream) {
   if (chunks <= 4096 || chunks >= 16384) p.shift = 0;
   const RowChoice c = choose_rows(sizeof(T), SOFTMAX, p.rows, p.cols);
   switch (choice_key(c.form, c.threads, c.chunks)) {
+    case choice_key(ROWS_PER_WAVEFRONT, 8, 0): return launch_wavefront<T, 8, 0, SOFTMAX>(p, stream);
     case choice_key(ROWS_PER_WAVEFRONT, 8, 1): return launch_wavefront<T, 8, 1, SOFTMAX>(p, stream);
     case choice_key(ROWS_PER_WAVEFRONT, 16, 1): return launch_wavefront<T, 16, 1, SOFTMAX>(p, stream);
     case choice_key(ROWS_PER_WAVEFRONT, 32, 1): return launch_wavefront<T, 32, 1, SOFTMAX>(p, stream);

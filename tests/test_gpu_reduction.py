@@ -283,3 +283,33 @@ def test_many_rows_of_medium_length(dtype):
             assert np.all(np.abs(to_f64(y[hb.HIDET_REDUCE_SUM]) - x64.sum(1)) <= 1e-6 * np.abs(x64).sum(1)), (cols, n)
             assert np.all(np.abs(to_f64(y[hb.HIDET_REDUCE_MEAN]) - x64.mean(1)) <= 1e-6 * np.abs(x64).mean(1)), (cols, n)
             assert np.array_equal(to_f64(y[hb.HIDET_REDUCE_MAX]), x64.max(1)), (cols, n)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_rows_shorter_than_one_access(dtype):
+    """Rows of fewer elements than 16 bytes hold: nothing beside them is read (NaN) or written, and an empty row is not read."""
+    vec = 4 if dtype == "f32" else 8
+    g = wl.rng(9800)
+    for cols in range(0, vec + 1):
+        rows, ld = 1001, cols + 2
+        x = wl.to_storage((g.standard_normal((rows, ld)) * 3).astype(np.float32), dtype)
+        x64 = wl.widen(x, dtype)[:, :cols]
+        dx = to_gpu(x, dtype)
+        dx[:, cols:] = float("nan")
+        out = torch.full_like(dx, 7.0)
+        hb.hidet_softmax_rows(dx[:, :cols], out[:, :cols])
+        y = {op: torch.full((rows,), 7.0, dtype=torch.float32, device="cuda")
+             for op in (hb.HIDET_REDUCE_SUM, hb.HIDET_REDUCE_MEAN, hb.HIDET_REDUCE_MAX)}
+        for op in y:
+            hb.hidet_reduce_rows(dx[:, :cols], y[op], op)
+        torch.cuda.synchronize()
+        assert torch.all(out[:, cols:] == 7.0), cols
+        if cols == 0:
+            assert torch.all(y[hb.HIDET_REDUCE_SUM] == 0) and torch.all(y[hb.HIDET_REDUCE_MAX] == -float("inf"))
+            assert torch.all(torch.isnan(y[hb.HIDET_REDUCE_MEAN]))
+            continue
+        ref = red.softmax_rows(x64)
+        assert within_bound(oracle.rel_frobenius(to_f64(out)[:, :cols], ref), ref, dtype), cols
+        assert np.all(np.abs(to_f64(y[hb.HIDET_REDUCE_SUM]) - x64.sum(1)) <= 1e-6 * np.abs(x64).sum(1)), cols
+        assert np.all(np.abs(to_f64(y[hb.HIDET_REDUCE_MEAN]) - x64.mean(1)) <= 1e-6 * np.abs(x64).mean(1)), cols
+        assert np.array_equal(to_f64(y[hb.HIDET_REDUCE_MAX]), x64.max(1)), cols

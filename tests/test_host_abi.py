@@ -315,6 +315,13 @@ def test_thousands_of_medium_rows_take_a_wavefront_each(dtype, softmax):
     assert form(4096, 512 * vec) == softmax and form(8193, 512 * vec) == 1 and form(4096, 513 * vec) == 1
 
 
+def test_rows_shorter_than_one_access_are_read_by_one_lane():
+    for dtype, vec in ((hb.HIDET_F32, 4), (hb.HIDET_F16, 8), (hb.HIDET_BF16, 8)):
+        for softmax in (0, 1):
+            held = [hb.hidet_row_schedule(dtype, softmax, 1000, cols)["chunks_per_thread"] for cols in range(0, vec + 2)]
+            assert held == [0] * vec + [1, 1]
+
+
 def test_reductions_of_many_long_rows_are_streamed():
     """Nothing of a row is needed after its sum: from 512 rows on, long rows of whole chunks are not held in registers."""
     for dtype, vec in ((hb.HIDET_F32, 4), (hb.HIDET_F16, 8), (hb.HIDET_BF16, 8)):
