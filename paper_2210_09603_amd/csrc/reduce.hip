@@ -205,7 +205,9 @@ __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams 
       for (int r = 0; r < R; ++r) raw[r] = load_raw<T>(xr, (r * L + sub) * VEC, p.cols);
 #pragma unroll
       for (int r = 0; r < R; ++r)
-        widen_masked<T, RAGGED>(raw[r], (r * L + sub) * VEC, p.cols, (r + 1) * L * VEC <= p.cols, fill, v[r]);
+        // (one whole chunk each: masking costs less than finding out that it need not be masked, 3.9 against 4.1 us for
+        // a sum of 100000 x 64 fp32)
+        widen_masked<T, RAGGED>(raw[r], (r * L + sub) * VEC, p.cols, (RAGGED || R > 1) && (r + 1) * L * VEC <= p.cols, fill, v[r]);
     }
     float m = fill;
     if (is_max) {
