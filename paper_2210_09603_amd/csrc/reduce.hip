@@ -520,15 +520,16 @@ RowChoice choose_rows(int elem_size, bool softmax, long long rows, int cols) {
   // thousands of rows the compute units are full either way, and the threads that a row does not fill and the two
   // barriers cost more than they give, so a wavefront per row is faster (65536 x 1152 fp16 softmax: 92 us on 256
   // threads, 50 us on a wavefront; 16384 x 576 fp32 sum 10.8 and 6.7 us) -- up to 384 chunks, where the widened row begins
-  // to crowd the registers.  Reductions keep nothing after the sum and gain up to 512 chunks as long as the rows are not
-  // so many that memory alone decides (4096 x 1600 fp32: 5.2 and 3.9 us; 16384 x 2048 fp32: 21 us on either).
+  // to crowd the registers.  Reductions keep nothing after the sum and gain up to 512 chunks (4096 x 1600 fp32: 5.2 and
+  // 3.9 us).  The more rows, the more memory alone decides, which 256 threads use better: up to 320 chunks (65536 x 1400
+  // fp32 sum 58 us on 256 threads, 64 us on a wavefront; 65536 x 1200 58 and 49 us), in an fp32 softmax, with half the
+  // arithmetic per byte, up to 256 (16384 x 1200: 29.9 and 31.4 us) and then 192 (65536 x 1000: 90 and 100 us, x 768: 79
+  // and 75 us).
   // Masks of a ragged length are paid by every lane: there it takes more rows and stops at 256 chunks (1024 x 1149 fp16
-  // softmax: 4.2 us on 256 threads, 4.7 us on a wavefront; 4096 rows 9.0 and 7.9 us).  An fp32 softmax beyond the
-  // Infinity Cache is bound by memory, which more threads use better (65536 x 1000: 90 us on 256 threads, 100 us on a
-  // wavefront), unless a quarter of them would have nothing to do (65536 x 768: 79 and 75 us).
+  // softmax: 4.2 us on 256 threads, 4.7 us on a wavefront; 4096 rows 9.0 and 7.9 us).
   const bool ragged = cols % (16 / elem_size) != 0;
-  int wavefront_chunks = ragged ? 256 : (!softmax && rows <= 8192) ? 512 : 384;
-  if (softmax && elem_size == 4 && rows >= 32768) wavefront_chunks = 192;
+  int wavefront_chunks = ragged ? 256 : rows >= 16384 ? 320 : softmax || rows > 8192 ? 384 : 512;
+  if (softmax && elem_size == 4 && rows >= 16384) wavefront_chunks = rows >= 32768 ? 192 : 256;
   if (rows >= (ragged ? 2048 : 1024) && chunks <= wavefront_chunks)
     return {ROWS_PER_WAVEFRONT, 64, chunks <= 256 ? 4 : 8};
   if (chunks <= 256) return {ROW_PER_WORKGROUP, 256, 1};

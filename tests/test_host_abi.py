@@ -307,9 +307,10 @@ def test_thousands_of_medium_rows_take_a_wavefront_each(dtype, softmax):
     form = lambda rows, cols: hb.hidet_row_schedule(dtype, softmax, rows, cols)["form"]
     for chunks in (129, 150, 192, 250, 256, 257, 300, 384):
         assert [form(r, chunks * vec) for r in (1, 64, 512, 1023)] == [1] * 4, chunks
-        assert [form(r, chunks * vec) for r in (1024, 8192, 32767)] == [0] * 3, chunks
-        # an fp32 softmax larger than the Infinity Cache keeps its 256 threads, unless a quarter of them would idle
-        assert form(2 ** 17, chunks * vec) == int(softmax and vec == 4 and chunks > 192), chunks
+        assert [form(r, chunks * vec) for r in (1024, 8192, 16383)] == [0] * 3, chunks
+        # the more rows, the more memory alone decides, an fp32 softmax first
+        assert form(16384, chunks * vec) == int(chunks > (256 if softmax and vec == 4 else 320)), chunks
+        assert form(2 ** 17, chunks * vec) == int(chunks > (192 if softmax and vec == 4 else 320)), chunks
         assert form(2047, chunks * vec - 1) == 1
         assert form(2048, chunks * vec - 1) == int(chunks > 256), chunks
     assert form(4096, 512 * vec) == softmax and form(8193, 512 * vec) == 1 and form(4096, 513 * vec) == 1
