@@ -273,6 +273,14 @@ hidet_status_t hidet_tune_conv2d_packed(int32_t in, int32_t out, int64_t Nb, int
                                         const hidet_epilogue_t* epi, void* workspace, int64_t workspace_bytes, void* stream,
                                         int32_t iters, int32_t* best_config, int32_t* best_slices, float* best_us);
 /*
+ * Test aid: the tile configuration that hidet_conv2d_implicit_gemm (packed = 0) or hidet_conv2d_implicit_gemm_packed
+ * (packed = 1) takes for dense, 16-byte aligned tensors of these sizes without an epilogue, when the caller names none
+ * and nothing has been tuned.  Runs nothing.  -1 for an empty output.  Fails as those calls do for sizes they refuse.
+ */
+hidet_status_t hidet_conv2d_untuned_config(int32_t in, int64_t Nb, int64_t IC, int64_t H, int64_t W, int64_t OC, int64_t KH,
+                                           int64_t KW, int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w,
+                                           int32_t packed, int32_t* config);
+/*
  * Workspace of the K-parallel convolution (Sections 5.2 and 6.3.4: the convolution is the matrix multiplication
  * with GEMM M = OC and GEMM N = Nb*OH*roundup(OW, 8), the padded-row column order of the img2col prologue):
  * bytes that hidet_conv2d_implicit_gemm_splitk needs for an output y[Nb][OC][OH][OW] cut into k_slices.

@@ -68,7 +68,7 @@ EXPORTS = (
     "hidet_conv2d_implicit_gemm_splitk", "hidet_tune_gemm_splitk", "hidet_tune_conv2d_splitk", "hidet_reduce_rows",
     "hidet_softmax_rows", "hidet_host_div", "hidet_conv2d_splitk_workspace_bytes", "hidet_static_scratch_bytes",
     "hidet_batched_gemm_splitk_static", "hidet_conv2d_pack_weights", "hidet_conv2d_implicit_gemm_packed",
-    "hidet_tune_conv2d_packed", "hidet_row_schedule",
+    "hidet_tune_conv2d_packed", "hidet_row_schedule", "hidet_conv2d_untuned_config",
 )
 
 _lib = None
@@ -113,6 +113,7 @@ def lib():
         L.hidet_host_div.argtypes = [_i64, _i32, ctypes.POINTER(_i32)]
         L.hidet_reduce_rows.argtypes = [_i32, _i32, _i32, _i64, _i64, _vp, _i64, _vp, _vp]
         L.hidet_softmax_rows.argtypes = [_i32, _i64, _i64, _vp, _i64, _vp, _i64, _vp]
+        L.hidet_conv2d_untuned_config.argtypes = [_i32] + [_i64] * 11 + [_i32, ctypes.POINTER(_i32)]
         L.hidet_row_schedule.argtypes = [_i32, _i32, _i64, _i64, ctypes.POINTER(hidet_row_schedule_t)]
         L.hidet_tune_last_times.argtypes = [ctypes.POINTER(ctypes.c_float), _i32]
         L.hidet_tune_clear.restype = None
@@ -460,6 +461,14 @@ def hidet_softmax_rows(x, y, stream=None):
     _, _, ldy = _rows_view(y)
     st = lib().hidet_softmax_rows(_dtype(x), rows, cols, _ptr(x), ldx, _ptr(y), ldy, _stream(stream))
     _check(st, "hidet_softmax_rows")
+
+
+def hidet_conv2d_untuned_config(dtype, x_shape, w_shape, stride=(1, 1), pad=(0, 0), packed=False):
+    """The configuration of a convolution (x NCHW, w OIHW) that names none, with nothing tuned; runs nothing."""
+    (Nb, IC, H, W), (OC, _, KH, KW), config = x_shape, w_shape, _i32(-1)
+    _check(lib().hidet_conv2d_untuned_config(dtype, Nb, IC, H, W, OC, KH, KW, stride[0], stride[1], pad[0], pad[1], int(packed),
+                                             ctypes.byref(config)), "hidet_conv2d_untuned_config")
+    return config.value
 
 
 def hidet_row_schedule(dtype, softmax, rows, cols):

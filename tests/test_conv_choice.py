@@ -1,0 +1,29 @@
+"""The tile configuration that a convolution gets when it names none, as the size-based rule settles it on the host."""
+import ctypes
+
+import pytest
+
+from paper_2210_09603_amd import binding as hb
+
+
+def chosen(Nb, IC, H, W, OC, k, s, pad, packed=False, dtype=hb.HIDET_F16):
+    """(rows, columns, K tile, matrix-core shape, schedule) of the tile."""
+    c = hb.hidet_conv2d_untuned_config(dtype, (Nb, IC, H, W), (OC, IC, k, k), (s, s), (pad, pad), packed)
+    i = hb.hidet_config_info(c)
+    return i["block_m"], i["block_n"], i["block_k"], i["mfma"], i["schedule"]
+
+
+@pytest.mark.parametrize("Nb,IC,H,OC,s", [(8, 16, 112, 24, 2), (2, 3, 224, 32, 2), (2, 3, 112, 24, 1), (8, 256, 112, 32, 2)])
+def test_few_channels_and_many_columns_do_not_take_the_single_wavefront(Nb, IC, H, OC, s):
+    """392 tiles of 64 columns: not enough for 64-column tiles of 32 rows, so it is the 32x32 tile of four wavefronts."""
+    bm, bn, bk, mfma, schedule = chosen(Nb, IC, H, H, OC, 3, s, 1)
+    assert (bm, bn, mfma) == (32, 32, 16)
+
+
+def test_untuned_config_arguments():
+    f = lambda *a: hb.lib().hidet_conv2d_untuned_config(*a, ctypes.byref(c))
+    c = ctypes.c_int32(7)
+    assert f(hb.HIDET_F16, 0, 8, 4, 4, 8, 1, 1, 1, 1, 0, 0, 0) == 0 and c.value == -1  # empty
+    assert f(9, 1, 8, 4, 4, 8, 1, 1, 1, 1, 0, 0, 0) == 1 and f(hb.HIDET_F16, 1, 8, 4, 4, 8, 0, 1, 1, 1, 0, 0, 0) == 1
+    assert f(hb.HIDET_F16, 1, 7, 14, 14, 8, 3, 3, 1, 1, 1, 1, 1) == 2  # repacked weights need whole chunks of channels
+    assert hb.lib().hidet_conv2d_untuned_config(hb.HIDET_F16, 1, 8, 4, 4, 8, 1, 1, 1, 1, 0, 0, 0, None) == 1
