@@ -335,9 +335,12 @@ LaunchFn find_partial_launcher(const Problem& pr, int config) {
 // mostly output, not padding, and on a short K (fill and drain of the pipeline count) they need the round nearly full,
 // or lose to small tiles that share a compute unit (128x28x28, 7 images, K = 1152: 64x64 18 us, 128x64 17 us, two
 // 64x32 tiles of the two-stage form 15 us); the largest need half a round in any case (repacked weights allow only K tiles
-// that divide IC: 5 images of 128x27x27, 5x5: 68 tiles of 128x64 33 us, 270 of 64x32 28 us).  -1: none fits.
+// that divide IC: 5 images of 128x27x27, 5x5: 68 tiles of 128x64 33 us, 270 of 64x32 28 us).  On a long K the 64x64 tile
+// may be half padding: what it competes with there are two-stage tiles (36 images of 512x13x13, 80 channels, 3x3: 36 us
+// on 234 of them, 59 us on 351 two-stage tiles of 32x64).  -1: none fits.
+constexpr long long kConvLongK = 2048;
 int one_round_config(const Problem& pr) {
-  constexpr long long kComputeUnits = 256, kLongK = 2048;
+  constexpr long long kComputeUnits = 256;
   const long long M = pr.p.M, N = pr.p.N;
   int best = -1;
   long long best_area = 0;
@@ -347,9 +350,11 @@ int one_round_config(const Problem& pr) {
     const long long area = (long long)r.bm * r.bn;
     const long long tiles = ((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
     if (tiles > kComputeUnits || tiles < kComputeUnits / 4) continue;
-    if (area >= 64 * 64) {
+    if (area == 64 * 64 && pr.p.K >= kConvLongK) {
+      if (2 * M * N < tiles * area) continue;
+    } else if (area >= 64 * 64) {
       if (4 * M * N < 3 * tiles * area) continue;
-      if (pr.p.K < kLongK && (area == 64 * 64 || tiles < kComputeUnits * 3 / 4)) continue;
+      if (pr.p.K < kConvLongK && (area == 64 * 64 || tiles < kComputeUnits * 3 / 4)) continue;
       if (area > 64 * 64 && tiles < kComputeUnits / 2) continue;
     }
     // (of two tiles of one size the taller one: it gathers fewer columns)

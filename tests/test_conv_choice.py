@@ -20,6 +20,12 @@ def test_few_channels_and_many_columns_do_not_take_the_single_wavefront(Nb, IC, 
     assert (bm, bn, mfma) == (32, 32, 16)
 
 
+def test_half_padded_tiles_split_a_long_k_in_one_round():
+    """72 and 80 channels leave a 64x64 tile less than three quarters full; one round of them is still the best there is."""
+    for case in ((36, 512, 13, 13, 80, 3, 1, 1), (7, 512, 56, 56, 80, 5, 2, 2), (2, 128, 56, 56, 72, 5, 1, 2)):
+        assert chosen(*case)[:2] == (64, 64) and chosen(*case)[4] == 3, case
+
+
 def test_untuned_config_arguments():
     f = lambda *a: hb.lib().hidet_conv2d_untuned_config(*a, ctypes.byref(c))
     c = ctypes.c_int32(7)
