@@ -413,8 +413,11 @@ int default_config(const Problem& pr, int slices = 1) {
     }
     const long long tiles = ((M + r.bm - 1) >> __builtin_ctz(r.bm)) * ((N + r.bn - 1) >> __builtin_ctz(r.bn));
     const long long blocks = sat_mul(tiles, pr.batch * (slices > 1 ? slices : 1));
-    // (a convolution: what one round of them can do has been decided above)
-    if (conv16 && r.sched == 3 && (blocks > 256 || (pr.p.K >= 512 && (long long)r.bm * r.bn >= 64 * 64))) {
+    // (a convolution: what one round of them can do has been decided above; the small ones, of which a compute unit holds
+    // two, still win a little beyond it for few channels on a long K: 43 images of 512x28x28, 24 channels, 3x3, stride 2:
+    // 41 us on 301 of 32x32, 50 us on two-stage tiles)
+    const long long resident = conv16 && M <= 32 && r.bm * r.bn <= 32 * 32 && pr.p.K >= kConvLongK ? 640 : 256;
+    if (conv16 && r.sched == 3 && (blocks > resident || (pr.p.K >= 512 && (long long)r.bm * r.bn >= 64 * 64))) {
       passed_over = c;
       continue;
     }

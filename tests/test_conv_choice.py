@@ -26,6 +26,13 @@ def test_half_padded_tiles_split_a_long_k_in_one_round():
         assert chosen(*case)[:2] == (64, 64) and chosen(*case)[4] == 3, case
 
 
+def test_small_k_splitting_tiles_a_little_beyond_one_round():
+    """Two workgroups of a small K-splitting tile are resident together: 301 of them are no second round."""
+    for case in ((43, 512, 28, 28, 24, 3, 2, 1), (23, 256, 17, 17, 24, 7, 1, 3), (39, 384, 28, 28, 8, 5, 2, 2)):
+        assert chosen(*case)[0] * chosen(*case)[1] <= 32 * 32 and chosen(*case)[4] == 3, case
+    assert chosen(64, 64, 56, 56, 64, 3, 1, 1)[4] != 3  # (a throughput problem)
+
+
 def test_untuned_config_arguments():
     f = lambda *a: hb.lib().hidet_conv2d_untuned_config(*a, ctypes.byref(c))
     c = ctypes.c_int32(7)
