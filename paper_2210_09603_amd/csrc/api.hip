@@ -446,12 +446,15 @@ int default_config(const Problem& pr, int slices = 1) {
     // a K of at most two stages runs the two-slot ring: two workgroups of a 256x128 tile share a compute unit and
     // outrun one of a 256x256 tile
     if (ring && pr.p.K <= 2 * r.bk && area == 256 * 128) key += weight * (3LL << 22);
-    if (blocks >= enough && key > best_key) {
+    // (the gather is paid once per row of tiles, so a flat tile is the last resort of a convolution of more rows: 7 images
+    // of 192x28x28, 72 channels, 3x3: 26.5 us on three rows of 32x64 tiles, 20 us on two of 64x32)
+    const bool flat = conv16 && M > 64 && r.bm < 64 && r.bn >= 64;
+    if (blocks >= enough && key > best_key && !flat) {
       best = c;
       best_key = key;
     }
     // second choice when no tile gives that many workgroups: the same order among the tiles that still give 64
-    if (blocks >= 64 && key > fewer_key) {
+    if (blocks >= 64 && key > fewer_key && !flat) {
       fewer = c;
       fewer_key = key;
     }

@@ -33,6 +33,12 @@ def test_small_k_splitting_tiles_a_little_beyond_one_round():
     assert chosen(64, 64, 56, 56, 64, 3, 1, 1)[4] != 3  # (a throughput problem)
 
 
+def test_more_than_64_channels_do_not_take_flat_tiles():
+    """Every row of tiles gathers the same columns again: three rows of 32x64 tiles against two of 64x32."""
+    for case in ((7, 192, 28, 28, 72, 3, 1, 1), (2, 32, 56, 56, 96, 7, 1, 3), (9, 160, 20, 20, 160, 3, 1, 1)):
+        assert chosen(*case)[:2] == (64, 32), case
+
+
 def test_untuned_config_arguments():
     f = lambda *a: hb.lib().hidet_conv2d_untuned_config(*a, ctypes.byref(c))
     c = ctypes.c_int32(7)
