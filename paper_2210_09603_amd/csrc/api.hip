@@ -19,7 +19,7 @@ using namespace hidet;
 // Table of contents of the schedule space + the launchers registered by the instance objects.
 // ------------------------------------------------------------------------------------------------
 #define HIDET_ALL
-static const ConfigRow kConfigs[] = {
+static constexpr ConfigRow kConfigs[] = {
 #define X16(idx, BM, BN, BK, WM, WN, MI, TA, SC) {idx, BM, BN, BK, WM, WN, MI, TA, SC, 0},
 #define X32(idx, BM, BN, BK, WM, WN, MI, TA, SC) {idx, BM, BN, BK, WM, WN, MI, TA, SC, 1},
 #include "configs.def"
@@ -56,6 +56,12 @@ static const Registry& registry() {
 #undef HIDET_ALL
 
 static_assert(sizeof(kConfigs) / sizeof(kConfigs[0]) <= kMaxConfigs, "raise kMaxConfigs");
+static constexpr bool tile_extents_are_powers_of_two() {
+  for (const ConfigRow& r : kConfigs)
+    if ((r.bm & (r.bm - 1)) != 0 || (r.bn & (r.bn - 1)) != 0) return false;
+  return true;
+}
+static_assert(tile_extents_are_powers_of_two(), "the size-based choice shifts by the logarithm of a tile extent");
 
 // ------------------------------------------------------------------------------------------------
 // Problem description shared by GEMM, batched GEMM and conv.

@@ -1,9 +1,13 @@
 """The tile configuration that a convolution gets when it names none, as the size-based rule settles it on the host."""
 import ctypes
+import os
+import shutil
+import subprocess
 
 import pytest
 
 from paper_2210_09603_amd import binding as hb
+from paper_2210_09603_amd import build
 
 
 def chosen(Nb, IC, H, W, OC, k, s, pad, packed=False, dtype=hb.HIDET_F16):
@@ -46,3 +50,24 @@ def test_untuned_config_arguments():
     assert f(9, 1, 8, 4, 4, 8, 1, 1, 1, 1, 0, 0, 0) == 1 and f(hb.HIDET_F16, 1, 8, 4, 4, 8, 0, 1, 1, 1, 0, 0, 0) == 1
     assert f(hb.HIDET_F16, 1, 7, 14, 14, 8, 3, 3, 1, 1, 1, 1, 1) == 2  # repacked weights need whole chunks of channels
     assert hb.lib().hidet_conv2d_untuned_config(hb.HIDET_F16, 1, 8, 4, 4, 8, 1, 1, 1, 1, 0, 0, 0, None) == 1
+
+
+@pytest.mark.parametrize("tile", ["96, 64", "64, 192"])
+def test_tile_extents_that_are_no_power_of_two_do_not_compile(tmp_path, tile):
+    """The choice counts tiles with shifts: a table with another extent has to fail to compile, not to miscount."""
+    csrc = tmp_path / "package" / "csrc"
+    shutil.copytree(build.CSRC, csrc)
+    shutil.copytree(os.path.join(build.HERE, "..", "include"), tmp_path / "include")
+    table = (csrc / "configs.def").read_text()
+    assert "X16(5, 128, 64," in table
+
+    def compiles():
+        cmd = [build.HIPCC, "--offload-arch=gfx950", "--cuda-host-only", "-std=c++17", "-fsyntax-only", str(csrc / "api.hip")]
+        r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        return r.returncode == 0, r.stdout
+
+    ok, log = compiles()
+    assert ok, log
+    (csrc / "configs.def").write_text(table.replace("X16(5, 128, 64,", "X16(5, %s," % tile))
+    ok, log = compiles()
+    assert not ok and "tile_extents_are_powers_of_two" in log, log
