@@ -436,10 +436,12 @@ int default_config(const Problem& pr, int slices = 1) {
     // still the better choice; from 128 down the smaller tile fits into one round and wins.
     const long long area = (long long)r.bm * r.bn;
     const bool self_overlapping = ring_any && pr.p.K >= 128;
-    // A convolution outside the rule above takes 64x64 tiles only where every compute unit gets more than one (7 images
-    // of 64x56x56, 5x5: 64x64 tiles 26.5 us, 64x32 21.8 us; 9 images of 128x28x28, 3x3: 18.3 us and 14.8 us).  From
-    // 64x32 down one round is enough (18 images of 128x28x28 repacked, stride 2: 64x32 13.5 us, 32x32 15.4 us).
-    const long long enough = throughput ? (self_overlapping ? 129 : 400) : (conv16 && area >= 64 * 64) ? 400 : 192;
+    const long long enough = !throughput ? 192 : self_overlapping ? 129 : 400;
+    // Tiles of 64x64 and more are no first choice of a convolution outside the rule above that is bound by latency (fewer
+    // than 384 of them: 7 images of 64x56x56, 5x5: 343 tiles of 64x64 26.5 us, 64x32 21.8 us; 9 images of 128x28x28, 3x3:
+    // 18.3 us and 14.8 us).  From 64x32 down one round is enough (18 images of 128x28x28 repacked, stride 2: 64x32 13.5
+    // us, 32x32 15.4 us).
+    const bool large = conv16 && !throughput && area >= 64 * 64;
 
     // useful outputs per workgroup, discounted by the share of the tile that is padding, decide; then the smaller
     // tile, then the schedule preferences
@@ -455,7 +457,7 @@ int default_config(const Problem& pr, int slices = 1) {
     // (the gather is paid once per row of tiles, so a flat tile is the last resort of a convolution of more rows: 7 images
     // of 192x28x28, 72 channels, 3x3: 26.5 us on three rows of 32x64 tiles, 20 us on two of 64x32)
     const bool flat = conv16 && M > 64 && r.bm < 64 && r.bn >= 64;
-    if (blocks >= enough && key > best_key && !flat) {
+    if (blocks >= enough && key > best_key && !flat && !large) {
       best = c;
       best_key = key;
     }
