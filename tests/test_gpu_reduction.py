@@ -180,35 +180,66 @@ def test_stream_bandwidth_probe_reports_plausible_rates():
         hb.hidet_probe_stream_bandwidth(ring[: 100 << 20], 0)
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 def test_rows_at_the_edges_of_the_kernels(dtype):
-    """Row lengths on both sides of every boundary between the kernels (64, 128, 256, ... 16384 chunks of 16 bytes), with
-    whole and ragged last chunks, in and out of place, rows aligned and not.  Same bounds as the tests above."""
+    """Row lengths on both sides of every boundary between the kernels (64, 128, 256, ... 16384 chunks of 16 bytes; the one
+    before 8192 lies at 8191 and 8192), with whole and ragged last chunks, in and out of place, rows aligned and not.  Same
+    bounds as the tests above."""
     vec = 4 if dtype == "f32" else 8
     g = wl.rng(9600)
-    for chunks in (8, 16, 32, 64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384):
+    for chunks in (8, 16, 32, 64, 128, 256, 512, 768, 1024, 2048, 4096, 6283, 8191, 8192, 16383, 16384):
         for cols in (chunks * vec, chunks * vec - 1, chunks * vec + 1, (chunks - 1) * vec + 1):
             for ld in (cols, cols + 3):
                 rows = 3
                 x = wl.to_storage((g.standard_normal((rows, ld)) * 3).astype(np.float32), dtype)
                 dx = to_gpu(x, dtype)
-                ref = red.softmax_rows(wl.widen(x, dtype)[:, :cols])
+                x64 = wl.widen(x, dtype)[:, :cols]
+                ref = red.softmax_rows(x64)
                 out = torch.full((rows, ld), 7.0, dtype=TORCH_DTYPE[dtype], device="cuda")
                 hb.hidet_softmax_rows(dx[:, :cols], out[:, :cols])
-                y32 = torch.full((rows,), float("nan"), dtype=torch.float32, device="cuda")
-                hb.hidet_reduce_rows(dx[:, :cols], y32, hb.HIDET_REDUCE_SUM)
-                ymax = torch.full_like(y32, float("nan"))
-                hb.hidet_reduce_rows(dx[:, :cols], ymax, hb.HIDET_REDUCE_MAX)
+                y = {op: torch.full((rows,), float("nan"), dtype=torch.float32, device="cuda")
+                     for op in (hb.HIDET_REDUCE_SUM, hb.HIDET_REDUCE_MEAN, hb.HIDET_REDUCE_MAX)}
+                for op in y:
+                    hb.hidet_reduce_rows(dx[:, :cols], y[op], op)
                 torch.cuda.synchronize()
-                x64 = wl.widen(x, dtype)[:, :cols]
                 assert within_bound(oracle.rel_frobenius(to_f64(out)[:, :cols], ref), ref, dtype), (cols, ld)
                 assert torch.all(out[:, cols:] == 7.0), (cols, ld)
                 # fp32 sums of signed values: the bound is relative to the sum of magnitudes
-                assert np.all(np.abs(to_f64(y32) - x64.sum(1)) <= 1e-6 * np.abs(x64).sum(1)), (cols, ld)
-                assert np.array_equal(to_f64(ymax), x64.max(1)), (cols, ld)
+                assert np.all(np.abs(to_f64(y[hb.HIDET_REDUCE_SUM]) - x64.sum(1)) <= 1e-6 * np.abs(x64).sum(1)), (cols, ld)
+                assert np.all(np.abs(to_f64(y[hb.HIDET_REDUCE_MEAN]) - x64.mean(1)) <= 1e-6 * np.abs(x64).mean(1)), (cols, ld)
+                assert np.array_equal(to_f64(y[hb.HIDET_REDUCE_MAX]), x64.max(1)), (cols, ld)
                 hb.hidet_softmax_rows(dx[:, :cols], dx[:, :cols])  # in place
                 torch.cuda.synchronize()
                 assert torch.equal(dx[:, :cols], out[:, :cols]), (cols, ld)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_shifted_chunks_of_long_softmax_rows(dtype):
+    """Rows of 4097 to 16383 chunks whose output is not 16-byte aligned are cut on the output's own 16-byte grid, which may
+    take one chunk more: the longest rows that each kernel holds, at every offset of the output, with a prefix of -inf, a row
+    of -inf alone and a NaN; nothing beside the rows is written."""
+    vec = 4 if dtype == "f32" else 8
+    g = wl.rng(9900)
+    for chunks in (4097, 6283, 8191, 8192, 16383):
+        for cols in (chunks * vec, (chunks - 1) * vec + 1):
+            rows, ld = 4, cols + 1 + cols % 2  # (an odd step: the offset within 16 bytes differs from row to row)
+            x = wl.to_storage((g.standard_normal((rows, cols)) * 3).astype(np.float32), dtype)
+            x64 = wl.widen(x, dtype)
+            x64[1, : cols // 3] = -np.inf
+            x64[2, :] = -np.inf
+            x64[3, cols - 2] = np.nan
+            dx = torch.from_numpy(x64).to(TORCH_DTYPE[dtype]).cuda()
+            for offset in (0, 1, vec - 1):
+                buf = torch.full((offset + rows * ld + 16,), 7.0, dtype=TORCH_DTYPE[dtype], device="cuda")
+                out = buf[offset: offset + rows * ld].view(rows, ld)
+                hb.hidet_softmax_rows(dx, out[:, :cols])
+                torch.cuda.synchronize()
+                got = to_f64(out)[:, :cols]
+                ref = red.softmax_rows(x64[:2])
+                assert within_bound(oracle.rel_frobenius(got[:2], ref), ref, dtype), (cols, offset)
+                assert np.all(got[1, : cols // 3] == 0.0) and np.all(np.isnan(got[2:])), (cols, offset)
+                assert torch.all(out[:, cols:] == 7.0) and torch.all(buf[:offset] == 7.0), (cols, offset)
+                assert torch.all(buf[offset + rows * ld:] == 7.0), (cols, offset)
 
 
 @pytest.mark.parametrize("dtype,rows", [("f32", 600), ("bf16", 520)])
