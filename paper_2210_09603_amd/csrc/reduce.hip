@@ -304,14 +304,19 @@ __global__ void __launch_bounds__(NT, R <= 8 ? 8 : 4) rows_in_workgroup_kernel(c
       }
     }
   }
-  // a value from every wavefront, combined in wavefront order
+  // a value from every wavefront, combined in a tree: one after another, every addition would round at the size of the
+  // whole (sums of 700 rows of 9001 fp32 differ from 64 bits by 4.7e-8 in the norm, by 6.8e-8 one after another)
   auto across = [&](int slot, float x, bool max) {
     if (lane == 0) red[slot][wave] = x;
     __syncthreads();
-    float t = red[slot][0];
+    float t[NW];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) t = max ? fmaxf(t, red[slot][w]) : t + red[slot][w];
-    return t;
+    for (int w = 0; w < NW; ++w) t[w] = red[slot][w];
+#pragma unroll
+    for (int n = NW / 2; n >= 1; n /= 2)
+#pragma unroll
+      for (int w = 0; w < n; ++w) t[w] = max ? fmaxf(t[w], t[w + n]) : t[w] + t[w + n];
+    return t[0];
   };
   if (is_max) m = across(0, group_max<64>(m), true);
   if constexpr (SOFTMAX) {
@@ -421,17 +426,26 @@ __global__ void __launch_bounds__(NT) long_rows_kernel(const RowParams p) {
       red_s[wave] = s;
     }
     __syncthreads();
-    m = red_m[0];
-    s = red_s[0];
+    // (in a tree, as in the kernel above)
+    float mw[NW], sw[NW];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) {
-      if constexpr (SOFTMAX)
-        merge(m, s, red_m[w], red_s[w]);
-      else {
-        m = fmaxf(m, red_m[w]);
-        s += red_s[w];
-      }
+    for (int w = 0; w < NW; ++w) {
+      mw[w] = red_m[w];
+      sw[w] = red_s[w];
     }
+#pragma unroll
+    for (int n = NW / 2; n >= 1; n /= 2)
+#pragma unroll
+      for (int w = 0; w < n; ++w) {
+        if constexpr (SOFTMAX)
+          merge(mw[w], sw[w], mw[w + n], sw[w + n]);
+        else {
+          mw[w] = fmaxf(mw[w], mw[w + n]);
+          sw[w] += sw[w + n];
+        }
+      }
+    m = mw[0];
+    s = sw[0];
     if constexpr (SOFTMAX) {
       const float inv = 1.0f / s;
       T* yr = reinterpret_cast<T*>(p.y) + row * p.ldy;

@@ -344,3 +344,35 @@ def test_rows_shorter_than_one_access(dtype):
         assert np.all(np.abs(to_f64(y[hb.HIDET_REDUCE_SUM]) - x64.sum(1)) <= 1e-6 * np.abs(x64).sum(1)), cols
         assert np.all(np.abs(to_f64(y[hb.HIDET_REDUCE_MEAN]) - x64.mean(1)) <= 1e-6 * np.abs(x64).mean(1)), cols
         assert np.array_equal(to_f64(y[hb.HIDET_REDUCE_MAX]), x64.max(1)), cols
+
+
+@pytest.mark.parametrize("rows,cols", [(6, 1000), (6, 4100), (6, 12000), (6, 70000), (600, 6000), (520, 33001)])
+def test_sums_of_the_wavefronts_meet_in_a_tree(rows, cols):
+    """2^24 in the chunks of the first wavefront, 1 in those of every other one.  Added in a tree of log2(wavefronts) levels
+    a sum rounds once a level, by at most 1 (half a unit of [2^24, 2^25)); one after another it loses every 1."""
+    s = hb.hidet_row_schedule(hb.HIDET_F32, 0, rows, cols)
+    assert s["form"] > 0
+    waves = s["workgroup_size"] // 64
+    x = torch.zeros(rows, cols, device="cuda")
+    x[:, 0] = 2.0 ** 24
+    for w in range(1, waves):
+        x[:, w * 64 * 4] = 1.0
+    y = torch.empty(rows, device="cuda")
+    hb.hidet_reduce_rows(x, y)
+    torch.cuda.synchronize()
+    assert float((y.double() - (2.0 ** 24 + waves - 1)).abs().max()) <= int(np.log2(waves))
+
+
+@pytest.mark.parametrize("cols", [12000, 70000])
+def test_softmax_sums_of_the_wavefronts_meet_in_a_tree(cols):
+    """As above, with exponentials of 1 and 2^-24 over sixteen wavefronts: four roundings of the sum by at most 2^-24, one
+    reciprocal, one product and one exponential (2^-23 each); one after another the sum is off by 15 * 2^-24."""
+    assert hb.hidet_row_schedule(hb.HIDET_F32, 1, 3, cols)["workgroup_size"] == 1024
+    x = torch.full((3, cols), -float("inf"), device="cuda")
+    x[:, 0] = 0.0
+    for w in range(1, 16):
+        x[:, w * 64 * 4] = -24 * float(np.log(2.0))
+    y = torch.empty_like(x)
+    hb.hidet_softmax_rows(x, y)
+    torch.cuda.synchronize()
+    assert float((y[:, 0].double() - torch.softmax(x.double(), 1)[:, 0]).abs().max()) <= (4 + 3 * 2) * 2.0 ** -24
