@@ -343,11 +343,18 @@ LaunchFn find_partial_launcher(const Problem& pr, int config) {
 // 64x32 tiles of the two-stage form 15 us); the largest need half a round in any case (repacked weights allow only K tiles
 // that divide IC: 5 images of 128x27x27, 5x5: 68 tiles of 128x64 33 us, 270 of 64x32 28 us).  On a long K the 64x64 tile
 // may be half padding: what it competes with there are two-stage tiles (36 images of 512x13x13, 80 channels, 3x3: 36 us
-// on 234 of them, 59 us on 351 two-stage tiles of 32x64).  -1: none fits.
+// on 234 of them, 59 us on 351 two-stage tiles of 32x64).
+// With strides above 2 the gather is one load per element, so the sixteen wavefronts of a K-splitting tile have more to win
+// over the four of the others: they do so half padded, from K = 768 on, and the 64x32 tile (32x32 of at most 32 channels)
+// also with one and a half workgroups per compute unit (40 images of 192x14x15, 512 channels, 3x3, stride 3: 34 us on 200
+// tiles of 64x64, 46 us on 400 two-stage tiles of 64x32; 5 of 160x56x56, 512 channels, stride 4: 36 us on 280 tiles of
+// 64x32, 42 us on 144 of 64x64, 47 us two-stage).  -1: none fits.
 constexpr long long kConvLongK = 2048;
 int one_round_config(const Problem& pr) {
   constexpr long long kComputeUnits = 256;
   const long long M = pr.p.M, N = pr.p.N;
+  const bool by_element = pr.p.g.sw > 2;
+  const long long long_k = by_element ? 768 : kConvLongK;
   int best = -1;
   long long best_area = 0;
   for (int c = 0; c < kNumConfigs; ++c) {
@@ -355,12 +362,13 @@ int one_round_config(const Problem& pr) {
     if (r.sched != 3 || pr.p.K < r.bk || !find_launcher(pr, c)) continue;
     const long long area = (long long)r.bm * r.bn;
     const long long tiles = ((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
-    if (tiles > kComputeUnits || tiles < kComputeUnits / 4) continue;
-    if (area == 64 * 64 && pr.p.K >= kConvLongK) {
+    const bool more = by_element && area == (M > 32 ? 64 * 32 : 32 * 32);
+    if (tiles > (more ? kComputeUnits * 3 / 2 : kComputeUnits) || tiles < kComputeUnits / 4) continue;
+    if (area == 64 * 64 && pr.p.K >= long_k) {
       if (2 * M * N < tiles * area) continue;
     } else if (area >= 64 * 64) {
-      if (4 * M * N < 3 * tiles * area) continue;
-      if (pr.p.K < kConvLongK && (area == 64 * 64 || tiles < kComputeUnits * 3 / 4)) continue;
+      if (by_element ? 2 * M * N < tiles * area : 4 * M * N < 3 * tiles * area) continue;
+      if (pr.p.K < long_k && (area == 64 * 64 || tiles < kComputeUnits * 3 / 4)) continue;
       if (area > 64 * 64 && tiles < kComputeUnits / 2) continue;
     }
     // (of two tiles of one size the taller one: it gathers fewer columns)

@@ -43,6 +43,15 @@ def test_more_than_64_channels_do_not_take_flat_tiles():
         assert chosen(*case)[:2] == (64, 32), case
 
 
+def test_strides_above_2_take_k_splitting_tiles():
+    """Gathered element by element: half padded, from K = 768 on, 64x32 (32x32) of them up to one and a half rounds."""
+    for case, tile in (((40, 192, 14, 15, 512, 3, 3, 1), (64, 64)), ((5, 160, 56, 56, 512, 3, 4, 1), (64, 32)),
+                       ((51, 160, 28, 28, 320, 3, 4, 1), (64, 64)), ((17, 48, 56, 56, 192, 5, 3, 2), (128, 64)),
+                       ((19, 192, 35, 35, 192, 3, 3, 1), (64, 32)), ((44, 64, 56, 56, 32, 5, 5, 2), (32, 32))):
+        assert chosen(*case)[:2] == tile and chosen(*case)[4] == 3, case
+    assert chosen(57, 85, 35, 35, 128, 3, 4, 1)[4] != 3  # K = 765, 129 tiles of 128x64: too short for half a round of them
+
+
 def test_untuned_config_arguments():
     f = lambda *a: hb.lib().hidet_conv2d_untuned_config(*a, ctypes.byref(c))
     c = ctypes.c_int32(7)

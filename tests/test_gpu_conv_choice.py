@@ -31,6 +31,11 @@ SHAPES = {
     "200 tiles of 128x128": ((1, 64, 128, 193, 128, 3, 1, 1), (128, 128, 64, 16, 3), (128, 128, 64, 16, 3)),
     "one output pixel": ((1, 64, 3, 3, 40, 3, 1, 0), (16, 16, 512, 16, 3), (32, 32, 64, 16, 2)),
     "strided": ((3, 64, 31, 29, 72, 5, 2, 2), (16, 16, 512, 16, 3), (32, 32, 64, 16, 2)),
+    "stride 3, 193 tiles of 64x64, K 765": ((7, 85, 132, 118, 64, 3, 3, 1), (64, 32, 64, 16, 2)),
+    "stride 3, 193 tiles of 64x64, K 774": ((7, 86, 132, 118, 64, 3, 3, 1), (64, 64, 256, 16, 3)),
+    "stride 3, 384 tiles of 64x32": ((8, 64, 144, 96, 64, 3, 3, 1), (64, 32, 256, 16, 3)),
+    "stride 3, 384 tiles of 32x32": ((8, 64, 144, 96, 32, 3, 3, 1), (32, 32, 256, 16, 3)),
+    "stride 3, half-padded tiles": ((8, 64, 147, 96, 64, 3, 3, 1), (128, 64, 128, 16, 3)),
 }
 
 
