@@ -260,9 +260,11 @@ __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams 
 // ---- the row lives in the registers of a workgroup ---------------------------------------------------------
 // Every thread holds R chunks as they were loaded (four registers each) and widens them again in each pass: with the
 // widened values kept instead, half as many bytes would be in flight per register (1024 x 50257 bf16: two workgroups of
-// 1024 threads per compute unit instead of one, 60 -> 53 us).  The row is read once.  Bound by memory, with the vector
-// instructions of the two exponentials per element (about 20 lane operations) not far below it: 1024 x 50257 bf16
-// 155 us (element-wise loads, row read twice) -> 48 us = 4.3 TB/s, 1024 x 50304 60 -> 46 us, 4096 x 8200 37 -> 28 us.
+// 1024 threads per compute unit instead of one, 60 -> 53 us).  The row is read once.  Long 16-bit softmax rows are bound
+// by vector instructions, with memory not far below: 21 an element for 1024 x 50257 bf16, two of them exponentials, keep
+// the vector units busy 94 % of the time (87 % for 50304 columns, which need no masks) while 206 MB move at 4.9 (5.6)
+// TB/s; 155 us (element-wise loads, row read twice) -> 47 us between other passes, 1024 x 50304 60 -> 46 us, 4096 x 8200
+// 37 -> 28 us.
 template <typename T, int NT, int R, bool RAGGED, bool SOFTMAX>
 __global__ void __launch_bounds__(NT, R <= 8 ? 8 : 4) rows_in_workgroup_kernel(const RowParams p) {
   constexpr int VEC = Chunk<T>::VEC, NW = NT / 64;
