@@ -457,7 +457,13 @@ int default_config(const Problem& pr, int slices = 1) {
     const long long weight = (useful * useful) >> __builtin_ctzll(area);
     // (the 64x64 tile alone: the 32x32 one of that matrix-core shape is a single wavefront with a deep K tile; 8 images of
     // 16x112x112, 24 channels, 3x3, stride 2: 10.1 us on it, 7.5 us on the 32x32 tile of 16x16)
-    const long long preference = (conv_few_rows && throughput && r.mfma == 32 && area == 64 * 64) ? 8 : rank(r) & 63;
+    // Not on a long K while the tiles of three stages, three to a compute unit, are all resident at once: the third stage
+    // hides the gather better, most of all a strided one (40 images of 192x56x56, 64 channels, 5x5, stride 2, 560 tiles: 102
+    // us on 32x32 of two stages, 96 us on 16x16 of three; 16 tiles more than 768 are a second round, 1.15 times slower
+    // than two stages).  With stride 1 this ends at two to a compute unit (384-512 tiles: 0.99 of the time, 513-768: 1.02).
+    const bool all_resident = long_k && tiles <= (pr.p.g.sw > 1 ? 768 : 512);
+    const long long preference =
+        (conv_few_rows && throughput && !all_resident && r.mfma == 32 && area == 64 * 64) ? 8 : rank(r) & 63;
     long long key = weight * (1LL << 23) - area * 64 + preference;
     // a K of at most two stages runs the two-slot ring: two workgroups of a 256x128 tile share a compute unit and
     // outrun one of a 256x256 tile

@@ -37,6 +37,15 @@ def test_small_k_splitting_tiles_a_little_beyond_one_round():
     assert chosen(64, 64, 56, 56, 64, 3, 1, 1)[4] != 3  # (a throughput problem)
 
 
+def test_at_most_64_channels_take_more_stages_while_all_tiles_are_resident():
+    """A compute unit holds three of the 64x64 tiles with three stages: the gather of a long K is hidden better by them."""
+    for case, stages in (((54, 96, 56, 56, 48, 5, 2, 2), 3), ((40, 192, 56, 56, 64, 5, 2, 2), 3), ((34, 64, 56, 56, 64, 3, 2, 1), 3),
+                         ((9, 64, 55, 55, 64, 3, 1, 1), 3), ((48, 256, 64, 64, 64, 3, 2, 1), 3), ((49, 256, 64, 64, 64, 3, 2, 1), 2),
+                         ((16, 64, 32, 64, 64, 3, 1, 1), 3), ((1, 64, 65, 512, 64, 3, 1, 1), 2), ((34, 48, 56, 56, 64, 3, 2, 1), 2)):
+        assert chosen(*case)[:4] == ((64, 64, 64, 16) if stages == 3 else (64, 64, 64, 32)), case
+        assert chosen(*case)[4] == (2 if stages == 3 else 0), case
+
+
 def test_more_than_64_channels_do_not_take_flat_tiles():
     """Every row of tiles gathers the same columns again: three rows of 32x64 tiles against two of 64x32."""
     for case in ((7, 192, 28, 28, 72, 3, 1, 1), (2, 32, 56, 56, 96, 7, 1, 3), (9, 160, 20, 20, 160, 3, 1, 1)):
