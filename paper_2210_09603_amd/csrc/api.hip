@@ -363,7 +363,12 @@ int one_round_config(const Problem& pr) {
     const long long area = (long long)r.bm * r.bn;
     const long long tiles = ((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
     const bool more = by_element && area == (M > 32 ? 64 * 32 : 32 * 32);
-    if (tiles > (more ? kComputeUnits * 3 / 2 : kComputeUnits) || tiles < kComputeUnits / 4) continue;
+    // Of the 32x32 tile two workgroups share a compute unit: on a long K 512 of them beat the half-padded 64x64 tile and the
+    // two-stage ones for 17 to 32 channels (28 images of 256x35x35, 32 channels, 5x5, stride 2, 378 tiles: 48 us, 64x64 55 us,
+    // 32x64 of two stages 74 us; 64 of 256x28x28, 448 tiles: 44, 51 and 73 us).
+    const bool pairs = M > 16 && M <= 32 && r.bm == 32 && r.bn == 32 && pr.p.K >= long_k;
+    const long long round = pairs ? kComputeUnits * 2 : more ? kComputeUnits * 3 / 2 : kComputeUnits;
+    if (tiles > round || tiles < kComputeUnits / 4) continue;
     if (area == 64 * 64 && pr.p.K >= long_k) {
       if (2 * M * N < tiles * area) continue;
     } else if (area >= 64 * 64) {

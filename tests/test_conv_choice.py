@@ -30,6 +30,13 @@ def test_half_padded_tiles_split_a_long_k_in_one_round():
         assert chosen(*case)[:2] == (64, 64) and chosen(*case)[4] == 3, case
 
 
+def test_32_channels_on_a_long_k_are_no_half_of_64():
+    """A 64x64 K-splitting tile half of whose rows are padding is no tile for 32 channels: 32x32, two to a compute unit."""
+    for case in ((28, 256, 35, 35, 32, 5, 2, 2), (4, 256, 45, 45, 32, 3, 1, 1), (12, 128, 28, 28, 32, 5, 1, 2),
+                 (24, 256, 45, 45, 32, 3, 2, 1), (18, 256, 28, 28, 24, 3, 1, 1), (62, 192, 56, 56, 32, 3, 4, 1)):
+        assert chosen(*case) == (32, 32, 256, 16, 3), case
+
+
 def test_small_k_splitting_tiles_a_little_beyond_one_round():
     """Two workgroups of a small K-splitting tile are resident together: 301 of them are no second round."""
     for case in ((43, 512, 28, 28, 24, 3, 2, 1), (23, 256, 17, 17, 24, 7, 1, 3), (39, 384, 28, 28, 8, 5, 2, 2)):
