@@ -37,6 +37,15 @@ def test_32_channels_on_a_long_k_are_no_half_of_64():
         assert chosen(*case) == (32, 32, 256, 16, 3), case
 
 
+def test_half_padded_128x64_tiles_on_a_long_k():
+    """129 to 192 channels fill two rows of 128x64 tiles at least half: one round of them, K split, from K = 1408 on."""
+    for case in ((35, 256, 14, 14, 144, 7, 1, 3), (32, 384, 14, 14, 160, 5, 1, 2), (17, 192, 35, 35, 160, 5, 2, 2),
+                 (31, 192, 14, 14, 192, 3, 1, 1), (30, 160, 15, 15, 144, 3, 1, 1), (48, 256, 28, 28, 72, 3, 2, 1)):
+        assert chosen(*case)[:2] == (128, 64) and chosen(*case)[4] == 3, case
+    for case in ((30, 128, 15, 15, 144, 3, 1, 1), (16, 160, 28, 28, 64, 3, 1, 1)):  # K = 1152; 64 channels are no more than half
+        assert chosen(*case)[:2] != (128, 64), case
+
+
 def test_small_k_splitting_tiles_a_little_beyond_one_round():
     """Two workgroups of a small K-splitting tile are resident together: 301 of them are no second round."""
     for case in ((43, 512, 28, 28, 24, 3, 2, 1), (23, 256, 17, 17, 24, 7, 1, 3), (39, 384, 28, 28, 8, 5, 2, 2)):

@@ -30,6 +30,8 @@ SHAPES = {
     "32 channels, 544 tiles of 32x32, K 2304": ((2, 256, 64, 129, 32, 3, 1, 1), (32, 64, 64, 16, 2)),
     "64 channels, stride 2, 768 tiles of 64x64": ((6, 64, 128, 256, 64, 3, 2, 1), (64, 64, 64, 16, 2)),
     "64 channels, stride 2, 816 tiles of 64x64": ((6, 64, 128, 264, 64, 3, 2, 1), (64, 64, 64, 32, 0)),
+    "half-padded 128x64 tiles, K 1440": ((30, 160, 15, 15, 144, 3, 1, 1), (128, 64, 128, 16, 3)),
+    "half-padded 128x64 tiles, K 2304": ((12, 256, 28, 28, 72, 3, 1, 1), (128, 64, 128, 16, 3), (128, 64, 128, 16, 3)),
     "no flat tiles": ((7, 192, 28, 28, 72, 3, 1, 1), (64, 32, 64, 16, 2), (64, 32, 64, 16, 2)),
     "224 tiles of 128x64": ((4, 128, 56, 57, 96, 3, 1, 1), (128, 64, 128, 16, 3), (128, 64, 128, 16, 3)),
     "200 tiles of 128x128": ((1, 64, 128, 193, 128, 3, 1, 1), (128, 128, 64, 16, 3), (128, 128, 64, 16, 3)),
