@@ -341,9 +341,9 @@ LaunchFn find_partial_launcher(const Problem& pr, int config) {
 // mostly output, not padding, and on a short K (fill and drain of the pipeline count) they need the round nearly full,
 // or lose to small tiles that share a compute unit (128x28x28, 7 images, K = 1152: 64x64 18 us, 128x64 17 us, two
 // 64x32 tiles of the two-stage form 15 us); the largest need half a round in any case (repacked weights allow only K tiles
-// that divide IC: 5 images of 128x27x27, 5x5: 68 tiles of 128x64 33 us, 270 of 64x32 28 us).  On a long K the 64x64 tile
-// may be half padding: what it competes with there are two-stage tiles (36 images of 512x13x13, 80 channels, 3x3: 36 us
-// on 234 of them, 59 us on 351 two-stage tiles of 32x64).
+// that divide IC: 5 images of 128x27x27, 5x5: 68 tiles of 128x64 33 us, 270 of 64x32 28 us).  On a long K the 64x64
+// and 128x64 tiles may be half padding: what they compete with there are two-stage tiles (36 images of 512x13x13, 80
+// channels, 3x3: 36 us on 234 of 64x64, 59 us on 351 two-stage tiles of 32x64).
 // With strides above 2 the gather is one load per element, so the sixteen wavefronts of a K-splitting tile have more to win
 // over the four of the others: they do so half padded, from K = 768 on, and the 64x32 tile (32x32 of at most 32 channels)
 // also with one and a half workgroups per compute unit (40 images of 192x14x15, 512 channels, 3x3, stride 3: 34 us on 200
