@@ -379,6 +379,9 @@ int one_round_config(const Problem& pr) {
       if (by_element ? 2 * M * N < tiles * area : 4 * M * N < 3 * tiles * area) continue;
       if (pr.p.K < long_k && (area == 64 * 64 || tiles < kComputeUnits * 3 / 4)) continue;
       if (area > 64 * 64 && tiles < kComputeUnits / 2) continue;
+      // (half a round of 128x128 with a quarter of it padding loses to 64x32 of two stages where loads are by element: 37
+      // images of 192x56x56, 192 channels, 3x3, stride 4: 111 and 76 us; 41 of 256x56x56, 320 channels: 146 and 159 us)
+      if (by_element && area == 128 * 128 && 5 * M * N < 4 * tiles * area) continue;
     }
     // (of two tiles of one size the taller one: it gathers fewer columns)
     if (best < 0 || area < best_area || (area == best_area && r.bm > kConfigs[best].bm)) {

@@ -74,6 +74,9 @@ def test_strides_above_2_take_k_splitting_tiles():
                        ((51, 160, 28, 28, 320, 3, 4, 1), (64, 64)), ((17, 48, 56, 56, 192, 5, 3, 2), (128, 64)),
                        ((19, 192, 35, 35, 192, 3, 3, 1), (64, 32)), ((44, 64, 56, 56, 32, 5, 5, 2), (32, 32))):
         assert chosen(*case)[:2] == tile and chosen(*case)[4] == 3, case
+    for case in ((37, 128, 56, 56, 192, 3, 4, 1), (44, 128, 35, 35, 192, 5, 3, 2)):  # 128x128 would be a quarter padding
+        assert chosen(*case)[:2] != (128, 128), case
+    assert chosen(41, 256, 56, 56, 320, 3, 4, 1)[:2] == (128, 128)
     assert chosen(57, 85, 35, 35, 128, 3, 4, 1)[4] != 3  # K = 765, 129 tiles of 128x64: too short for half a round of them
 
 
