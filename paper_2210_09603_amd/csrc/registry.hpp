@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "gemm_kernel.hpp"
+#include "wave_kernel.hpp"
 
 namespace hidet {
 
@@ -29,6 +30,17 @@ inline int conv_variant(int elem_mode) { return 8 + (elem_mode ? 1 : 0); }
 constexpr int kPartialVariants = 10;  // offset of the K-parallel partial-sum kernels
 constexpr int kConvTapVariant = 20;   // convolution over the tap-major K order (repacked weights); +1: partial sums
 
+// Whether the direct loads of gemm_kernel_waves stay inside the operands.  Offsets inside a step are 32-bit; and where rows
+// are only element aligned, the 16 bytes that begin in the last columns of an M/N-contiguous operand must not reach past
+// the row that follows.  What remains runs the general schedule on the same tile.
+constexpr long long kMaxDirectLd = 4LL << 20;
+template <class Cfg>
+bool waves_can_stream(const GemmParams& p) {
+  if (p.lda > kMaxDirectLd || p.ldb > kMaxDirectLd) return false;
+  if (Cfg::MODE_A != LD_ELEM) return true;
+  return (Cfg::LA == L_KC || p.lda >= Cfg::VEC) && (Cfg::LB == L_KC || p.ldb >= Cfg::VEC);
+}
+
 template <class Cfg>
 hipError_t launch_kernel(const GemmParams& p, hipStream_t stream) {
   // the element-mode variant of a ring tile also serves what the direct loads cannot do (input prologue, head-split
@@ -43,6 +55,9 @@ hipError_t launch_kernel(const GemmParams& p, hipStream_t stream) {
       hipLaunchKernelGGL((gemm_kernel_pingpong<Cfg, 2>), dim3((unsigned)p.total_blocks), dim3(Cfg::NT), 0, stream, p);
     else
       hipLaunchKernelGGL((gemm_kernel_pingpong<Cfg, 4>), dim3((unsigned)p.total_blocks), dim3(Cfg::NT), 0, stream, p);
+  } else if (WaveStream<Cfg>::BUILT && waves_can_stream<Cfg>(p)) {
+    if constexpr (WaveStream<Cfg>::BUILT)
+      hipLaunchKernelGGL(gemm_kernel_waves<Cfg>, dim3((unsigned)p.total_blocks), dim3(WaveStream<Cfg>::NT), 0, stream, p);
   } else
     hipLaunchKernelGGL(gemm_kernel<Cfg>, dim3((unsigned)p.total_blocks), dim3(Cfg::NT), 0, stream, p);
   return hipGetLastError();

@@ -1,0 +1,361 @@
+// The K-splitting schedule of small output tiles: every wavefront streams its own share of K.
+//
+// A problem with few output tiles is bound by the chain of one workgroup, not by throughput: with the K tiles shared by
+// all wavefronts (gemm_kernel) each of them is a round trip to memory, an LDS write, a barrier and the dependent
+// fragment reads.  Here nothing is shared before the end.  K is consumed in steps; wavefront w owns the steps w, w + 8, ...
+// of the whole BM x BN tile, fetches them with direct global -> LDS loads into a ring of its own (D steps in flight, waited
+// for by count), and multiplies them without meeting another wavefront.  The partial tiles meet in LDS once, where each
+// group of four outputs is summed in wavefront order and stored.
+//
+// What bounds it is the rate at which a compute unit's first-level cache takes lines, about one a clock, whatever is used of
+// them.  A step is therefore 64 values of k on tiles up to 32x32, a whole line of every row of a K-contiguous operand, with
+// eight wavefronts; with steps of 32 and sixteen wavefronts, which keep as many bytes in flight, 8x3072x768 on 16x32 tiles
+// takes 5.0 us instead of 4.3, 128x768x3072 9.1 instead of 8.5.  On the larger tiles, whose LDS has no room for two steps of
+// 64 and eight wavefronts, steps of 32 and eight wavefronts win over steps of 64 and four (1024^3 on 64x64: 9.3 and 10.7 us).
+// Against the shared K tiles (microseconds in a replayed graph): aligned rows 8x3072x768 5.4 -> 4.3, 8x768x3072 7.6 -> 7.1,
+// 128x768x3072 9.3 -> 8.5, 200x512x2048 on 32x32 7.9 -> 6.6; element-aligned ones, which the general schedule fetches
+// through registers under predicates, 37x82x2658 14.0 -> 5.7, 80x45x796 6.1 -> 4.7.  Empty kernels take 1.5 there, and
+// the shortest chain of a product about 3.3.
+//
+// What a direct load cannot do is kept out of the loop: the last step of K goes through registers with its elements
+// predicated, whole or not if rows are only element aligned (no 16-byte access then touches the last row of an
+// M/N-contiguous operand); it is requested before the loop, so that it is there when its wavefront comes to it.
+#pragma once
+
+#include "epilogue.hpp"
+
+namespace hidet {
+
+// The same tile with wavefronts that stream K (Cfg describes the tile as the general schedule runs it).
+template <class Cfg>
+struct WaveStream {
+  static constexpr int BM = Cfg::BM, BN = Cfg::BN;
+  static constexpr int STEP = BM * BN > 32 * 32 ? 32 : 64;
+  static constexpr bool BUILT = Cfg::SCHED == SCHED_KSPLIT && !Cfg::IS_F32 && Cfg::MI == 16 && BM <= 64 && BN <= 64 && !Cfg::GATHER_B;
+  static constexpr int NW = 8;
+  static constexpr int NT = NW * 64;
+  static constexpr int A_BYTES = BM * STEP * 2, B_BYTES = BN * STEP * 2, STEP_BYTES = A_BYTES + B_BYTES;
+  static constexpr int FIT = 144 * 1024 / (NW * STEP_BYTES);
+  static constexpr int D = FIT > 4 ? 4 : FIT;  // steps of a wavefront's ring
+  static constexpr int RING_BYTES = D * STEP_BYTES;
+  static constexpr int ROW_BYTES = BN * 4 + 16;  // of a partial tile: rows start 4 banks apart
+  static constexpr int PART_BYTES = BM * ROW_BYTES;
+  static constexpr int LDS_BYTES = NW * (RING_BYTES > PART_BYTES ? RING_BYTES : PART_BYTES);
+  static_assert(!BUILT || (D >= 2 && LDS_BYTES <= 160 * 1024), "a ring of two steps at least, in the LDS of a compute unit");
+};
+
+// at most N vector memory operations in flight
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "6-bit counter");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+template <class Frag>
+__device__ __forceinline__ Frag relu_fragment(Frag f) {  // (a negative value is negative as an integer: Operand::store)
+  typedef short i16x8 __attribute__((ext_vector_type(8)));
+  const i16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
+  return __builtin_bit_cast(Frag, __builtin_elementwise_max(__builtin_bit_cast(i16x8, f), z));
+}
+
+// ---- the fused epilogue of a group of four columns, in two parts -- what it reads, what it computes and stores (store4
+// does both at the end, where the large tiles, short of registers, want them) ------------------------------------------
+template <typename TO>
+struct __attribute__((packed, aligned(sizeof(TO)))) GroupOf4 {  // one access; the address need only be element aligned
+  TO e[4];
+};
+
+// The residual of a group, widened (zeros where there is none): a kernel that is bound by one latency chain asks for it
+// before its main loop.
+template <typename TO>
+__device__ __forceinline__ void load_residual4(const GemmParams& p, const TO* __restrict__ R, int m, int n, long long ccol,
+                                               int nvalid, float (&res)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) res[e] = 0.0f;
+  if (R == nullptr || m >= p.M || nvalid <= 0) return;
+  const bool remap = p.out_map != 0;
+  const long long rrow = remap ? row_offset<MAP_PLAIN>(p, m, p.ldc) : (long long)m * p.ldr;
+  const long long roff = rrow + ccol;
+  if (p.vec_store && nvalid == 4) {
+    TO r[4];
+    *reinterpret_cast<GroupOf4<TO>*>(r) = *reinterpret_cast<const GroupOf4<TO>*>(R + roff);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) res[e] = to_f32(r[e]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (e < nvalid) {
+        long long ro = roff + e;
+        if (remap) ro = rrow + col_offset<MAP_PLAIN>(p, n + e);
+        res[e] = to_f32(R[ro]);
+      }
+    }
+  }
+}
+
+// The group's results from its sums, biases and residual.
+template <typename TO>
+__device__ __forceinline__ void finish4(const GemmParams& p, TO* __restrict__ C, const float (&bias)[4], const float (&res)[4],
+                                        bool residual, int m, int n, long long ccol, int nvalid, const float (&acc)[4]) {
+  if (m >= p.M || nvalid <= 0) return;
+  const bool remap = p.out_map != 0;
+  const long long crow = row_offset<MAP_PLAIN>(p, m, p.ldc);
+  const long long off = crow + ccol;
+  const bool whole = p.vec_store && nvalid == 4;
+  float v[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = p.alpha * acc[e] + bias[e];  // zeros where there is no bias
+  if (residual) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += res[e];
+  }
+  if (p.relu) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = v[e] < 0.0f ? 0.0f : v[e];
+  }
+  TO o[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = from_f32<TO>(v[e]);
+  if (whole) {
+    // the output is not read again by this kernel: streamed, or written through the die's L2 (see store_group)
+    if (p.vec_store >= 2) {  // 4-element aligned address
+      if constexpr (sizeof(TO) == 2)
+        store_group(C + off, o, p.vec_store == 3);
+      else
+        __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(o), reinterpret_cast<u32x4*>(C + off));
+    } else {
+      *reinterpret_cast<GroupOf4<TO>*>(C + off) = *reinterpret_cast<const GroupOf4<TO>*>(o);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (e < nvalid) {
+        long long oo = off + e;
+        if (remap) oo = crow + col_offset<MAP_PLAIN>(p, n + e);
+        C[oo] = o[e];
+      }
+    }
+  }
+}
+
+// ---- the last step of K, through registers ------------------------------------------------------------------------------
+// Requested without a branch and finished when it is stored, so that nothing waits for it in between (under the predicates of
+// the general schedule instead, 80x45x796 on 16x16 tiles takes 4.9 us, not 4.7): a chunk that sticks out of the operand's end
+// is read as the last 16 bytes of the operand and shifted down afterwards.  Along M/N what lies past the edge only reaches
+// outputs that are never stored; along K it becomes zero.
+template <class Op, int LAYOUT>
+struct TailStep {
+  static_assert(Op::VEC == 8, "16-bit types");
+  u32x4 raw[Op::NL];
+  int keep[Op::NL], down[Op::NL];  // elements that lie inside K; by how many elements the chunk is to be shifted down
+
+  __device__ __forceinline__ void request(const Op& op, int lane, int k0) {
+#pragma unroll
+    for (int q = 0; q < Op::NL; ++q) {
+      const tmap::Task t = Op::LoadMap::task(lane, q);
+      const int sr = t.i, sc = t.j * 8;
+      if (op.span < 8) {  // (uniform: an operand of less than 16 bytes)
+        raw[q] = op.gather(sr, sc, k0);
+        keep[q] = 8;
+        down[q] = 0;
+        continue;
+      }
+      long long base;
+      int inside;
+      if constexpr (LAYOUT == L_KC) {
+        base = (long long)(sr < op.rows_left ? sr : op.rows_left - 1) * op.ld + (k0 + sc);
+        inside = op.K - (k0 + sc);
+      } else {
+        base = (long long)(k0 + sr) * op.ld + (sc < op.rows_left ? sc : 0);
+        inside = k0 + sr < op.K ? 8 : 0;
+      }
+      if (inside <= 0) base = 0;
+      const long long over = base + 8 - op.span;
+      down[q] = over > 0 ? (int)over : 0;
+      keep[q] = inside < 0 ? 0 : (inside > 8 ? 8 : inside);
+      raw[q] = reinterpret_cast<const typename Op::Unaligned*>(op.src + (base - down[q]))->v;
+    }
+  }
+
+  __device__ __forceinline__ void store(const Op& op, int lane, unsigned char* tile) {
+#pragma unroll
+    for (int q = 0; q < Op::NL; ++q) {
+      u32x4 v = raw[q];
+      const int d = down[q], n = keep[q];
+      if (d & 4) v = u32x4{v[2], v[3], 0u, 0u};
+      if (d & 2) v = u32x4{v[1], v[2], v[3], 0u};
+      if (d & 1) v = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] &= n >= 2 * i + 2 ? 0xffffffffu : (n == 2 * i + 1 ? 0x0000ffffu : 0u);
+      raw[q] = v;
+    }
+    op.store(raw, lane, tile);
+  }
+};
+
+template <class Cfg>
+__global__ void __launch_bounds__(WaveStream<Cfg>::NT) gemm_kernel_waves(const GemmParams p) {
+  using S = WaveStream<Cfg>;
+  using T = typename Cfg::T;
+  using TO = typename Cfg::TO;
+  constexpr int BM = S::BM, BN = S::BN, STEP = S::STEP, NW = S::NW, D = S::D, KS = STEP / 32, FM = BM / 16, FN = BN / 16;
+  constexpr bool ELEM = Cfg::MODE_A == LD_ELEM;
+  static_assert(Cfg::MODE_A == Cfg::MODE_B && Cfg::MAPPER == MAP_PLAIN, "plain GEMM operands");
+  // one wavefront loads a whole step
+  using OpA = Operand<T, BM, STEP, Cfg::LA, Cfg::MODE_A, 64, 16>;
+  using OpB = Operand<T, BN, STEP, Cfg::LB, Cfg::MODE_B, 64, 16>;
+  constexpr int LOADS = OpA::NL + OpB::NL;  // direct loads of a step
+  static_assert(D * LOADS < 64, "the loads in flight are counted in six bits");
+
+  __shared__ __attribute__((aligned(16))) unsigned char smem[S::LDS_BYTES];
+
+  const int lane = threadIdx.x % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const BlockCoords bc = block_coords<BM, BN>(p);
+  OpA opa;
+  OpB opb;
+  setup_operands<Cfg>(p, bc, opa, opb);
+
+  // ---- steps by direct loads: the whole ones, without the last one where rows are only element aligned
+  const int whole = ELEM ? (bc.k_len > 0 ? (bc.k_len - 1) / STEP : 0) : bc.k_len / STEP;
+  const int mine = whole > wave ? (whole - wave + NW - 1) / NW : 0;
+  const bool tail = whole * STEP < bc.k_len && wave == whole % NW;  // this wavefront multiplies the last step
+  unsigned char* ring = smem + wave * S::RING_BYTES;
+  const unsigned ring_lds = (unsigned)(size_t)(__attribute__((address_space(3))) void*)ring;
+  opa.init_direct(lane, ELEM);
+  opb.init_direct(lane, ELEM);
+  auto request = [&](int i, int slot) {  // this wavefront's step i
+    const int k0 = (wave + i * NW) * STEP;
+    opa.load_direct(ring_lds + (unsigned)(slot * S::STEP_BYTES), 0, k0);
+    opb.load_direct(ring_lds + (unsigned)(slot * S::STEP_BYTES + S::A_BYTES), 0, k0);
+  };
+#pragma unroll
+  for (int i = 0; i < D; ++i)
+    if (i < mine) request(i, i);
+
+  // ---- what the end needs is requested behind them (a count of the loads above can only be waited for too long)
+  TailStep<OpA, Cfg::LA> ta;
+  TailStep<OpB, Cfg::LB> tb;
+  if (tail) {
+    ta.request(opa, lane, whole * STEP);
+    tb.request(opb, lane, whole * STEP);
+  }
+  // a thread finishes groups of four columns: `tid`, `tid` + NT, ... in row-major order over the tile
+  constexpr int GROUPS = BM * BN / 4, PER_ROW = BN / 4, PASSES = (GROUPS + S::NT - 1) / S::NT;
+  static_assert(S::NT % PER_ROW == 0, "a thread keeps its columns");
+  const int c4 = (int)threadIdx.x % PER_ROW;
+  const int n = bc.n0 + c4 * 4;
+  TO* C = reinterpret_cast<TO*>(p.C) + (long long)bc.cbatch * p.strideC;
+  const TO* R = p.residual ? reinterpret_cast<const TO*>(p.residual) + (long long)bc.batch * p.strideR : nullptr;
+  const TO* bias_ptr = reinterpret_cast<const TO*>(p.bias);
+  const long long ccol = col_offset<MAP_PLAIN>(p, n);
+  const int valid = group_valid<MAP_PLAIN>(p, n);
+  float bias[PASSES][4], res[PASSES][4];
+#pragma unroll
+  for (int s = 0; s < PASSES; ++s) {
+    const int g = s * S::NT + (int)threadIdx.x, m = bc.m0 + g / PER_ROW;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bias[s][e] = res[s][e] = 0.0f;
+    if (g < GROUPS && m < p.M) {
+      if (p.bias_axis != 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (p.bias_axis == 2 || e < valid) bias[s][e] = to_f32(bias_ptr[p.bias_axis == 2 ? m : n + e]);
+      }
+      load_residual4<TO>(p, R, m, n, ccol, valid, res[s]);
+    }
+  }
+
+  f32x4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  typename OpA::Frag fa[KS][FM];
+  typename OpB::Frag fb[KS][FN];
+  auto load_frags = [&](const unsigned char* step) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i) fa[ks][i] = opa.fragment(step, lane, 0, i, ks);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) fb[ks][j] = opb.fragment(step + S::A_BYTES, lane, 0, j, ks);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot may be filled again
+  };
+  auto mfmas = [&]() {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (p.relu_a) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i) fa[ks][i] = relu_fragment(fa[ks][i]);
+      }
+      if (p.relu_b) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j) fb[ks][j] = relu_fragment(fb[ks][j]);
+      }
+      // (operands swapped: the accumulator holds C transposed, four columns of a row per lane)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = mfma_op(fb[ks][j], fa[ks][i], acc[i][j]);
+    }
+  };
+  int slot = 0;
+  for (int i = 0; i < mine; ++i) {
+    const int younger = mine - 1 - i;  // steps in flight behind step i, at most D - 1
+    if (younger >= 3 && D >= 4)
+      wait_vmcnt<(D >= 4 ? 3 : 0) * LOADS>();
+    else if (younger >= 2 && D >= 3)
+      wait_vmcnt<(D >= 3 ? 2 : 0) * LOADS>();
+    else if (younger >= 1)
+      wait_vmcnt<LOADS>();
+    else
+      wait_vmcnt<0>();
+    load_frags(ring + slot * S::STEP_BYTES);
+    if (i + D < mine) request(i + D, slot);
+    mfmas();
+    slot = slot + 1 == D ? 0 : slot + 1;
+  }
+  if (tail) {
+    ta.store(opa, lane, ring);
+    tb.store(opb, lane, ring + S::A_BYTES);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    load_frags(ring);
+    mfmas();
+  }
+
+  // ---- the partial tiles meet
+  __syncthreads();  // (the rings are read no more, and nothing is in flight towards them)
+  const int steps = whole + (whole * STEP < bc.k_len ? 1 : 0);
+  const int active = steps < NW ? steps : NW;  // wavefronts that had a step
+  if (wave < active) {
+    unsigned char* part = smem + wave * S::PART_BYTES;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        *reinterpret_cast<f32x4*>(part + (i * 16 + lane % 16) * S::ROW_BYTES + (j * 16 + 4 * (lane / 16)) * 4) = acc[i][j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < PASSES; ++s) {
+    const int g = s * S::NT + (int)threadIdx.x, row = g / PER_ROW;
+    if (g < GROUPS) {
+      const unsigned char* src = smem + row * S::ROW_BYTES + c4 * 16;
+      f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+      f32x4 v[NW];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) v[w] = *reinterpret_cast<const f32x4*>(src + (w < active ? w : 0) * S::PART_BYTES);
+#pragma unroll
+      for (int w = 0; w < NW; ++w)
+        if (w < active) sum += v[w];
+      const float out[4] = {sum[0], sum[1], sum[2], sum[3]};
+      finish4<TO>(p, C, bias[s], res[s], R != nullptr, bc.m0 + row, n, ccol, valid, out);
+    }
+  }
+}
+
+}  // namespace hidet
