@@ -665,11 +665,10 @@ hidet_status_t launch(const Problem& pr_in, int config, const SplitK& sk, hipStr
   LaunchFn fn = find_launcher(pr, config);
   if (!fn) return HIDET_ERR_NO_CONFIG;
   const ConfigRow& r = kConfigs[config];
-  p.tiles_m = (p.M + r.bm - 1) / r.bm;
-  p.tiles_n = (p.N + r.bn - 1) / r.bn;
+  const int tiles_m = (p.M + r.bm - 1) / r.bm, tiles_n = (p.N + r.bn - 1) / r.bn;
   // grouped traversal: each run of 32 consecutive workgroups (one die's share of a 256-tile wave)
   // should cover a near-square patch of tiles
-  p.group = p.tiles_m >= 4 ? 4 : p.tiles_m;
+  set_block_mapping(p, tiles_m, tiles_n, tiles_m >= 4 ? 4 : tiles_m);
   p.k_slices = 1;
   p.k_slice_len = p.K;
   long long len = p.K, actual = 1;

@@ -352,7 +352,7 @@ struct Operand {
   // operand is read where it lies -- what follows the row's end is the next row, and the columns it fills are never
   // stored -- instead of being moved back to end at the edge, which is only right when whole chunks stick out.
   // The caller keeps such loads away from the operand's last row.
-  int doff[NL];
+  unsigned doff[NL];  // in bytes; rows times leading dimension below 2^31 elements
   __device__ __forceinline__ void init_direct(int tid, bool in_place = false) {
     static_assert(std::is_same<LoadMap, LoadMapRowMajor<SROWS, CPR, NT>>::value, "stored positions in row-major order");
 #pragma unroll
@@ -364,26 +364,26 @@ struct Operand {
       const int lc = pc ^ ((LAYOUT == L_KC) ? swz_kc<CPR, MI>(row) : swz_mc<CPR, MI>(row));
       if constexpr (LAYOUT == L_KC) {
         const int r = row < rows_left ? row : rows_left - 1;
-        doff[q] = r * (int)ld + lc * VEC;
+        doff[q] = ((unsigned)r * (unsigned)ld + (unsigned)(lc * VEC)) * (unsigned)sizeof(T);
       } else {
         int c = lc * VEC + VEC <= rows_left ? lc * VEC : rows_left - VEC;
         if (in_place) c = lc * VEC < rows_left ? lc * VEC : 0;
-        doff[q] = row * (int)ld + c;
+        doff[q] = ((unsigned)row * (unsigned)ld + (unsigned)c) * (unsigned)sizeof(T);
       }
     }
   }
-  // `tile_lds`: LDS byte address of the tile; `wave`: wave index (both wave-uniform).
+  // `tile_lds`: LDS byte address of the tile; `wave`: wave index (both wave-uniform).  The tile's address is a scalar
+  // and the chunk's offset from it 32 bits wide, so that a load costs no vector instruction beside itself.
   __device__ __forceinline__ void load_direct(unsigned tile_lds, int wave, int k0) const {
     const T* base = (LAYOUT == L_KC) ? src + k0 : src + (long long)k0 * ld;
 #pragma unroll
     for (int q = 0; q < NL; ++q) {
-      const T* g = base + doff[q];
       const unsigned dst = tile_lds + (unsigned)((q * NT + wave * 64) * 16);
       // M0 (the LDS destination of the load) is written here, so it is named as clobbered: the compiler must not
       // keep a value of its own in it across the statement.  It reserves M0 and says so in a warning, silenced here.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-      asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(dst) : "memory", "m0");
+      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(doff[q]), "s"(base), "s"(dst) : "memory", "m0");
 #pragma clang diagnostic pop
     }
   }

@@ -46,11 +46,15 @@ struct FastDiv {
 
 inline FastDiv make_fastdiv(long long d) {
   FastDiv f;
-  unsigned int l = 0;
-  while ((1LL << l) < d) ++l;
+  const unsigned int l = d > 1 ? 64 - (unsigned int)__builtin_clzll((unsigned long long)d - 1) : 0;
   f.shift = 31 + l;
-  const unsigned __int128 one = 1;
-  f.mul = (unsigned int)(((one << f.shift) + (unsigned __int128)d - 1) / (unsigned __int128)d);
+  // (divisors of the domain, below 2^31, stay within 64 bits; a call makes a dozen of these)
+  if (l <= 32) {
+    f.mul = (unsigned int)(((1ULL << f.shift) + (unsigned long long)d - 1) / (unsigned long long)d);
+  } else {
+    const unsigned __int128 one = 1;
+    f.mul = (unsigned int)(((one << f.shift) + (unsigned __int128)d - 1) / (unsigned __int128)d);
+  }
   return f;
 }
 
@@ -83,6 +87,9 @@ struct GemmParams {
                   // 0 no, 1 yes at element alignment, 2 yes and every group is aligned to 4 elements,
                   // 3 as 2 and the groups are written through the L2 (row-major 16-bit output with rows >= 4 KB apart)
   int tiles_m, tiles_n, group;
+  // dividers of the block-level mapping (set_block_mapping): by tiles_m * tiles_n, by group * tiles_n, by group, and by the
+  // rows of the last, shorter panel
+  FastDiv d_tiles, d_panel, d_group, d_last;
   int total_blocks;
   int k_slices;     // > 1: parallel reduction on K -- workgroup z of a tile works on K range [z*k_slice_len, ...)
   int k_slice_len;  // and writes raw fp32 partial sums to slice z of the workspace (C points at the workspace)
@@ -95,6 +102,18 @@ struct GemmParams {
   long long out_inner;  // MAP_NCHW: OH*OW
   long long out_outer;  // MAP_NCHW: OC*OH*OW
 };
+
+// Fills the block-level mapping of a grid of tiles_m x tiles_n tiles walked `group` tile rows at a time.
+inline void set_block_mapping(GemmParams& p, int tiles_m, int tiles_n, int group) {
+  p.tiles_m = tiles_m;
+  p.tiles_n = tiles_n;
+  p.group = group;
+  const int last = tiles_m % group;
+  p.d_tiles = make_fastdiv((long long)tiles_m * tiles_n);
+  p.d_panel = make_fastdiv((long long)group * tiles_n);
+  p.d_group = make_fastdiv(group);
+  p.d_last = make_fastdiv(last ? last : group);
+}
 
 // ---------------------------------------------------------------------------------------------
 // LDS swizzles.  Tiles are stored without padding; bank conflicts are avoided by XOR-ing the
