@@ -388,6 +388,26 @@ struct Operand {
     }
   }
 
+  // The same for a tile that K ends in, chunks of which lie inside K or outside (LD_VEC): lanes outside write zeros to the
+  // place that their chunk would take.  `tile`: the tile as it is addressed by this lane, `tile_lds` as above.
+  __device__ __forceinline__ void load_direct_edge(unsigned char* tile, unsigned tile_lds, int tid, int wave, int k0) const {
+    const T* base = (LAYOUT == L_KC) ? src + k0 : src + (long long)k0 * ld;
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+      const tmap::Task t = LoadMap::task(tid, q);
+      const int k = (LAYOUT == L_KC) ? (t.j ^ swz_kc<CPR, MI>(t.i)) * VEC : t.i;
+      const unsigned dst = tile_lds + (unsigned)((q * NT + wave * 64) * 16);
+      if (k0 + k < K) {
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(doff[q]), "s"(base), "s"(dst) : "memory", "m0");
+#pragma clang diagnostic pop
+      } else {
+        *reinterpret_cast<u32x4*>(tile + (q * NT + tid) * 16) = u32x4{0u, 0u, 0u, 0u};
+      }
+    }
+  }
+
   // A K tile that lies entirely inside the matrix: no predicates at all in vector mode.
   __device__ __forceinline__ void load_full(u32x4 (&regs)[NL], int tid, int k0, const ConvGeom& g) {
     if constexpr (MODE == LD_VEC) {

@@ -17,8 +17,8 @@
 // through registers under predicates, 37x82x2658 14.0 -> 5.7, 80x45x796 6.1 -> 4.7.  Empty kernels take 1.5 there, and
 // the shortest chain of a product about 3.3.
 //
-// What a direct load cannot do is kept out of the loop: the last step of K goes through registers with its elements
-// predicated, whole or not if rows are only element aligned (no 16-byte access then touches the last row of an
+// A last step that K ends in takes part in a ring with zeros in the place of the chunks outside.  Where rows are only
+// element aligned, the last step goes through registers, whole or not (no 16-byte access then touches the last row of an
 // M/N-contiguous operand); it is requested before the loop, so that it is there when its wavefront comes to it.
 #pragma once
 
@@ -66,16 +66,14 @@ struct __attribute__((packed, aligned(sizeof(TO)))) GroupOf4 {  // one access; t
 };
 
 // The residual of a group, widened (zeros where there is none): a kernel that is bound by one latency chain asks for it
-// before its main loop.
+// before its main loop.  `row`: offset of the group's row, `ccol`: of its first column.
 template <typename TO>
-__device__ __forceinline__ void load_residual4(const GemmParams& p, const TO* __restrict__ R, int m, int n, long long ccol,
+__device__ __forceinline__ void load_residual4(const GemmParams& p, const TO* __restrict__ R, long long row, int n, long long ccol,
                                                int nvalid, float (&res)[4]) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) res[e] = 0.0f;
-  if (R == nullptr || m >= p.M || nvalid <= 0) return;
-  const bool remap = p.out_map != 0;
-  const long long rrow = remap ? row_offset<MAP_PLAIN>(p, m, p.ldc) : (long long)m * p.ldr;
-  const long long roff = rrow + ccol;
+  if (R == nullptr || nvalid <= 0) return;
+  const long long roff = row + ccol;
   if (p.vec_store && nvalid == 4) {
     TO r[4];
     *reinterpret_cast<GroupOf4<TO>*>(r) = *reinterpret_cast<const GroupOf4<TO>*>(R + roff);
@@ -86,7 +84,7 @@ __device__ __forceinline__ void load_residual4(const GemmParams& p, const TO* __
     for (int e = 0; e < 4; ++e) {
       if (e < nvalid) {
         long long ro = roff + e;
-        if (remap) ro = rrow + col_offset<MAP_PLAIN>(p, n + e);
+        if (p.out_map != 0) ro = row + col_offset<MAP_PLAIN>(p, n + e);
         res[e] = to_f32(R[ro]);
       }
     }
@@ -96,11 +94,9 @@ __device__ __forceinline__ void load_residual4(const GemmParams& p, const TO* __
 // The group's results from its sums, biases and residual.
 template <typename TO>
 __device__ __forceinline__ void finish4(const GemmParams& p, TO* __restrict__ C, const float (&bias)[4], const float (&res)[4],
-                                        bool residual, int m, int n, long long ccol, int nvalid, const float (&acc)[4]) {
-  if (m >= p.M || nvalid <= 0) return;
-  const bool remap = p.out_map != 0;
-  const long long crow = row_offset<MAP_PLAIN>(p, m, p.ldc);
-  const long long off = crow + ccol;
+                                        bool residual, long long row, int n, long long ccol, int nvalid, const float (&acc)[4]) {
+  if (nvalid <= 0) return;
+  const long long off = row + ccol;
   const bool whole = p.vec_store && nvalid == 4;
   float v[4];
 #pragma unroll
@@ -131,14 +127,14 @@ __device__ __forceinline__ void finish4(const GemmParams& p, TO* __restrict__ C,
     for (int e = 0; e < 4; ++e) {
       if (e < nvalid) {
         long long oo = off + e;
-        if (remap) oo = crow + col_offset<MAP_PLAIN>(p, n + e);
+        if (p.out_map != 0) oo = row + col_offset<MAP_PLAIN>(p, n + e);
         C[oo] = o[e];
       }
     }
   }
 }
 
-// ---- the last step of K, through registers ------------------------------------------------------------------------------
+// ---- the last step of K on element-aligned rows, through registers ------------------------------------------------------------------------------
 // Requested without a branch and finished when it is stored, so that nothing waits for it in between (under the predicates of
 // the general schedule instead, 80x45x796 on 16x16 tiles takes 4.9 us, not 4.7): a chunk that sticks out of the operand's end
 // is read as the last 16 bytes of the operand and shifted down afterwards.  Along M/N what lies past the edge only reaches
@@ -220,23 +216,29 @@ __global__ void __launch_bounds__(WaveStream<Cfg>::NT) gemm_kernel_waves(const G
   const int whole = ELEM ? (bc.k_len > 0 ? (bc.k_len - 1) / STEP : 0) : bc.k_len / STEP;
   const int mine = whole > wave ? (whole - wave + NW - 1) / NW : 0;
   const bool tail = whole * STEP < bc.k_len && wave == whole % NW;  // this wavefront multiplies the last step
+  const int n = mine + (!ELEM && tail ? 1 : 0);                      // steps of its ring
   unsigned char* ring = smem + wave * S::RING_BYTES;
   const unsigned ring_lds = (unsigned)(size_t)(__attribute__((address_space(3))) void*)ring;
   opa.init_direct(lane, ELEM);
   opb.init_direct(lane, ELEM);
   auto request = [&](int i, int slot) {  // this wavefront's step i
     const int k0 = (wave + i * NW) * STEP;
-    opa.load_direct(ring_lds + (unsigned)(slot * S::STEP_BYTES), 0, k0);
-    opb.load_direct(ring_lds + (unsigned)(slot * S::STEP_BYTES + S::A_BYTES), 0, k0);
+    const unsigned at = ring_lds + (unsigned)(slot * S::STEP_BYTES);
+    if (ELEM || i < mine) {
+      opa.load_direct(at, 0, k0);
+      opb.load_direct(at + S::A_BYTES, 0, k0);
+    } else {
+      opa.load_direct_edge(ring + slot * S::STEP_BYTES, at, lane, 0, k0);
+      opb.load_direct_edge(ring + slot * S::STEP_BYTES + S::A_BYTES, at + S::A_BYTES, lane, 0, k0);
+    }
   };
-#pragma unroll
-  for (int i = 0; i < D; ++i)
-    if (i < mine) request(i, i);
+#pragma unroll 1
+  for (int i = 0; i < (n < D ? n : D); ++i) request(i, i);
 
   // ---- what the end needs is requested behind them (a count of the loads above can only be waited for too long)
   TailStep<OpA, Cfg::LA> ta;
   TailStep<OpB, Cfg::LB> tb;
-  if (tail) {
+  if (ELEM && tail) {
     ta.request(opa, lane, whole * STEP);
     tb.request(opb, lane, whole * STEP);
   }
@@ -244,25 +246,28 @@ __global__ void __launch_bounds__(WaveStream<Cfg>::NT) gemm_kernel_waves(const G
   constexpr int GROUPS = BM * BN / 4, PER_ROW = BN / 4, PASSES = (GROUPS + S::NT - 1) / S::NT;
   static_assert(S::NT % PER_ROW == 0, "a thread keeps its columns");
   const int c4 = (int)threadIdx.x % PER_ROW;
-  const int n = bc.n0 + c4 * 4;
+  const int col = bc.n0 + c4 * 4;
   TO* C = reinterpret_cast<TO*>(p.C) + (long long)bc.cbatch * p.strideC;
   const TO* R = p.residual ? reinterpret_cast<const TO*>(p.residual) + (long long)bc.batch * p.strideR : nullptr;
   const TO* bias_ptr = reinterpret_cast<const TO*>(p.bias);
-  const long long ccol = col_offset<MAP_PLAIN>(p, n);
-  const int valid = group_valid<MAP_PLAIN>(p, n);
+  const long long ccol = col_offset<MAP_PLAIN>(p, col);
+  const int valid = group_valid<MAP_PLAIN>(p, col);
   float bias[PASSES][4], res[PASSES][4];
+  long long row_at[PASSES];  // offset of the group's row in C; negative: no row of C
 #pragma unroll
   for (int s = 0; s < PASSES; ++s) {
     const int g = s * S::NT + (int)threadIdx.x, m = bc.m0 + g / PER_ROW;
+    row_at[s] = g < GROUPS && m < p.M ? row_offset<MAP_PLAIN>(p, m, p.ldc) : -1;
+    asm volatile("" : "+v"(row_at[s]));  // (now, while the first step is on its way, not at the end)
 #pragma unroll
     for (int e = 0; e < 4; ++e) bias[s][e] = res[s][e] = 0.0f;
     if (g < GROUPS && m < p.M) {
       if (p.bias_axis != 0) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (p.bias_axis == 2 || e < valid) bias[s][e] = to_f32(bias_ptr[p.bias_axis == 2 ? m : n + e]);
+          if (p.bias_axis == 2 || e < valid) bias[s][e] = to_f32(bias_ptr[p.bias_axis == 2 ? m : col + e]);
       }
-      load_residual4<TO>(p, R, m, n, ccol, valid, res[s]);
+      load_residual4<TO>(p, R, p.out_map != 0 ? row_at[s] : (long long)m * p.ldr, col, ccol, valid, res[s]);
     }
   }
 
@@ -302,8 +307,10 @@ __global__ void __launch_bounds__(WaveStream<Cfg>::NT) gemm_kernel_waves(const G
     }
   };
   int slot = 0;
-  for (int i = 0; i < mine; ++i) {
-    const int younger = mine - 1 - i;  // steps in flight behind step i, at most D - 1
+  for (int i = 0; i < n; ++i) {
+    // whole steps in flight behind step i, at most D - 1 (the last step of K may have loads of its own behind them or,
+    // where all its chunks lie outside, none: it is not counted)
+    const int younger = mine - 1 - i;
     if (younger >= 3 && D >= 4)
       wait_vmcnt<(D >= 4 ? 3 : 0) * LOADS>();
     else if (younger >= 2 && D >= 3)
@@ -313,11 +320,11 @@ __global__ void __launch_bounds__(WaveStream<Cfg>::NT) gemm_kernel_waves(const G
     else
       wait_vmcnt<0>();
     load_frags(ring + slot * S::STEP_BYTES);
-    if (i + D < mine) request(i + D, slot);
+    if (i + D < n) request(i + D, slot);
     mfmas();
     slot = slot + 1 == D ? 0 : slot + 1;
   }
-  if (tail) {
+  if (ELEM && tail) {
     ta.store(opa, lane, ring);
     tb.store(opb, lane, ring + S::A_BYTES);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
@@ -329,31 +336,26 @@ __global__ void __launch_bounds__(WaveStream<Cfg>::NT) gemm_kernel_waves(const G
 
   // ---- the partial tiles meet
   __syncthreads();  // (the rings are read no more, and nothing is in flight towards them)
-  const int steps = whole + (whole * STEP < bc.k_len ? 1 : 0);
-  const int active = steps < NW ? steps : NW;  // wavefronts that had a step
-  if (wave < active) {
-    unsigned char* part = smem + wave * S::PART_BYTES;
+  unsigned char* part = smem + wave * S::PART_BYTES;  // (of zeros from a wavefront that had no step)
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < FN; ++j)
-        *reinterpret_cast<f32x4*>(part + (i * 16 + lane % 16) * S::ROW_BYTES + (j * 16 + 4 * (lane / 16)) * 4) = acc[i][j];
-  }
+    for (int j = 0; j < FN; ++j)
+      *reinterpret_cast<f32x4*>(part + (i * 16 + lane % 16) * S::ROW_BYTES + (j * 16 + 4 * (lane / 16)) * 4) = acc[i][j];
   __syncthreads();
 #pragma unroll
   for (int s = 0; s < PASSES; ++s) {
-    const int g = s * S::NT + (int)threadIdx.x, row = g / PER_ROW;
-    if (g < GROUPS) {
+    if (row_at[s] >= 0) {
+      const int row = (s * S::NT + (int)threadIdx.x) / PER_ROW;
       const unsigned char* src = smem + row * S::ROW_BYTES + c4 * 16;
-      f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
       f32x4 v[NW];
 #pragma unroll
-      for (int w = 0; w < NW; ++w) v[w] = *reinterpret_cast<const f32x4*>(src + (w < active ? w : 0) * S::PART_BYTES);
+      for (int w = 0; w < NW; ++w) v[w] = *reinterpret_cast<const f32x4*>(src + w * S::PART_BYTES);
+      f32x4 sum = v[0];
 #pragma unroll
-      for (int w = 0; w < NW; ++w)
-        if (w < active) sum += v[w];
+      for (int w = 1; w < NW; ++w) sum += v[w];
       const float out[4] = {sum[0], sum[1], sum[2], sum[3]};
-      finish4<TO>(p, C, bias[s], res[s], R != nullptr, bc.m0 + row, n, ccol, valid, out);
+      finish4<TO>(p, C, bias[s], res[s], R != nullptr, row_at[s], col, ccol, valid, out);
     }
   }
 }
