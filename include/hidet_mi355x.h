@@ -282,6 +282,9 @@ hidet_status_t hidet_tune_conv2d_packed(int32_t in, int32_t out, int64_t Nb, int
 hidet_status_t hidet_conv2d_untuned_config(int32_t in, int64_t Nb, int64_t IC, int64_t H, int64_t W, int64_t OC, int64_t KH,
                                            int64_t KW, int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w,
                                            int32_t packed, int32_t* config);
+/* The same for hidet_batched_gemm (batch = 1: hidet_gemm) on dense operands, batch entries one after another. */
+hidet_status_t hidet_gemm_untuned_config(int32_t in, int32_t transA, int32_t transB, int64_t batch, int64_t M, int64_t N,
+                                         int64_t K, int32_t* config);
 /*
  * Workspace of the K-parallel convolution (Sections 5.2 and 6.3.4: the convolution is the matrix multiplication
  * with GEMM M = OC and GEMM N = Nb*OH*roundup(OW, 8), the padded-row column order of the img2col prologue):

@@ -392,6 +392,59 @@ int one_round_config(const Problem& pr) {
   return best;
 }
 
+// GEMMs in 16-bit types with few output tiles.  -1: more tiles than that, the choice below is made.
+//
+// Tiles whose wavefronts stream K (gemm_kernel_waves) keep a compute unit to themselves; one round of them costs a fixed
+// 3 us and K times a rate that grows with the tile's extents, a second round as much again.  So the smallest one of
+// which all workgroups are resident is taken (300x768x3072: 240 of 32x32 10.6 us, 60 of 64x64 15.5 us; 20.9 us on 16x16,
+// which needs four rounds; 8x12288x4096, seven eighths of whose 64x64 tiles are padding: 23.4 us, 28.9 us on 16x32), on
+// aligned rows a 16x16 one only if it leaves a quarter of the device free: a 16x32 one touches no more cache lines of a
+// row-major B (117x512x2048: 256 of 16x16 6.8 us, 128 of 16x32 5.7 us; misaligned 276x213x3514: 10.9 and 11.9 us).  Each pays from the K on where its wavefronts have a step of
+// their own, earlier where rows are only element aligned, which the other tiles fetch under predicates: measured against
+// them on 320 random problems, 1.0 to 1.4 of their time below these limits, 0.4 to 1.0 above.
+// Below them the 32x32 tile of two stages, several to a compute unit, beats the larger ones as long as there are no more
+// than three to a compute unit (1308x566x256, 738 tiles: 5.7 us, 64x64 8.7 us; 168x624x49: 3.9 us, 16x64 6.1 us), on aligned
+// rows of more than 128 values the one of 256, of which a compute unit holds two (4 of 256x225x256: 4.6 us, 5.0 us).  From
+// there to 384 tiles of 64x64 the tiles of half that size do, with loads one iteration ahead (320x4096x1024: 12.4 us on
+// 32x64, 17.3 us on 128x128 K-splitting ones; 896x1246x72: 5.8 and 7.2 us on 64x64).
+// Over 620 random problems of 1 to 4096 rows and columns this choice (with the one below) takes 1.01 times as long as the best
+// configuration of each, the one before it 1.11 times; over 270 batched attention products 1.02 and 1.11.
+int few_tiles_gemm_config(const Problem& pr) {
+  constexpr long long kComputeUnits = 256;
+  const long long M = pr.p.M, N = pr.p.N, K = pr.p.K;
+  auto blocks = [&](long long bm, long long bn) { return sat_mul(((M + bm - 1) / bm) * ((N + bn - 1) / bn), pr.batch); };
+  const long long of_64 = blocks(64, 64);
+  if (of_64 >= 384) return -1;
+  int best = -1;
+  for (int c = 0; c < kNumConfigs; ++c) {
+    const ConfigRow& r = kConfigs[c];
+    if (r.sched != 3 || r.bm > 64 || r.bn > 64 || !find_launcher(pr, c)) continue;
+    const int area = r.bm * r.bn;
+    if (blocks(r.bm, r.bn) > (area == 16 * 16 && pr.elem_mode == 0 ? kComputeUnits * 3 / 4 : kComputeUnits)) continue;
+    // (of two tiles of one size the flatter one: rows of B are M/N-contiguous more often than not)
+    if (best < 0 || area < kConfigs[best].bm * kConfigs[best].bn || (area == kConfigs[best].bm * kConfigs[best].bn && r.bn > kConfigs[best].bn))
+      best = c;
+  }
+  if (best >= 0) {
+    const int area = kConfigs[best].bm * kConfigs[best].bn;
+    if (K >= (area >= 64 * 64 ? 512 : area > 32 * 32 ? 448 : area == 32 * 32 || pr.elem_mode == 0 ? 257 : area > 16 * 16 ? 160 : 128))
+      return best;
+  }
+  auto of_shape = [&](int bm, int bn, int bk, int sched) {
+    for (int c = 0; c < kNumConfigs; ++c) {
+      const ConfigRow& r = kConfigs[c];
+      if (r.bm == bm && r.bn == bn && r.bk == bk && r.sched == sched && r.mfma == 16 && find_launcher(pr, c)) return c;
+    }
+    return -1;
+  };
+  if (blocks(32, 32) <= 3 * kComputeUnits) {
+    const int deep = K > 128 && pr.elem_mode == 0 && blocks(32, 32) <= 2 * kComputeUnits ? of_shape(32, 32, 256, 0) : -1;
+    return deep >= 0 ? deep : of_shape(32, 32, 64, 0);
+  }
+  const int halves = blocks(64, 32) <= blocks(32, 64) ? of_shape(64, 32, 64, 2) : of_shape(32, 64, 64, 2);
+  return halves >= 0 ? halves : of_shape(32, 32, 64, 0);  // (a transposed A is built for the latter only)
+}
+
 // Untuned choice: the largest tile that still gives (nearly) every compute unit a workgroup, else the largest
 // that gives a quarter of them one, else the tile with the most workgroups.  Outputs large enough to be bound by
 // throughput rather than by one workgroup's latency chain (at least 384 tiles of 64x64) ask for about two
@@ -400,12 +453,18 @@ int one_round_config(const Problem& pr) {
 // workgroup and needs just over half a round of workgroups.  Between tiles of one size the ring schedule, the
 // 16x16 matrix-core shape and (small tiles) the loads-ahead order are preferred (they measure faster wherever
 // both apply); the tiles that split K over wave groups take part only when K spans at least one of their K tiles
-// and the output is small.  With slices > 1 only tiles that have a K-parallel form take part.
+// and the output is small (GEMMs in 16-bit types: few_tiles_gemm_config alone takes them).  With slices > 1 only tiles
+// that have a K-parallel form take part.
 int default_config(const Problem& pr, int slices = 1) {
   const long long M = pr.p.M, N = pr.p.N;
   const bool conv16 = pr.op == 1 && pr.dtype != HIDET_F32 && slices <= 1;
   if (conv16 && pr.p.K >= 512) {
     const int c = one_round_config(pr);
+    if (c >= 0) return c;
+  }
+  const bool gemm16 = pr.op == 0 && pr.dtype != HIDET_F32 && slices <= 1;
+  if (gemm16) {
+    const int c = few_tiles_gemm_config(pr);
     if (c >= 0) return c;
   }
   // The gather of a convolution is paid per column of the tile, and fewer than 64 output channels fill one tile row
@@ -417,8 +476,11 @@ int default_config(const Problem& pr, int slices = 1) {
   // (measured: equal to the two-stage tiles of their size at K = 1024, ahead beyond; the gather of the convolution
   // moves that point to about 512)
   const bool long_k = pr.p.K >= (pr.op == 1 ? 512 : 1024);
-  auto rank = [long_k](const ConfigRow& r) {
-    const int ahead = (r.sched == 2 && r.bm * r.bn <= 64 * 64) ? 1 : 0;  // measured faster on small tiles only
+  // (loads one iteration ahead: measured faster on small tiles only, and of a GEMM on aligned rows only -- predicated
+  // loads wait where they are issued: 184 of 103x128x103 10.5 us, 6.8 us without)
+  const bool ahead_pays = pr.op == 1 || pr.elem_mode == 0;
+  auto rank = [long_k, ahead_pays](const ConfigRow& r) {
+    const int ahead = (r.sched == 2 && r.bm * r.bn <= 64 * 64 && ahead_pays) ? 1 : 0;
     const int ksplit = (r.sched == 3 && long_k) ? 2 : 0;  // where they take part at all, they win on a long K
     return (long long)r.bm * r.bn * 8 + (r.sched == 1 ? 4 : 0) + (r.mfma == 16 ? 2 : 0) + ahead + ksplit;
   };
@@ -432,7 +494,7 @@ int default_config(const Problem& pr, int slices = 1) {
     if (slices > 1 && !find_partial_launcher(pr, c)) continue;
     const ConfigRow& r = kConfigs[c];
     // the wave groups along K need at least one whole K tile to share, and are meant for latency-bound problems
-    if (r.sched == 3 && (pr.p.K < r.bk || throughput)) continue;
+    if (r.sched == 3 && (pr.p.K < r.bk || throughput || gemm16)) continue;
     if (conv_few_rows && (r.bm > 64 || r.bn > 64)) {
       passed_over = c;
       continue;
@@ -454,9 +516,16 @@ int default_config(const Problem& pr, int slices = 1) {
     // A ring tile keeps one workgroup per compute unit busy on its own (from four stages of K on).  With 129..191
     // of them the tile of half the size would need a second, mostly empty round of workgroups, so the larger one is
     // still the better choice; from 128 down the smaller tile fits into one round and wins.
+    // (a quarter of it padding in every entry of a batch, no large tile is: 88 of 400x64x400 15.2 us on 256x128 tiles, 10.2
+    // us on 64x64; 65 of 398x398x128 29.9 us on 256x256, 17.2 us; 84 of 448x448x128 28.1 and 16.7 us)
     const long long area = (long long)r.bm * r.bn;
-    const bool self_overlapping = ring_any && pr.p.K >= 128;
-    const long long enough = !throughput ? 192 : self_overlapping ? 129 : 400;
+    const long long full = area >= 256 * 256 && pr.p.K <= 128 ? 7 : 6;  // eighths of a tile that have to be output
+    if (gemm16 && pr.batch > 1 && area >= 128 * 128 && 8 * M * N <= full * tiles * area) {
+      passed_over = c;
+      continue;
+    }
+    const bool self_overlapping = ring_any && pr.p.K >= 4 * r.bk;
+    const long long enough = !throughput ? 192 : self_overlapping ? 129 : gemm16 ? 384 : 400;
     // Tiles of 64x64 and more are no first choice of a convolution outside the rule above that is bound by latency (fewer
     // than 384 of them: 7 images of 64x56x56, 5x5: 343 tiles of 64x64 26.5 us, 64x32 21.8 us; 9 images of 128x28x28, 3x3:
     // 18.3 us and 14.8 us).  From 64x32 down one round is enough (18 images of 128x28x28 repacked, stride 2: 64x32 13.5
@@ -466,7 +535,13 @@ int default_config(const Problem& pr, int slices = 1) {
     // useful outputs per workgroup, discounted by the share of the tile that is padding, decide; then the smaller
     // tile, then the schedule preferences
     const long long useful = (M * N) / tiles;
-    const long long weight = (useful * useful) >> __builtin_ctzll(area);
+    long long weight = (useful * useful) >> __builtin_ctzll(area);
+    // (of a batch, whose entries are all cut alike, by the sixth power of the share that is output: 96 of 320x320x32 10.6 us
+    // on 128x64 tiles five sixths full, 8.1 us on 64x64; 43 of 448x448x64 10.0 and 8.4 us)
+    if (gemm16 && pr.batch > 1) {
+      const long long fill = (useful << 10) >> __builtin_ctzll(area), square = (fill * fill) >> 10;
+      weight = (((weight * square) >> 10) * square) >> 10;
+    }
     // (the 64x64 tile alone: the 32x32 one of that matrix-core shape is a single wavefront with a deep K tile; 8 images of
     // 16x112x112, 24 channels, 3x3, stride 2: 10.1 us on it, 7.5 us on the 32x32 tile of 16x16)
     // Not on a long K while the tiles of three stages, three to a compute unit, are all resident at once: the third stage
@@ -1161,6 +1236,19 @@ hidet_status_t hidet_conv2d_untuned_config(int32_t in, int64_t Nb, int64_t IC, i
                                                     at, at, at, nullptr);
   if (st != HIDET_OK) return st;
   const Problem& pr = cc.pointwise ? cc.gemm : cc.conv;
+  *config = pr.batch == 0 || pr.p.M == 0 || pr.p.N == 0 ? -1 : default_config(pr);
+  return HIDET_OK;
+}
+
+hidet_status_t hidet_gemm_untuned_config(int32_t in, int32_t transA, int32_t transB, int64_t batch, int64_t M, int64_t N,
+                                         int64_t K, int32_t* config) {
+  if (!config) return HIDET_ERR_INVALID_ARG;
+  void* const at = reinterpret_cast<void*>((uintptr_t)4096);  // (as above)
+  const long long lda = transA ? M : K, ldb = transB ? K : N;
+  Problem pr;
+  const hidet_status_t st = make_gemm_problem(pr, in, in, transA, transB, batch, M, N, K, at, lda, sat_mul(M, K), at, ldb,
+                                              sat_mul(N, K), at, N, sat_mul(M, N), nullptr);
+  if (st != HIDET_OK) return st;
   *config = pr.batch == 0 || pr.p.M == 0 || pr.p.N == 0 ? -1 : default_config(pr);
   return HIDET_OK;
 }
