@@ -6,12 +6,15 @@ fallback: if libhidet_mi355x.so has not been built, or a call returns a non-zero
 exception is raised.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libhidet_mi355x.so")
+HOST_CALLS_PATH = os.path.join(HERE, "_host_calls.so")
 
 HIDET_F32, HIDET_F16, HIDET_BF16 = 0, 1, 2
 HIDET_BIAS_NONE, HIDET_BIAS_PER_COL, HIDET_BIAS_PER_ROW = 0, 1, 2
@@ -138,14 +141,40 @@ def lib():
     return _lib
 
 
+# The plain form of a call goes through an extension module that reads the tensors itself (csrc/host_calls.cpp).  A
+# negative answer means that the arguments are not of that form and that nothing was called.
+_host_calls = None
+
+
+def _load_host_calls(L):
+    if not os.path.exists(HOST_CALLS_PATH):
+        raise RuntimeError("host extension missing: %s (build it with `python -m paper_2210_09603_amd.build`)" % HOST_CALLS_PATH)
+    loader = importlib.machinery.ExtensionFileLoader("_host_calls", HOST_CALLS_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_host_calls", loader))
+    loader.exec_module(module)
+    entry = (L.hidet_gemm_cfg, L.hidet_batched_gemm_cfg, L.hidet_conv2d_implicit_gemm_cfg,
+             L.hidet_conv2d_implicit_gemm_packed, L.hidet_softmax_rows, L.hidet_reduce_rows)
+    c = torch._C
+    unavailable = lambda *a: None  # (a torch without the GPU: the general path says so)
+    return module.Calls(tuple(ctypes.cast(f, _vp).value for f in entry), hidet_epilogue_t,
+                        getattr(c, "_cuda_isInBadFork", unavailable), getattr(c, "_cuda_getDevice", unavailable),
+                        getattr(c, "_cuda_getCurrentRawStream", unavailable))
+
+
+def _calls():
+    global _host_calls
+    if _host_calls is None:
+        _host_calls = _load_host_calls(lib())
+    return _host_calls
+
+
 def _check(status, where):
     if status != 0:
         raise HidetError(status, where)
 
 
-# A small call costs what its host path costs (the kernel of a 256^3 product runs 3 us), so the helpers below hand plain
-# integers to ctypes (argtypes converts them), read each shape and stride tuple once and take the current stream's
-# handle without building a Stream object.
+# The helpers of the general path hand plain integers to ctypes (argtypes converts them), read each shape and stride tuple
+# once and take the current stream's handle without building a Stream object.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
@@ -220,6 +249,14 @@ def _gemm_dims(A, B, transA, transB):
 
 def hidet_gemm(A, B, C, transA=False, transB=False, epilogue=None, stream=None, config=-1):
     """C[M,N] = epilogue(op(A) . op(B)); A, B, C are 2-D GPU tensors (row-major, any leading dimension)."""
+    st = (_host_calls or _calls()).gemm(A, B, C, transA, transB, epilogue, stream, config)
+    if st < 0:
+        _gemm(A, B, C, transA, transB, epilogue, stream, config)
+    else:
+        _check(st, "hidet_gemm")
+
+
+def _gemm(A, B, C, transA, transB, epilogue, stream, config):
     M, N, K = _gemm_dims(A, B, transA, transB)
     if epilogue is not None and epilogue.out_map == HIDET_MAP_HEAD_SPLIT:
         want = (M // epilogue.map_seq, N // epilogue.map_head_dim, epilogue.map_seq, epilogue.map_head_dim)
@@ -243,6 +280,14 @@ def _bstride(t):
 
 def hidet_batched_gemm(A, B, C, transA=False, transB=False, epilogue=None, stream=None, config=-1):
     """Batched form: A, B, C are 3-D GPU tensors [batch, rows, cols]."""
+    st = (_host_calls or _calls()).batched_gemm(A, B, C, transA, transB, epilogue, stream, config)
+    if st < 0:
+        _batched_gemm(A, B, C, transA, transB, epilogue, stream, config)
+    else:
+        _check(st, "hidet_batched_gemm")
+
+
+def _batched_gemm(A, B, C, transA, transB, epilogue, stream, config):
     M, N, K = _gemm_dims(A, B, transA, transB)
     batch = A.shape[0]
     if B.shape[0] != batch or C.shape != (batch, M, N):
@@ -272,6 +317,14 @@ def conv_out_shape(x_shape, w_shape, stride, pad):
 
 def hidet_conv2d_implicit_gemm(x, w, y, stride=(1, 1), pad=(0, 0), epilogue=None, stream=None, config=-1):
     """y = epilogue(conv2d(x, w)), NCHW / OIHW / NCHW dense GPU tensors; bias (if any) is per output channel."""
+    st = (_host_calls or _calls()).conv2d(x, w, y, stride, pad, epilogue, stream, config)
+    if st < 0:
+        _conv2d(x, w, y, stride, pad, epilogue, stream, config)
+    else:
+        _check(st, "hidet_conv2d_implicit_gemm")
+
+
+def _conv2d(x, w, y, stride, pad, epilogue, stream, config):
     if y.shape != conv_out_shape(x.shape, w.shape, stride, pad):
         raise ValueError("y has the wrong shape")
     st = lib().hidet_conv2d_implicit_gemm_cfg(config, *_conv_args(x, w, y, stride, pad), _epi_ref(epilogue),
@@ -394,6 +447,16 @@ def _packed_conv_args(x, w_packed, y, stride, pad):
 def hidet_conv2d_implicit_gemm_packed(x, w_packed, y, stride=(1, 1), pad=(0, 0), epilogue=None, stream=None, config=-1,
                                       k_slices=0, workspace=None):
     """The convolution from weights repacked by hidet_conv2d_pack_weights ([OC][KH][KW][IC])."""
+    st = -1
+    if workspace is None:
+        st = (_host_calls or _calls()).conv2d_packed(x, w_packed, y, stride, pad, epilogue, stream, config, k_slices)
+    if st < 0:
+        _conv2d_packed(x, w_packed, y, stride, pad, epilogue, stream, config, k_slices, workspace)
+    else:
+        _check(st, "hidet_conv2d_implicit_gemm_packed")
+
+
+def _conv2d_packed(x, w_packed, y, stride, pad, epilogue, stream, config, k_slices, workspace):
     wp, wb = _ws(workspace)
     st = lib().hidet_conv2d_implicit_gemm_packed(config, k_slices, *_packed_conv_args(x, w_packed, y, stride, pad),
                                                  _epi_ref(epilogue), wp, wb, _stream(stream))
@@ -448,6 +511,14 @@ def _rows_view(t):
 
 def hidet_reduce_rows(x, y, op=HIDET_REDUCE_SUM, stream=None):
     """y[i] = reduce over the last axis of x; y has one element per row, dtype of x or float32."""
+    st = (_host_calls or _calls()).reduce_rows(x, y, op, stream)
+    if st < 0:
+        _reduce_rows(x, y, op, stream)
+    else:
+        _check(st, "hidet_reduce_rows")
+
+
+def _reduce_rows(x, y, op, stream):
     rows, cols, ld = _rows_view(x)
     if y.numel() != rows or not y.is_contiguous():
         raise ValueError("y must be a dense tensor with one element per row")
@@ -457,6 +528,14 @@ def hidet_reduce_rows(x, y, op=HIDET_REDUCE_SUM, stream=None):
 
 def hidet_softmax_rows(x, y, stream=None):
     """y = softmax of x along the last axis (same shape and dtype; y may be x itself)."""
+    st = (_host_calls or _calls()).softmax_rows(x, y, stream)
+    if st < 0:
+        _softmax_rows(x, y, stream)
+    else:
+        _check(st, "hidet_softmax_rows")
+
+
+def _softmax_rows(x, y, stream):
     if x.shape != y.shape or x.dtype != y.dtype:
         raise ValueError("x and y must agree in shape and dtype")
     rows, cols, ldx = _rows_view(x)

@@ -1,4 +1,5 @@
-"""Build libhidet_mi355x.so: every (tile configuration, input type) instance object plus the C ABI.
+"""Build libhidet_mi355x.so: every (tile configuration, input type) instance object plus the C ABI; and _host_calls.so, the
+extension module through which the binding reaches it.
 
     python -m paper_2210_09603_amd.build            # incremental
     python -m paper_2210_09603_amd.build --force    # recompile everything
@@ -13,11 +14,13 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libhidet_mi355x.so")
+HOST_CALLS = os.path.join(HERE, "_host_calls.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -46,9 +49,23 @@ def _sources_digest():
     return h.hexdigest()
 
 
+def _host_flags():
+    """g++ flags of the extension module, which reads torch tensors: to compile it, to link it (against the libraries that
+    `import torch` has loaded before it)."""
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+
+    abi = "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)
+    compile_flags = ["-O2", "-std=c++17", "-fPIC", "-Wall", abi, "-I" + sysconfig.get_paths()["include"]]
+    return compile_flags + ["-isystem" + d for d in include_paths()], ["-L" + d for d in library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def _compile(args):
     src, obj, defines = args
-    cmd = [HIPCC] + FLAGS + defines + ["-c", src, "-o", obj]
+    if src.endswith(".cpp"):
+        cmd = [os.environ.get("CXX", "g++")] + _host_flags()[0] + ["-c", src, "-o", obj]
+    else:
+        cmd = [HIPCC] + FLAGS + defines + ["-c", src, "-o", obj]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     # hipcc's host pass does not know the packed-fp32 feature and says so on every file; drop that line
     log = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l)
@@ -79,6 +96,9 @@ def build(force=False, jobs=None, verbose=True):
         objs.append(obj)
         if not os.path.exists(obj):
             tasks.append((os.path.join(CSRC, name + ".hip"), obj, []))
+    host_obj = os.path.join(BUILD, "host_calls.o")
+    if not os.path.exists(host_obj):
+        tasks.append((os.path.join(CSRC, "host_calls.cpp"), host_obj, []))
     jobs = jobs or min(8, os.cpu_count() or 1)
     failed = False
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
@@ -96,6 +116,9 @@ def build(force=False, jobs=None, verbose=True):
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs, check=True)
     os.replace(tmp, LIB)
+    tmp = HOST_CALLS + ".tmp.%d" % os.getpid()
+    subprocess.run([os.environ.get("CXX", "g++"), "-shared", "-fPIC", "-o", tmp, host_obj] + _host_flags()[1], check=True)
+    os.replace(tmp, HOST_CALLS)
     with open(stamp, "w") as fh:
         fh.write(digest)
     return LIB
