@@ -118,7 +118,12 @@ struct Operand {
   static constexpr bool GATHER = MODE == LD_IM2COL || MODE == LD_IM2COL_TAP;
   static constexpr int NP = GATHER ? NL : 1;
   u32x4 win2[NP];  // stride 2: the second half of the window
-  u32x4 wmask[NP]; // the 16-byte mask that keeps elements [lo, hi)
+  // The 16-byte mask that keeps elements [lo, hi): held from the request on, except by sixteen wavefronts of two chunks a
+  // thread, which have 128 registers each.  There four registers a chunk made the 64x64 tile spill 41 in its main loop (12
+  // images of 256x14x14: 32.6 us, 20.36 us with the mask read when the tile is stored); elsewhere that read is one more LDS
+  // round trip before the barrier (37 images of 128x27x27, 5x5: 54.4 -> 56.2 us).
+  static constexpr bool LATE_MASK = NT >= 1024 && NL >= 2;
+  u32x4 wmask[LATE_MASK ? 1 : NP];
   int wstart[NP];  // element offset of the window
   int winfo[NP];   // lo * (VEC + 1) + hi: elements [lo, hi) are kept; bit 8: the window leaves the tensor
   int wsw;         // 2: windows are 2 * VEC elements of which the even ones are used; else 1
@@ -174,15 +179,15 @@ struct Operand {
       const T* win = src + ((any && inside) ? start : 0);
       wstart[q] = start;
       winfo[q] = (lo * (VEC + 1) + hi) | ((any && !inside) ? 0x100 : 0);
-      wmask[q] = *reinterpret_cast<const u32x4*>(masks + (lo * (VEC + 1) + hi) * 16);
+      if constexpr (!LATE_MASK) wmask[q] = *reinterpret_cast<const u32x4*>(masks + (lo * (VEC + 1) + hi) * 16);
       wsw = sw;
       if (sw == 2) win2[q] = reinterpret_cast<const Unaligned*>(win + VEC)->v;
       return reinterpret_cast<const Unaligned*>(win)->v;
     }
     // Other strides: element e is input pixel (ih, iwf + e * sw), fetched one by one.
     wstart[q] = 0;
-    winfo[q] = 0;
-    wmask[q] = u32x4{0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+    winfo[q] = VEC;  // all of them
+    if constexpr (!LATE_MASK) wmask[q] = u32x4{0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
     wsw = 1;
     const int step = g.sw, W = g.W, cnt = row_ok ? pcnt : 0;
     return gather_elements(start, step, [=](int e) { return e < cnt && (unsigned)(iwf + e * step) < (unsigned)W; });
@@ -275,8 +280,13 @@ struct Operand {
                   (w[0] & 0xffffu) | (w[1] << 16), (w[2] & 0xffffu) | (w[3] << 16)};
       }
     }
+    u32x4 mask;
+    if constexpr (LATE_MASK)
+      mask = *reinterpret_cast<const u32x4*>(masks + (info & 0xff) * 16);
+    else
+      mask = wmask[q];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] &= wmask[q][i];
+    for (int i = 0; i < 4; ++i) v[i] &= mask[i];
     if (info & 0x100) {
       // first or last pixels of the tensor: the window would have left the allocation (it was read from a
       // valid address instead and is replaced here, element by element)
