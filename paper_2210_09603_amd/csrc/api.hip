@@ -76,6 +76,7 @@ struct Problem {
   long long batch = 1;
   int elem_mode = 0;  // 1: some operand is not 16-byte aligned -> element loads
   int packed = 0;     // convolution only: 1 = weights repacked to the tap-major K order (kh, kw, ic)
+  int images = 0;     // convolution only: 1 = 1x1, its columns run through all images, ring schedule
   GemmParams p{};
   // conv-only key fields
   long long Nb = 0, OC = 0;
@@ -311,6 +312,7 @@ LaunchFn find_launcher(const Problem& pr, int config) {
   if (config < 0 || config >= kNumConfigs) return nullptr;
   // The ring schedule is built without the run-time output map; a head-split problem takes the same tile's
   // element-mode variant, whose launcher then picks the through-registers form of the schedule.
+  if (pr.images != 0) return registry().fn[config][pr.dtype][kPointwiseVariant];
   // repacked weights: the K axis is (kh, kw, ic) and a K tile must lie within one filter tap
   if (pr.packed) return pr.p.g.IC % kConfigs[config].bk == 0 ? registry().fn[config][pr.dtype][kConvTapVariant] : nullptr;
   // The ring schedule is also built without the input prologue (its direct loads bypass the registers): such a
@@ -877,6 +879,42 @@ struct ConvCall {
   bool pointwise = false;
 };
 
+// A 1x1 convolution as one product whose columns run through all images (pixels of an image rounded up to whole chunks of
+// eight), on the 128x128 ring tile with stages of 32, two workgroups to a compute unit: the configuration, or -1 where the
+// batched GEMM is taken.  Against it there is no padding of every image to whole tiles, rows of 49 or 169 pixels come in by
+// direct loads, the weights are read once per 128 columns and the residual is fetched at once (64 images of 512x7x7, 2048
+// channels, with residual: 37.7 -> 18.4 us; 64 of 128x28x28, 512 channels, with residual: 66 -> 34 us; 57 of 192x21x21, 336
+// channels: 25 -> 17 us).
+// It wants more than half a round of tiles, a whole one where the batched GEMM has aligned rows (110 random problems, its time
+// over the GEMM's: 0.42 to 1.04 from 120 tiles on rows that are not, but 1.2 at 69 to 80; on aligned ones 0.43 to 0.89 beyond
+// 256 tiles, 1.15 at 208), and twice two rounds where half of a tile or more is padding (64 channels: 0.8 at 518 tiles, 1.1 at
+// 417; 32 channels 1.35 at 356, 0.67 at 627).
+int images_config(const Problem& conv, bool pointwise, const SplitK& sk) {
+  const ConvGeom& g = conv.p.g;
+  // (a K slice or an input prologue needs another kernel; direct loads need aligned weights, and rows of a chunk at least, so
+  // that one leaves the tensor in the last stage alone; their offsets from the tile's first image are 32 bits wide)
+  if (!pointwise || conv.dtype == HIDET_F32 || conv.elem_mode != 0 || conv.p.relu_b != 0 || sk.slices > 1) return -1;
+  if (conv.p.K == 0 || conv.p.N == 0 || conv.p.M == 0 || g.HW < 8) return -1;
+  if ((128 / g.HW + 2) * (long long)g.IC * g.HW > (1LL << 30)) return -1;
+  const long long tiles = (((long long)conv.p.M + 127) >> 7) * ((conv.Nb * ((g.HW + 7) / 8 * 8) + 127) >> 7);
+  if (tiles < (conv.p.M <= 64 ? 512 : g.HW % 8 != 0 ? 120 : 257)) return -1;
+  for (int c = 0; c < kNumConfigs; ++c)
+    if (registry().fn[c][conv.dtype][kPointwiseVariant]) return c;
+  return -1;
+}
+Problem images_problem(const Problem& conv) {
+  Problem pr = conv;
+  ConvGeom& g = pr.p.g;
+  pr.images = 1;
+  g.H = g.OH = 1;
+  g.W = g.OW = g.HW;
+  g.OWP = (g.HW + 7) / 8 * 8;
+  g.d_owp = make_fastdiv(g.OWP);
+  g.d_oh = make_fastdiv(1);
+  pr.p.N = (int)(conv.Nb * g.OWP);
+  return pr;
+}
+
 hidet_status_t make_conv_call(ConvCall& cc, int in, int out, long long Nb, long long IC, long long H, long long W,
                               long long OC, long long KH, long long KW, long long sh, long long sw, long long ph,
                               long long pw, const void* x, const void* w, void* y, const hidet_epilogue_t* epi) {
@@ -902,7 +940,7 @@ hidet_status_t make_conv_call(ConvCall& cc, int in, int out, long long Nb, long 
 }
 
 // An explicit configuration always runs the gather form; config < 0 runs what the tuner remembered for this
-// convolution, else (1x1 convolutions) the batched-GEMM form with its size-based default.
+// convolution, else (1x1 convolutions) the product over all images or the batched-GEMM form with its size-based default.
 hidet_status_t launch_conv(const ConvCall& cc, int config, const SplitK& sk, hipStream_t stream) {
   if (config >= 0 || !cc.pointwise) return launch(cc.conv, config, sk, stream);
   Tuned t{-1, 1, 0};
@@ -911,7 +949,10 @@ hidet_status_t launch_conv(const ConvCall& cc, int config, const SplitK& sk, hip
     auto it = find_tuned(cc.conv, sk);
     if (it != g_cache.end()) t = it->second;
   }
-  if (t.config < 0) return launch(cc.gemm, -1, sk, stream);
+  if (t.config < 0) {
+    const int c = images_config(cc.conv, cc.pointwise, sk);
+    return c >= 0 ? launch(images_problem(cc.conv), c, SplitK(), stream) : launch(cc.gemm, -1, sk, stream);
+  }
   SplitK one = sk;
   if (one.slices < 0) one.slices = t.slices;
   return launch(t.route == 1 ? cc.gemm : cc.conv, t.config, one, stream);
@@ -1236,7 +1277,8 @@ hidet_status_t hidet_conv2d_untuned_config(int32_t in, int64_t Nb, int64_t IC, i
                                                     at, at, at, nullptr);
   if (st != HIDET_OK) return st;
   const Problem& pr = cc.pointwise ? cc.gemm : cc.conv;
-  *config = pr.batch == 0 || pr.p.M == 0 || pr.p.N == 0 ? -1 : default_config(pr);
+  const int images = images_config(cc.conv, cc.pointwise, SplitK());
+  *config = images >= 0 ? images : pr.batch == 0 || pr.p.M == 0 || pr.p.N == 0 ? -1 : default_config(pr);
   return HIDET_OK;
 }
 

@@ -214,6 +214,18 @@ __device__ __forceinline__ void setup_operands(const GemmParams& p, const BlockC
   opa.r0 = bc.m0;
   opa.span = (Cfg::LA == L_KC) ? (long long)(opa.rows_left - 1) * p.lda + (p.K - bc.k_begin)
                                : (long long)(p.K - bc.k_begin - 1) * p.lda + opa.rows_left;
+  if constexpr (Cfg::MODE_B == LD_IMAGES) {
+    const int img0 = __builtin_amdgcn_readfirstlane(p.g.d_owp.div(bc.n0));
+    const long long first = (long long)img0 * (p.g.IC * p.g.HW);  // the tile's first image
+    opb.src = B + first;
+    opb.ld = p.g.HW;
+    opb.rows_left = p.N - bc.n0;
+    opb.K = bc.k_len;
+    opb.kofs = bc.k_begin;
+    opb.r0 = bc.n0;
+    opb.span = p.g.numel_x - first;
+    return;
+  }
   if constexpr (Cfg::GATHER_B)
     opb.src = B;  // the gather addresses the whole input tensor
   else
@@ -353,5 +365,127 @@ __device__ __forceinline__ void epilogue(const GemmParams& p, const BlockCoords&
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
   }
 }
+
+// The epilogue of a 1x1 convolution whose columns run through all images (LD_IMAGES): the same transposition through LDS,
+// read back and stored a chunk of eight pixels at a time (a chunk never leaves its image, and rows of one image follow one
+// another in y, whatever their alignment).  The biases and the residual, as many bytes as the output, are requested all at
+// once, before the last stage is multiplied (request), instead of by the group where they are added: 64 images of 512x7x7, 2048
+// channels, with residual on 256x128 tiles 28.5 us with the general epilogue, 20.2 us with this one (25.7 MB of residual and
+// output: 4 us at the rate of a copy).
+template <class Cfg>
+struct ImagesEpilogue {
+  using TO = typename Cfg::TO;
+  static constexpr int MI = Cfg::MI, FM = Cfg::FM, FN = Cfg::FN, WTN = Cfg::WTN;
+  static constexpr int LANES_PER_ROW = WTN / 8, READS = MI * LANES_PER_ROW / 64;
+  static constexpr int ROW_BYTES = WTN * 4 + 16;  // +16: consecutive rows start 4 banks apart
+  static_assert(sizeof(TO) == 2 && 64 % LANES_PER_ROW == 0 && MI * LANES_PER_ROW % 64 == 0, "whole passes of 16-byte chunks");
+  struct __attribute__((packed, aligned(2))) Chunk {
+    u32x4 v;
+  };
+  struct __attribute__((packed, aligned(2))) Half {
+    u32x2 v;
+  };
+  struct __attribute__((packed, aligned(2))) Quarter {
+    unsigned int v;
+  };
+  int valid;        // pixels of this lane's column chunk that are outputs
+  long long first;  // offset of the chunk in row 0 of y's image
+  u32x4 res[FM][READS];
+  TO bias[FM][READS];
+
+  __device__ __forceinline__ int row(int i, int t, int lane) const { return i * MI + (t * 64 + lane) / LANES_PER_ROW; }
+
+  __device__ __forceinline__ void request(const GemmParams& p, int m0, int n0, int lane) {
+    const int n = n0 + (lane % LANES_PER_ROW) * 8, img = p.g.d_owp.div(n), pixel = n - img * p.g.OWP;
+    const int left = n < p.N ? p.g.OW - pixel : 0;
+    valid = left > 8 ? 8 : left;
+    first = (long long)img * p.out_outer + pixel;
+    const TO* R = reinterpret_cast<const TO*>(p.residual);
+    const long long end = (long long)(p.N / p.g.OWP) * p.out_outer;  // elements of y
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int t = 0; t < READS; ++t) {
+        const int m = m0 + row(i, t, lane);
+        bias[i][t] = (TO)0.0f;
+        res[i][t] = u32x4{0u, 0u, 0u, 0u};
+        if (p.bias_axis == 2) bias[i][t] = reinterpret_cast<const TO*>(p.bias)[m < p.M ? m : 0];
+        if (R != nullptr && m < p.M && valid > 0) {
+          const long long at = first + (long long)m * p.out_inner;
+          if (at + 8 <= end) {
+            res[i][t] = reinterpret_cast<const Chunk*>(R + at)->v;
+          } else {  // the last pixels of the tensor
+            TO r[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r[e] = R[e < valid ? at + e : at];
+            res[i][t] = __builtin_bit_cast(u32x4, r);
+          }
+        }
+      }
+  }
+
+  template <class Acc>
+  __device__ __forceinline__ void finish(const GemmParams& p, int wave, int lane, int m0, Acc (&acc)[FM][FN], unsigned char* smem) {
+    constexpr int GROUPS = (MI == 32) ? 4 : 1;
+    unsigned char* region = smem + wave * (MI * ROW_BYTES);
+    TO* C = reinterpret_cast<TO*>(p.C) + first;
+    const bool residual = p.residual != nullptr, streamed = p.vec_store >= 2 && p.g.OW % 8 == 0 && (reinterpret_cast<size_t>(p.C) & 15) == 0;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int gq = 0; gq < GROUPS; ++gq) {
+          const int nl = j * MI + ((MI == 32) ? 8 * gq + 4 * (lane / 32) : 4 * (lane / 16));
+          const f32x4 v = {acc[i][j][4 * gq + 0], acc[i][j][4 * gq + 1], acc[i][j][4 * gq + 2], acc[i][j][4 * gq + 3]};
+          *reinterpret_cast<f32x4*>(region + (lane % MI) * ROW_BYTES + nl * 4) = v;
+        }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+#pragma unroll
+      for (int t = 0; t < READS; ++t) {
+        const unsigned char* src = region + (row(0, t, lane)) * ROW_BYTES + (lane % LANES_PER_ROW) * 32;
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(src), hi = *reinterpret_cast<const f32x4*>(src + 16);
+        const float b = to_f32(bias[i][t]);
+        TO r[8], o[8];
+        __builtin_memcpy(r, &res[i][t], 16);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          float x = p.alpha * (e < 4 ? lo[e & 3] : hi[e & 3]) + b;
+          if (residual) x += to_f32(r[e]);
+          if (p.relu) x = x < 0.0f ? 0.0f : x;
+          o[e] = from_f32<TO>(x);
+        }
+        const int m = m0 + row(i, t, lane);
+        if (m >= p.M) continue;
+        TO* dst = C + (long long)m * p.out_inner;
+        u32x4 v;
+        __builtin_memcpy(&v, o, 16);
+        if (valid == 8) {
+          if (streamed)
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
+          else
+            reinterpret_cast<Chunk*>(dst)->v = v;
+        } else if (valid > 0) {
+          if (valid & 4) {
+            reinterpret_cast<Half*>(dst)->v = u32x2{v[0], v[1]};
+            dst += 4;
+            v = u32x4{v[2], v[3], 0u, 0u};
+          }
+          if (valid & 2) {
+            reinterpret_cast<Quarter*>(dst)->v = v[0];
+            dst += 2;
+            v[0] = v[1];
+          }
+          if (valid & 1) *dst = __builtin_bit_cast(TO, (unsigned short)v[0]);
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    }
+  }
+};
 
 }  // namespace hidet

@@ -278,6 +278,8 @@ __global__ void __launch_bounds__(Cfg::NT) gemm_kernel(const GemmParams p) {
 // last row of a row-major operand, where reading past the last column would leave the allocation
 // (on every other row it reads the beginning of the next one, into columns that are never stored).
 // ---------------------------------------------------------------------------------------------
+// A 1x1 convolution (LD_IMAGES) runs it over the columns of all images, with an epilogue of its own.
+//
 // SLOTS = 2 is the same kernel for a K range of at most two stages: nothing is ever requested into a slot that was
 // used before, two slots of LDS are enough, and two such workgroups fit on a compute unit where the registers allow
 // (the output write of one then overlaps the loads and the matrix-core work of the other).
@@ -287,7 +289,8 @@ __global__ void __launch_bounds__(Cfg::NT) gemm_kernel_pingpong(const GemmParams
   using Acc = typename AccT<Cfg::MI>::type;
   constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK, MI = Cfg::MI, NT = Cfg::NT;
   constexpr int FM = Cfg::FM, FN = Cfg::FN, KS = Cfg::KS;
-  static_assert(Cfg::NWAVES == 8 && !Cfg::IS_F32 && Cfg::MODE_A == Cfg::MODE_B &&
+  constexpr bool IMAGES = Cfg::MODE_B == LD_IMAGES;  // a 1x1 convolution
+  static_assert(Cfg::NWAVES == 8 && !Cfg::IS_F32 && (Cfg::MODE_A == Cfg::MODE_B || (IMAGES && Cfg::MODE_A == LD_VEC)) &&
                     (Cfg::MODE_A == LD_VEC || Cfg::MODE_A == LD_ELEM) && Cfg::STAGES == 4,
                 "ping-pong schedule: 8 waves, 16-bit types, plain operands, 4 LDS stages");
   constexpr bool ELEM = Cfg::MODE_A == LD_ELEM;  // rows only element aligned
@@ -348,8 +351,22 @@ __global__ void __launch_bounds__(Cfg::NT) gemm_kernel_pingpong(const GemmParams
     __builtin_amdgcn_sched_barrier(0);
   };
   const unsigned smem_lds = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
+  [[maybe_unused]] typename std::conditional<IMAGES, ImagesEpilogue<Cfg>, char>::type images;
+  // stages loaded directly: the full ones; all but the last one for element-aligned operands; all of them for a 1x1
+  // convolution, where lanes whose chunk lies outside K or leaves the tensor fill its place themselves
+  const int S = IMAGES ? (bc.k_len + BK - 1) / BK : ELEM ? (bc.k_len > 0 ? (bc.k_len - 1) / BK : 0) : bc.k_len / BK;
+  // those that every wavefront has LOADS loads of in flight: not the last one where lanes do so
+  const int counted = IMAGES && (bc.k_len % BK != 0 || bc.n0 + BN >= p.N) ? S - 1 : S;
   auto request = [&](int s) {  // direct loads of stage s into ring slot s % 4
     const unsigned slot = smem_lds + (unsigned)((s & (SLOTS - 1)) * Cfg::STAGE_BYTES);
+    if constexpr (IMAGES) {
+      if (s >= counted) {
+        unsigned char* at = smem + (s & (SLOTS - 1)) * Cfg::STAGE_BYTES;
+        opa.load_direct_edge(at, slot, tid, wave, s * BK);
+        opb.load_direct_edge(at + Cfg::A_BYTES, slot + Cfg::A_BYTES, tid, wave, s * BK);
+        return;
+      }
+    }
     opa.load_direct(slot, wave, s * BK);
     opb.load_direct(slot + Cfg::A_BYTES, wave, s * BK);
   };
@@ -363,31 +380,42 @@ __global__ void __launch_bounds__(Cfg::NT) gemm_kernel_pingpong(const GemmParams
       __builtin_amdgcn_s_waitcnt(0x0070);
   };
 
-  // stages loaded directly: the full ones; all but the last one for element-aligned operands
-  const int S = ELEM ? (bc.k_len > 0 ? (bc.k_len - 1) / BK : 0) : bc.k_len / BK;
   if (S > 0) {
     opa.init_direct(tid, ELEM);
-    opb.init_direct(tid, ELEM);
+    if constexpr (IMAGES)
+      opb.init_images(tid, p.g);
+    else
+      opb.init_direct(tid, ELEM);
     const int pre = S < 3 ? S : 3;
     for (int s = 0; s < pre; ++s) request(s);
-    wait_stage(pre - 1);
+    wait_stage((counted < pre ? counted : pre) - 1);
     phase_barrier();
     if (grp == 1) phase_barrier();
-    for (int s = 0; s < S; ++s) {
-      // ---- memory phase
-      load_frags(smem + (s & (SLOTS - 1)) * Cfg::STAGE_BYTES);
-      if (s + 3 < S) request(s + 3);
-      wait_stage((s + 2 < S) + (s + 3 < S));
-      phase_barrier();
-      // ---- compute phase
+    auto compute_phase = [&]() {
       __builtin_amdgcn_s_setprio(1);
       mfmas();
       __builtin_amdgcn_s_setprio(0);
       phase_barrier();
+    };
+    const int looped = IMAGES ? S - 1 : S;
+    for (int s = 0; s < looped; ++s) {
+      // ---- memory phase
+      load_frags(smem + (s & (SLOTS - 1)) * Cfg::STAGE_BYTES);
+      if (s + 3 < S) request(s + 3);
+      wait_stage((s + 2 < counted) + (s + 3 < counted));
+      phase_barrier();
+      compute_phase();
+    }
+    if constexpr (IMAGES) {  // the last stage, for which nothing is in flight: what the end needs is requested before it
+      images.request(p, bc.m0 + wm0, bc.n0 + wn0, lane);
+      load_frags(smem + (looped & (SLOTS - 1)) * Cfg::STAGE_BYTES);
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // (LDS only)
+      phase_barrier();
+      compute_phase();
     }
     if (grp == 0) phase_barrier();
   }
-  if (S * BK < bc.k_len) {  // the last stage (partial, or any for element-aligned operands), through registers with zero fill
+  if (!IMAGES && S * BK < bc.k_len) {  // the last stage (partial, or any for element-aligned operands), through registers with zero fill
     u32x4 ra[OpA::NL], rb[OpB::NL];
     opa.init(tid, p.g);
     opb.init(tid, p.g);
@@ -402,7 +430,10 @@ __global__ void __launch_bounds__(Cfg::NT) gemm_kernel_pingpong(const GemmParams
   }
   __syncthreads();  // the epilogue reuses the LDS
 
-  epilogue<Cfg, Acc, false>(p, bc, wave, lane, wm0, wn0, acc, col_bias, smem);
+  if constexpr (IMAGES)
+    images.finish(p, wave, lane, bc.m0 + wm0, acc, smem);
+  else
+    epilogue<Cfg, Acc, false>(p, bc, wave, lane, wm0, wn0, acc, col_bias, smem);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -382,6 +382,21 @@ struct Operand {
       }
     }
   }
+  // LD_IMAGES (1x1 convolutions of unit stride, no padding): column n = image * OWP + pixel, where OWP is the number of pixels
+  // rounded up to whole chunks, so that a chunk is eight pixels of one image.  `src` is the first image of the tile.  A chunk
+  // that sticks out of its image's row is read where it lies (the next row, or the next image: columns that are never stored);
+  // chunks past the last column take the first one.
+  __device__ __forceinline__ void init_images(int tid, const ConvGeom& g) {
+    const int img0 = g.d_owp.div(r0);
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+      const tmap::Task t = LoadMap::task(tid, q);
+      const int sc = (t.j ^ swz_mc<CPR, MI>(t.i)) * VEC;
+      const int n = sc < rows_left ? r0 + sc : img0 * g.OWP, img = g.d_owp.div(n);
+      const unsigned pixel = (unsigned)(img - img0) * (unsigned)(g.IC * g.HW) + (unsigned)(n - img * g.OWP);
+      doff[q] = ((unsigned)t.i * (unsigned)g.HW + pixel) * (unsigned)sizeof(T);
+    }
+  }
   // `tile_lds`: LDS byte address of the tile; `wave`: wave index (both wave-uniform).  The tile's address is a scalar
   // and the chunk's offset from it 32 bits wide, so that a load costs no vector instruction beside itself.
   __device__ __forceinline__ void load_direct(unsigned tile_lds, int wave, int k0) const {
@@ -398,15 +413,30 @@ struct Operand {
     }
   }
 
-  // The same for a tile that K ends in, chunks of which lie inside K or outside (LD_VEC): lanes outside write zeros to the
-  // place that their chunk would take.  `tile`: the tile as it is addressed by this lane, `tile_lds` as above.
+  // The same for a tile that K ends in, chunks of which lie inside K or outside (LD_VEC, LD_IMAGES): lanes outside write zeros to
+  // the place that their chunk would take, lanes whose chunk leaves the tensor (LD_IMAGES) what is left of it.  `tile`: the tile as it is addressed by this lane, `tile_lds` as above.
   __device__ __forceinline__ void load_direct_edge(unsigned char* tile, unsigned tile_lds, int tid, int wave, int k0) const {
     const T* base = (LAYOUT == L_KC) ? src + k0 : src + (long long)k0 * ld;
+    if constexpr (MODE == LD_IMAGES) {  // (the branches below must not move it to vector registers)
+      const unsigned long long bits = reinterpret_cast<unsigned long long>(base);
+      const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)bits), hi = __builtin_amdgcn_readfirstlane((unsigned)(bits >> 32));
+      base = reinterpret_cast<const T*>(((unsigned long long)hi << 32) | lo);
+    }
 #pragma unroll
     for (int q = 0; q < NL; ++q) {
       const tmap::Task t = LoadMap::task(tid, q);
       const int k = (LAYOUT == L_KC) ? (t.j ^ swz_kc<CPR, MI>(t.i)) * VEC : t.i;
       const unsigned dst = tile_lds + (unsigned)((q * NT + wave * 64) * 16);
+      if constexpr (MODE == LD_IMAGES) {
+        const long long at = (long long)k0 * ld + (long long)(doff[q] / (unsigned)sizeof(T));
+        if (k0 + k < K && at + VEC > span) {
+          T tmp[VEC];
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) tmp[e] = src[at + e < span ? at + e : 0];
+          *reinterpret_cast<u32x4*>(tile + (q * NT + tid) * 16) = __builtin_bit_cast(u32x4, tmp);
+          continue;
+        }
+      }
       if (k0 + k < K) {
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"

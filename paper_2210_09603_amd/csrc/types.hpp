@@ -23,8 +23,9 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 enum : int { L_KC = 0, L_MC = 1 };                    // operand contiguity
 // how a chunk is fetched from global memory; LD_IM2COL_TAP is the img2col gather over a K axis ordered (kh, kw, ic)
-// with ic fastest (weights repacked to match), so that a K tile lies within one filter tap
-enum : int { LD_VEC = 0, LD_ELEM = 1, LD_IM2COL = 2, LD_IM2COL_TAP = 3 };
+// with ic fastest (weights repacked to match), so that a K tile lies within one filter tap; LD_IMAGES the input of a 1x1
+// convolution, whose columns run through all images
+enum : int { LD_VEC = 0, LD_ELEM = 1, LD_IM2COL = 2, LD_IM2COL_TAP = 3, LD_IMAGES = 4 };
 enum : int { MAP_PLAIN = 0, MAP_NCHW = 1 };           // output index map
 enum : int { SCHED_SIMPLE = 0, SCHED_PINGPONG = 1, SCHED_AHEAD = 2, SCHED_KSPLIT = 3 };  // main-loop schedule
 
