@@ -282,7 +282,13 @@ hidet_status_t hidet_tune_conv2d_packed(int32_t in, int32_t out, int64_t Nb, int
 hidet_status_t hidet_conv2d_untuned_config(int32_t in, int64_t Nb, int64_t IC, int64_t H, int64_t W, int64_t OC, int64_t KH,
                                            int64_t KW, int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w,
                                            int32_t packed, int32_t* config);
-/* The same for hidet_batched_gemm (batch = 1: hidet_gemm) on dense operands, batch entries one after another. */
+/*
+ * Test aid: the rows of the tiles on which the same call (packed = 0) runs from a patch of the input in LDS (3x3, unit stride,
+ * padding 1); 0 where it runs the configuration above, as such a convolution does after tuning.
+ */
+hidet_status_t hidet_conv2d_patch_rows(int32_t in, int64_t Nb, int64_t IC, int64_t H, int64_t W, int64_t OC, int64_t KH, int64_t KW,
+                                       int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w, int32_t* rows);
+/* The configuration, likewise, of hidet_batched_gemm (batch = 1: hidet_gemm) on dense operands, batch entries one after another. */
 hidet_status_t hidet_gemm_untuned_config(int32_t in, int32_t transA, int32_t transB, int64_t batch, int64_t M, int64_t N,
                                          int64_t K, int32_t* config);
 /*

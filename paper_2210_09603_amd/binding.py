@@ -72,7 +72,7 @@ EXPORTS = (
     "hidet_softmax_rows", "hidet_host_div", "hidet_conv2d_splitk_workspace_bytes", "hidet_static_scratch_bytes",
     "hidet_batched_gemm_splitk_static", "hidet_conv2d_pack_weights", "hidet_conv2d_implicit_gemm_packed",
     "hidet_tune_conv2d_packed", "hidet_row_schedule", "hidet_conv2d_untuned_config",
-    "hidet_gemm_untuned_config",
+    "hidet_gemm_untuned_config", "hidet_conv2d_patch_rows",
 )
 
 _lib = None
@@ -118,6 +118,7 @@ def lib():
         L.hidet_reduce_rows.argtypes = [_i32, _i32, _i32, _i64, _i64, _vp, _i64, _vp, _vp]
         L.hidet_softmax_rows.argtypes = [_i32, _i64, _i64, _vp, _i64, _vp, _i64, _vp]
         L.hidet_conv2d_untuned_config.argtypes = [_i32] + [_i64] * 11 + [_i32, ctypes.POINTER(_i32)]
+        L.hidet_conv2d_patch_rows.argtypes = [_i32] + [_i64] * 11 + [ctypes.POINTER(_i32)]
         L.hidet_gemm_untuned_config.argtypes = [_i32, _i32, _i32] + [_i64] * 4 + [ctypes.POINTER(_i32)]
         L.hidet_row_schedule.argtypes = [_i32, _i32, _i64, _i64, ctypes.POINTER(hidet_row_schedule_t)]
         L.hidet_tune_last_times.argtypes = [ctypes.POINTER(ctypes.c_float), _i32]
@@ -550,6 +551,14 @@ def hidet_conv2d_untuned_config(dtype, x_shape, w_shape, stride=(1, 1), pad=(0, 
     _check(lib().hidet_conv2d_untuned_config(dtype, Nb, IC, H, W, OC, KH, KW, stride[0], stride[1], pad[0], pad[1], int(packed),
                                              ctypes.byref(config)), "hidet_conv2d_untuned_config")
     return config.value
+
+
+def hidet_conv2d_patch_rows(dtype, x_shape, w_shape, stride=(1, 1), pad=(0, 0)):
+    """Rows of the tiles on which such a convolution runs from a patch of the input in LDS; 0: it does not."""
+    (Nb, IC, H, W), (OC, _, KH, KW), rows = x_shape, w_shape, _i32(0)
+    _check(lib().hidet_conv2d_patch_rows(dtype, Nb, IC, H, W, OC, KH, KW, stride[0], stride[1], pad[0], pad[1], ctypes.byref(rows)),
+           "hidet_conv2d_patch_rows")
+    return rows.value
 
 
 def hidet_gemm_untuned_config(dtype, M, N, K, batch=1, transA=False, transB=False):

@@ -13,6 +13,11 @@
 #include "../../include/hidet_mi355x.h"
 #include "registry.hpp"
 
+namespace hidet {  // conv3x3.hip
+hipError_t launch_conv3x3_f16(const GemmParams& p, int bm, hipStream_t stream);
+hipError_t launch_conv3x3_bf16(const GemmParams& p, int bm, hipStream_t stream);
+}  // namespace hidet
+
 using namespace hidet;
 
 // ------------------------------------------------------------------------------------------------
@@ -939,16 +944,59 @@ hidet_status_t make_conv_call(ConvCall& cc, int in, int out, long long Nb, long 
   return HIDET_OK;
 }
 
+// 3x3 convolutions of unit stride and padding 1 in 16-bit types, from OIHW weights: whether they run from a patch of the input
+// in LDS (conv3x3.hip), and on tiles of how many rows; 0: from the gather.
+// It wants 72 tiles of 64x128 (of columns with the zero columns and rows among them).  Over 130 random problems of 16 to 512
+// channels its time over the gather's is 0.75 to 0.87 from 76 to 88 tiles, 0.42 to 0.9 beyond (1.03 once), but 1.1 to 1.3 from
+// 44 to 64, where the gather's K-splitting tiles have twice the workgroups; 58 to 63 tiles of a long K, 0.75 to 0.8, are not
+// told from those.  The zeros are no more than two fifths of the outputs (images of 6x6: 1.36 times as many columns, 0.94 to
+// 1.07 of the gather's), and the 256 pixels of a patch hold the border of rows of 62.
+// 128 rows fetch the input half as often and win from the point where 64 rows are more than one to a compute unit (26 images
+// of 128x28x28: 14.7 us, 16.9 us on 64; at most 256 tiles of 64: 1.25 of the time of 64), unless they make a second round
+// that is less than half full (47 of 96x27x27, 80 channels, 288 tiles: 23.1 and 21.0 us; 60 of 96x30x30, 451: 26.8 and 29.0
+// us; beyond two rounds the two are level, or 64 ahead: 44 of 192x23x23, 384 channels: 57.7 and 55.7 us).
+int patch_rows(const Problem& conv, const SplitK& sk) {
+  const ConvGeom& g = conv.p.g;
+  if (conv.op != 1 || conv.dtype == HIDET_F32 || conv.packed || conv.elem_mode != 0 || conv.p.relu_b != 0 || sk.slices > 1) return 0;
+  if (g.KH != 3 || g.KW != 3 || g.sh != 1 || g.sw != 1 || g.ph != 1 || g.pw != 1 || g.IC % 16 != 0) return 0;
+  if (conv.p.M < 16 || conv.Nb == 0 || g.IC == 0 || g.W > 62 || g.HW < 8) return 0;
+  const long long plane = (long long)(g.H + 1) * (g.W + 1), columns = sat_mul(conv.Nb, plane);
+  if (5 * plane > 7 * (long long)g.HW || columns > kMaxDim) return 0;
+  const long long across = (columns + 127) >> 7, of_64 = ((conv.p.M + 63LL) >> 6) * across, of_128 = ((conv.p.M + 127LL) >> 7) * across;
+  if (of_64 < 72) return 0;
+  return conv.p.M > 64 && of_64 > 256 && (of_128 <= 256 || (of_128 > 384 && of_128 <= 512)) ? 128 : 64;
+}
+hidet_status_t launch_patch(const Problem& conv, int bm, hipStream_t stream) {
+  GemmParams p = conv.p;
+  p.g.d_owp = make_fastdiv(p.g.W + 1);
+  p.g.d_oh = make_fastdiv(p.g.H + 1);
+  p.N = (int)(conv.Nb * (p.g.H + 1) * (p.g.W + 1));
+  const int tiles_m = (p.M + bm - 1) / bm, tiles_n = (p.N + 127) / 128;
+  set_block_mapping(p, tiles_m, tiles_n, tiles_m >= 4 ? 4 : tiles_m);
+  p.k_slices = 1;
+  p.k_slice_len = p.K;
+  const long long total = (long long)tiles_m * tiles_n;
+  if (total > kIntMax) return HIDET_ERR_UNSUPPORTED;
+  p.total_blocks = (int)total;
+  const hipError_t e = conv.dtype == HIDET_F16 ? launch_conv3x3_f16(p, bm, stream) : launch_conv3x3_bf16(p, bm, stream);
+  if (e != hipSuccess) return HIDET_ERR_LAUNCH;
+  ++g_kernel_launches;
+  return HIDET_OK;
+}
+
 // An explicit configuration always runs the gather form; config < 0 runs what the tuner remembered for this
-// convolution, else (1x1 convolutions) the product over all images or the batched-GEMM form with its size-based default.
+// convolution, else (3x3 convolutions) the patch kernel or (1x1 convolutions) the product over all images or the batched-GEMM
+// form with its size-based default.
 hidet_status_t launch_conv(const ConvCall& cc, int config, const SplitK& sk, hipStream_t stream) {
-  if (config >= 0 || !cc.pointwise) return launch(cc.conv, config, sk, stream);
+  const int rows = config < 0 ? patch_rows(cc.conv, sk) : 0;
+  if (config >= 0 || (!cc.pointwise && rows == 0)) return launch(cc.conv, config, sk, stream);
   Tuned t{-1, 1, 0};
   {
     std::lock_guard<std::mutex> lock(g_mutex);
     auto it = find_tuned(cc.conv, sk);
     if (it != g_cache.end()) t = it->second;
   }
+  if (t.config < 0 && rows > 0) return launch_patch(cc.conv, rows, stream);
   if (t.config < 0) {
     const int c = images_config(cc.conv, cc.pointwise, sk);
     return c >= 0 ? launch(images_problem(cc.conv), c, SplitK(), stream) : launch(cc.gemm, -1, sk, stream);
@@ -1279,6 +1327,18 @@ hidet_status_t hidet_conv2d_untuned_config(int32_t in, int64_t Nb, int64_t IC, i
   const Problem& pr = cc.pointwise ? cc.gemm : cc.conv;
   const int images = images_config(cc.conv, cc.pointwise, SplitK());
   *config = images >= 0 ? images : pr.batch == 0 || pr.p.M == 0 || pr.p.N == 0 ? -1 : default_config(pr);
+  return HIDET_OK;
+}
+
+hidet_status_t hidet_conv2d_patch_rows(int32_t in, int64_t Nb, int64_t IC, int64_t H, int64_t W, int64_t OC, int64_t KH, int64_t KW,
+                                       int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w, int32_t* rows) {
+  if (!rows) return HIDET_ERR_INVALID_ARG;
+  void* const at = reinterpret_cast<void*>((uintptr_t)4096);  // (as above)
+  ConvCall cc;
+  const hidet_status_t st =
+      make_conv_call(cc, in, in, Nb, IC, H, W, OC, KH, KW, stride_h, stride_w, pad_h, pad_w, at, at, at, nullptr);
+  if (st != HIDET_OK) return st;
+  *rows = patch_rows(cc.conv, SplitK());
   return HIDET_OK;
 }
 
