@@ -531,6 +531,12 @@ int default_config(const Problem& pr, int slices = 1) {
       passed_over = c;
       continue;
     }
+    // (nor, into rows that are only element aligned, a 128x64 or 64x128 one: 128 of 327x327x32 18.6 and 18.8 us, 17.5 us on
+    // 64x64; 64 of 255x255x128 8.0, 8.1 and 7.1 us; 190 of 191x191x128 13.4, 13.9 and 10.3 us)
+    if (gemm16 && pr.batch > 1 && pr.p.vec_store < 2 && pr.p.out_map == 0 && area == 128 * 64) {
+      passed_over = c;
+      continue;
+    }
     const bool self_overlapping = ring_any && pr.p.K >= 4 * r.bk;
     const long long enough = !throughput ? 192 : self_overlapping ? 129 : gemm16 ? 384 : 400;
     // Tiles of 64x64 and more are no first choice of a convolution outside the rule above that is bound by latency (fewer
