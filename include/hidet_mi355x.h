@@ -283,8 +283,8 @@ hidet_status_t hidet_conv2d_untuned_config(int32_t in, int64_t Nb, int64_t IC, i
                                            int64_t KW, int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w,
                                            int32_t packed, int32_t* config);
 /*
- * Test aid: the rows of the tiles on which the same call (packed = 0) runs from a patch of the input in LDS (3x3, unit stride,
- * padding 1); 0 where it runs the configuration above, as such a convolution does after tuning.
+ * Test aid: the rows of the tiles on which the same call (packed = 0) runs from a patch of the input in LDS (3x3 or 5x5, unit
+ * stride, the output as large as the input); 0 where it runs the configuration above, as such a convolution does after tuning.
  */
 hidet_status_t hidet_conv2d_patch_rows(int32_t in, int64_t Nb, int64_t IC, int64_t H, int64_t W, int64_t OC, int64_t KH, int64_t KW,
                                        int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w, int32_t* rows);

@@ -13,9 +13,9 @@
 #include "../../include/hidet_mi355x.h"
 #include "registry.hpp"
 
-namespace hidet {  // conv3x3.hip
-hipError_t launch_conv3x3_f16(const GemmParams& p, int bm, hipStream_t stream);
-hipError_t launch_conv3x3_bf16(const GemmParams& p, int bm, hipStream_t stream);
+namespace hidet {  // conv_patch.hip
+hipError_t launch_conv_patch_f16(const GemmParams& p, int bm, hipStream_t stream);
+hipError_t launch_conv_patch_bf16(const GemmParams& p, int bm, hipStream_t stream);
 }  // namespace hidet
 
 using namespace hidet;
@@ -950,13 +950,17 @@ hidet_status_t make_conv_call(ConvCall& cc, int in, int out, long long Nb, long 
   return HIDET_OK;
 }
 
-// 3x3 convolutions of unit stride and padding 1 in 16-bit types, from OIHW weights: whether they run from a patch of the input
-// in LDS (conv3x3.hip), and on tiles of how many rows; 0: from the gather.
+// 3x3 and 5x5 convolutions of unit stride that keep the size, in 16-bit types, from OIHW weights: whether they run from a patch of the input
+// in LDS (conv_patch.hip), and on tiles of how many rows; 0: from the gather.
 // It wants 72 tiles of 64x128 (of columns with the zero columns and rows among them).  Over 130 random problems of 16 to 512
 // channels its time over the gather's is 0.75 to 0.87 from 76 to 88 tiles, 0.42 to 0.9 beyond (1.03 once), but 1.1 to 1.3 from
 // 44 to 64, where the gather's K-splitting tiles have twice the workgroups; 58 to 63 tiles of a long K, 0.75 to 0.8, are not
 // told from those.  The zeros are no more than two fifths of the outputs (images of 6x6: 1.36 times as many columns, 0.94 to
 // 1.07 of the gather's), and the 256 pixels of a patch hold the border of rows of 62.
+// 5x5: 64 rows only, one workgroup to a compute unit, and rows of 29 at most.  Over 60 random problems 0.51 to 0.99 of the
+// gather's time from 146 tiles on; 0.69 to 0.89 from 88 to 130 tiles of up to 256 channels, but 1.14 to 1.20 of more (their
+// weights do not fit a die's L2), and 1.2 to 1.8 from 48 to 80.  (47 images of 384x10x10, where the zeros make it 1.44 times
+// as many columns: 0.86; 58 of 512x6x6, 1.78 times: 0.93, not told from the tiles alone and left to the gather.)
 // 128 rows fetch the input half as often and win from the point where 64 rows are more than one to a compute unit (26 images
 // of 128x28x28: 14.7 us, 16.9 us on 64; at most 256 tiles of 64: 1.25 of the time of 64), unless they make a second round
 // that is less than half full (47 of 96x27x27, 80 channels, 288 tiles: 23.1 and 21.0 us; 60 of 96x30x30, 451: 26.8 and 29.0
@@ -964,19 +968,21 @@ hidet_status_t make_conv_call(ConvCall& cc, int in, int out, long long Nb, long 
 int patch_rows(const Problem& conv, const SplitK& sk) {
   const ConvGeom& g = conv.p.g;
   if (conv.op != 1 || conv.dtype == HIDET_F32 || conv.packed || conv.elem_mode != 0 || conv.p.relu_b != 0 || sk.slices > 1) return 0;
-  if (g.KH != 3 || g.KW != 3 || g.sh != 1 || g.sw != 1 || g.ph != 1 || g.pw != 1 || g.IC % 16 != 0) return 0;
-  if (conv.p.M < 16 || conv.Nb == 0 || g.IC == 0 || g.W > 62 || g.HW < 8) return 0;
-  const long long plane = (long long)(g.H + 1) * (g.W + 1), columns = sat_mul(conv.Nb, plane);
-  if (5 * plane > 7 * (long long)g.HW || columns > kMaxDim) return 0;
+  if (g.KH != g.KW || (g.KW != 3 && g.KW != 5) || g.sh != 1 || g.sw != 1 || g.ph != g.KH / 2 || g.pw != g.KW / 2) return 0;
+  if (g.IC % 16 != 0 || g.IC == 0 || conv.p.M < 16 || conv.Nb == 0 || g.W > (g.KW == 3 ? 62 : 29) || g.HW < 8) return 0;
+  const long long plane = (long long)(g.H + g.ph) * (g.W + g.pw), columns = sat_mul(conv.Nb, plane);
+  if (5 * plane > (g.KW == 3 ? 7 : 9) * (long long)g.HW || columns > kMaxDim) return 0;
   const long long across = (columns + 127) >> 7, of_64 = ((conv.p.M + 63LL) >> 6) * across, of_128 = ((conv.p.M + 127LL) >> 7) * across;
+  if (g.KW == 5) return of_64 >= (g.IC <= 256 ? 104 : 150) ? 64 : 0;
   if (of_64 < 72) return 0;
   return conv.p.M > 64 && of_64 > 256 && (of_128 <= 256 || (of_128 > 384 && of_128 <= 512)) ? 128 : 64;
 }
 hidet_status_t launch_patch(const Problem& conv, int bm, hipStream_t stream) {
   GemmParams p = conv.p;
-  p.g.d_owp = make_fastdiv(p.g.W + 1);
-  p.g.d_oh = make_fastdiv(p.g.H + 1);
-  p.N = (int)(conv.Nb * (p.g.H + 1) * (p.g.W + 1));
+  const int zeros = p.g.KW / 2;
+  p.g.d_owp = make_fastdiv(p.g.W + zeros);
+  p.g.d_oh = make_fastdiv(p.g.H + zeros);
+  p.N = (int)(conv.Nb * (p.g.H + zeros) * (p.g.W + zeros));
   const int tiles_m = (p.M + bm - 1) / bm, tiles_n = (p.N + 127) / 128;
   set_block_mapping(p, tiles_m, tiles_n, tiles_m >= 4 ? 4 : tiles_m);
   p.k_slices = 1;
@@ -984,7 +990,7 @@ hidet_status_t launch_patch(const Problem& conv, int bm, hipStream_t stream) {
   const long long total = (long long)tiles_m * tiles_n;
   if (total > kIntMax) return HIDET_ERR_UNSUPPORTED;
   p.total_blocks = (int)total;
-  const hipError_t e = conv.dtype == HIDET_F16 ? launch_conv3x3_f16(p, bm, stream) : launch_conv3x3_bf16(p, bm, stream);
+  const hipError_t e = conv.dtype == HIDET_F16 ? launch_conv_patch_f16(p, bm, stream) : launch_conv_patch_bf16(p, bm, stream);
   if (e != hipSuccess) return HIDET_ERR_LAUNCH;
   ++g_kernel_launches;
   return HIDET_OK;
