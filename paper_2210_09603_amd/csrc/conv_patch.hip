@@ -215,7 +215,8 @@ __global__ void __launch_bounds__(S::NT, S::PER_SIMD) conv_patch_kernel(const Ge
   if (s < stages) step(s, l[S::SETS - 1]);
 
   // ---- epilogue, from the accumulators: a lane holds one column, 16 rows; the two halves of a wavefront store 32 consecutive
-  // pixels of one row each
+  // pixels of one row each.  (Through LDS, in groups of four pixels gathered from between the zero columns and stored by 8 bytes:
+  // 64 images of 256x14x14 32.0 us instead of 26 to 28, 64x56x56 47.7 us instead of 38.)
   const T* const bias = reinterpret_cast<const T*>(p.bias);
   const T* const R = reinterpret_cast<const T*>(p.residual);
   T* const C = reinterpret_cast<T*>(p.C);
