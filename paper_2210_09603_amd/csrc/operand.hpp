@@ -361,8 +361,8 @@ struct Operand {
   // `in_place` (element-aligned operands): a chunk that sticks out past the last column of an M/N-contiguous
   // operand is read where it lies -- what follows the row's end is the next row, and the columns it fills are never
   // stored -- instead of being moved back to end at the edge, which is only right when whole chunks stick out.
-  // The caller keeps such loads away from the operand's last row.
-  unsigned doff[NL];  // in bytes; rows times leading dimension below 2^31 elements
+  // The caller keeps such loads away from the operand's last row, and rows shorter than a chunk away from this form.
+  unsigned doff[NL];  // in bytes; what would leave 32 bits is not launched in this form (direct_loads_fit)
   __device__ __forceinline__ void init_direct(int tid, bool in_place = false) {
     static_assert(std::is_same<LoadMap, LoadMapRowMajor<SROWS, CPR, NT>>::value, "stored positions in row-major order");
 #pragma unroll

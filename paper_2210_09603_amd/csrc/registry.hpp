@@ -32,13 +32,15 @@ constexpr int kPartialVariants = 10;  // offset of the K-parallel partial-sum ke
 constexpr int kPointwiseVariant = 22;
 constexpr int kConvTapVariant = 20;   // convolution over the tap-major K order (repacked weights); +1: partial sums
 
-// Whether the direct loads of gemm_kernel_waves stay inside the operands.  Offsets inside a step are 32-bit; and where rows
-// are only element aligned, the 16 bytes that begin in the last columns of an M/N-contiguous operand must not reach past
-// the row that follows.  What remains runs the general schedule on the same tile.
-constexpr long long kMaxDirectLd = 4LL << 20;
+// Whether direct loads on plain operands stay where they belong.  Their offsets inside a tile are unsigned 32-bit byte offsets
+// (Operand::init_direct); and where rows are only element aligned, the 16 bytes that begin in the last columns of an
+// M/N-contiguous operand must not reach past the row that follows.  What remains goes through registers on the same tile.
+constexpr bool direct_offsets_fit(long long rows, long long ld) { return ld <= (1LL << 31) / rows; }  // (of 16-bit elements)
 template <class Cfg>
-bool waves_can_stream(const GemmParams& p) {
-  if (p.lda > kMaxDirectLd || p.ldb > kMaxDirectLd) return false;
+bool direct_loads_fit(const GemmParams& p) {
+  if (!direct_offsets_fit(Cfg::LA == L_KC ? Cfg::BM : Cfg::BK, p.lda)) return false;
+  if (Cfg::MODE_B == LD_IMAGES) return true;  // (its input has offsets of its own, bounded where the form is chosen)
+  if (!direct_offsets_fit(Cfg::LB == L_KC ? Cfg::BN : Cfg::BK, p.ldb)) return false;
   if (Cfg::MODE_A != LD_ELEM) return true;
   return (Cfg::LA == L_KC || p.lda >= Cfg::VEC) && (Cfg::LB == L_KC || p.ldb >= Cfg::VEC);
 }
@@ -46,8 +48,9 @@ bool waves_can_stream(const GemmParams& p) {
 template <class Cfg>
 hipError_t launch_kernel(const GemmParams& p, hipStream_t stream) {
   // the element-mode variant of a ring tile also serves what the direct loads cannot do (input prologue, head-split
-  // output map), with its stages staged through registers
-  if (Cfg::SCHED == SCHED_PINGPONG && Cfg::MODE_A == LD_ELEM && (p.out_map != 0 || p.relu_a != 0 || p.relu_b != 0)) {
+  // output map, rows too far apart or too short), with its stages staged through registers
+  if (Cfg::SCHED == SCHED_PINGPONG && Cfg::MODE_A == LD_ELEM &&
+      (p.out_map != 0 || p.relu_a != 0 || p.relu_b != 0 || !direct_loads_fit<Cfg>(p))) {
     if constexpr (Cfg::SCHED == SCHED_PINGPONG && Cfg::MODE_A == LD_ELEM)
       hipLaunchKernelGGL(gemm_kernel_pingpong_regs<Cfg>, dim3((unsigned)p.total_blocks), dim3(Cfg::NT), 0, stream, p);
   } else if constexpr (Cfg::SCHED == SCHED_PINGPONG) {
@@ -57,7 +60,7 @@ hipError_t launch_kernel(const GemmParams& p, hipStream_t stream) {
       hipLaunchKernelGGL((gemm_kernel_pingpong<Cfg, 2>), dim3((unsigned)p.total_blocks), dim3(Cfg::NT), 0, stream, p);
     else
       hipLaunchKernelGGL((gemm_kernel_pingpong<Cfg, 4>), dim3((unsigned)p.total_blocks), dim3(Cfg::NT), 0, stream, p);
-  } else if (WaveStream<Cfg>::BUILT && waves_can_stream<Cfg>(p)) {
+  } else if (WaveStream<Cfg>::BUILT && direct_loads_fit<Cfg>(p)) {
     if constexpr (WaveStream<Cfg>::BUILT)
       hipLaunchKernelGGL(gemm_kernel_waves<Cfg>, dim3((unsigned)p.total_blocks), dim3(WaveStream<Cfg>::NT), 0, stream, p);
   } else

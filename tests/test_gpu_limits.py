@@ -9,7 +9,8 @@ import oracle
 from paper_2210_09603_amd import binding as hb
 from paper_2210_09603_amd import workloads as wl
 
-from helpers import TOL, TORCH_DTYPE, to_f64, to_gpu
+from helpers import (TOL, TORCH_DTYPE, applicable_configs, assert_elementwise, gemm_scale, run_gemm_case, to_f64, to_gpu,
+                     within_bound)
 
 pytestmark = pytest.mark.gpu
 
@@ -76,6 +77,54 @@ def test_gemm_operand_beyond_2_31_elements(lda):
     At64 = to_f64(At)
     ref = oracle.gemm(At64, wl.widen(c["B"], dtype)[:Kt], transA=True)
     assert oracle.rel_frobenius(to_f64(Ct), ref) <= TOL[dtype]
+
+
+def _config(bm, bn, schedule):
+    for i in range(hb.hidet_config_count()):
+        c = hb.hidet_config_info(i)
+        if not c["is_f32"] and (c["block_m"], c["block_n"], c["schedule"]) == (bm, bn, schedule):
+            return i, c
+    raise AssertionError("no such configuration")
+
+
+@pytest.mark.parametrize("side", ["below", "above", "far above"])
+@pytest.mark.parametrize("operand", ["A", "B"])
+@pytest.mark.parametrize("tile", [(256, 256, 1), (64, 64, 3)])
+def test_direct_loads_end_where_their_offsets_would(tile, operand, side):
+    """Rows so far apart that the byte offsets of a tile's direct loads come close to 2^32 (the largest leading dimension that
+    they take, element mode because of its size), and beyond, where the tile is loaded through registers."""
+    dtype = "f16"
+    cfg, info = _config(*tile)
+    rows = info["block_m"] if operand == "A" else info["block_k"]  # (A: K-contiguous; B: N-contiguous)
+    ld = 2 ** 31 // rows + {"below": 0, "above": 8, "far above": 2 ** 31 // rows // 4 + 3}[side]
+    M, N, K = (info["block_m"] + 9, 40, 3 * info["block_k"] + 5) if operand == "A" else (40, info["block_n"] + 9, info["block_k"] + 5)
+    c = wl.gemm_case(7260, M, N, K, dtype)
+    A, B = to_gpu(c["A"], dtype), to_gpu(c["B"], dtype)
+    wide = A if operand == "A" else B
+    spread = torch.zeros((wide.shape[0], ld), dtype=TORCH_DTYPE[dtype], device="cuda")[:, :wide.shape[1]]
+    spread.copy_(wide)
+    C = torch.full((M, N), float("nan"), dtype=TORCH_DTYPE[dtype], device="cuda")
+    print("gemm %dx%dx%d, rows of %s %d apart, config %d" % (M, N, K, operand, ld, cfg), flush=True)
+    hb.hidet_gemm(*((spread, B) if operand == "A" else (A, spread)), C, config=cfg)
+    torch.cuda.synchronize()
+    A64, B64 = wl.widen(c["A"], dtype), wl.widen(c["B"], dtype)
+    assert_elementwise(to_f64(C), oracle.gemm(A64, B64), gemm_scale(A64, B64, False, False, 1.0), dtype, K, "%s %s" % (operand, side))
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 200), (300, 3, 129), (3, 270, 130), (5, 8, 200), (7, 7, 131)])
+def test_ring_tiles_on_rows_shorter_than_one_access(M, N, K):
+    """M/N-contiguous rows of fewer than eight elements: a direct load would reach past the row that follows."""
+    for cfg in applicable_configs("f16"):
+        if hb.hidet_config_info(cfg)["schedule"] != 1:
+            continue
+        for tA in (False, True):
+            c = wl.gemm_case(7270 + cfg, M, N, K, "f16", transA=tA, bias="col")
+            try:
+                err, _, ref = run_gemm_case(c, config=cfg)
+            except hb.HidetError as e:
+                assert tA and e.status == 4  # (few ring tiles are built for a transposed A)
+                continue
+            assert within_bound(err, ref, "f16"), (cfg, tA, err)
 
 
 def test_conv_input_near_the_limit_and_output_beyond_2_31_elements():
