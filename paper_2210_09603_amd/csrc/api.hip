@@ -1008,14 +1008,15 @@ hidet_status_t launch_conv(const ConvCall& cc, int config, const SplitK& sk, hip
     auto it = find_tuned(cc.conv, sk);
     if (it != g_cache.end()) t = it->second;
   }
-  if (t.config < 0 && rows > 0) return launch_patch(cc.conv, rows, stream);
-  if (t.config < 0) {
-    const int c = images_config(cc.conv, cc.pointwise, sk);
-    return c >= 0 ? launch(images_problem(cc.conv), c, SplitK(), stream) : launch(cc.gemm, -1, sk, stream);
-  }
   SplitK one = sk;
   if (one.slices < 0) one.slices = t.slices;
-  return launch(t.route == 1 ? cc.gemm : cc.conv, t.config, one, stream);
+  const Problem& remembered = t.route == 1 && cc.pointwise ? cc.gemm : cc.conv;
+  // (an entry of a file written elsewhere may name a configuration that cannot serve this call: as if nothing were remembered)
+  if (find_launcher(remembered, t.config) && (one.slices <= 1 || find_partial_launcher(remembered, t.config)))
+    return launch(remembered, t.config, one, stream);
+  if (rows > 0) return launch_patch(cc.conv, rows, stream);
+  const int c = images_config(cc.conv, cc.pointwise, sk);
+  return c >= 0 ? launch(images_problem(cc.conv), c, SplitK(), stream) : launch(cc.gemm, -1, sk, stream);
 }
 
 // Tunes the gather form and, for a 1x1 convolution, the batched-GEMM form; the faster one is remembered under
