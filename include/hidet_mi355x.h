@@ -48,6 +48,14 @@ typedef enum { HIDET_F32 = 0, HIDET_F16 = 1, HIDET_BF16 = 2 } hidet_dtype_t;
 typedef enum { HIDET_BIAS_NONE = 0, HIDET_BIAS_PER_COL = 1 /* length N */, HIDET_BIAS_PER_ROW = 2 /* length M */ } hidet_bias_axis_t;
 typedef enum { HIDET_ACT_NONE = 0, HIDET_ACT_RELU = 1 } hidet_act_t;
 typedef enum { HIDET_MAP_PLAIN = 0, HIDET_MAP_HEAD_SPLIT = 1 } hidet_out_map_t;
+/* Forms of a convolution (hidet_conv2d_implicit_gemm). */
+typedef enum {
+  HIDET_CONV_GATHER = 0,    /* implicit GEMM with the img2col gather */
+  HIDET_CONV_BATCHED = 1,   /* 1x1: batched GEMM, an entry per image */
+  HIDET_CONV_IMAGES = 2,    /* 1x1: one product whose columns run through all images */
+  HIDET_CONV_PATCH_64 = 3,  /* 3x3, 5x5: from a patch of the input in LDS, tiles of 64 output channels */
+  HIDET_CONV_PATCH_128 = 4  /* 3x3: the same with tiles of 128 */
+} hidet_conv_form_t;
 typedef enum { HIDET_PROLOGUE_NONE = 0, HIDET_PROLOGUE_RELU = 1 } hidet_prologue_t;
 
 /*
@@ -131,11 +139,12 @@ hidet_status_t hidet_batched_gemm(int32_t in, int32_t out, int32_t transA, int32
  * fused epilogue, so no img2col matrix is ever materialised.  In the epilogue, bias (if any) must
  * be HIDET_BIAS_PER_ROW, i.e. one value per output channel, and residual (if any) is a dense
  * tensor of y's shape (ld_residual and batch_stride_residual are ignored).
- * A 1x1 convolution with unit stride and no padding needs no gather (image b of x already is the IC x H*W
- * row-major matrix of the GEMM): without an explicit configuration it runs as the batched GEMM
- * y[b] = w . x[b], weights shared across the batch, unless hidet_tune_conv2d measured the gather form to be
- * faster for this problem; a call with an explicit configuration always runs the gather form.  The results of
- * the two forms agree to rounding (different summation order).
+ * A call with an explicit configuration always runs that gather.  Without one, a convolution may run in another form:
+ *   1x1, unit stride, no padding (image b of x already is the IC x H*W row-major matrix of the GEMM): the batched GEMM
+ *   y[b] = w . x[b], weights shared across the batch, or (16-bit types) one product whose columns run through all images;
+ *   3x3 and 5x5, unit stride, output as large as the input (16-bit types): from a patch of the input in LDS.
+ * The form is the fastest that hidet_tune_conv2d measured for this problem, otherwise a size-based choice
+ * (hidet_conv2d_untuned_form).  The results of the forms agree to rounding (different summation order).
  * Limits (HIDET_ERR_UNSUPPORTED beyond them): x has at most 2^31 - 65537 elements (y may have more),
  * H + 2*pad_h, W + 2*pad_w, KH, KW, stride_h and stride_w are at most 32767, and OC, Nb*OH*roundup(OW, 8)
  * and IC*KH*KW are at most 2^31 - 65537.
@@ -194,9 +203,9 @@ hidet_status_t hidet_config_info(int32_t config, hidet_config_info_t* info);
  * time `iters` launches of each with HIP events on `stream`, remember the fastest under a key made
  * of (operation, dtypes, transposes, sizes, epilogue kind) and report it.  The output buffer is
  * overwritten with valid results.  best_config / best_us may be NULL.  Synchronises `stream`.
- * For a 1x1 convolution with unit stride and no padding both forms (gather, batched GEMM) are enumerated and
- * the faster one is remembered; the reported configuration may then belong to the batched-GEMM form, which
- * only a call without an explicit configuration runs.
+ * For a convolution every form that can run it (see hidet_conv2d_implicit_gemm) is timed and the fastest is remembered;
+ * the reported time is that of the fastest form, which only a call without an explicit configuration runs if it is not the
+ * gather.  The reported configuration is that of the form, for the patch forms, which have none, that of the fastest gather.
  */
 hidet_status_t hidet_tune_gemm(int32_t in, int32_t out, int32_t transA, int32_t transB, int64_t batch, int64_t M,
                                int64_t N, int64_t K, const void* A, int64_t lda, int64_t strideA, const void* B,
@@ -278,14 +287,16 @@ hidet_status_t hidet_tune_conv2d_packed(int32_t in, int32_t out, int64_t Nb, int
  * Test aid: the tile configuration that hidet_conv2d_implicit_gemm (packed = 0) or hidet_conv2d_implicit_gemm_packed
  * (packed = 1) takes for dense, 16-byte aligned tensors of these sizes without an epilogue, when the caller names none
  * and nothing has been tuned.  Runs nothing.  -1 for an empty output.  Fails as those calls do for sizes they refuse.
+ * For HIDET_CONV_IMAGES the configuration whose tile that form takes, with stages of 32 values of k instead of its own; where
+ * a patch form is taken, the configuration that the gather would have.
  */
 hidet_status_t hidet_conv2d_untuned_config(int32_t in, int64_t Nb, int64_t IC, int64_t H, int64_t W, int64_t OC, int64_t KH,
                                            int64_t KW, int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w,
                                            int32_t packed, int32_t* config);
-/*
- * Test aid: the rows of the tiles on which the same call (packed = 0) runs from a patch of the input in LDS (3x3 or 5x5, unit
- * stride, the output as large as the input); 0 where it runs the configuration above, as such a convolution does after tuning.
- */
+/* Test aid: the form (HIDET_CONV_) that the same call (packed = 0) takes; -1 for an empty output. */
+hidet_status_t hidet_conv2d_untuned_form(int32_t in, int64_t Nb, int64_t IC, int64_t H, int64_t W, int64_t OC, int64_t KH, int64_t KW,
+                                         int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w, int32_t* form);
+/* Test aid: the rows of the tiles on which the same call runs from a patch of the input in LDS; 0 where it takes another form. */
 hidet_status_t hidet_conv2d_patch_rows(int32_t in, int64_t Nb, int64_t IC, int64_t H, int64_t W, int64_t OC, int64_t KH, int64_t KW,
                                        int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w, int32_t* rows);
 /* The configuration, likewise, of hidet_batched_gemm (batch = 1: hidet_gemm) on dense operands, batch entries one after another. */
@@ -337,7 +348,7 @@ int32_t hidet_tune_last_times(float* us_per_config, int32_t capacity);
 /* Forget every tuned entry. */
 void hidet_tune_clear(void);
 /* Persist / restore the tuned-config cache as a text file (host paths): one line `key config k_slices form` per
- * problem (form: 1 = batched-GEMM form of a 1x1 convolution, else 0; a line without it reads as 0; malformed or
+ * problem (form: a HIDET_CONV_ number for convolutions, else 0; a line without it reads as 0; malformed or
  * out-of-range lines are skipped).  Returns HIDET_ERR_INVALID_ARG on I/O errors. */
 hidet_status_t hidet_tune_save(const char* path);
 hidet_status_t hidet_tune_load(const char* path);

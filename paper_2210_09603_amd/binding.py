@@ -17,6 +17,7 @@ LIB_PATH = os.path.join(HERE, "libhidet_mi355x.so")
 HOST_CALLS_PATH = os.path.join(HERE, "_host_calls.so")
 
 HIDET_F32, HIDET_F16, HIDET_BF16 = 0, 1, 2
+HIDET_CONV_GATHER, HIDET_CONV_BATCHED, HIDET_CONV_IMAGES, HIDET_CONV_PATCH_64, HIDET_CONV_PATCH_128 = 0, 1, 2, 3, 4
 HIDET_BIAS_NONE, HIDET_BIAS_PER_COL, HIDET_BIAS_PER_ROW = 0, 1, 2
 HIDET_ACT_NONE, HIDET_ACT_RELU = 0, 1
 HIDET_MAP_PLAIN, HIDET_MAP_HEAD_SPLIT = 0, 1
@@ -72,7 +73,7 @@ EXPORTS = (
     "hidet_softmax_rows", "hidet_host_div", "hidet_conv2d_splitk_workspace_bytes", "hidet_static_scratch_bytes",
     "hidet_batched_gemm_splitk_static", "hidet_conv2d_pack_weights", "hidet_conv2d_implicit_gemm_packed",
     "hidet_tune_conv2d_packed", "hidet_row_schedule", "hidet_conv2d_untuned_config",
-    "hidet_gemm_untuned_config", "hidet_conv2d_patch_rows",
+    "hidet_gemm_untuned_config", "hidet_conv2d_patch_rows", "hidet_conv2d_untuned_form",
 )
 
 _lib = None
@@ -118,6 +119,7 @@ def lib():
         L.hidet_reduce_rows.argtypes = [_i32, _i32, _i32, _i64, _i64, _vp, _i64, _vp, _vp]
         L.hidet_softmax_rows.argtypes = [_i32, _i64, _i64, _vp, _i64, _vp, _i64, _vp]
         L.hidet_conv2d_untuned_config.argtypes = [_i32] + [_i64] * 11 + [_i32, ctypes.POINTER(_i32)]
+        L.hidet_conv2d_untuned_form.argtypes = [_i32] + [_i64] * 11 + [ctypes.POINTER(_i32)]
         L.hidet_conv2d_patch_rows.argtypes = [_i32] + [_i64] * 11 + [ctypes.POINTER(_i32)]
         L.hidet_gemm_untuned_config.argtypes = [_i32, _i32, _i32] + [_i64] * 4 + [ctypes.POINTER(_i32)]
         L.hidet_row_schedule.argtypes = [_i32, _i32, _i64, _i64, ctypes.POINTER(hidet_row_schedule_t)]
@@ -551,6 +553,14 @@ def hidet_conv2d_untuned_config(dtype, x_shape, w_shape, stride=(1, 1), pad=(0, 
     _check(lib().hidet_conv2d_untuned_config(dtype, Nb, IC, H, W, OC, KH, KW, stride[0], stride[1], pad[0], pad[1], int(packed),
                                              ctypes.byref(config)), "hidet_conv2d_untuned_config")
     return config.value
+
+
+def hidet_conv2d_untuned_form(dtype, x_shape, w_shape, stride=(1, 1), pad=(0, 0)):
+    """The form (HIDET_CONV_) of such a convolution that names no configuration, with nothing tuned; runs nothing."""
+    (Nb, IC, H, W), (OC, _, KH, KW), form = x_shape, w_shape, _i32(-1)
+    _check(lib().hidet_conv2d_untuned_form(dtype, Nb, IC, H, W, OC, KH, KW, stride[0], stride[1], pad[0], pad[1], ctypes.byref(form)),
+           "hidet_conv2d_untuned_form")
+    return form.value
 
 
 def hidet_conv2d_patch_rows(dtype, x_shape, w_shape, stride=(1, 1), pad=(0, 0)):

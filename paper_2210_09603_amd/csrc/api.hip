@@ -620,9 +620,9 @@ hidet_status_t scratch_of_current_device(void** out) {
   return HIDET_OK;
 }
 struct Tuned {
-  int config;
+  int config;  // of the form; of the fastest gather with the patch forms, which have none
   int slices;
-  int route = 0;  // convolutions only: 1 = the remembered choice is for the batched-GEMM form of a 1x1 convolution
+  int form = HIDET_CONV_GATHER;  // convolutions only
 };
 std::map<std::string, Tuned> g_cache;
 std::vector<float> g_last_times;
@@ -813,35 +813,59 @@ hidet_status_t launch(const Problem& pr_in, int config, const SplitK& sk, hipStr
 
 const int kSliceChoices[] = {1, 2, 3, 4, 6, 8, 12, 16};
 
+// Times `iters` launches in a row on a stream.
+class Stopwatch {
+ public:
+  Stopwatch(hipStream_t stream, int iters) : stream_(stream), iters_(iters > 0 ? iters : 10) {
+    if (hipEventCreate(&e0_) != hipSuccess) e0_ = nullptr;
+    if (hipEventCreate(&e1_) != hipSuccess) e1_ = nullptr;
+  }
+  ~Stopwatch() {
+    if (e0_) (void)hipEventDestroy(e0_);
+    if (e1_) (void)hipEventDestroy(e1_);
+  }
+  Stopwatch(const Stopwatch&) = delete;
+  Stopwatch& operator=(const Stopwatch&) = delete;
+  bool ready() const { return e0_ && e1_; }
+  // Mean microseconds of `run` after a first one, which also loads the code object; -1 where it refuses.  False: the stream failed.
+  template <class F>
+  bool time(F run, float* us) {
+    *us = -1.0f;
+    if (run() != HIDET_OK) return true;
+    (void)hipEventRecord(e0_, stream_);
+    for (int i = 0; i < iters_; ++i) run();
+    (void)hipEventRecord(e1_, stream_);
+    if (hipEventSynchronize(e1_) != hipSuccess) return false;
+    float ms = 0.0f;
+    (void)hipEventElapsedTime(&ms, e0_, e1_);
+    *us = ms * 1000.0f / (float)iters_;
+    return true;
+  }
+
+ private:
+  hipStream_t stream_;
+  int iters_;
+  hipEvent_t e0_ = nullptr, e1_ = nullptr;
+};
+
 // Enumerates the schedule space (x the K-slice choices when a workspace is given) on the caller's fused problem.
 hidet_status_t tune(const Problem& pr, const SplitK& sk, hipStream_t stream, int iters, int32_t* best_config,
                     int32_t* best_slices, float* best_us) {
-  if (iters <= 0) iters = 10;
   std::vector<float> times(kNumConfigs, -1.0f);
   int best = -1, best_sl = 1;
   float best_t = 0.0f;
   if (!(pr.batch == 0 || pr.p.M == 0 || pr.p.N == 0)) {
-    hipEvent_t e0, e1;
-    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return HIDET_ERR_LAUNCH;
+    Stopwatch watch(stream, iters);
+    if (!watch.ready()) return HIDET_ERR_LAUNCH;
     for (int c = 0; c < kNumConfigs; ++c) {
       if (!find_launcher(pr, c)) continue;
       for (int sl : kSliceChoices) {
         if (sl > 1 && !sk.workspace) break;
         SplitK one = sk;
         one.slices = sl;
-        hidet_status_t st = launch(pr, c, one, stream);  // warm-up, also loads the code object
-        if (st != HIDET_OK) continue;
-        (void)hipEventRecord(e0, stream);
-        for (int i = 0; i < iters; ++i) launch(pr, c, one, stream);
-        (void)hipEventRecord(e1, stream);
-        if (hipEventSynchronize(e1) != hipSuccess) {
-          (void)hipEventDestroy(e0);
-          (void)hipEventDestroy(e1);
-          return HIDET_ERR_LAUNCH;
-        }
-        float ms = 0.0f;
-        (void)hipEventElapsedTime(&ms, e0, e1);
-        const float us = ms * 1000.0f / (float)iters;
+        float us = 0.0f;
+        if (!watch.time([&] { return launch(pr, c, one, stream); }, &us)) return HIDET_ERR_LAUNCH;
+        if (us < 0.0f) continue;
         if (times[c] < 0.0f || us < times[c]) times[c] = us;
         if (best < 0 || us < best_t) {
           best = c;
@@ -850,8 +874,6 @@ hidet_status_t tune(const Problem& pr, const SplitK& sk, hipStream_t stream, int
         }
       }
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     if (best < 0) return HIDET_ERR_NO_CONFIG;
     // leave the winner's output in the buffer
     SplitK win = sk;
@@ -890,6 +912,18 @@ struct ConvCall {
   bool pointwise = false;
 };
 
+// The configuration of a 1x1 convolution as one product whose columns run through all images; -1: this form cannot run it.
+// (A K slice or an input prologue needs another kernel; direct loads need aligned weights, and rows of a chunk at least, so
+// that one leaves the tensor in the last stage alone; their offsets from the tile's first image are 32 bits wide.)
+int images_form(const Problem& conv, bool pointwise, const SplitK& sk) {
+  const ConvGeom& g = conv.p.g;
+  if (!pointwise || conv.dtype == HIDET_F32 || conv.elem_mode != 0 || conv.p.relu_b != 0 || sk.slices > 1) return -1;
+  if (conv.p.K == 0 || conv.p.N == 0 || conv.p.M == 0 || g.HW < 8) return -1;
+  if ((128 / g.HW + 2) * (long long)g.IC * g.HW > (1LL << 30)) return -1;
+  for (int c = 0; c < kNumConfigs; ++c)
+    if (registry().fn[c][conv.dtype][kPointwiseVariant]) return c;
+  return -1;
+}
 // A 1x1 convolution as one product whose columns run through all images (pixels of an image rounded up to whole chunks of
 // eight), on the 128x128 ring tile with stages of 32, two workgroups to a compute unit: the configuration, or -1 where the
 // batched GEMM is taken.  Against it there is no padding of every image to whole tiles, rows of 49 or 169 pixels come in by
@@ -901,17 +935,11 @@ struct ConvCall {
 // 256 tiles, 1.15 at 208), and twice two rounds where half of a tile or more is padding (64 channels: 0.8 at 518 tiles, 1.1 at
 // 417; 32 channels 1.35 at 356, 0.67 at 627).
 int images_config(const Problem& conv, bool pointwise, const SplitK& sk) {
+  const int c = images_form(conv, pointwise, sk);
+  if (c < 0) return -1;
   const ConvGeom& g = conv.p.g;
-  // (a K slice or an input prologue needs another kernel; direct loads need aligned weights, and rows of a chunk at least, so
-  // that one leaves the tensor in the last stage alone; their offsets from the tile's first image are 32 bits wide)
-  if (!pointwise || conv.dtype == HIDET_F32 || conv.elem_mode != 0 || conv.p.relu_b != 0 || sk.slices > 1) return -1;
-  if (conv.p.K == 0 || conv.p.N == 0 || conv.p.M == 0 || g.HW < 8) return -1;
-  if ((128 / g.HW + 2) * (long long)g.IC * g.HW > (1LL << 30)) return -1;
   const long long tiles = (((long long)conv.p.M + 127) >> 7) * ((conv.Nb * ((g.HW + 7) / 8 * 8) + 127) >> 7);
-  if (tiles < (conv.p.M <= 64 ? 512 : g.HW % 8 != 0 ? 120 : 257)) return -1;
-  for (int c = 0; c < kNumConfigs; ++c)
-    if (registry().fn[c][conv.dtype][kPointwiseVariant]) return c;
-  return -1;
+  return tiles < (conv.p.M <= 64 ? 512 : g.HW % 8 != 0 ? 120 : 257) ? -1 : c;
 }
 Problem images_problem(const Problem& conv) {
   Problem pr = conv;
@@ -950,13 +978,21 @@ hidet_status_t make_conv_call(ConvCall& cc, int in, int out, long long Nb, long 
   return HIDET_OK;
 }
 
-// 3x3 and 5x5 convolutions of unit stride that keep the size, in 16-bit types, from OIHW weights: whether they run from a patch of the input
-// in LDS (conv_patch.hip), and on tiles of how many rows; 0: from the gather.
+// 3x3 and 5x5 convolutions of unit stride that keep the size, in 16-bit types, from OIHW weights, run from a patch of the input
+// in LDS (conv_patch.hip): whole stages of 16 channels, and rows whose border the 256 pixels of a patch hold.
+bool patch_form(const Problem& conv, const SplitK& sk) {
+  const ConvGeom& g = conv.p.g;
+  if (conv.op != 1 || conv.dtype == HIDET_F32 || conv.packed || conv.elem_mode != 0 || conv.p.relu_b != 0 || sk.slices > 1) return false;
+  if (g.KH != g.KW || (g.KW != 3 && g.KW != 5) || g.sh != 1 || g.sw != 1 || g.ph != g.KH / 2 || g.pw != g.KW / 2) return false;
+  if (g.IC % 16 != 0 || g.IC == 0 || conv.p.M == 0 || conv.Nb == 0 || g.W > (g.KW == 3 ? 62 : 29) || g.HW < 8) return false;
+  return sat_mul(conv.Nb, (long long)(g.H + g.ph) * (g.W + g.pw)) <= kMaxDim;
+}
+// Whether they are the better choice, and on tiles of how many rows; 0: the gather is.
 // It wants 72 tiles of 64x128 (of columns with the zero columns and rows among them).  Over 130 random problems of 16 to 512
 // channels its time over the gather's is 0.75 to 0.87 from 76 to 88 tiles, 0.42 to 0.9 beyond (1.03 once), but 1.1 to 1.3 from
 // 44 to 64, where the gather's K-splitting tiles have twice the workgroups; 58 to 63 tiles of a long K, 0.75 to 0.8, are not
 // told from those.  The zeros are no more than two fifths of the outputs (images of 6x6: 1.36 times as many columns, 0.94 to
-// 1.07 of the gather's), and the 256 pixels of a patch hold the border of rows of 62.
+// 1.07 of the gather's).
 // 5x5: 64 rows only, one workgroup to a compute unit, and rows of 29 at most.  Over 60 random problems 0.51 to 0.99 of the
 // gather's time from 146 tiles on; 0.69 to 0.89 from 88 to 130 tiles of up to 256 channels, but 1.14 to 1.20 of more (their
 // weights do not fit a die's L2), and 1.2 to 1.8 from 48 to 80.  (47 images of 384x10x10, where the zeros make it 1.44 times
@@ -967,12 +1003,10 @@ hidet_status_t make_conv_call(ConvCall& cc, int in, int out, long long Nb, long 
 // us; beyond two rounds the two are level, or 64 ahead: 44 of 192x23x23, 384 channels: 57.7 and 55.7 us).
 int patch_rows(const Problem& conv, const SplitK& sk) {
   const ConvGeom& g = conv.p.g;
-  if (conv.op != 1 || conv.dtype == HIDET_F32 || conv.packed || conv.elem_mode != 0 || conv.p.relu_b != 0 || sk.slices > 1) return 0;
-  if (g.KH != g.KW || (g.KW != 3 && g.KW != 5) || g.sh != 1 || g.sw != 1 || g.ph != g.KH / 2 || g.pw != g.KW / 2) return 0;
-  if (g.IC % 16 != 0 || g.IC == 0 || conv.p.M < 16 || conv.Nb == 0 || g.W > (g.KW == 3 ? 62 : 29) || g.HW < 8) return 0;
-  const long long plane = (long long)(g.H + g.ph) * (g.W + g.pw), columns = sat_mul(conv.Nb, plane);
-  if (5 * plane > (g.KW == 3 ? 7 : 9) * (long long)g.HW || columns > kMaxDim) return 0;
-  const long long across = (columns + 127) >> 7, of_64 = ((conv.p.M + 63LL) >> 6) * across, of_128 = ((conv.p.M + 127LL) >> 7) * across;
+  if (!patch_form(conv, sk) || conv.p.M < 16) return 0;
+  const long long plane = (long long)(g.H + g.ph) * (g.W + g.pw);
+  if (5 * plane > (g.KW == 3 ? 7 : 9) * (long long)g.HW) return 0;
+  const long long across = (conv.Nb * plane + 127) >> 7, of_64 = ((conv.p.M + 63LL) >> 6) * across, of_128 = ((conv.p.M + 127LL) >> 7) * across;
   if (g.KW == 5) return of_64 >= (g.IC <= 256 ? 104 : 150) ? 64 : 0;
   if (of_64 < 72) return 0;
   return conv.p.M > 64 && of_64 > 256 && (of_128 <= 256 || (of_128 > 384 && of_128 <= 512)) ? 128 : 64;
@@ -996,13 +1030,36 @@ hidet_status_t launch_patch(const Problem& conv, int bm, hipStream_t stream) {
   return HIDET_OK;
 }
 
+// One form of a convolution; a form that cannot run the call is refused before anything is launched.
+hidet_status_t launch_form(const ConvCall& cc, int form, int config, const SplitK& sk, hipStream_t stream) {
+  switch (form) {
+    case HIDET_CONV_GATHER: return launch(cc.conv, config, sk, stream);
+    case HIDET_CONV_BATCHED: return cc.pointwise ? launch(cc.gemm, config, sk, stream) : HIDET_ERR_NO_CONFIG;
+    case HIDET_CONV_IMAGES:
+      if (images_form(cc.conv, cc.pointwise, sk) < 0) return HIDET_ERR_NO_CONFIG;
+      return launch(images_problem(cc.conv), config, SplitK(), stream);
+    case HIDET_CONV_PATCH_64:
+    case HIDET_CONV_PATCH_128:
+      if (!patch_form(cc.conv, sk) || (form == HIDET_CONV_PATCH_128 && cc.conv.p.g.KW != 3)) return HIDET_ERR_NO_CONFIG;
+      return launch_patch(cc.conv, form == HIDET_CONV_PATCH_64 ? 64 : 128, stream);
+    default: return HIDET_ERR_NO_CONFIG;
+  }
+}
+
+// What a call runs that names no configuration and for which nothing is remembered.
+int untuned_form(const ConvCall& cc, const SplitK& sk) {
+  const int rows = patch_rows(cc.conv, sk);
+  if (rows > 0) return rows == 64 ? HIDET_CONV_PATCH_64 : HIDET_CONV_PATCH_128;
+  if (!cc.pointwise) return HIDET_CONV_GATHER;
+  return images_config(cc.conv, cc.pointwise, sk) >= 0 ? HIDET_CONV_IMAGES : HIDET_CONV_BATCHED;
+}
+
 // An explicit configuration always runs the gather form; config < 0 runs what the tuner remembered for this
-// convolution, else (3x3 convolutions) the patch kernel or (1x1 convolutions) the product over all images or the batched-GEMM
-// form with its size-based default.
+// convolution, else (3x3 and 5x5 convolutions) the patch kernel or (1x1 convolutions) the product over all images or the
+// batched-GEMM form with its size-based default.
 hidet_status_t launch_conv(const ConvCall& cc, int config, const SplitK& sk, hipStream_t stream) {
-  const int rows = config < 0 ? patch_rows(cc.conv, sk) : 0;
-  if (config >= 0 || (!cc.pointwise && rows == 0)) return launch(cc.conv, config, sk, stream);
-  Tuned t{-1, 1, 0};
+  if (config >= 0 || (!cc.pointwise && !patch_form(cc.conv, sk))) return launch(cc.conv, config, sk, stream);
+  Tuned t{-1, 1, HIDET_CONV_GATHER};
   {
     std::lock_guard<std::mutex> lock(g_mutex);
     auto it = find_tuned(cc.conv, sk);
@@ -1010,21 +1067,28 @@ hidet_status_t launch_conv(const ConvCall& cc, int config, const SplitK& sk, hip
   }
   SplitK one = sk;
   if (one.slices < 0) one.slices = t.slices;
-  const Problem& remembered = t.route == 1 && cc.pointwise ? cc.gemm : cc.conv;
-  // (an entry of a file written elsewhere may name a configuration that cannot serve this call: as if nothing were remembered)
-  if (find_launcher(remembered, t.config) && (one.slices <= 1 || find_partial_launcher(remembered, t.config)))
+  // (an entry that cannot serve this call -- more K slices than the remembered form has, a file written elsewhere -- counts for
+  // the configuration of the gather where it is one, else as if nothing were remembered)
+  if (t.config >= 0 && t.form >= HIDET_CONV_IMAGES) {
+    const hidet_status_t st = launch_form(cc, t.form, t.config, sk, stream);
+    if (st != HIDET_ERR_NO_CONFIG) return st;
+  }
+  const Problem& remembered = t.form == HIDET_CONV_BATCHED && cc.pointwise ? cc.gemm : cc.conv;
+  if (t.form != HIDET_CONV_IMAGES && find_launcher(remembered, t.config) &&
+      (one.slices <= 1 || find_partial_launcher(remembered, t.config)))
     return launch(remembered, t.config, one, stream);
-  if (rows > 0) return launch_patch(cc.conv, rows, stream);
-  const int c = images_config(cc.conv, cc.pointwise, sk);
-  return c >= 0 ? launch(images_problem(cc.conv), c, SplitK(), stream) : launch(cc.gemm, -1, sk, stream);
+  const int form = untuned_form(cc, sk);
+  const int c = form == HIDET_CONV_GATHER ? default_config(cc.conv) : form == HIDET_CONV_IMAGES ? images_form(cc.conv, cc.pointwise, sk) : -1;
+  return launch_form(cc, form, c, sk, stream);
 }
 
-// Tunes the gather form and, for a 1x1 convolution, the batched-GEMM form; the faster one is remembered under
-// the convolution's key.
+// Tunes the gather and whatever other forms can run the call -- the batched GEMM and the product over all images of a 1x1
+// convolution, the patch of a 3x3 or 5x5 one; the fastest is remembered under the convolution's key.
 hidet_status_t tune_conv(const ConvCall& cc, const SplitK& sk, hipStream_t stream, int iters, int32_t* best_config,
                          int32_t* best_slices, float* best_us) {
   int32_t c0 = -1, s0 = 1;
   float t0 = 0.0f;
+  int form = HIDET_CONV_GATHER;
   hidet_status_t st = tune(cc.conv, sk, stream, iters, &c0, &s0, &t0);
   if (st != HIDET_OK) return st;
   if (cc.pointwise) {
@@ -1041,11 +1105,37 @@ hidet_status_t tune_conv(const ConvCall& cc, const SplitK& sk, hipStream_t strea
     for (size_t i = 0; i < g_last_times.size() && i < times0.size(); ++i)
       if (times0[i] >= 0.0f && (g_last_times[i] < 0.0f || times0[i] < g_last_times[i])) g_last_times[i] = times0[i];
     if (c1 >= 0 && (c0 < 0 || t1 < t0)) {
-      g_cache[problem_key(cc.conv, sk.workspace != nullptr)] = Tuned{c1, s1, 1};
+      form = HIDET_CONV_BATCHED;
       c0 = c1;
       s0 = s1;
       t0 = t1;
     }
+  }
+  if (c0 >= 0) {
+    const SplitK whole;
+    const int images = images_form(cc.conv, cc.pointwise, whole);
+    Stopwatch watch(stream, iters);
+    if (!watch.ready()) return HIDET_ERR_LAUNCH;
+    for (int f : {HIDET_CONV_IMAGES, HIDET_CONV_PATCH_64, HIDET_CONV_PATCH_128}) {
+      float us = 0.0f;
+      if (!watch.time([&] { return launch_form(cc, f, images, whole, stream); }, &us)) return HIDET_ERR_LAUNCH;
+      if (us < 0.0f) continue;
+      std::lock_guard<std::mutex> lock(g_mutex);
+      if (f == HIDET_CONV_IMAGES && (g_last_times[images] < 0.0f || us < g_last_times[images])) g_last_times[images] = us;
+      if (us >= t0) continue;
+      form = f;
+      t0 = us;
+      if (f == HIDET_CONV_IMAGES) {
+        c0 = images;
+        s0 = 1;
+      }
+    }
+    SplitK win = form <= HIDET_CONV_BATCHED ? sk : whole;  // (the winner's output is left in the buffer)
+    if (form <= HIDET_CONV_BATCHED) win.slices = s0;
+    launch_form(cc, form, c0, win, stream);
+    (void)hipStreamSynchronize(stream);
+    std::lock_guard<std::mutex> lock(g_mutex);
+    g_cache[problem_key(cc.conv, sk.workspace != nullptr)] = Tuned{c0, s0, form};
   }
   if (best_config) *best_config = c0;
   if (best_slices) *best_slices = s0;
@@ -1343,6 +1433,18 @@ hidet_status_t hidet_conv2d_untuned_config(int32_t in, int64_t Nb, int64_t IC, i
   return HIDET_OK;
 }
 
+hidet_status_t hidet_conv2d_untuned_form(int32_t in, int64_t Nb, int64_t IC, int64_t H, int64_t W, int64_t OC, int64_t KH, int64_t KW,
+                                         int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w, int32_t* form) {
+  if (!form) return HIDET_ERR_INVALID_ARG;
+  void* const at = reinterpret_cast<void*>((uintptr_t)4096);  // (as above)
+  ConvCall cc;
+  const hidet_status_t st =
+      make_conv_call(cc, in, in, Nb, IC, H, W, OC, KH, KW, stride_h, stride_w, pad_h, pad_w, at, at, at, nullptr);
+  if (st != HIDET_OK) return st;
+  *form = cc.conv.p.M == 0 || cc.conv.p.N == 0 ? -1 : untuned_form(cc, SplitK());
+  return HIDET_OK;
+}
+
 hidet_status_t hidet_conv2d_patch_rows(int32_t in, int64_t Nb, int64_t IC, int64_t H, int64_t W, int64_t OC, int64_t KH, int64_t KW,
                                        int64_t stride_h, int64_t stride_w, int64_t pad_h, int64_t pad_w, int32_t* rows) {
   if (!rows) return HIDET_ERR_INVALID_ARG;
@@ -1448,7 +1550,7 @@ hidet_status_t hidet_tune_save(const char* path) {
   FILE* f = std::fopen(path, "w");
   if (!f) return HIDET_ERR_INVALID_ARG;
   for (const auto& kv : g_cache)
-    std::fprintf(f, "%s %d %d %d\n", kv.first.c_str(), kv.second.config, kv.second.slices, kv.second.route);
+    std::fprintf(f, "%s %d %d %d\n", kv.first.c_str(), kv.second.config, kv.second.slices, kv.second.form);
   std::fclose(f);
   return HIDET_OK;
 }
@@ -1461,10 +1563,10 @@ hidet_status_t hidet_tune_load(const char* path) {
   const hidet_status_t st = guarded([&] {
     std::lock_guard<std::mutex> lock(g_mutex);
     while (std::fgets(line, sizeof(line), f)) {
-      int cfg = 0, slices = 1, route = 0;  // the route is absent from files written before it existed
-      if (std::sscanf(line, "%255s %d %d %d", key, &cfg, &slices, &route) < 3) continue;
-      if (cfg >= 0 && cfg < kNumConfigs && slices >= 1 && slices <= 1024 && (route == 0 || route == 1))
-        g_cache[std::string(key)] = Tuned{cfg, slices, route};
+      int cfg = 0, slices = 1, form = 0;  // the form is absent from files written before it existed
+      if (std::sscanf(line, "%255s %d %d %d", key, &cfg, &slices, &form) < 3) continue;
+      if (cfg >= 0 && cfg < kNumConfigs && slices >= 1 && slices <= 1024 && form >= HIDET_CONV_GATHER && form <= HIDET_CONV_PATCH_128)
+        g_cache[std::string(key)] = Tuned{cfg, slices, form};
     }
     return HIDET_OK;
   });
