@@ -1605,9 +1605,12 @@ hidet_status_t hidet_taskmap_tasks(int32_t index, int32_t worker, int32_t* tasks
 
 hidet_status_t hidet_block_task(int32_t tiles_m, int32_t tiles_n, int32_t group, int32_t w, int32_t* tile_i,
                                 int32_t* tile_j) {
-  if (tiles_m <= 0 || tiles_n <= 0 || group <= 0 || w < 0 || w >= tiles_m * tiles_n || !tile_i || !tile_j)
-    return HIDET_ERR_INVALID_ARG;
-  const tmap::Task t = tmap::GroupedSpatial{tiles_m, tiles_n, group}.task(w);
+  if (tiles_m <= 0 || tiles_n <= 0 || group <= 0 || w < 0 || !tile_i || !tile_j) return HIDET_ERR_INVALID_ARG;
+  const long long tiles = (long long)tiles_m * tiles_n;
+  if (w >= tiles || tiles > kIntMax) return HIDET_ERR_INVALID_ARG;
+  GemmParams p;
+  set_block_mapping(p, tiles_m, tiles_n, group < tiles_m ? group : tiles_m);  // (as a launch does)
+  const tmap::Task t = grouped_tile(p, w);
   *tile_i = t.i;
   *tile_j = t.j;
   return HIDET_OK;

@@ -162,8 +162,12 @@ struct BlockCoords {
 // Step 1, block-level task mapping.  Workgroups are handed to the 8 accelerator dies (XCDs)
 // round-robin; they are renumbered so that each die, which has a private L2, works on one
 // contiguous run of tiles of the grouped traversal.
-// (the mapping itself is tmap::GroupedSpatial, with its divisions by multiplication)
-__device__ __forceinline__ tmap::Task grouped_tile(const GemmParams& p, int w) {
+
+// The mapping spatial(tiles_m, tiles_n) with a grouped traversal: consecutive workgroup ids walk down `group` tile rows before
+// moving to the next tile column, so that the workgroups resident together reuse the same A and B panels (the "thread block
+// swizzle" the paper lists among the optimisations a tensor program must be able to express, Section 3.1).  Divisions are by
+// multiplication (set_block_mapping).
+__host__ __device__ __forceinline__ tmap::Task grouped_tile(const GemmParams& p, int w) {
   const int panel = p.d_panel.div(w), first = panel * p.group;
   const int left = p.tiles_m - first;
   const bool full = left >= p.group;

@@ -66,23 +66,5 @@ struct ChainImpl<F> {
 template <class... Fs>
 using Chain = typename ChainImpl<Fs...>::type;
 
-// Run-time block-level mapping spatial(tiles_m, tiles_n) with a grouped traversal: consecutive
-// workgroup ids walk down `group` tile rows before moving to the next tile column, so that the
-// workgroups resident together reuse the same A and B panels (the "thread block swizzle" the
-// paper lists among the optimisations a tensor program must be able to express, Section 3.1).
-struct GroupedSpatial {
-  int tiles_m;
-  int tiles_n;
-  int group;
-  __host__ __device__ Task task(int w) const {
-    const int per_panel = group * tiles_n;
-    const int panel = w / per_panel;
-    const int first = panel * group;
-    const int rows = (tiles_m - first) < group ? (tiles_m - first) : group;
-    const int within = w - panel * per_panel;
-    return Task{first + within % rows, within / rows};
-  }
-};
-
 }  // namespace tmap
 }  // namespace hidet

@@ -393,6 +393,22 @@ def test_block_level_mapping_is_a_permutation_and_groups_rows():
         assert len(rows) == 4 and len(cols) == 8
 
 
+@pytest.mark.parametrize("tiles_m,tiles_n,group", [(1, 1, 1), (1, 9, 4), (2, 5, 4), (3, 7, 8), (4, 3, 4), (5, 7, 4), (6, 1, 4), (9, 16, 4),
+                                                   (16, 16, 4), (31, 33, 7), (1021, 2039, 4), (4, 500_000_003, 4), (500_000_003, 4, 4),
+                                                   (2 ** 31 - 1, 1, 4), (1, 2 ** 31 - 1, 1)])
+def test_block_level_mapping_of_the_kernels(tiles_m, tiles_n, group):
+    """The routine that the kernels call, with its divisions by multiplication, against the mapping in whole numbers: short last
+    panels, fewer tile rows than a group, grids up to the largest."""
+    total = tiles_m * tiles_n
+    ws = range(total) if total <= 2000 else sorted({0, 1, total // 2, total - 1} | {(total - 1) * i // 997 for i in range(998)})
+    for w in ws:
+        panel, within = divmod(w, group * tiles_n)
+        rows = min(group, tiles_m - panel * group)
+        assert hb.hidet_block_task(tiles_m, tiles_n, group, w) == (panel * group + within % rows, within // rows), w
+    with pytest.raises(hb.HidetError):
+        hb.hidet_block_task(tiles_m, tiles_n, group, total)
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys
