@@ -9,6 +9,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import sys
 
 import torch
 
@@ -149,12 +150,20 @@ def lib():
 _host_calls = None
 
 
+def built_for():
+    """What an extension module has to have been compiled for to read this process's tensors."""
+    return "torch %s, Python %d.%d" % (torch.__version__, sys.version_info[0], sys.version_info[1])
+
+
 def _load_host_calls(L):
     if not os.path.exists(HOST_CALLS_PATH):
         raise RuntimeError("host extension missing: %s (build it with `python -m paper_2210_09603_amd.build`)" % HOST_CALLS_PATH)
     loader = importlib.machinery.ExtensionFileLoader("_host_calls", HOST_CALLS_PATH)
     module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_host_calls", loader))
     loader.exec_module(module)
+    if module.built_for != built_for():
+        raise RuntimeError("host extension %s was built for %s, this is %s (run `python -m paper_2210_09603_amd.build`)"
+                           % (HOST_CALLS_PATH, module.built_for, built_for()))
     entry = (L.hidet_gemm_cfg, L.hidet_batched_gemm_cfg, L.hidet_conv2d_implicit_gemm_cfg,
              L.hidet_conv2d_implicit_gemm_packed, L.hidet_softmax_rows, L.hidet_reduce_rows)
     c = torch._C

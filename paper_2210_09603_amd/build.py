@@ -39,7 +39,7 @@ def schedule_space():
 
 def _sources_digest():
     h = hashlib.sha256()
-    for name in sorted(os.listdir(CSRC)):
+    for name in sorted(n for n in os.listdir(CSRC) if not n.endswith(".cpp")):
         with open(os.path.join(CSRC, name), "rb") as fh:
             h.update(name.encode())
             h.update(fh.read())
@@ -49,23 +49,55 @@ def _sources_digest():
     return h.hexdigest()
 
 
-def _host_flags():
-    """g++ flags of the extension module, which reads torch tensors: to compile it, to link it (against the libraries that
+def _host_commands(obj, out):
+    """The g++ commands that compile and link the extension module, which reads torch tensors (against the libraries that
     `import torch` has loaded before it)."""
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
+    from paper_2210_09603_amd.binding import built_for
 
-    abi = "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)
-    compile_flags = ["-O2", "-std=c++17", "-fPIC", "-Wall", abi, "-I" + sysconfig.get_paths()["include"]]
-    return compile_flags + ["-isystem" + d for d in include_paths()], ["-L" + d for d in library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-lc10"]
+    cxx = os.environ.get("CXX", "g++")
+    flags = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+             '-DHIDET_BUILT_FOR="%s"' % built_for(), "-I" + sysconfig.get_paths()["include"]] + ["-isystem" + d for d in include_paths()]
+    libraries = ["-L" + d for d in library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-lc10"]
+    return ([cxx] + flags + ["-c", os.path.join(CSRC, "host_calls.cpp"), "-o", obj], [cxx, "-shared", "-fPIC", "-o", out, obj] + libraries)
+
+
+def _host_digest():
+    """Of the module's sources, of what it is compiled against and of how."""
+    h = hashlib.sha256()
+    for path in (os.path.join(CSRC, "host_calls.cpp"), os.path.join(HERE, "..", "include", "hidet_mi355x.h")):
+        with open(path, "rb") as fh:
+            h.update(fh.read())
+    h.update(repr(_host_commands("", "")).encode())
+    return h.hexdigest()
+
+
+def _up_to_date(stamp, digest):
+    return os.path.exists(stamp) and open(stamp).read() == digest
+
+
+def _write(path, text):
+    with open(path, "w") as fh:
+        fh.write(text)
+
+
+def _build_host_calls(force):
+    obj, stamp = os.path.join(BUILD, "host_calls.o"), os.path.join(BUILD, "host_digest.txt")
+    digest = _host_digest()
+    if not force and os.path.exists(HOST_CALLS) and _up_to_date(stamp, digest):
+        return
+    tmp = HOST_CALLS + ".tmp.%d" % os.getpid()
+    for cmd in _host_commands(obj, tmp):
+        if subprocess.run(cmd).returncode != 0:
+            raise RuntimeError("%s failed on %s (%s is built)" % (cmd[0], os.path.basename(HOST_CALLS), os.path.basename(LIB)))
+    os.replace(tmp, HOST_CALLS)
+    _write(stamp, digest)
 
 
 def _compile(args):
     src, obj, defines = args
-    if src.endswith(".cpp"):
-        cmd = [os.environ.get("CXX", "g++")] + _host_flags()[0] + ["-c", src, "-o", obj]
-    else:
-        cmd = [HIPCC] + FLAGS + defines + ["-c", src, "-o", obj]
+    cmd = [HIPCC] + FLAGS + defines + ["-c", src, "-o", obj]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     # hipcc's host pass does not know the packed-fp32 feature and says so on every file; drop that line
     log = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l)
@@ -78,9 +110,9 @@ def build(force=False, jobs=None, verbose=True):
     subset = os.environ.get("HIDET_CONFIGS")
     chosen = None if not subset else {int(x) for x in subset.split(",") if x.strip()}
     stamp = os.path.join(BUILD, "digest.txt")
-    if force or not os.path.exists(stamp) or open(stamp).read() != digest:
+    if force or not _up_to_date(stamp, digest):
         for f in os.listdir(BUILD):
-            if f.endswith(".o"):
+            if f.endswith(".o") and f != "host_calls.o":
                 os.remove(os.path.join(BUILD, f))
     tasks, objs = [], []
     for idx, is_f32 in schedule_space():
@@ -96,9 +128,6 @@ def build(force=False, jobs=None, verbose=True):
         objs.append(obj)
         if not os.path.exists(obj):
             tasks.append((os.path.join(CSRC, name + ".hip"), obj, []))
-    host_obj = os.path.join(BUILD, "host_calls.o")
-    if not os.path.exists(host_obj):
-        tasks.append((os.path.join(CSRC, "host_calls.cpp"), host_obj, []))
     jobs = jobs or min(8, os.cpu_count() or 1)
     failed = False
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
@@ -116,11 +145,8 @@ def build(force=False, jobs=None, verbose=True):
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs, check=True)
     os.replace(tmp, LIB)
-    tmp = HOST_CALLS + ".tmp.%d" % os.getpid()
-    subprocess.run([os.environ.get("CXX", "g++"), "-shared", "-fPIC", "-o", tmp, host_obj] + _host_flags()[1], check=True)
-    os.replace(tmp, HOST_CALLS)
-    with open(stamp, "w") as fh:
-        fh.write(digest)
+    _write(stamp, digest)
+    _build_host_calls(force)
     return LIB
 
 

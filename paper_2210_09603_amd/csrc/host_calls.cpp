@@ -345,7 +345,9 @@ PyMODINIT_FUNC PyInit__host_calls() {
   if (PyType_Ready(&g_type) < 0) return nullptr;
   PyObject* m = PyModule_Create(&g_module);
   if (!m) return nullptr;
-  if (PyModule_AddObjectRef(m, "Calls", reinterpret_cast<PyObject*>(&g_type)) < 0) {
+  // (what this was compiled for: the binding refuses it under another torch or Python, whose tensors it would misread)
+  if (PyModule_AddObjectRef(m, "Calls", reinterpret_cast<PyObject*>(&g_type)) < 0 ||
+      PyModule_AddStringConstant(m, "built_for", HIDET_BUILT_FOR) < 0) {
     Py_DECREF(m);
     return nullptr;
   }

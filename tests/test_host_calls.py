@@ -184,3 +184,21 @@ def test_missing_extension_fails_loudly(monkeypatch):
     monkeypatch.setattr(hb, "HOST_CALLS_PATH", "/nonexistent/_host_calls.so")
     with pytest.raises(RuntimeError, match="host extension missing"):
         hb.hidet_gemm(t(4, 8), t(8, 6), t(4, 6))
+
+
+def test_extension_built_for_another_torch_is_refused(monkeypatch):
+    monkeypatch.setattr(hb, "_host_calls", None)
+    monkeypatch.setattr(hb, "built_for", lambda: "torch 0.0, Python 3.0")
+    with pytest.raises(RuntimeError, match="was built for torch"):
+        hb._calls()
+
+
+def test_extension_is_rebuilt_for_another_torch_or_compiler(monkeypatch):
+    from paper_2210_09603_amd import build
+
+    seen = {build._host_digest()}
+    monkeypatch.setenv("CXX", "another-compiler")
+    seen.add(build._host_digest())
+    monkeypatch.setattr(hb, "built_for", lambda: "torch 0.0, Python 3.0")
+    seen.add(build._host_digest())
+    assert len(seen) == 3
