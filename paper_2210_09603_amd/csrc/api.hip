@@ -93,7 +93,6 @@ constexpr long long kIntMax = 2147483647LL;
 // Largest extent of a GEMM dimension (and of the input tensor of a convolution, in elements): the kernels keep
 // such indices in 32 bits and step past them by at most one tile (or one gather window) before comparing.
 constexpr long long kMaxDim = kIntMax - 65536;
-constexpr long long kMaxVecLd = 4LL << 20;  // in-tile element offsets (row * ld + col, row < 256) stay below 2^31
 // An operand spans (rows - 1) * ld + cols elements per batch entry and batch * stride over the batch; both are
 // kept below 2^47 (no allocation is larger), so that neither the checks here nor the 64-bit offsets of the kernels
 // can overflow.

@@ -32,39 +32,52 @@ constexpr int kPartialVariants = 10;  // offset of the K-parallel partial-sum ke
 constexpr int kPointwiseVariant = 22;
 constexpr int kConvTapVariant = 20;   // convolution over the tap-major K order (repacked weights); +1: partial sums
 
-// Whether direct loads on plain operands stay where they belong.  Their offsets inside a tile are unsigned 32-bit byte offsets
-// (Operand::init_direct); and where rows are only element aligned, the 16 bytes that begin in the last columns of an
-// M/N-contiguous operand must not reach past the row that follows.  What remains goes through registers on the same tile.
+// Largest leading dimension for vector loads: in-tile element offsets (row * ld + col, row < 512) stay below 2^31.
+constexpr long long kMaxVecLd = 4LL << 20;
+
+// Whether direct loads on element-aligned operands stay where they belong.  Their offsets inside a tile are unsigned 32-bit
+// byte offsets (Operand::init_direct), and the 16 bytes that begin in the last columns of an M/N-contiguous operand must not
+// reach past the row that follows.  What remains goes through registers on the same tile.
 constexpr bool direct_offsets_fit(long long rows, long long ld) { return ld <= (1LL << 31) / rows; }  // (of 16-bit elements)
 template <class Cfg>
 bool direct_loads_fit(const GemmParams& p) {
-  if (!direct_offsets_fit(Cfg::LA == L_KC ? Cfg::BM : Cfg::BK, p.lda)) return false;
-  if (Cfg::MODE_B == LD_IMAGES) return true;  // (its input has offsets of its own, bounded where the form is chosen)
-  if (!direct_offsets_fit(Cfg::LB == L_KC ? Cfg::BN : Cfg::BK, p.ldb)) return false;
-  if (Cfg::MODE_A != LD_ELEM) return true;
-  return (Cfg::LA == L_KC || p.lda >= Cfg::VEC) && (Cfg::LB == L_KC || p.ldb >= Cfg::VEC);
+  static_assert(Cfg::MODE_A == LD_ELEM && Cfg::MODE_B == LD_ELEM, "rows of aligned operands are whole chunks, kMaxVecLd apart at most");
+  return direct_offsets_fit(Cfg::LA == L_KC ? Cfg::BM : Cfg::BK, p.lda) && direct_offsets_fit(Cfg::LB == L_KC ? Cfg::BN : Cfg::BK, p.ldb) &&
+         (Cfg::LA == L_KC || p.lda >= Cfg::VEC) && (Cfg::LB == L_KC || p.ldb >= Cfg::VEC);
 }
 
 template <class Cfg>
 hipError_t launch_kernel(const GemmParams& p, hipStream_t stream) {
-  // the element-mode variant of a ring tile also serves what the direct loads cannot do (input prologue, head-split
-  // output map, rows too far apart or too short), with its stages staged through registers
-  if (Cfg::SCHED == SCHED_PINGPONG && Cfg::MODE_A == LD_ELEM &&
-      (p.out_map != 0 || p.relu_a != 0 || p.relu_b != 0 || !direct_loads_fit<Cfg>(p))) {
-    if constexpr (Cfg::SCHED == SCHED_PINGPONG && Cfg::MODE_A == LD_ELEM)
-      hipLaunchKernelGGL(gemm_kernel_pingpong_regs<Cfg>, dim3((unsigned)p.total_blocks), dim3(Cfg::NT), 0, stream, p);
-  } else if constexpr (Cfg::SCHED == SCHED_PINGPONG) {
+  const dim3 grid((unsigned)p.total_blocks);
+  constexpr bool ELEM = Cfg::MODE_A == LD_ELEM, RING = Cfg::SCHED == SCHED_PINGPONG, WAVES = WaveStream<Cfg>::BUILT;
+  static_assert(!(RING || WAVES) || direct_offsets_fit(Cfg::BM > Cfg::BN ? Cfg::BM : Cfg::BN, kMaxVecLd), "rows of a tile");
+  static_assert(!(RING || WAVES) || direct_offsets_fit(Cfg::BK, kMaxVecLd), "rows of a tile");
+  if constexpr (RING) {
+    // the element-mode variant of a ring tile also serves what the direct loads cannot do (input prologue, head-split
+    // output map, rows too far apart or too short), with its stages staged through registers
+    if constexpr (ELEM) {
+      if (p.out_map != 0 || p.relu_a != 0 || p.relu_b != 0 || !direct_loads_fit<Cfg>(p)) {
+        hipLaunchKernelGGL(gemm_kernel_pingpong_regs<Cfg>, grid, dim3(Cfg::NT), 0, stream, p);
+        return hipGetLastError();
+      }
+    }
     // a K range of at most two stages never reuses a ring slot: the two-slot form leaves LDS for a second workgroup
     const int k_len = p.k_slices > 1 ? p.k_slice_len : p.K;
     if (k_len <= 2 * Cfg::BK)
-      hipLaunchKernelGGL((gemm_kernel_pingpong<Cfg, 2>), dim3((unsigned)p.total_blocks), dim3(Cfg::NT), 0, stream, p);
+      hipLaunchKernelGGL((gemm_kernel_pingpong<Cfg, 2>), grid, dim3(Cfg::NT), 0, stream, p);
     else
-      hipLaunchKernelGGL((gemm_kernel_pingpong<Cfg, 4>), dim3((unsigned)p.total_blocks), dim3(Cfg::NT), 0, stream, p);
-  } else if (WaveStream<Cfg>::BUILT && direct_loads_fit<Cfg>(p)) {
-    if constexpr (WaveStream<Cfg>::BUILT)
-      hipLaunchKernelGGL(gemm_kernel_waves<Cfg>, dim3((unsigned)p.total_blocks), dim3(WaveStream<Cfg>::NT), 0, stream, p);
-  } else
-    hipLaunchKernelGGL(gemm_kernel<Cfg>, dim3((unsigned)p.total_blocks), dim3(Cfg::NT), 0, stream, p);
+      hipLaunchKernelGGL((gemm_kernel_pingpong<Cfg, 4>), grid, dim3(Cfg::NT), 0, stream, p);
+  } else if constexpr (WAVES) {
+    if constexpr (ELEM) {
+      if (!direct_loads_fit<Cfg>(p)) {
+        hipLaunchKernelGGL(gemm_kernel<Cfg>, grid, dim3(Cfg::NT), 0, stream, p);
+        return hipGetLastError();
+      }
+    }
+    hipLaunchKernelGGL(gemm_kernel_waves<Cfg>, grid, dim3(WaveStream<Cfg>::NT), 0, stream, p);
+  } else {
+    hipLaunchKernelGGL(gemm_kernel<Cfg>, grid, dim3(Cfg::NT), 0, stream, p);
+  }
   return hipGetLastError();
 }
 
