@@ -33,6 +33,19 @@ def test_the_choice_between_the_two_forms():
     assert tile(4000, 256, 1, 7, 256)[:2] != (128, 128) or tile(4000, 256, 1, 7, 256)[2] != 1  # no row of a chunk
 
 
+def test_the_form_that_is_taken():
+    """The tile alone does not tell the forms apart: the batched GEMM takes the same one for some layers."""
+    def form(Nb, IC, H, W, OC, dtype=hb.HIDET_F16):
+        return hb.hidet_conv2d_untuned_form(dtype, (Nb, IC, H, W), (OC, IC, 1, 1))
+
+    for Nb, IC, H, W, OC, _ in SHAPES:
+        assert form(Nb, IC, H, W, OC) == hb.HIDET_CONV_IMAGES and form(Nb, IC, H, W, OC, hb.HIDET_F32) == hb.HIDET_CONV_BATCHED
+    assert form(274, 512, 7, 7, 128) == hb.HIDET_CONV_IMAGES and form(272, 512, 7, 7, 128) == hb.HIDET_CONV_BATCHED
+    assert form(514, 256, 8, 8, 80) == hb.HIDET_CONV_IMAGES and form(512, 256, 8, 8, 80) == hb.HIDET_CONV_BATCHED
+    assert form(1170, 64, 7, 7, 64) == hb.HIDET_CONV_IMAGES and form(1168, 64, 7, 7, 64) == hb.HIDET_CONV_BATCHED
+    assert form(4000, 256, 1, 7, 256) == hb.HIDET_CONV_BATCHED and form(140, 60, 7, 7, 200) == hb.HIDET_CONV_BATCHED
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("shape", SHAPES)

@@ -120,3 +120,17 @@ def test_infinities_beyond_k_do_not_reach_the_result():
             hb.hidet_gemm(A[:, :K], B[:K], C, config=cfg)
             torch.cuda.synchronize()
             assert (C == 0.5 * K).all(), (cfg, K)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_a_residual_that_is_the_output_itself(dtype):
+    """It is read before the main loop; each element by the thread that stores it."""
+    for cfg, bm, bn in streaming():
+        for M, N, K in ((3 * bm + 1, 2 * bn + 8, 600), (2 * bm, 3 * bn + 3, 601)):
+            c = wl.gemm_case(9900 + cfg, M, N, K, dtype, bias="col", residual=True)
+            A, B, bias, C = (to_gpu(c[n], dtype) for n in ("A", "B", "bias", "residual"))
+            hb.hidet_gemm(A, B, C, epilogue=hb.make_epilogue(bias=bias, bias_axis=hb.HIDET_BIAS_PER_COL, residual=C), config=cfg)
+            torch.cuda.synchronize()
+            A64, B64, b64, r64 = (wl.widen(c[n], dtype) for n in ("A", "B", "bias", "residual"))
+            ref = oracle.gemm(A64, B64, bias=b64, bias_axis=oracle.BIAS_PER_COL, residual=r64)
+            assert_elementwise(to_f64(C), ref, gemm_scale(A64, B64, False, False, 1.0, b64, "col", r64), dtype, K, "config %d" % cfg)
