@@ -525,8 +525,18 @@ int default_config(const Problem& pr, int slices = 1) {
     // (a quarter of it padding in every entry of a batch, no large tile is: 88 of 400x64x400 15.2 us on 256x128 tiles, 10.2
     // us on 64x64; 65 of 398x398x128 29.9 us on 256x256, 17.2 us; 84 of 448x448x128 28.1 and 16.7 us)
     const long long area = (long long)r.bm * r.bn;
-    const long long full = area >= 256 * 256 && pr.p.K <= 128 ? 7 : 6;  // eighths of a tile that have to be output
+    // (half of one is enough on a long K, and on element-aligned rows for 128x128 tiles, against which smaller ones load under
+    // predicates: 78 of 96x729x512 19.3 us on 128x256, 30.9 us on 32x64; 111 of 88x511x42 8.4 us on 128x128, 11.6 us on 32x64)
+    const bool half_pays = pr.p.K >= 256 || (area == 128 * 128 && pr.elem_mode != 0);
+    const long long full = area >= 256 * 256 && pr.p.K <= 128 ? 7 : half_pays ? 4 : 6;  // eighths of a tile that have to be output
     if (gemm16 && pr.batch > 1 && area >= 128 * 128 && 8 * M * N <= full * tiles * area) {
+      passed_over = c;
+      continue;
+    }
+    // (nor does a batch take the 16x64 tile, two wavefronts that need as long as the four of a 32x64 one: 96 of 48x196x1024
+    // 46.3 and 22.8 us, 148 of 48x169x64 10.7 and 5.1 us, 94 of 10x358x36 8.1 and 4.7 us; but for aligned rows and no more
+    // than 16 of them, 40 of 16x1600x256: 6.1 and 6.9 us)
+    if (gemm16 && pr.batch > 1 && r.bm == 16 && r.bn == 64 && (M > 16 || pr.elem_mode != 0)) {
       passed_over = c;
       continue;
     }

@@ -70,3 +70,14 @@ def test_arguments():
     assert f(hb.HIDET_F16, 0, 0, 1, 0, 8, 8) == 0 and c.value == -1  # empty
     assert f(9, 0, 0, 1, 8, 8, 8) == 1 and f(hb.HIDET_F16, 0, 0, 1, -1, 8, 8) == 1
     assert hb.lib().hidet_gemm_untuned_config(hb.HIDET_F16, 0, 0, 1, 8, 8, 8, None) == 1
+
+
+def test_batches_on_tiles_that_carry_them():
+    """Two wavefronts of 16x64 need as long as the four of 32x64, whatever share of the tile is output; a half-filled large tile
+    beats full small ones on a long K and, on element-aligned rows, at 128x128."""
+    assert chosen(48, 196, 1024, batch=96)[:2] != (16, 64)
+    assert chosen(48, 169, 64, batch=148)[:2] != (16, 64)
+    assert chosen(10, 358, 36, batch=94, dtype=hb.HIDET_BF16)[:2] != (16, 64)
+    assert chosen(16, 1600, 256, batch=40)[:2] == (16, 64)  # aligned, no row of it padding
+    assert chosen(96, 729, 512, batch=78)[:2] == (128, 256)
+    assert chosen(88, 511, 42, batch=111)[:2] == (128, 128)
