@@ -996,6 +996,45 @@ bool patch_form(const Problem& conv, const SplitK& sk) {
   if (g.IC % 16 != 0 || g.IC == 0 || conv.p.M == 0 || conv.Nb == 0 || g.W > (g.KW == 3 ? 62 : 29) || g.HW < 8) return false;
   return sat_mul(conv.Nb, (long long)(g.H + g.ph) * (g.W + g.pw)) <= kMaxDim;
 }
+// Microseconds of a convolution through the gather on the tile that would be taken, and from a patch: predictions for the choice
+// between the two alone.  A tile that owns a compute unit (schedules 1 and 3) takes a fixed time and a rate per value of K for
+// each round of 256 workgroups, several that share one as much for what they are of a round; a patch a rate per stage, per
+// store of its outputs and, for 5x5, a quarter more where the weights that a die's workgroups read (four rows of tiles, all of
+// them where its run of tiles crosses into the next four) leave no room in its L2.  Fitted to 2600 random convolutions of 16 to
+// 1024 channels and planes of 6x6 to 62x62 (relative): 5 % to 95 % of predictions over measurements 0.91 to 1.07 for the
+// K-splitting tiles, 0.84 to 1.15 for the others, 0.92 to 1.13 and 0.81 to 1.09 for patches of 5x5 and 3x3.
+struct GatherTime {
+  int bm, bn, sched;  // (0: schedules 0 and 2)
+  double fixed, per_k;  // us; of 4608 values of K
+};
+constexpr GatherTime kGatherTimes[] = {
+    {16, 16, 3, 5.5, 11},   {32, 16, 3, 5.5, 11.5}, {16, 32, 3, 5.5, 11.5}, {32, 32, 3, 5.5, 13}, {64, 32, 3, 6, 16},
+    {64, 64, 3, 7.5, 28},   {128, 64, 3, 10.5, 34}, {128, 128, 3, 10, 58.5}, {128, 128, 1, 14, 80}, {256, 128, 1, 26, 112},
+    {128, 256, 1, 28, 140}, {256, 256, 1, 30, 220}, {16, 64, 0, 11, 41},    {32, 32, 0, 6, 17.5}, {64, 32, 0, 6.5, 19.5},
+    {32, 64, 0, 8, 26},     {64, 64, 0, 7, 33},     {128, 64, 0, 10, 42},   {64, 128, 0, 10.5, 67}};
+double gather_us(const Problem& conv) {
+  const int c = default_config(conv);
+  if (c < 0) return 0.0;
+  const ConfigRow& r = kConfigs[c];
+  const long long tiles = sat_mul((conv.p.M + r.bm - 1) / r.bm, (conv.p.N + r.bn - 1) / r.bn);
+  const double rounds = r.sched == 1 || r.sched == 3 ? (double)((tiles + 255) >> 8) : std::max(1.0, (double)tiles / 256.0);
+  for (const GatherTime& t : kGatherTimes)
+    if (t.bm == r.bm && t.bn == r.bn && t.sched == (r.sched == 2 ? 0 : r.sched)) return t.fixed + t.per_k * rounds * conv.p.K / 4608.0;
+  return 0.0;
+}
+double patch_us(const Problem& conv, int rows) {
+  const ConvGeom& g = conv.p.g;
+  const long long tiles_m = (conv.p.M + rows - 1) / rows, columns = conv.Nb * (g.H + g.ph) * (g.W + g.pw);
+  const long long tiles = sat_mul(tiles_m, (columns + 127) >> 7);
+  const double stages = g.IC / 16, whole = (double)((tiles + 255) >> 8);
+  const bool residual = conv.p.residual != nullptr;
+  if (g.KW == 3 && rows == 64) return 4.0 + std::max(1.0, (double)tiles / 256.0) * (2.3 + (residual ? 0.8 : 0.0) + 0.75 * stages);
+  if (g.KW == 3) return 1.5 + whole * (5.2 + (residual ? 1.4 : 0.0) + 1.07 * stages);
+  const long long panels = tiles_m / 4;
+  const bool crosses = tiles_m > 4 && (tiles_m % 4 != 0 || (panels < 8 ? 8 % panels != 0 : panels % 8 != 0));
+  const double die = (double)std::min<long long>(conv.p.M, crosses ? 512 : 256) * g.IC * 50.0 + (double)conv.Nb * g.IC * g.HW * 2.0 / 8.0;
+  return 2.0 + whole * (4.0 + (residual ? 1.3 : 0.0) + (die > 4194304.0 ? 2.75 : 2.1) * stages);
+}
 // Whether they are the better choice, and on tiles of how many rows; 0: the gather is.
 // It wants 72 tiles of 64x128 (of columns with the zero columns and rows among them).  Over 130 random problems of 16 to 512
 // channels its time over the gather's is 0.75 to 0.87 from 76 to 88 tiles, 0.42 to 0.9 beyond (1.03 once), but 1.1 to 1.3 from
@@ -1010,15 +1049,20 @@ bool patch_form(const Problem& conv, const SplitK& sk) {
 // of 128x28x28: 14.7 us, 16.9 us on 64; at most 256 tiles of 64: 1.25 of the time of 64), unless they make a second round
 // that is less than half full (47 of 96x27x27, 80 channels, 288 tiles: 23.1 and 21.0 us; 60 of 96x30x30, 451: 26.8 and 29.0
 // us; beyond two rounds the two are level, or 64 ahead: 44 of 192x23x23, 384 channels: 57.7 and 55.7 us).
+// The counts know neither how many of the gather's columns are padding (none in rows of 8 or 16) nor which tiles it has: where
+// the predictions say that it is faster it is taken.  Of 2600 random convolutions 136 were more than 4 % slower than through it
+// by the counts alone (101 of 256x8x8, 5x5, with residual: 59 and 91 us; 13 of 512x8x8, 3x3: 22 and 28 us), 16 are now, none by
+// more than a quarter (154 of 96x8x8, 384 channels, 3x3, with residual: 20.9 and 25.8 us).
 int patch_rows(const Problem& conv, const SplitK& sk) {
   const ConvGeom& g = conv.p.g;
   if (!patch_form(conv, sk) || conv.p.M < 16) return 0;
   const long long plane = (long long)(g.H + g.ph) * (g.W + g.pw);
   if (5 * plane > (g.KW == 3 ? 7 : 9) * (long long)g.HW) return 0;
   const long long across = (conv.Nb * plane + 127) >> 7, of_64 = ((conv.p.M + 63LL) >> 6) * across, of_128 = ((conv.p.M + 127LL) >> 7) * across;
-  if (g.KW == 5) return of_64 >= (g.IC <= 256 ? 104 : 150) ? 64 : 0;
-  if (of_64 < 72) return 0;
-  return conv.p.M > 64 && of_64 > 256 && (of_128 <= 256 || (of_128 > 384 && of_128 <= 512)) ? 128 : 64;
+  if (of_64 < (g.KW == 3 ? 72 : g.IC <= 256 ? 104 : 150)) return 0;
+  const int rows = g.KW == 3 && conv.p.M > 64 && of_64 > 256 && (of_128 <= 256 || (of_128 > 384 && of_128 <= 512)) ? 128 : 64;
+  const double gather = gather_us(conv);
+  return gather > 0.0 && patch_us(conv, rows) > gather * (g.KW == 3 ? 1.05 : 1.0) ? 0 : rows;
 }
 hidet_status_t launch_patch(const Problem& conv, int bm, hipStream_t stream) {
   GemmParams p = conv.p;

@@ -38,6 +38,14 @@ def test_the_choice_between_patch_and_gather():
     assert rows(40, 64, 29, 29, 64, k=5, pad=2) == 64 and rows(40, 64, 29, 30, 64, k=5, pad=2) == 0
 
 
+def test_the_gather_where_it_is_faster():
+    """Rows of 8 and 16 pixels, of which no column of the gather is padding, and weights beyond a die's L2."""
+    assert rows(101, 256, 8, 8, 256, k=5, pad=2) == 0 and rows(64, 128, 16, 16, 128, k=5, pad=2) == 0
+    assert rows(13, 512, 8, 8, 512) == 0 and rows(128, 128, 8, 8, 32) == 0
+    assert rows(8, 1024, 15, 15, 1024, k=5, pad=2) == 0 and rows(32, 512, 16, 16, 128, k=5, pad=2) == 0
+    assert rows(64, 512, 7, 7, 512) == 64 and rows(64, 256, 14, 14, 256) == 128 and rows(60, 256, 14, 14, 256, k=5, pad=2) == 64
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("shape", SHAPES)
