@@ -933,6 +933,50 @@ int images_form(const Problem& conv, bool pointwise, const SplitK& sk) {
     if (registry().fn[c][conv.dtype][kPointwiseVariant]) return c;
   return -1;
 }
+// Microseconds of a batched GEMM on the tile that would be taken, and of the product over all images: predictions for the choice
+// between the two alone.  A fixed time, one for each wave of resident workgroups where that shows, and for each round of 256
+// workgroups (whole ones of ring tiles) the time of a workgroup's output, of its residual and of 32 values of K.  Fitted to
+// 3300 random convolutions of 16 to 2048 channels: 5 % to 95 % of predictions over measurements 0.8 to 1.15, of the product
+// 0.84 to 1.18.
+struct BatchedTime {
+  int bm, bn, ring, resident;  // ring: 1 with a K of at most two stages (two workgroups to a compute unit), 2 beyond
+  double fixed, wave, out, residual, per_k;  // us
+};
+constexpr BatchedTime kAlignedTimes[] = {
+    {32, 32, 0, 1, 4, 0, 0, 0.1, 0.085},         {16, 64, 0, 1, 4, 0, 0.5, 0.2, 0.11},        {64, 32, 0, 1, 4, 0, 0.33, 0.1, 0.092},
+    {32, 64, 0, 1, 4, 0, 0.42, 0.15, 0.095},     {64, 64, 0, 5, 3.1, 2.1, 0.18, 0.33, 0.154}, {128, 64, 0, 3, 3.9, 2.6, 0.67, 0.66, 0.19},
+    {64, 128, 0, 3, 3.2, 3.6, 0.4, 0.94, 0.22},  {128, 128, 1, 1, 4, 0, 3, 0.8, 0.32},        {256, 128, 1, 1, 4, 0, 4.7, 4.1, 0.64},
+    {128, 256, 1, 1, 4, 0, 5.6, 3.1, 0.6},       {256, 256, 1, 1, 4, 0, 14, 11.2, 0.64},      {128, 128, 2, 1, 2, 0, 4.4, 1.7, 0.279},
+    {256, 128, 2, 1, 1.6, 0, 7.9, 4.9, 0.523},   {128, 256, 2, 1, 1.3, 0, 8.6, 4.9, 0.478},   {256, 256, 2, 1, 4, 0, 14, 11.2, 0.64}};
+constexpr BatchedTime kElementTimes[] = {
+    {32, 32, 0, 1, 4, 0, 0.12, 0.1, 0.107},      {16, 64, 0, 1, 4, 0, 1.2, 0.3, 0.16},        {64, 32, 0, 1, 4, 0, 0.35, 0.2, 0.135},
+    {32, 64, 0, 1, 4, 0, 0.52, 0.17, 0.155},     {64, 64, 0, 1, 4, 0, 0.95, 0.43, 0.21},      {128, 64, 0, 1, 4, 0, 3.3, 0.9, 0.25},
+    {64, 128, 0, 1, 4, 0, 2.7, 1.4, 0.28},       {128, 128, 1, 1, 4, 0, 2.8, 1.5, 0.39},      {256, 128, 1, 1, 4, 0, 5.2, 4.3, 0.69},
+    {128, 256, 1, 1, 4, 0, 5.7, 5.4, 0.7},       {256, 256, 1, 1, 4, 0, 15, 12.6, 0.68},      {128, 128, 2, 1, 1.9, 0, 6.1, 2, 0.288},
+    {256, 128, 2, 1, 2.9, 0, 8.5, 5.7, 0.544},   {128, 256, 2, 1, 2.2, 0, 9.3, 6.2, 0.492},   {256, 256, 2, 1, 4, 0, 15, 12.6, 0.68}};
+double batched_us(const Problem& gemm) {
+  const int c = default_config(gemm);
+  if (c < 0 || kConfigs[c].sched == 3) return 0.0;  // (K-splitting tiles: few of them, not compared)
+  const ConfigRow& r = kConfigs[c];
+  const int ring = r.sched != 1 ? 0 : gemm.p.K <= 2 * r.bk ? 1 : 2;
+  const long long tiles = sat_mul(gemm.batch, sat_mul((gemm.p.M + r.bm - 1) / r.bm, (gemm.p.N + r.bn - 1) / r.bn));
+  const BatchedTime* const times = gemm.elem_mode != 0 ? kElementTimes : kAlignedTimes;
+  static_assert(sizeof(kElementTimes) == sizeof(kAlignedTimes), "the same tiles");
+  for (size_t i = 0; i < sizeof(kAlignedTimes) / sizeof(kAlignedTimes[0]); ++i) {
+    const BatchedTime& t = times[i];
+    if (t.bm != r.bm || t.bn != r.bn || t.ring != ring) continue;
+    const double rounds = ring ? (double)((tiles + 255) >> 8) : std::max(1.0, (double)tiles / 256.0);
+    const long long resident = 256LL * t.resident;
+    return t.fixed + t.wave * (double)((tiles + resident - 1) / resident) +
+           rounds * (t.out + (gemm.p.residual ? t.residual : 0.0) + t.per_k * gemm.p.K / 32.0);
+  }
+  return 0.0;
+}
+double images_us(const Problem& conv, long long tiles) {  // (two workgroups to a compute unit; one alone takes 1.5 times its half)
+  const double rounds = std::max(1.5, (double)((tiles + 255) >> 8));
+  return 2.4 + rounds * (2.5 + (conv.p.residual ? 0.3 : 0.0) + 0.284 * conv.p.K / 32.0);
+}
+
 // A 1x1 convolution as one product whose columns run through all images (pixels of an image rounded up to whole chunks of
 // eight), on the 128x128 ring tile with stages of 32, two workgroups to a compute unit: the configuration, or -1 where the
 // batched GEMM is taken.  Against it there is no padding of every image to whole tiles, rows of 49 or 169 pixels come in by
@@ -943,12 +987,21 @@ int images_form(const Problem& conv, bool pointwise, const SplitK& sk) {
 // over the GEMM's: 0.42 to 1.04 from 120 tiles on rows that are not, but 1.2 at 69 to 80; on aligned ones 0.43 to 0.89 beyond
 // 256 tiles, 1.15 at 208), and twice two rounds where half of a tile or more is padding (64 channels: 0.8 at 518 tiles, 1.1 at
 // 417; 32 channels 1.35 at 356, 0.67 at 627).
-int images_config(const Problem& conv, bool pointwise, const SplitK& sk) {
-  const int c = images_form(conv, pointwise, sk);
+// The counts know neither the batched GEMM's tile nor its rounds: where the predictions say that it is faster by a twelfth (of
+// K = 64 they are no better than that) it is taken.  Of 3300 random convolutions 295 were more than 4 % slower than through it
+// by the counts alone (64 images of 1024x14x14, 256 channels: 16.6 and 19.0 us; 125 of 2048x14x14, 512 channels: 64 and 79 us;
+// 65 of 192x32x32, 32 channels: 7.8 and 13.1 us; 26 of 64x56x56, 64 channels: 9.4 and 12.6 us), 139 are now, by a quarter at
+// most (95 of 64x11x11, 160 channels: 6.0 and 7.5 us); of the others 18 lost as much (32 of 64x56x56, 64 channels: 12.7 and
+// 14.2 us).
+int images_config(const ConvCall& cc, const SplitK& sk) {
+  const Problem& conv = cc.conv;
+  const int c = images_form(conv, cc.pointwise, sk);
   if (c < 0) return -1;
   const ConvGeom& g = conv.p.g;
   const long long tiles = (((long long)conv.p.M + 127) >> 7) * ((conv.Nb * ((g.HW + 7) / 8 * 8) + 127) >> 7);
-  return tiles < (conv.p.M <= 64 ? 512 : g.HW % 8 != 0 ? 120 : 257) ? -1 : c;
+  if (tiles < (conv.p.M <= 64 ? 512 : g.HW % 8 != 0 ? 120 : 257)) return -1;
+  const double batched = g.HW >= 64 ? batched_us(cc.gemm) : 0.0;  // (smaller planes are not predicted: a tile is half padding)
+  return batched > 0.0 && images_us(conv, tiles) > 1.08 * batched ? -1 : c;
 }
 Problem images_problem(const Problem& conv) {
   Problem pr = conv;
@@ -1104,7 +1157,7 @@ int untuned_form(const ConvCall& cc, const SplitK& sk) {
   const int rows = patch_rows(cc.conv, sk);
   if (rows > 0) return rows == 64 ? HIDET_CONV_PATCH_64 : HIDET_CONV_PATCH_128;
   if (!cc.pointwise) return HIDET_CONV_GATHER;
-  return images_config(cc.conv, cc.pointwise, sk) >= 0 ? HIDET_CONV_IMAGES : HIDET_CONV_BATCHED;
+  return images_config(cc, sk) >= 0 ? HIDET_CONV_IMAGES : HIDET_CONV_BATCHED;
 }
 
 // An explicit configuration always runs the gather form; config < 0 runs what the tuner remembered for this
@@ -1481,7 +1534,7 @@ hidet_status_t hidet_conv2d_untuned_config(int32_t in, int64_t Nb, int64_t IC, i
                                                     at, at, at, nullptr);
   if (st != HIDET_OK) return st;
   const Problem& pr = cc.pointwise ? cc.gemm : cc.conv;
-  const int images = images_config(cc.conv, cc.pointwise, SplitK());
+  const int images = images_config(cc, SplitK());
   *config = images >= 0 ? images : pr.batch == 0 || pr.p.M == 0 || pr.p.N == 0 ? -1 : default_config(pr);
   return HIDET_OK;
 }

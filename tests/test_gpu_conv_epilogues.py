@@ -14,7 +14,7 @@ from helpers import TORCH_DTYPE, assert_elementwise, conv_scale, to_f64, to_gpu
 PATCHES = (hb.HIDET_CONV_PATCH_64, hb.HIDET_CONV_PATCH_128)
 # images, input channels, height, width, output channels, filter, forms
 SHAPES = [(64, 32, 14, 14, 80, 3, PATCHES), (70, 32, 14, 15, 200, 3, PATCHES), (60, 16, 14, 13, 66, 5, PATCHES),
-          (300, 64, 7, 7, 136, 1, (hb.HIDET_CONV_IMAGES,)), (240, 72, 8, 8, 260, 1, (hb.HIDET_CONV_IMAGES,))]
+          (300, 64, 7, 7, 136, 1, (hb.HIDET_CONV_IMAGES,)), (240, 200, 8, 8, 260, 1, (hb.HIDET_CONV_IMAGES,))]
 
 
 def test_the_forms_under_test():

@@ -43,6 +43,9 @@ def test_the_form_that_is_taken():
     assert form(274, 512, 7, 7, 128) == hb.HIDET_CONV_IMAGES and form(272, 512, 7, 7, 128) == hb.HIDET_CONV_BATCHED
     assert form(514, 256, 8, 8, 80) == hb.HIDET_CONV_IMAGES and form(512, 256, 8, 8, 80) == hb.HIDET_CONV_BATCHED
     assert form(1170, 64, 7, 7, 64) == hb.HIDET_CONV_IMAGES and form(1168, 64, 7, 7, 64) == hb.HIDET_CONV_BATCHED
+    # tiles enough, but one round of large ones or a few full small ones carry the batched GEMM faster
+    assert form(64, 1024, 14, 14, 256) == hb.HIDET_CONV_BATCHED and form(125, 2048, 14, 14, 512) == hb.HIDET_CONV_BATCHED
+    assert form(65, 192, 32, 32, 32) == hb.HIDET_CONV_BATCHED and form(64, 512, 7, 7, 2048) == hb.HIDET_CONV_IMAGES
     assert form(4000, 256, 1, 7, 256) == hb.HIDET_CONV_BATCHED and form(140, 60, 7, 7, 200) == hb.HIDET_CONV_BATCHED
 
 
