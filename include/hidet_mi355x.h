@@ -20,7 +20,8 @@
  *   - On any status other than HIDET_OK nothing has been launched and no output byte was written, unless the
  *     status is HIDET_ERR_LAUNCH (the HIP runtime refused a launch) from a call that launches two kernels: a
  *     K-parallel form, whose first kernel writes the workspace only, or a large GEMM cut in two (see
- *     hidet_kernel_launch_count), whose first kernel writes its rows or columns of C.  No C++ exception leaves the library; a failed host allocation is reported as HIDET_ERR_LAUNCH.
+ *     hidet_kernel_launch_count), whose first kernel writes its rows or columns of C.
+ *     No C++ exception leaves the library; a failed host allocation is reported as HIDET_ERR_LAUNCH.
  *     M == 0, N == 0 or batch == 0 is an OK no-op; K == 0 writes C = epilogue(0).
  *   - Thread safety: entry points may be called from several host threads; the tuned-config cache
  *     is guarded by a mutex.

@@ -405,9 +405,10 @@ int one_round_config(const Problem& pr) {
 // which all workgroups are resident is taken (300x768x3072: 240 of 32x32 10.6 us, 60 of 64x64 15.5 us; 20.9 us on 16x16,
 // which needs four rounds; 8x12288x4096, seven eighths of whose 64x64 tiles are padding: 23.4 us, 28.9 us on 16x32), on
 // aligned rows a 16x16 one only if it leaves a quarter of the device free: a 16x32 one touches no more cache lines of a
-// row-major B (117x512x2048: 256 of 16x16 6.8 us, 128 of 16x32 5.7 us; misaligned 276x213x3514: 10.9 and 11.9 us).  Each pays from the K on where its wavefronts have a step of
-// their own, earlier where rows are only element aligned, which the other tiles fetch under predicates: measured against
-// them on 320 random problems, 1.0 to 1.4 of their time below these limits, 0.4 to 1.0 above.
+// row-major B (117x512x2048: 256 of 16x16 6.8 us, 128 of 16x32 5.7 us; misaligned 276x213x3514: 10.9 and 11.9 us).  Each pays
+// from the K on where its wavefronts have a step of their own, earlier where rows are only element aligned, which the other
+// tiles fetch under predicates: measured against them on 320 random problems, 1.0 to 1.4 of their time below these limits, 0.4
+// to 1.0 above.
 // Below them the 32x32 tile of two stages, several to a compute unit, beats the larger ones as long as there are no more
 // than three to a compute unit (1308x566x256, 738 tiles: 5.7 us, 64x64 8.7 us; 168x624x49: 3.9 us, 16x64 6.1 us), on aligned
 // rows of more than 128 values the one of 256, of which a compute unit holds two (4 of 256x225x256: 4.6 us, 5.0 us).  From
@@ -428,8 +429,8 @@ int few_tiles_gemm_config(const Problem& pr) {
     const int area = r.bm * r.bn;
     if (blocks(r.bm, r.bn) > (area == 16 * 16 && pr.elem_mode == 0 ? kComputeUnits * 3 / 4 : kComputeUnits)) continue;
     // (of two tiles of one size the flatter one: rows of B are M/N-contiguous more often than not)
-    if (best < 0 || area < kConfigs[best].bm * kConfigs[best].bn || (area == kConfigs[best].bm * kConfigs[best].bn && r.bn > kConfigs[best].bn))
-      best = c;
+    const int best_area = best < 0 ? 0 : kConfigs[best].bm * kConfigs[best].bn;
+    if (best < 0 || area < best_area || (area == best_area && r.bn > kConfigs[best].bn)) best = c;
   }
   if (best >= 0) {
     const int area = kConfigs[best].bm * kConfigs[best].bn;
@@ -1044,7 +1045,8 @@ hidet_status_t make_conv_call(ConvCall& cc, int in, int out, long long Nb, long 
 // in LDS (conv_patch.hip): whole stages of 16 channels, and rows whose border the 256 pixels of a patch hold.
 bool patch_form(const Problem& conv, const SplitK& sk) {
   const ConvGeom& g = conv.p.g;
-  if (conv.op != 1 || conv.dtype == HIDET_F32 || conv.packed || conv.elem_mode != 0 || conv.p.relu_b != 0 || sk.slices > 1) return false;
+  if (conv.op != 1 || conv.dtype == HIDET_F32 || conv.packed || conv.elem_mode != 0) return false;
+  if (conv.p.relu_b != 0 || sk.slices > 1) return false;
   if (g.KH != g.KW || (g.KW != 3 && g.KW != 5) || g.sh != 1 || g.sw != 1 || g.ph != g.KH / 2 || g.pw != g.KW / 2) return false;
   if (g.IC % 16 != 0 || g.IC == 0 || conv.p.M == 0 || conv.Nb == 0 || g.W > (g.KW == 3 ? 62 : 29) || g.HW < 8) return false;
   return sat_mul(conv.Nb, (long long)(g.H + g.ph) * (g.W + g.pw)) <= kMaxDim;
@@ -1072,7 +1074,8 @@ double gather_us(const Problem& conv) {
   const long long tiles = sat_mul((conv.p.M + r.bm - 1) / r.bm, (conv.p.N + r.bn - 1) / r.bn);
   const double rounds = r.sched == 1 || r.sched == 3 ? (double)((tiles + 255) >> 8) : std::max(1.0, (double)tiles / 256.0);
   for (const GatherTime& t : kGatherTimes)
-    if (t.bm == r.bm && t.bn == r.bn && t.sched == (r.sched == 2 ? 0 : r.sched)) return t.fixed + t.per_k * rounds * conv.p.K / 4608.0;
+    if (t.bm == r.bm && t.bn == r.bn && t.sched == (r.sched == 2 ? 0 : r.sched))
+      return t.fixed + t.per_k * rounds * conv.p.K / 4608.0;
   return 0.0;
 }
 double patch_us(const Problem& conv, int rows) {
@@ -1085,7 +1088,8 @@ double patch_us(const Problem& conv, int rows) {
   if (g.KW == 3) return 1.5 + whole * (5.2 + (residual ? 1.4 : 0.0) + 1.07 * stages);
   const long long panels = tiles_m / 4;
   const bool crosses = tiles_m > 4 && (tiles_m % 4 != 0 || (panels < 8 ? 8 % panels != 0 : panels % 8 != 0));
-  const double die = (double)std::min<long long>(conv.p.M, crosses ? 512 : 256) * g.IC * 50.0 + (double)conv.Nb * g.IC * g.HW * 2.0 / 8.0;
+  const double weights = (double)std::min<long long>(conv.p.M, crosses ? 512 : 256) * g.IC * 50.0;
+  const double die = weights + (double)conv.Nb * g.IC * g.HW * 2.0 / 8.0;  // bytes that a die's workgroups read
   return 2.0 + whole * (4.0 + (residual ? 1.3 : 0.0) + (die > 4194304.0 ? 2.75 : 2.1) * stages);
 }
 // Whether they are the better choice, and on tiles of how many rows; 0: the gather is.
@@ -1111,7 +1115,8 @@ int patch_rows(const Problem& conv, const SplitK& sk) {
   if (!patch_form(conv, sk) || conv.p.M < 16) return 0;
   const long long plane = (long long)(g.H + g.ph) * (g.W + g.pw);
   if (5 * plane > (g.KW == 3 ? 7 : 9) * (long long)g.HW) return 0;
-  const long long across = (conv.Nb * plane + 127) >> 7, of_64 = ((conv.p.M + 63LL) >> 6) * across, of_128 = ((conv.p.M + 127LL) >> 7) * across;
+  const long long across = (conv.Nb * plane + 127) >> 7;
+  const long long of_64 = ((conv.p.M + 63LL) >> 6) * across, of_128 = ((conv.p.M + 127LL) >> 7) * across;
   if (of_64 < (g.KW == 3 ? 72 : g.IC <= 256 ? 104 : 150)) return 0;
   const int rows = g.KW == 3 && conv.p.M > 64 && of_64 > 256 && (of_128 <= 256 || (of_128 > 384 && of_128 <= 512)) ? 128 : 64;
   const double gather = gather_us(conv);
@@ -1184,7 +1189,9 @@ hidet_status_t launch_conv(const ConvCall& cc, int config, const SplitK& sk, hip
       (one.slices <= 1 || find_partial_launcher(remembered, t.config)))
     return launch(remembered, t.config, one, stream);
   const int form = untuned_form(cc, sk);
-  const int c = form == HIDET_CONV_GATHER ? default_config(cc.conv) : form == HIDET_CONV_IMAGES ? images_form(cc.conv, cc.pointwise, sk) : -1;
+  const int c = form == HIDET_CONV_GATHER   ? default_config(cc.conv)
+                : form == HIDET_CONV_IMAGES ? images_form(cc.conv, cc.pointwise, sk)
+                                            : -1;
   return launch_form(cc, form, c, sk, stream);
 }
 

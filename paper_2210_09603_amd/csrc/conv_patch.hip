@@ -6,9 +6,9 @@
 //
 //   columns   The output columns run through a plane with one zero column behind every row and one zero row behind every
 //             image (two of each for 5x5), n = (image * (H + 1) + row) * (W + 1) + column, so that filter tap (kh, kw) of
-//             every column is the pixel (kh - 1) * (W + 1) + (kw - 1) further on: a zero where the filter leaves the image, whichever side it leaves on
-//             (of the columns 1.15 times as many as outputs at 14x14, 1.07 at 28x28; the padding in the gather's columns is
-//             1.14).  Columns of zeros are computed and never stored.
+//             every column is the pixel (kh - 1) * (W + 1) + (kw - 1) further on: a zero where the filter leaves the image,
+//             whichever side it leaves on (of the columns 1.15 times as many as outputs at 14x14, 1.07 at 28x28; the padding in
+//             the gather's columns is 1.14).  Columns of zeros are computed and never stored.
 //   patch     [2 x 8 channels][256 pixels][8] in LDS, two of them: the 128 columns of the tile and W + 2 pixels on either side.
 //             A thread has two neighbouring pixels for the whole kernel, so their address and which of them are zeros are
 //             worked out once.  The channels of a pixel lie together, so a fragment is one 16-byte read whatever the tap.

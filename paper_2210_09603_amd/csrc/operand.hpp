@@ -449,7 +449,8 @@ struct Operand {
   }
 
   // The same for a tile that K ends in, chunks of which lie inside K or outside (LD_VEC, LD_IMAGES): lanes outside write zeros to
-  // the place that their chunk would take, lanes whose chunk leaves the tensor (LD_IMAGES) what is left of it.  `tile`: the tile as it is addressed by this lane, `tile_lds` as above.
+  // the place that their chunk would take, lanes whose chunk leaves the tensor (LD_IMAGES) what is left of it.  `tile`: the tile
+  // as it is addressed by this lane, `tile_lds` as above.
   __device__ __forceinline__ void load_direct_edge(unsigned char* tile, unsigned tile_lds, int tid, int wave, int k0) const {
     const T* base = (LAYOUT == L_KC) ? src + k0 : src + (long long)k0 * ld;
     if constexpr (MODE == LD_IMAGES) {  // (the branches below must not move it to vector registers)

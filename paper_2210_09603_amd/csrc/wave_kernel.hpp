@@ -7,8 +7,9 @@
 // for by count), and multiplies them without meeting another wavefront.  The partial tiles meet in LDS once, where each
 // group of four outputs is summed in wavefront order and stored.
 //
-// What bounds it is the rate at which a compute unit's first-level cache takes lines, about one a clock, whatever is used of
-// them.  A step is therefore 64 values of k on tiles up to 32x32, a whole line of every row of a K-contiguous operand, with
+// What bounds it is the chain itself: at 128x768x3072 a wavefront issues one instruction in 17 clocks of its 18 thousand (of the
+// kernel's 19), and the first-level cache of a compute unit takes 4800 accesses, a quarter of the clocks at one a clock.  That
+// part decides the width of a step: 64 values of k on tiles up to 32x32, a whole line of every row of a K-contiguous operand, with
 // eight wavefronts; with steps of 32 and sixteen wavefronts, which keep as many bytes in flight, 8x3072x768 on 16x32 tiles
 // takes 5.0 us instead of 4.3, 128x768x3072 9.1 instead of 8.5.  On the larger tiles, whose LDS has no room for two steps of
 // 64 and eight wavefronts, steps of 32 and eight wavefronts win over steps of 64 and four (1024^3 on 64x64: 9.3 and 10.7 us).
@@ -134,7 +135,7 @@ __device__ __forceinline__ void finish4(const GemmParams& p, TO* __restrict__ C,
   }
 }
 
-// ---- the last step of K on element-aligned rows, through registers ------------------------------------------------------------------------------
+// ---- the last step of K on element-aligned rows, through registers ----------------------------------------------------------
 // Requested without a branch and finished when it is stored, so that nothing waits for it in between (under the predicates of
 // the general schedule instead, 80x45x796 on 16x16 tiles takes 4.9 us, not 4.7): a chunk that sticks out of the operand's end
 // is read as the last 16 bytes of the operand and shifted down afterwards.  Along M/N what lies past the edge only reaches
