@@ -376,3 +376,37 @@ def test_softmax_sums_of_the_wavefronts_meet_in_a_tree(cols):
     hb.hidet_softmax_rows(x, y)
     torch.cuda.synchronize()
     assert float((y[:, 0].double() - torch.softmax(x.double(), 1)[:, 0]).abs().max()) <= (4 + 3 * 2) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("dtype,cols", [("f16", 1100), ("bf16", 2049), ("f16", 8200), ("bf16", 33000), ("f16", 50257), ("bf16", 70001),
+                                        ("f32", 600), ("f32", 4099), ("f32", 16500), ("f32", 40000)])
+def test_softmax_held_by_a_workgroup_of_values_of_any_size(dtype, cols):
+    """The maximum is found without widening a value and exponentials are taken relative to a scaled maximum: rows of one
+    sign, of huge values, with infinities, a NaN, and a maximum in the first, the last or a masked place."""
+    g = wl.rng(9600 + cols)
+    x = (g.standard_normal((12, cols)) * 3).astype(np.float32)
+    big = 6.0e4 if dtype == "f16" else 3.0e38
+    x[1] = -np.abs(x[1]) - 1  # negative throughout
+    x[2] -= 3.0e4  # (a row of large values among which only steps of the type differ)
+    x[3] = np.where(g.random(cols) < 0.5, -big, x[3])
+    x[4, :] = big
+    x[5, cols // 3] = big
+    x[6, -1], x[6, 0] = 40.0, 39.0
+    x[7, 0] = 70.0
+    x[8, : cols - 1] = -np.inf
+    x[9, cols // 2:] = -np.inf
+    x[10, cols - 2] = np.inf
+    x[11, 1] = np.nan
+    s = wl.to_storage(x, dtype)
+    ref = red.softmax_rows(np.where(np.isfinite(wl.widen(s, dtype)), wl.widen(s, dtype), -np.inf))
+    for shift in (0, 1):
+        buf = torch.zeros(12 * cols + 8, dtype=TORCH_DTYPE[dtype], device="cuda")
+        dx = buf[shift: shift + 12 * cols].view(12, cols)
+        dx.copy_(to_gpu(s, dtype))
+        dy = torch.full_like(dx, 3.0)
+        hb.hidet_softmax_rows(dx, dy)
+        torch.cuda.synchronize()
+        got = to_f64(dy)
+        assert np.isnan(got[10:]).all()
+        for i in range(10):
+            assert within_bound(oracle.rel_frobenius(got[i:i + 1], ref[i:i + 1]), ref[i:i + 1], dtype), (i, shift)
