@@ -34,8 +34,9 @@ namespace hidet {
 // the same steps: SCHED_SIMPLE issues the loads of the next tile at the top of an iteration,
 // SCHED_AHEAD one iteration earlier.
 // ---------------------------------------------------------------------------------------------
-template <class Cfg>
-__global__ void __launch_bounds__(Cfg::NT) gemm_kernel(const GemmParams p) {
+template <class Cfg, class Params>
+__global__ void __launch_bounds__(Cfg::NT) gemm_kernel(const Params params) {
+  const GemmParams& p = whole_params<Cfg::BM, Cfg::BN>(params);
   using T = typename Cfg::T;
   using Acc = typename AccT<Cfg::MI>::type;
   constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK, MI = Cfg::MI, NT = Cfg::NT;

@@ -46,6 +46,11 @@ bool direct_loads_fit(const GemmParams& p) {
          (Cfg::LA == L_KC || p.lda >= Cfg::VEC) && (Cfg::LB == L_KC || p.ldb >= Cfg::VEC);
 }
 
+// Tiles of products that can be as short as their launch (see PlainParams).
+template <class Cfg>
+constexpr bool kSmallPlain = Cfg::MAPPER == MAP_PLAIN && std::is_same<typename Cfg::T, typename Cfg::TO>::value &&
+                             !Cfg::GATHER_B && Cfg::MODE_B != LD_IMAGES && Cfg::BM * Cfg::BN <= 64 * 64;
+
 template <class Cfg>
 hipError_t launch_kernel(const GemmParams& p, hipStream_t stream) {
   const dim3 grid((unsigned)p.total_blocks);
@@ -70,13 +75,25 @@ hipError_t launch_kernel(const GemmParams& p, hipStream_t stream) {
   } else if constexpr (WAVES) {
     if constexpr (ELEM) {
       if (!direct_loads_fit<Cfg>(p)) {
-        hipLaunchKernelGGL(gemm_kernel<Cfg>, grid, dim3(Cfg::NT), 0, stream, p);
+        hipLaunchKernelGGL((gemm_kernel<Cfg, GemmParams>), grid, dim3(Cfg::NT), 0, stream, p);
         return hipGetLastError();
       }
     }
-    hipLaunchKernelGGL(gemm_kernel_waves<Cfg>, grid, dim3(WaveStream<Cfg>::NT), 0, stream, p);
+    if constexpr (kSmallPlain<Cfg>) {
+      if (PlainParams c; plain_params(p, c)) {
+        hipLaunchKernelGGL((gemm_kernel_waves<Cfg, PlainParams>), grid, dim3(WaveStream<Cfg>::NT), 0, stream, c);
+        return hipGetLastError();
+      }
+    }
+    hipLaunchKernelGGL((gemm_kernel_waves<Cfg, GemmParams>), grid, dim3(WaveStream<Cfg>::NT), 0, stream, p);
   } else {
-    hipLaunchKernelGGL(gemm_kernel<Cfg>, grid, dim3(Cfg::NT), 0, stream, p);
+    if constexpr (kSmallPlain<Cfg>) {
+      if (PlainParams c; plain_params(p, c)) {
+        hipLaunchKernelGGL((gemm_kernel<Cfg, PlainParams>), grid, dim3(Cfg::NT), 0, stream, c);
+        return hipGetLastError();
+      }
+    }
+    hipLaunchKernelGGL((gemm_kernel<Cfg, GemmParams>), grid, dim3(Cfg::NT), 0, stream, p);
   }
   return hipGetLastError();
 }

@@ -190,8 +190,9 @@ struct TailStep {
   }
 };
 
-template <class Cfg>
-__global__ void __launch_bounds__(WaveStream<Cfg>::NT) gemm_kernel_waves(const GemmParams p) {
+template <class Cfg, class Params>
+__global__ void __launch_bounds__(WaveStream<Cfg>::NT) gemm_kernel_waves(const Params params) {
+  const GemmParams& p = whole_params<Cfg::BM, Cfg::BN>(params);
   using S = WaveStream<Cfg>;
   using T = typename Cfg::T;
   using TO = typename Cfg::TO;
