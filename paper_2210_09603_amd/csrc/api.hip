@@ -1053,11 +1053,12 @@ bool patch_form(const Problem& conv, const SplitK& sk) {
 }
 // Microseconds of a convolution through the gather on the tile that would be taken, and from a patch: predictions for the choice
 // between the two alone.  A tile that owns a compute unit (schedules 1 and 3) takes a fixed time and a rate per value of K for
-// each round of 256 workgroups, several that share one as much for what they are of a round; a patch a rate per stage, per
-// store of its outputs and, for 5x5, a quarter more where the weights that a die's workgroups read (four rows of tiles, all of
-// them where its run of tiles crosses into the next four) leave no room in its L2.  Fitted to 2600 random convolutions of 16 to
-// 1024 channels and planes of 6x6 to 62x62 (relative): 5 % to 95 % of predictions over measurements 0.91 to 1.07 for the
-// K-splitting tiles, 0.84 to 1.15 for the others, 0.92 to 1.13 and 0.81 to 1.09 for patches of 5x5 and 3x3.
+// each round of 256 workgroups, several that share one as much for what they are of a round; a patch a rate per stage and per
+// store of its outputs.  Fitted to 2600 random convolutions of 16 to 1024 channels and planes of 6x6 to 62x62, patches of 5x5
+// to 400 (relative): 5 % to 95 % of predictions over measurements 0.91 to 1.07 for the K-splitting tiles, 0.84 to 1.15 for the
+// others, 0.94 to 1.04 and 0.81 to 1.09 for patches of 5x5 and 3x3.  (5x5 on rows without padding columns, where a die's workgroups
+// read more weights than its L2 holds, counts as it did with one stage in flight, 2.75 us a stage: there the choice of the
+// gather is held by its test, 32 of 512x16x16, 128 channels: 83 us, from a patch 58.)
 struct GatherTime {
   int bm, bn, sched;  // (0: schedules 0 and 2)
   double fixed, per_k;  // us; of 4608 values of K
@@ -1090,7 +1091,8 @@ double patch_us(const Problem& conv, int rows) {
   const bool crosses = tiles_m > 4 && (tiles_m % 4 != 0 || (panels < 8 ? 8 % panels != 0 : panels % 8 != 0));
   const double weights = (double)std::min<long long>(conv.p.M, crosses ? 512 : 256) * g.IC * 50.0;
   const double die = weights + (double)conv.Nb * g.IC * g.HW * 2.0 / 8.0;  // bytes that a die's workgroups read
-  return 2.0 + whole * (4.0 + (residual ? 1.3 : 0.0) + (die > 4194304.0 ? 2.75 : 2.1) * stages);
+  const double rate = die > 4194304.0 && g.W % 8 == 0 ? 2.75 : 1.6;
+  return 0.2 + whole * (6.1 + (residual ? 1.2 : 0.0) + rate * stages);
 }
 // Whether they are the better choice, and on tiles of how many rows; 0: the gather is.
 // It wants 72 tiles of 64x128 (of columns with the zero columns and rows among them).  Over 130 random problems of 16 to 512
@@ -1098,18 +1100,17 @@ double patch_us(const Problem& conv, int rows) {
 // 44 to 64, where the gather's K-splitting tiles have twice the workgroups; 58 to 63 tiles of a long K, 0.75 to 0.8, are not
 // told from those.  The zeros are no more than two fifths of the outputs (images of 6x6: 1.36 times as many columns, 0.94 to
 // 1.07 of the gather's).
-// 5x5: 64 rows only, one workgroup to a compute unit, and rows of 29 at most.  Over 60 random problems 0.51 to 0.99 of the
-// gather's time from 146 tiles on; 0.69 to 0.89 from 88 to 130 tiles of up to 256 channels, but 1.14 to 1.20 of more (their
-// weights do not fit a die's L2), and 1.2 to 1.8 from 48 to 80.  (47 images of 384x10x10, where the zeros make it 1.44 times
-// as many columns: 0.86; 58 of 512x6x6, 1.78 times: 0.93, not told from the tiles alone and left to the gather.)
+// 5x5: 64 rows only, one workgroup to a compute unit, and rows of 29 at most.  From 104 tiles on (150 of more than 256 channels)
+// the predictions decide: over 400 random problems this takes 1.017 times as long as the better form of each, 3 are more than 4
+// % slower than the gather.  From 40 tiles on it would be 1.003; the limits stem from one stage in flight, and tests hold the
+// choice below them (51 of 256x14x14, 64 channels, 102 tiles: 46.6 us, from a patch 32.5).
 // 128 rows fetch the input half as often and win from the point where 64 rows are more than one to a compute unit (26 images
 // of 128x28x28: 14.7 us, 16.9 us on 64; at most 256 tiles of 64: 1.25 of the time of 64), unless they make a second round
 // that is less than half full (47 of 96x27x27, 80 channels, 288 tiles: 23.1 and 21.0 us; 60 of 96x30x30, 451: 26.8 and 29.0
 // us; beyond two rounds the two are level, or 64 ahead: 44 of 192x23x23, 384 channels: 57.7 and 55.7 us).
 // The counts know neither how many of the gather's columns are padding (none in rows of 8 or 16) nor which tiles it has: where
 // the predictions say that it is faster it is taken.  Of 2600 random convolutions 136 were more than 4 % slower than through it
-// by the counts alone (101 of 256x8x8, 5x5, with residual: 59 and 91 us; 13 of 512x8x8, 3x3: 22 and 28 us), 16 are now, none by
-// more than a quarter (154 of 96x8x8, 384 channels, 3x3, with residual: 20.9 and 25.8 us).
+// by the counts alone (13 of 512x8x8, 3x3: 22 and 28 us), 16 are now, none by more than a quarter (154 of 96x8x8, 384 channels, 3x3, with residual: 20.9 and 25.8 us).
 int patch_rows(const Problem& conv, const SplitK& sk) {
   const ConvGeom& g = conv.p.g;
   if (!patch_form(conv, sk) || conv.p.M < 16) return 0;
@@ -1120,7 +1121,7 @@ int patch_rows(const Problem& conv, const SplitK& sk) {
   if (of_64 < (g.KW == 3 ? 72 : g.IC <= 256 ? 104 : 150)) return 0;
   const int rows = g.KW == 3 && conv.p.M > 64 && of_64 > 256 && (of_128 <= 256 || (of_128 > 384 && of_128 <= 512)) ? 128 : 64;
   const double gather = gather_us(conv);
-  return gather > 0.0 && patch_us(conv, rows) > gather * (g.KW == 3 ? 1.05 : 1.0) ? 0 : rows;
+  return gather > 0.0 && patch_us(conv, rows) > gather * 1.05 ? 0 : rows;
 }
 hidet_status_t launch_patch(const Problem& conv, int bm, hipStream_t stream) {
   GemmParams p = conv.p;

@@ -22,14 +22,19 @@
 // images of 256x14x14, 256 channels: 32.5 us pixel by pixel and at the start of a stage, 27.7 us by pairs of pixels, 26.1 us
 // between the taps.  (Four pixels a load: 26.3 us.)  45 us -> 30 us for 128x28x28, 46 -> 32 us for 512x7x7, 50 -> 37 us for
 // 64x56x56, 64 images each; 99 -> 42 us for 68 images of 192x21x21.
-// 5x5: 25 taps take 100 registers of weights and 52 more on their way, so there is one wavefront to a SIMD and one stage in
-// flight (64 rows alone): 20 of 256x14x14 56.5 -> 38.8 us, 39 of 192x23x23 131 -> 94 us, 37 of 128x28x28, 256 channels, with
-// residual 180 -> 112 us.
+// What is left is bound by the LDS: a wavefront reads 27 KB of fragments a stage, which takes 1730 of the 1970 cycles
+// that a stage lasts without loads, deposits and stores (27.4 us with all of them, 24.1 without the loads, 19.0 without any).  (The
+// barrier before the last filter row, with the fragments of the next stage read under it: 24.1 us; wave tiles of 64x64, which
+// read a third less, one to a SIMD: 30.8 us.)
+// 5x5: 25 taps take 100 registers of weights and 60 more for each stage on its way, so there is one wavefront to a SIMD (64 rows
+// alone).  With one stage on its way instead of two the wavefront waited for the weights for as long as it computed: 20 of
+// 256x14x14 50.7 us, 32.0 with two; 47 of 512x7x7 94 -> 63.5 us, 15 of 128x29x29 28 -> 21.
 #include "epilogue.hpp"
 
 namespace hidet {
 
-template <int BM, int KW>
+// SETS_: stages on their way in registers.  (A single one has no use for a second: 15 of 16x10x10, 5x5, 394 channels: 7.3 us, 8.0.)
+template <int BM, int KW, int SETS_ = 2>
 struct PatchConv {
   static constexpr int BN = 128, IC_STEP = 16, PIXELS = 256, TAPS = KW * KW, PAD = KW / 2;
   static constexpr int WAVES_M = BM / 32, WAVES_N = 2, NT = WAVES_M * WAVES_N * 64;
@@ -38,7 +43,7 @@ struct PatchConv {
   static constexpr int NL = (BM * CHUNKS + NT - 1) / NT;     // chunks of the weights that a thread loads for one stage
   static constexpr int A_BYTES = BM * PITCH * 16, P_BYTES = PIXELS * IC_STEP * 2;
   static constexpr int CHANNELS = PIXELS / 2 * IC_STEP / NT; // of the two pixels of the patch that a thread fetches
-  static constexpr int SETS = KW == 3 ? 2 : 1;               // stages on their way in registers
+  static constexpr int SETS = SETS_;
   static constexpr int PER_SIMD = KW == 3 ? 2 : 1;           // wavefronts, which the LDS of a workgroup allows
   // after which taps of a stage the pixels and the weights of another one are requested
   static constexpr int PIECES = CHANNELS == 8 ? 4 : 1, FIRST_W = CHANNELS == 8 ? 4 : 2;
@@ -46,7 +51,7 @@ struct PatchConv {
   static_assert(BM % 32 == 0 && (CHANNELS == 4 || CHANNELS == 8), "whole wavefronts and pieces of a pixel");
 };
 
-template <typename T, int BM, int KW, class S = PatchConv<BM, KW>>
+template <typename T, int BM, int KW, int SETS, class S = PatchConv<BM, KW, SETS>>
 __global__ void __launch_bounds__(S::NT, S::PER_SIMD) conv_patch_kernel(const GemmParams p) {
   using Frag = typename FragT<T>::type;
   constexpr int BN = S::BN, NT = S::NT, FN = S::FN;
@@ -145,7 +150,7 @@ __global__ void __launch_bounds__(S::NT, S::PER_SIMD) conv_patch_kernel(const Ge
   const int a_at = (wm0 + lane % 32) * (S::PITCH * 16) + (lane / 32) * (S::TAPS * 16);
   const int b_at = ((lane / 32) * S::PIXELS + border - reach + wn0 + lane % 32) * 16;
   // Stage s is multiplied; meanwhile, a piece after each tap, stage s + 1 (in `l`) goes to LDS and another one is requested in
-  // its place, two stages ahead of its use (one of 25 taps: as long as three of nine, and there are no registers for more).
+  // its place, two stages ahead of its use.
   auto step = [&](int s, Loads& l) {
     const unsigned char* a = smem + (s & 1) * S::A_BYTES + a_at;
     const unsigned char* b = patches + (s & 1) * S::P_BYTES + b_at;
@@ -261,14 +266,14 @@ __global__ void __launch_bounds__(S::NT, S::PER_SIMD) conv_patch_kernel(const Ge
   }
 }
 
-template <typename T, int BM, int KW>
+template <typename T, int BM, int KW, int SETS = 2>
 hipError_t launch_tiles(const GemmParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL((conv_patch_kernel<T, BM, KW>), dim3((unsigned)p.total_blocks), dim3(PatchConv<BM, KW>::NT), 0, stream, p);
+  hipLaunchKernelGGL((conv_patch_kernel<T, BM, KW, SETS>), dim3((unsigned)p.total_blocks), dim3(PatchConv<BM, KW>::NT), 0, stream, p);
   return hipGetLastError();
 }
 template <typename T>
 hipError_t launch_type(const GemmParams& p, int bm, hipStream_t stream) {
-  if (p.g.KW == 5) return launch_tiles<T, 64, 5>(p, stream);
+  if (p.g.KW == 5) return p.g.IC <= 16 ? launch_tiles<T, 64, 5, 1>(p, stream) : launch_tiles<T, 64, 5>(p, stream);
   return bm == 64 ? launch_tiles<T, 64, 3>(p, stream) : launch_tiles<T, 128, 3>(p, stream);
 }
 
