@@ -452,6 +452,50 @@ int few_tiles_gemm_config(const Problem& pr) {
   return halves >= 0 ? halves : of_shape(32, 32, 64, 0);  // (a transposed A is built for the latter only)
 }
 
+// fp32 GEMMs with fewer than 384 tiles of 64x64, which are bound by latency: the tile with the shortest predicted time, a fixed
+// time and a rate per value of K for the first 256 workgroups, and as much again in other shares for what there are beyond
+// (whole rounds of the K-splitting ones, which keep a compute unit to themselves).  Fitted to 500 random products of 1 to 3000
+// rows, columns and values of K, 5 % to 95 % of predictions over measurements 0.85 to 1.15.  Over 200 others this takes 1.006
+// times as long as the best configuration of each, the order below 1.11 times (854x27x203 9.1 -> 4.6 us, which took the 16x64
+// tile, 128x1136x1029 18.9 -> 12.5, which took half as many K-splitting ones; a transposed A of a long K, for which those are
+// built as well, 16x40x1000 12.6 -> 6.9).
+struct SmallF32Time {
+  int bm, bn, bk, mfma, sched;
+  struct {
+    float fixed, per_k, more, more_per_k;  // us; of 1000 values of K
+  } at[2];                                 // aligned rows, element-aligned ones
+};
+constexpr SmallF32Time kSmallF32Times[] = {{64, 64, 16, 32, 0, {{3.33f, 30.6f, 0.0f, 28.1f}, {3.67f, 30.9f, 1.86f, 21.6f}}},
+                                           {64, 64, 16, 16, 0, {{3.47f, 26.2f, 0.0f, 28.2f}, {3.79f, 28.4f, 1.86f, 20.6f}}},
+                                           {32, 32, 32, 16, 0, {{2.65f, 12.1f, 0.27f, 6.24f}, {2.93f, 13.2f, 0.55f, 6.42f}}},
+                                           {32, 32, 32, 16, 2, {{2.74f, 9.76f, 0.22f, 6.92f}, {3.05f, 12.2f, 0.58f, 6.87f}}},
+                                           {32, 32, 64, 16, 2, {{2.94f, 7.82f, 0.37f, 6.73f}, {3.27f, 10.1f, 0.89f, 6.25f}}},
+                                           {32, 32, 128, 16, 3, {{3.70f, 6.48f, 1.07f, 5.52f}, {4.00f, 7.77f, 2.34f, 7.64f}}},
+                                           {16, 16, 256, 16, 3, {{3.55f, 2.86f, 1.53f, 2.85f}, {3.89f, 3.31f, 1.94f, 3.31f}}},
+                                           {16, 32, 256, 16, 3, {{3.82f, 4.04f, 2.39f, 4.44f}, {4.18f, 4.93f, 2.87f, 5.07f}}}};
+int few_tiles_f32_config(const Problem& pr) {
+  const long long M = pr.p.M, N = pr.p.N;
+  if (sat_mul(((M + 63) / 64) * ((N + 63) / 64), pr.batch) >= 384) return -1;
+  int best = -1;
+  float best_us = 0.0f;
+  for (int c = 0; c < kNumConfigs; ++c) {
+    const ConfigRow& r = kConfigs[c];
+    if (!r.is_f32 || !find_launcher(pr, c)) continue;
+    for (const SmallF32Time& t : kSmallF32Times) {
+      if (t.bm != r.bm || t.bn != r.bn || t.bk != r.bk || t.mfma != r.mfma || t.sched != r.sched) continue;
+      const long long tiles = sat_mul(((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn), pr.batch);
+      const float more = r.sched == 3 ? (float)((tiles + 255) / 256 - 1) : std::max(0.0f, (float)tiles / 256.0f - 1.0f);
+      const auto& at = t.at[pr.elem_mode != 0];
+      const float k = (float)pr.p.K / 1000.0f, us = at.fixed + at.per_k * k + more * (at.more + at.more_per_k * k);
+      if (best < 0 || us < best_us) {
+        best = c;
+        best_us = us;
+      }
+    }
+  }
+  return best;
+}
+
 // Untuned choice: the largest tile that still gives (nearly) every compute unit a workgroup, else the largest
 // that gives a quarter of them one, else the tile with the most workgroups.  Outputs large enough to be bound by
 // throughput rather than by one workgroup's latency chain (at least 384 tiles of 64x64) ask for about two
@@ -460,7 +504,7 @@ int few_tiles_gemm_config(const Problem& pr) {
 // workgroup and needs just over half a round of workgroups.  Between tiles of one size the ring schedule, the
 // 16x16 matrix-core shape and (small tiles) the loads-ahead order are preferred (they measure faster wherever
 // both apply); the tiles that split K over wave groups take part only when K spans at least one of their K tiles
-// and the output is small (GEMMs in 16-bit types: few_tiles_gemm_config alone takes them).  With slices > 1 only tiles
+// and the output is small (GEMMs: few_tiles_gemm_config and few_tiles_f32_config alone take them).  With slices > 1 only tiles
 // that have a K-parallel form take part.
 int default_config(const Problem& pr, int slices = 1) {
   const long long M = pr.p.M, N = pr.p.N;
@@ -470,8 +514,8 @@ int default_config(const Problem& pr, int slices = 1) {
     if (c >= 0) return c;
   }
   const bool gemm16 = pr.op == 0 && pr.dtype != HIDET_F32 && slices <= 1;
-  if (gemm16) {
-    const int c = few_tiles_gemm_config(pr);
+  if (pr.op == 0 && slices <= 1) {
+    const int c = gemm16 ? few_tiles_gemm_config(pr) : few_tiles_f32_config(pr);
     if (c >= 0) return c;
   }
   // The gather of a convolution is paid per column of the tile, and fewer than 64 output channels fill one tile row
