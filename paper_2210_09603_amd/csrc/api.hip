@@ -622,6 +622,13 @@ int default_config(const Problem& pr, int slices = 1) {
     // a K of at most two stages runs the two-slot ring: two workgroups of a 256x128 tile share a compute unit and
     // outrun one of a 256x256 tile
     if (ring && pr.p.K <= 2 * r.bk && area == 256 * 128) key += weight * (3LL << 22);
+    // of the two rectangular ring tiles the one of 128 rows, if it needs no round more, where B is row-major: each stage reads half
+    // as many pieces of 64 bytes of A's rows for it, and longer ones of B's (140 random products of 1200 to 4000: 0.93 of the
+    // time of 256x128 on aligned rows, 0.89 with an odd K, 0.85 with odd extents, 1.02 where both operands are read along K)
+    if (ring && gemm16 && pr.batch == 1 && !pr.transB && pr.p.K > 2 * r.bk && r.bm == 128 && r.bn == 256) {
+      const long long upright = ((M + 255) >> 8) * ((N + 127) >> 7);
+      if ((tiles + 255) >> 8 <= (upright + 255) >> 8) key += weight * (1LL << 21);
+    }
     // (the gather is paid once per row of tiles, so a flat tile is the last resort of a convolution of more rows: 7 images
     // of 192x28x28, 72 channels, 3x3: 26.5 us on three rows of 32x64 tiles, 20 us on two of 64x32)
     const bool flat = conv16 && M > 64 && r.bm < 64 && r.bn >= 64;
