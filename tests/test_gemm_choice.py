@@ -64,7 +64,7 @@ def test_rectangular_ring_tiles_lie_along_a_row_major_b():
     """128 rows of A are half as many short pieces as 256; not where B is read along K as well."""
     for problem in ((2639, 2104, 3735), (1488, 3408, 3240), (2992, 1896, 3816)):
         assert chosen(*problem)[:2] == (128, 256) and chosen(*problem, tB=True)[:2] == (256, 128), problem
-    assert chosen(2048, 3072, 64)[:2] == (256, 128)  # two stages of K: two workgroups of it to a compute unit
+    assert chosen(8192, 8192, 64)[:2] == (256, 128)  # two stages of K: two workgroups of it to a compute unit
 
 
 def test_fp32_is_not_concerned():
