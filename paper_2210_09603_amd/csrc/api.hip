@@ -455,24 +455,24 @@ int few_tiles_gemm_config(const Problem& pr) {
 // fp32 GEMMs with fewer than 384 tiles of 64x64, which are bound by latency: the tile with the shortest predicted time, a fixed
 // time and a rate per value of K for the first 256 workgroups, and as much again in other shares for what there are beyond
 // (whole rounds of the K-splitting ones, which keep a compute unit to themselves).  Fitted to 500 random products of 1 to 3000
-// rows, columns and values of K, 5 % to 95 % of predictions over measurements 0.85 to 1.15.  Over 200 others this takes 1.006
-// times as long as the best configuration of each, the order below 1.11 times (854x27x203 9.1 -> 4.6 us, which took the 16x64
-// tile, 128x1136x1029 18.9 -> 12.5, which took half as many K-splitting ones; a transposed A of a long K, for which those are
-// built as well, 16x40x1000 12.6 -> 6.9).
+// rows, columns and values of K, 5 % to 95 % of predictions over measurements 0.84 to 1.15.  Over 200 others this takes 1.008
+// times as long as the best configuration of each; an order by tile size, as below, takes 1.11 times (854x27x203 9.1 -> 3.9 us, which
+// took the 16x64 tile, 128x1136x1029 18.9 -> 10.7, which took half as many K-splitting ones; a transposed A of a long K, for
+// which those are built as well, 16x40x1000 12.6 -> 4.9).
 struct SmallF32Time {
   int bm, bn, bk, mfma, sched;
   struct {
     float fixed, per_k, more, more_per_k;  // us; of 1000 values of K
   } at[2];                                 // aligned rows, element-aligned ones
 };
-constexpr SmallF32Time kSmallF32Times[] = {{64, 64, 16, 32, 0, {{3.33f, 30.6f, 0.0f, 28.1f}, {3.67f, 30.9f, 1.86f, 21.6f}}},
-                                           {64, 64, 16, 16, 0, {{3.47f, 26.2f, 0.0f, 28.2f}, {3.79f, 28.4f, 1.86f, 20.6f}}},
-                                           {32, 32, 32, 16, 0, {{2.65f, 12.1f, 0.27f, 6.24f}, {2.93f, 13.2f, 0.55f, 6.42f}}},
-                                           {32, 32, 32, 16, 2, {{2.74f, 9.76f, 0.22f, 6.92f}, {3.05f, 12.2f, 0.58f, 6.87f}}},
-                                           {32, 32, 64, 16, 2, {{2.94f, 7.82f, 0.37f, 6.73f}, {3.27f, 10.1f, 0.89f, 6.25f}}},
-                                           {32, 32, 128, 16, 3, {{3.70f, 6.48f, 1.07f, 5.52f}, {4.00f, 7.77f, 2.34f, 7.64f}}},
-                                           {16, 16, 256, 16, 3, {{3.55f, 2.86f, 1.53f, 2.85f}, {3.89f, 3.31f, 1.94f, 3.31f}}},
-                                           {16, 32, 256, 16, 3, {{3.82f, 4.04f, 2.39f, 4.44f}, {4.18f, 4.93f, 2.87f, 5.07f}}}};
+constexpr SmallF32Time kSmallF32Times[] = {{64, 64, 16, 32, 0, {{3.33f, 30.7f, 0.0f, 27.8f}, {3.73f, 30.9f, 1.79f, 21.5f}}},
+                                           {64, 64, 16, 16, 0, {{3.47f, 26.3f, 0.0f, 28.1f}, {3.80f, 28.4f, 1.80f, 20.7f}}},
+                                           {32, 32, 32, 16, 0, {{2.65f, 12.1f, 0.25f, 6.22f}, {2.80f, 13.6f, 0.53f, 6.33f}}},
+                                           {32, 32, 32, 16, 2, {{2.74f, 9.73f, 0.20f, 6.96f}, {2.95f, 12.5f, 0.56f, 6.77f}}},
+                                           {32, 32, 64, 16, 2, {{2.93f, 7.83f, 0.33f, 6.96f}, {3.29f, 10.1f, 0.86f, 6.24f}}},
+                                           {32, 32, 128, 16, 3, {{3.31f, 6.35f, 1.64f, 6.06f}, {3.31f, 6.37f, 1.83f, 6.73f}}},
+                                           {16, 16, 256, 16, 3, {{3.25f, 1.88f, 1.32f, 1.87f}, {3.23f, 1.64f, 1.35f, 2.39f}}},
+                                           {16, 32, 256, 16, 3, {{3.19f, 3.65f, 1.25f, 3.77f}, {3.20f, 3.46f, 1.40f, 4.02f}}}};
 int few_tiles_f32_config(const Problem& pr) {
   const long long M = pr.p.M, N = pr.p.N;
   if (sat_mul(((M + 63) / 64) * ((N + 63) / 64), pr.batch) >= 384) return -1;

@@ -52,12 +52,21 @@ constexpr bool kSmallPlain = Cfg::MAPPER == MAP_PLAIN && std::is_same<typename C
                              !Cfg::GATHER_B && Cfg::MODE_B != LD_IMAGES && Cfg::BM * Cfg::BN <= 64 * 64;
 
 template <class Cfg>
+constexpr bool kWavesF32 = Cfg::IS_F32 && Cfg::SCHED == SCHED_KSPLIT && Cfg::MAPPER == MAP_PLAIN && !Cfg::GATHER_B;
+
+template <class Cfg>
 hipError_t launch_kernel(const GemmParams& p, hipStream_t stream) {
   const dim3 grid((unsigned)p.total_blocks);
   constexpr bool ELEM = Cfg::MODE_A == LD_ELEM, RING = Cfg::SCHED == SCHED_PINGPONG, WAVES = WaveStream<Cfg>::BUILT;
   static_assert(!(RING || WAVES) || direct_offsets_fit(Cfg::BM > Cfg::BN ? Cfg::BM : Cfg::BN, kMaxVecLd), "rows of a tile");
   static_assert(!(RING || WAVES) || direct_offsets_fit(Cfg::BK, kMaxVecLd), "rows of a tile");
-  if constexpr (RING) {
+  if constexpr (kWavesF32<Cfg>) {  // (at any alignment)
+    constexpr int BM = Cfg::BM, BN = Cfg::BN;
+    if (PlainParams c; plain_params(p, c))
+      hipLaunchKernelGGL((gemm_kernel_waves_f32<BM, BN, Cfg::LA, Cfg::LB, PlainParams>), grid, dim3(WaveStreamF32<BM, BN>::NT), 0, stream, c);
+    else
+      hipLaunchKernelGGL((gemm_kernel_waves_f32<BM, BN, Cfg::LA, Cfg::LB, GemmParams>), grid, dim3(WaveStreamF32<BM, BN>::NT), 0, stream, p);
+  } else if constexpr (RING) {
     // the element-mode variant of a ring tile also serves what the direct loads cannot do (input prologue, head-split
     // output map, rows too far apart or too short), with its stages staged through registers
     if constexpr (ELEM) {

@@ -39,8 +39,7 @@ struct WaveStream {
   static constexpr int FIT = 144 * 1024 / (NW * STEP_BYTES);
   static constexpr int D = FIT > 4 ? 4 : FIT;  // steps of a wavefront's ring
   static constexpr int RING_BYTES = D * STEP_BYTES;
-  static constexpr int ROW_BYTES = BN * 4 + 16;  // of a partial tile: rows start 4 banks apart
-  static constexpr int PART_BYTES = BM * ROW_BYTES;
+  static constexpr int PART_BYTES = BM * (BN * 4 + 16);  // (PartialTiles)
   static constexpr int LDS_BYTES = NW * (RING_BYTES > PART_BYTES ? RING_BYTES : PART_BYTES);
   static_assert(!BUILT || (D >= 2 && LDS_BYTES <= 160 * 1024), "a ring of two steps at least, in the LDS of a compute unit");
 };
@@ -134,6 +133,77 @@ __device__ __forceinline__ void finish4(const GemmParams& p, TO* __restrict__ C,
     }
   }
 }
+
+// ---- the end of a kernel whose wavefronts hold a partial tile each: they meet in LDS, where each group of four outputs is summed
+// in wavefront order and stored --------------------------------------------------------------------------------------------
+template <typename TO, int BM, int BN, int NW>
+struct PartialTiles {
+  static constexpr int NT = NW * 64, FM = BM / 16, FN = BN / 16;
+  static constexpr int ROW_BYTES = BN * 4 + 16;  // rows start 4 banks apart
+  static constexpr int PART_BYTES = BM * ROW_BYTES;
+  // a thread finishes groups of four columns: `tid`, `tid` + NT, ... in row-major order over the tile
+  static constexpr int GROUPS = BM * BN / 4, PER_ROW = BN / 4, PASSES = (GROUPS + NT - 1) / NT;
+  static_assert(NT % PER_ROW == 0, "a thread keeps its columns");
+  int c4, col, valid;
+  long long ccol;
+  TO* C;
+  const TO* R;
+  float bias[PASSES][4], res[PASSES][4];
+  long long row_at[PASSES];  // offset of the group's row in C; negative: no row of C
+
+  // what the end needs from memory, requested ahead of it
+  __device__ __forceinline__ void request(const GemmParams& p, const BlockCoords& bc) {
+    c4 = (int)threadIdx.x % PER_ROW;
+    col = bc.n0 + c4 * 4;
+    C = reinterpret_cast<TO*>(p.C) + (long long)bc.cbatch * p.strideC;
+    R = p.residual ? reinterpret_cast<const TO*>(p.residual) + (long long)bc.batch * p.strideR : nullptr;
+    const TO* bias_ptr = reinterpret_cast<const TO*>(p.bias);
+    ccol = col_offset<MAP_PLAIN>(p, col);
+    valid = group_valid<MAP_PLAIN>(p, col);
+#pragma unroll
+    for (int s = 0; s < PASSES; ++s) {
+      const int g = s * NT + (int)threadIdx.x, m = bc.m0 + g / PER_ROW;
+      row_at[s] = g < GROUPS && m < p.M ? row_offset<MAP_PLAIN>(p, m, p.ldc) : -1;
+      asm volatile("" : "+v"(row_at[s]));  // (now, while the first step is on its way, not at the end)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bias[s][e] = res[s][e] = 0.0f;
+      if (g < GROUPS && m < p.M) {
+        if (p.bias_axis != 0) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (p.bias_axis == 2 || e < valid) bias[s][e] = to_f32(bias_ptr[p.bias_axis == 2 ? m : col + e]);
+        }
+        load_residual4<TO>(p, R, p.out_map != 0 ? row_at[s] : (long long)m * p.ldr, col, ccol, valid, res[s]);
+      }
+    }
+  }
+
+  // (of zeros from a wavefront that had no step)
+  __device__ __forceinline__ void finish(const GemmParams& p, const f32x4 (&acc)[FM][FN], unsigned char* smem, int wave, int lane) {
+    unsigned char* part = smem + wave * PART_BYTES;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        *reinterpret_cast<f32x4*>(part + (i * 16 + lane % 16) * ROW_BYTES + (j * 16 + 4 * (lane / 16)) * 4) = acc[i][j];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < PASSES; ++s) {
+      if (row_at[s] >= 0) {
+        const int row = (s * NT + (int)threadIdx.x) / PER_ROW;
+        const unsigned char* src = smem + row * ROW_BYTES + c4 * 16;
+        f32x4 v[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v[w] = *reinterpret_cast<const f32x4*>(src + w * PART_BYTES);
+        f32x4 sum = v[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += v[w];
+        const float out[4] = {sum[0], sum[1], sum[2], sum[3]};
+        finish4<TO>(p, C, bias[s], res[s], R != nullptr, row_at[s], col, ccol, valid, out);
+      }
+    }
+  }
+};
 
 // ---- the last step of K on element-aligned rows, through registers ----------------------------------------------------------
 // Requested without a branch and finished when it is stored, so that nothing waits for it in between (under the predicates of
@@ -244,34 +314,8 @@ __global__ void __launch_bounds__(WaveStream<Cfg>::NT) gemm_kernel_waves(const P
     ta.request(opa, lane, whole * STEP);
     tb.request(opb, lane, whole * STEP);
   }
-  // a thread finishes groups of four columns: `tid`, `tid` + NT, ... in row-major order over the tile
-  constexpr int GROUPS = BM * BN / 4, PER_ROW = BN / 4, PASSES = (GROUPS + S::NT - 1) / S::NT;
-  static_assert(S::NT % PER_ROW == 0, "a thread keeps its columns");
-  const int c4 = (int)threadIdx.x % PER_ROW;
-  const int col = bc.n0 + c4 * 4;
-  TO* C = reinterpret_cast<TO*>(p.C) + (long long)bc.cbatch * p.strideC;
-  const TO* R = p.residual ? reinterpret_cast<const TO*>(p.residual) + (long long)bc.batch * p.strideR : nullptr;
-  const TO* bias_ptr = reinterpret_cast<const TO*>(p.bias);
-  const long long ccol = col_offset<MAP_PLAIN>(p, col);
-  const int valid = group_valid<MAP_PLAIN>(p, col);
-  float bias[PASSES][4], res[PASSES][4];
-  long long row_at[PASSES];  // offset of the group's row in C; negative: no row of C
-#pragma unroll
-  for (int s = 0; s < PASSES; ++s) {
-    const int g = s * S::NT + (int)threadIdx.x, m = bc.m0 + g / PER_ROW;
-    row_at[s] = g < GROUPS && m < p.M ? row_offset<MAP_PLAIN>(p, m, p.ldc) : -1;
-    asm volatile("" : "+v"(row_at[s]));  // (now, while the first step is on its way, not at the end)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bias[s][e] = res[s][e] = 0.0f;
-    if (g < GROUPS && m < p.M) {
-      if (p.bias_axis != 0) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (p.bias_axis == 2 || e < valid) bias[s][e] = to_f32(bias_ptr[p.bias_axis == 2 ? m : col + e]);
-      }
-      load_residual4<TO>(p, R, p.out_map != 0 ? row_at[s] : (long long)m * p.ldr, col, ccol, valid, res[s]);
-    }
-  }
+  PartialTiles<TO, BM, BN, NW> end;
+  end.request(p, bc);
 
   f32x4 acc[FM][FN];
 #pragma unroll
@@ -336,30 +380,154 @@ __global__ void __launch_bounds__(WaveStream<Cfg>::NT) gemm_kernel_waves(const P
     mfmas();
   }
 
-  // ---- the partial tiles meet
   __syncthreads();  // (the rings are read no more, and nothing is in flight towards them)
-  unsigned char* part = smem + wave * S::PART_BYTES;  // (of zeros from a wavefront that had no step)
+  end.finish(p, acc, smem, wave, lane);
+}
+
+// ---- fp32 -------------------------------------------------------------------------------------------------------------------
+// An fp32 matrix instruction takes one value of each operand a lane, so fragments come straight from memory into registers,
+// whatever the alignment: of four values of k in a row for each lane, 16 bytes of an operand that lies along K and four times 64
+// bytes to sixteen lanes of one that does not.  Sixteen wavefronts own the steps of 16 values of k in turn and meet once, at
+// the end, as above.  The order of k within a step is the same for both operands and nothing else depends on it.
+// Bound by the chain of one workgroup, as above, without the round trip through LDS and the barriers for each 256 values of k
+// that the shared K tiles had: microseconds queued, 256^3 4.0 -> 3.45, 64x384x400 4.7 -> 3.5, 119x323x1408 9.9 -> 6.0, 181x24x928
+// 6.5 -> 4.9 on 16x16 tiles, 128x1136x1029 12.1 -> 10.6 on 32x32 ones.  Two steps of a wavefront are on their way; with four 256^3
+// takes 3.6, with eight 3.9 (code for steps that a short K does not have), and a long K gains nothing.
+template <int BM, int BN>
+struct WaveStreamF32 {
+  static constexpr int NW = 16, NT = NW * 64, STEP = 16;
+  static constexpr int D = 2;
+  static constexpr int LDS_BYTES = NW * BM * (BN * 4 + 16);
+  static_assert(LDS_BYTES <= 160 * 1024, "LDS capacity of a gfx950 compute unit");
+};
+
+template <int BM, int BN, int LA, int LB, class Params, class S = WaveStreamF32<BM, BN>>
+__global__ void __launch_bounds__(S::NT) gemm_kernel_waves_f32(const Params params) {
+  const GemmParams& p = whole_params<BM, BN>(params);
+  constexpr int NW = S::NW, STEP = S::STEP, D = S::D, FM = BM / 16, FN = BN / 16;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[S::LDS_BYTES];
+  const int lane = threadIdx.x % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const BlockCoords bc = block_coords<BM, BN>(p);
+
+  struct __attribute__((packed, aligned(4))) Four {
+    f32x4 v;
+  };
+  // this lane's first values: row (column) lane % 16 of each fragment, four values of k from 4 (lane / 16) on; rows past the
+  // edge are the last one again, and feed outputs that are never stored
+  const float* a0 = reinterpret_cast<const float*>(p.A) + (long long)bc.batch * p.strideA;
+  const float* b0 = reinterpret_cast<const float*>(p.B) + (long long)bc.batch * p.strideB;
+  const int kl = bc.k_begin + 4 * (lane / 16);
+  const float *pa[FM], *pb[FN];
 #pragma unroll
-  for (int i = 0; i < FM; ++i)
+  for (int i = 0; i < FM; ++i) {
+    const int m = bc.m0 + i * 16 + lane % 16, row = m < p.M ? m : p.M - 1;
+    pa[i] = LA == L_KC ? a0 + (long long)row * p.lda + kl : a0 + (long long)kl * p.lda + row;
+  }
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
-      *reinterpret_cast<f32x4*>(part + (i * 16 + lane % 16) * S::ROW_BYTES + (j * 16 + 4 * (lane / 16)) * 4) = acc[i][j];
-  __syncthreads();
+  for (int j = 0; j < FN; ++j) {
+    const int n = bc.n0 + j * 16 + lane % 16, row = n < p.N ? n : p.N - 1;
+    pb[j] = LB == L_KC ? b0 + (long long)row * p.ldb + kl : b0 + (long long)kl * p.ldb + row;
+  }
+  struct Step {
+    f32x4 a[FM], b[FN];
+  };
+  auto request = [&](Step& r, int i) {  // this wavefront's step i, which lies inside K
+    const long long k = (long long)(wave + i * NW) * STEP;
 #pragma unroll
-  for (int s = 0; s < PASSES; ++s) {
-    if (row_at[s] >= 0) {
-      const int row = (s * S::NT + (int)threadIdx.x) / PER_ROW;
-      const unsigned char* src = smem + row * S::ROW_BYTES + c4 * 16;
-      f32x4 v[NW];
+    for (int m = 0; m < FM; ++m) {
+      if constexpr (LA == L_KC) {
+        r.a[m] = reinterpret_cast<const Four*>(pa[m] + k)->v;
+      } else {
 #pragma unroll
-      for (int w = 0; w < NW; ++w) v[w] = *reinterpret_cast<const f32x4*>(src + w * S::PART_BYTES);
-      f32x4 sum = v[0];
+        for (int e = 0; e < 4; ++e) r.a[m][e] = pa[m][(k + e) * p.lda];
+      }
+    }
 #pragma unroll
-      for (int w = 1; w < NW; ++w) sum += v[w];
-      const float out[4] = {sum[0], sum[1], sum[2], sum[3]};
-      finish4<TO>(p, C, bias[s], res[s], R != nullptr, row_at[s], col, ccol, valid, out);
+    for (int n = 0; n < FN; ++n) {
+      if constexpr (LB == L_KC) {
+        r.b[n] = reinterpret_cast<const Four*>(pb[n] + k)->v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r.b[n][e] = pb[n][(k + e) * p.ldb];
+      }
+    }
+  };
+  f32x4 acc[FM][FN];
+#pragma unroll
+  for (int m = 0; m < FM; ++m)
+#pragma unroll
+    for (int n = 0; n < FN; ++n) acc[m][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  auto multiply = [&](Step& r) {
+    if (p.relu_a) {
+#pragma unroll
+      for (int m = 0; m < FM; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r.a[m][e] = r.a[m][e] < 0.0f ? 0.0f : r.a[m][e];
+    }
+    if (p.relu_b) {
+#pragma unroll
+      for (int n = 0; n < FN; ++n)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r.b[n][e] = r.b[n][e] < 0.0f ? 0.0f : r.b[n][e];
+    }
+    // (operands swapped: the accumulator holds C transposed, four columns of a row per lane)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int m = 0; m < FM; ++m)
+#pragma unroll
+        for (int n = 0; n < FN; ++n) acc[m][n] = mfma_op(r.b[n][e], r.a[m][e], acc[m][n]);
+  };
+
+  const int whole = bc.k_len > 0 ? bc.k_len / STEP : 0;
+  const int mine = whole > wave ? (whole - wave + NW - 1) / NW : 0;
+  const bool tail = whole * STEP < bc.k_len && wave == whole % NW;  // this wavefront multiplies what is left of K
+  Step step[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (d < mine) request(step[d], d);
+  Step last;
+  if (tail) {
+    const int left = bc.k_len - whole * STEP - 4 * (lane / 16);  // values of k that this lane has
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool in = e < left;
+      const long long k = in ? (long long)whole * STEP + e : 0;
+      const long long back = in ? 0 : 4 * (lane / 16);  // (the first value of K, which there is)
+#pragma unroll
+      for (int m = 0; m < FM; ++m) {
+        const float x = LA == L_KC ? pa[m][k - back] : pa[m][(k - back) * p.lda];
+        last.a[m][e] = in ? x : 0.0f;
+      }
+#pragma unroll
+      for (int n = 0; n < FN; ++n) {
+        const float x = LB == L_KC ? pb[n][k - back] : pb[n][(k - back) * p.ldb];
+        last.b[n][e] = in ? x : 0.0f;
+      }
     }
   }
+  PartialTiles<float, BM, BN, NW> end;
+  end.request(p, bc);
+
+  int i = 0;
+  for (; i + 2 * D <= mine; i += D) {  // (without a branch: loads are counted)
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      multiply(step[d]);
+      request(step[d], i + D + d);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    if (i + d < mine) multiply(step[d]);
+    if (i + D + d < mine) request(step[d], i + D + d);
+  }
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (i + D + d < mine) multiply(step[d]);
+  if (tail) multiply(last);
+  end.finish(p, acc, smem, wave, lane);
 }
 
 }  // namespace hidet
