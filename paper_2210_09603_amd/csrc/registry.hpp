@@ -54,6 +54,10 @@ constexpr bool kSmallPlain = Cfg::MAPPER == MAP_PLAIN && std::is_same<typename C
 template <class Cfg>
 constexpr bool kWavesF32 = Cfg::IS_F32 && Cfg::SCHED == SCHED_KSPLIT && Cfg::MAPPER == MAP_PLAIN && !Cfg::GATHER_B;
 
+// (see gemm_kernel_waves_direct for where it is taken)
+template <class Cfg>
+constexpr bool kWavesDirect = Cfg::BM == 16 && Cfg::BN <= 32 && Cfg::LA == L_KC && Cfg::LB == L_MC;
+
 template <class Cfg>
 hipError_t launch_kernel(const GemmParams& p, hipStream_t stream) {
   const dim3 grid((unsigned)p.total_blocks);
@@ -83,6 +87,21 @@ hipError_t launch_kernel(const GemmParams& p, hipStream_t stream) {
       hipLaunchKernelGGL((gemm_kernel_pingpong<Cfg, 4>), grid, dim3(Cfg::NT), 0, stream, p);
   } else if constexpr (WAVES) {
     if constexpr (ELEM) {
+      if constexpr (kWavesDirect<Cfg>) {
+        using T = typename Cfg::T;
+        using TO = typename Cfg::TO;
+        using S = WaveDirect<Cfg::BM, Cfg::BN>;
+        const bool fit = direct_loads_fit<Cfg>(p);
+        const bool even = (((unsigned long long)p.A / 2 | (unsigned long long)p.lda | (unsigned long long)p.strideA) & 1) == 0;
+        const bool few_k = (p.k_slices > 1 ? p.k_slice_len : p.K) <= S::MAX_K;
+        if (p.N >= 2 && (even ? !fit || few_k : !fit && few_k)) {
+          if (PlainParams c; plain_params(p, c))
+            hipLaunchKernelGGL((gemm_kernel_waves_direct<T, TO, Cfg::BM, Cfg::BN, PlainParams>), grid, dim3(S::NT), 0, stream, c);
+          else
+            hipLaunchKernelGGL((gemm_kernel_waves_direct<T, TO, Cfg::BM, Cfg::BN, GemmParams>), grid, dim3(S::NT), 0, stream, p);
+          return hipGetLastError();
+        }
+      }
       if (!direct_loads_fit<Cfg>(p)) {
         hipLaunchKernelGGL((gemm_kernel<Cfg, GemmParams>), grid, dim3(Cfg::NT), 0, stream, p);
         return hipGetLastError();

@@ -178,14 +178,24 @@ struct PartialTiles {
     }
   }
 
-  // (of zeros from a wavefront that had no step)
+  // (of zeros from a wavefront that had no step).  PAIRS: fragments 2 j and 2 j + 1 hold the even and the odd ones of 32 columns.
+  template <bool PAIRS = false>
   __device__ __forceinline__ void finish(const GemmParams& p, const f32x4 (&acc)[FM][FN], unsigned char* smem, int wave, int lane) {
     unsigned char* part = smem + wave * PART_BYTES;
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+    for (int i = 0; i < FM; ++i) {
+      unsigned char* row = part + (i * 16 + lane % 16) * ROW_BYTES;
 #pragma unroll
-      for (int j = 0; j < FN; ++j)
-        *reinterpret_cast<f32x4*>(part + (i * 16 + lane % 16) * ROW_BYTES + (j * 16 + 4 * (lane / 16)) * 4) = acc[i][j];
+      for (int j = 0; j < FN; ++j) {
+        if constexpr (PAIRS) {
+          const f32x4 even = acc[i][j & ~1], odd = acc[i][j | 1];
+          const int r = 2 * (j & 1);
+          *reinterpret_cast<f32x4*>(row + ((j & ~1) * 16 + 8 * (lane / 16) + 4 * (j & 1)) * 4) = f32x4{even[r], odd[r], even[r + 1], odd[r + 1]};
+        } else {
+          *reinterpret_cast<f32x4*>(row + (j * 16 + 4 * (lane / 16)) * 4) = acc[i][j];
+        }
+      }
+    }
     __syncthreads();
 #pragma unroll
     for (int s = 0; s < PASSES; ++s) {
@@ -528,6 +538,157 @@ __global__ void __launch_bounds__(S::NT) gemm_kernel_waves_f32(const Params para
     if (i + D + d < mine) multiply(step[d]);
   if (tail) multiply(last);
   end.finish(p, acc, smem, wave, lane);
+}
+
+// ---- 16-bit types on element-aligned rows: A along K, B along N, tiles of 16 rows ---------------------------------------------
+// Fragments come straight from memory here too: eight values of k of a row of A to a lane, and of B, whose rows follow k, eight
+// values of a column (BN = 16) or of two neighbours (BN = 32, whose fragments hold the even and the odd columns).  There is no
+// last step under predicates but what K leaves of a step, and no rows too short for it.  Sixteen wavefronts, two steps of 32
+// on their way.
+// Bound by the chain of one wavefront: memory latency per step, and the transactions of B's columns.  Where the rows of A lie
+// a multiple of 4 bytes apart, 16x16 tiles take 0.92 of the time that direct loads into LDS take (67 random products of K up to
+// 3072: 0.74 to 1.04; 80x45x796 4.16 -> 3.60 us; longer ones 1.02 to 1.10), 16x32 ones 0.90 up to K = 1024 (9 products; 7 longer
+// ones 0.9 to 1.24).  Where the direct loads do not fit, as with N < 8, the general schedule is what is left: 0.42 to 0.79 of its
+// time up to K = 3072 (23 products; 14x7x1264 7.8 -> 3.6 us) on any rows, 0.33 to 0.49 beyond on even ones (5x5x3768 15.5 -> 5.1),
+// but 1.04 to 1.25 beyond on odd ones, where a load of 16 bytes into registers is broken up.  Left to the loads into LDS: odd rows
+// of A (0.88 to 1.58), operands that both lie along K (the same), and whole chunks, whose lines they share better (2 to 8 %).
+template <int BM, int BN>
+struct WaveDirect {
+  static constexpr int NW = 16, NT = NW * 64, STEP = 32, D = 2;
+  static constexpr int LDS_BYTES = NW * BM * (BN * 4 + 16);
+  static constexpr int MAX_K = BN == 16 ? 3072 : 1024;
+  static_assert(BM == 16 && (BN == 16 || BN == 32), "measured on these");
+};
+
+template <typename T, typename TO, int BM, int BN, class Params, class S = WaveDirect<BM, BN>>
+__global__ void __launch_bounds__(S::NT) gemm_kernel_waves_direct(const Params params) {
+  const GemmParams& p = whole_params<BM, BN>(params);
+  using Frag = typename FragT<T>::type;
+  constexpr int NW = S::NW, STEP = S::STEP, D = S::D, FN = BN / 16;
+  constexpr bool PAIRS = FN == 2;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[S::LDS_BYTES];
+  const int lane = threadIdx.x % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const BlockCoords bc = block_coords<BM, BN>(p);
+
+  struct __attribute__((packed, aligned(2))) Eight {
+    u32x4 v;
+  };
+  struct __attribute__((packed, aligned(2))) Two {
+    unsigned v;
+  };
+  // this lane's first values: row lane % 16 of A, column (pair) lane % 16 of B, eight values of k from 8 (lane / 16) on; what lies
+  // past an edge is the last row or column again, and feeds outputs that are never stored
+  const int kl = bc.k_begin + 8 * (lane / 16);
+  const int m = bc.m0 + lane % 16, n = bc.n0 + (PAIRS ? 2 : 1) * (lane % 16);
+  const T* pa = reinterpret_cast<const T*>(p.A) + (long long)bc.batch * p.strideA + (long long)(m < p.M ? m : p.M - 1) * p.lda + kl;
+  const T* pb = reinterpret_cast<const T*>(p.B) + (long long)bc.batch * p.strideB + (long long)kl * p.ldb;
+  int down = 0;  // bits: the last column, without a neighbour, is read as the second of a pair
+  if constexpr (PAIRS) {
+    pb += n < p.N - 1 ? n : p.N - 2;
+    down = n == p.N - 1 ? 16 : 0;
+  } else {
+    pb += n < p.N ? n : p.N - 1;
+  }
+  struct Step {
+    u32x4 a;
+    u32x4 b[FN];  // (pairs: the eight loads as they come)
+  };
+  auto request = [&](Step& r, int i) {  // this wavefront's step i, which lies inside K
+    const long long k = (long long)(wave + i * NW) * STEP;
+    r.a = reinterpret_cast<const Eight*>(pa + k)->v;
+    if constexpr (PAIRS) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) r.b[e / 4][e % 4] = reinterpret_cast<const Two*>(pb + (k + e) * p.ldb)->v;
+    } else {
+      T t[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) t[e] = pb[(k + e) * p.ldb];
+      r.b[0] = __builtin_bit_cast(u32x4, t);
+    }
+  };
+  f32x4 acc[1][FN];
+#pragma unroll
+  for (int j = 0; j < FN; ++j) acc[0][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  auto multiply = [&](const Step& r) {
+    Frag fa = __builtin_bit_cast(Frag, r.a), fb[FN];
+    if constexpr (PAIRS) {
+      u32x4 even, odd;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const unsigned x = r.b[i / 2][2 * (i % 2)], y = r.b[i / 2][2 * (i % 2) + 1];
+        odd[i] = __builtin_amdgcn_perm(y, x, 0x07060302u);
+        even[i] = __builtin_amdgcn_perm(y >> down, x >> down, 0x05040100u);
+      }
+      fb[0] = __builtin_bit_cast(Frag, even);
+      fb[1] = __builtin_bit_cast(Frag, odd);
+    } else {
+      fb[0] = __builtin_bit_cast(Frag, r.b[0]);
+    }
+    if (p.relu_a) fa = relu_fragment(fa);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      if (p.relu_b) fb[j] = relu_fragment(fb[j]);
+      acc[0][j] = mfma_op(fb[j], fa, acc[0][j]);  // (operands swapped, as above)
+    }
+  };
+
+  const int whole = bc.k_len > 0 ? bc.k_len / STEP : 0;
+  const int mine = whole > wave ? (whole - wave + NW - 1) / NW : 0;
+  const bool tail = whole * STEP < bc.k_len && wave == whole % NW;  // this wavefront multiplies what is left of K
+  Step step[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (d < mine) request(step[d], d);
+  Step last;
+  if (tail) {
+    const int left = bc.k_len - whole * STEP - 8 * (lane / 16);  // values of k that this lane has
+    T ta[8];
+    unsigned tb[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool in = e < left;
+      // (outside: the first value of K, which there is, as a zero)
+      const long long k = in ? (long long)whole * STEP + e : -8LL * (lane / 16);
+      const T x = pa[k];
+      ta[e] = in ? x : (T)0.0f;
+      unsigned y;
+      if constexpr (PAIRS)
+        y = reinterpret_cast<const Two*>(pb + k * p.ldb)->v;
+      else
+        y = __builtin_bit_cast(unsigned short, pb[k * p.ldb]);
+      tb[e] = in ? y : 0u;
+    }
+    last.a = __builtin_bit_cast(u32x4, ta);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if constexpr (PAIRS)
+        last.b[e / 4][e % 4] = tb[e];
+      else if (e % 2 == 0)
+        last.b[0][e / 2] = tb[e] | tb[e + 1] << 16;
+    }
+  }
+  PartialTiles<TO, BM, BN, NW> end;
+  end.request(p, bc);
+
+  int i = 0;
+  for (; i + 2 * D <= mine; i += D) {  // (without a branch: loads are counted)
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      multiply(step[d]);
+      request(step[d], i + D + d);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    if (i + d < mine) multiply(step[d]);
+    if (i + D + d < mine) request(step[d], i + D + d);
+  }
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (i + D + d < mine) multiply(step[d]);
+  if (tail) multiply(last);
+  end.template finish<PAIRS>(p, acc, smem, wave, lane);
 }
 
 }  // namespace hidet
