@@ -426,8 +426,8 @@ __device__ __forceinline__ u32x4 relative_to(u32x4 raw, float m) {
 // Memory, not arithmetic, should decide how long this takes, and a row's loads, arithmetic and stores follow one another,
 // with two long rows to a compute unit that do so in step.  So the sum of 16-bit rows is formed while the chunks arrive, each
 // thread's relative to the largest value it has seen; what is left behind the last one is a single meeting of the wavefronts,
-// and the second exponential beside the stores.  12 vector instructions an element, 21 with the maximum, the sum and the
-// results in three passes that each widen, and exponentials of differences.  1024 x 50257 bf16, in and out of HBM:
+// and the second exponential beside the stores.  16 vector instructions an element (15 without masks), 21 (18) with the maximum,
+// the sum and the results in three passes that each widen, and exponentials of differences; vector units 81 % busy, 94 % then.  1024 x 50257 bf16, in and out of HBM:
 // 47.7 -> 44.9 us, 42.0 with streaming stores (4.9 TB/s); 512 rows of it, all resident at once, 26.8 -> 20.6; 64 x 8192
 // 3.4 -> 2.9; 6 x 19018 fp16 5.7 -> 4.5.  (One workgroup to a compute unit that requests its next row before it works on the one
 // it has: 53 us; half the wavefronts cost more than the order gives.)
