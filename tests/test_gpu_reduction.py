@@ -410,3 +410,29 @@ def test_softmax_held_by_a_workgroup_of_values_of_any_size(dtype, cols):
         assert np.isnan(got[10:]).all()
         for i in range(10):
             assert within_bound(oracle.rel_frobenius(got[i:i + 1], ref[i:i + 1]), ref[i:i + 1], dtype), (i, shift)
+
+
+# Outputs on both sides of 4 MiB, from where on they are stored with the streaming hint unless they are the input: a wavefront's rows,
+# a workgroup's and streamed ones; whole chunks, ragged ends, and rows whose chunks are laid on the output's 16-byte grid.
+@pytest.mark.parametrize("dtype,rows,cols", [("f16", 4200, 512), ("bf16", 7300, 300), ("f32", 2100, 500), ("f16", 300, 8192), ("f16", 130, 8192),
+                                             ("bf16", 48, 50257), ("bf16", 36, 50257), ("f16", 64, 33001), ("f32", 24, 60001),
+                                             ("f16", 16, 140001), ("bf16", 3, 140008)])
+def test_softmax_of_large_outputs_beside_and_in_place_of_the_input(dtype, rows, cols):
+    g = wl.rng(9700 + cols + rows)
+    x = wl.to_storage((g.standard_normal((rows, cols)) * 3).astype(np.float32), dtype)
+    ref = red.softmax_rows(wl.widen(x, dtype))
+    for ld, shift in ((cols, 0), (cols + 3, 1)):
+        around = lambda: torch.full((rows * ld + shift + 16,), 7.0, dtype=TORCH_DTYPE[dtype], device="cuda")
+        inside = lambda buf: buf[shift: shift + rows * ld].view(rows, ld)[:, :cols]
+        src, dst = around(), around()
+        inside(src).copy_(to_gpu(x, dtype))
+        hb.hidet_softmax_rows(inside(src), inside(dst))
+        torch.cuda.synchronize()
+        assert torch.equal(inside(src), to_gpu(x, dtype)), "the input is read only"
+        err = oracle.rel_frobenius(to_f64(inside(dst)), ref)
+        assert within_bound(err, ref, dtype), (ld, err)
+        hb.hidet_softmax_rows(inside(src), inside(src))
+        torch.cuda.synchronize()
+        assert torch.equal(src, dst), "in place: the same bits, and nothing written beside the rows"
+        inside(dst).fill_(7.0)
+        assert bool((dst == 7.0).all())
