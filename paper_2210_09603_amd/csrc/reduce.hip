@@ -23,6 +23,8 @@
 // Arithmetic is fp32 whatever the storage type.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "../../include/hidet_mi355x.h"
 #include "gemm_kernel.hpp"
 
@@ -181,8 +183,16 @@ __device__ __forceinline__ void meet(float v, float& a, float& b) {
     }
   }
 }
-template <int L, bool MAX>
+template <int L, bool MAX, bool CROSSBAR = false>
 __device__ __forceinline__ float over_lanes(float v) {
+  if constexpr (CROSSBAR) {  // (see rows_in_turn; lanes meet in the same order, so the sum has the same bits)
+#pragma unroll
+    for (int o = 1; o < L; o <<= 1) {
+      const float w = __shfl_xor(v, o, 64);
+      v = MAX ? fmaxf(v, w) : v + w;
+    }
+    return v;
+  }
   float a, b;
   auto step = [&] { v = MAX ? fmaxf(a, b) : a + b; };
   if constexpr (L >= 2) { meet<1>(v, a, b); step(); }
@@ -193,13 +203,13 @@ __device__ __forceinline__ float over_lanes(float v) {
   if constexpr (L >= 64) { meet<32>(v, a, b); step(); }
   return v;
 }
-template <int L>
+template <int L, bool CROSSBAR = false>
 __device__ __forceinline__ float group_max(float v) {
-  return over_lanes<L, true>(v);
+  return over_lanes<L, true, CROSSBAR>(v);
 }
-template <int L>
+template <int L, bool CROSSBAR = false>
 __device__ __forceinline__ float group_sum(float v) {
-  return over_lanes<L, false>(v);
+  return over_lanes<L, false, CROSSBAR>(v);
 }
 
 __device__ __forceinline__ void write_scalar(const RowParams& p, long long row, float v, int dtype_tag) {
@@ -221,7 +231,7 @@ struct Tag {
 // ---- the row lives in the registers of L lanes of a wavefront ----------------------------------------
 // SHAPE: WHOLE chunks, RAGGED rows of at least one chunk, SHORT ones of less.
 enum RowShape { WHOLE, RAGGED_END, SHORT };
-template <typename T, int L, int R, RowShape SHAPE, bool SOFTMAX, bool STREAM>
+template <typename T, int L, int R, RowShape SHAPE, bool SOFTMAX, bool STREAM, bool CROSSBAR>
 __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams p) {
   constexpr int VEC = Chunk<T>::VEC;
   constexpr bool RAGGED = SHAPE != WHOLE;
@@ -252,7 +262,7 @@ __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams 
       for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) m = fmaxf(m, v[r][e]);
-      m = group_max<L>(m);
+      m = group_max<L, CROSSBAR>(m);
     }
     if constexpr (SOFTMAX) {
       float s = 0.0f;
@@ -263,7 +273,7 @@ __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams 
           v[r][e] = __expf(v[r][e] - m);  // padding: exp(-inf) = 0
           s += v[r][e];
         }
-      s = group_sum<L>(s);
+      s = group_sum<L, CROSSBAR>(s);
       const float inv = 1.0f / s;
       T* yr = reinterpret_cast<T*>(p.y) + row * p.ldy;
 #pragma unroll
@@ -686,14 +696,33 @@ bool streams_output(const RowParams& p) {
   return p.x != p.y && p.rows * (long long)p.cols >= (4LL << 20) / (long long)sizeof(T);
 }
 
-template <typename T, int L, int R, bool SOFTMAX, bool STREAM>
-hipError_t launch_wavefront_as(const RowParams& p, unsigned blocks, hipStream_t stream) {
+// A softmax whose wavefronts would work on more than eight rows of one chunk a lane in turn: with the short butterflies they go in
+// step, all of them read and then all of them write.  Rows that fill their lanes are spread out by the dispatcher, which gets a
+// workgroup for each few of them (attention's three calls on 192 entries of 512 x 512 93.9 us in turn, 91.8 this way; beside the
+// input 390625 x 128 fp16 35.9 and 32.9, 97656 x 256 fp32 35.5 and 33.0).  Others stay in turn, since a wavefront with fewer bytes is
+// worth less (130208 x 384 fp16 in place 36.8 us one by one, 35.2 in turn; 192 entries of 300 x 300 51.7 and 50.2), and combine their lanes
+// through the LDS crossbar, whose queue spreads them (166666 x 300 fp16 51.5 us with butterflies, 49.0 with the crossbar, 166666 x 150
+// fp32 43.4 and 40.7, attention on 339 of 384 x 384 105.0 and 103.6).  With fewer rows in turn neither pays: 23437 x 256 one by one 5.3
+// us, 4.9 in turn, 20000 x 150 fp32 through the crossbar 6.6, with butterflies 6.2.  Nor do they with more chunks a lane, or in
+// reductions, which write next to nothing.
+bool rows_in_turn(long long rows, int lanes, int chunks_per_lane) {
+  return chunks_per_lane == 1 && rows > 8LL * kMaxBlocks * 4 * (64 / lanes);
+}
+// Workgroups of a launch whose wavefronts share a row between `lanes` lanes.
+long long wavefront_blocks(bool softmax, long long rows, bool full, int lanes, int chunks_per_lane) {
+  const long long per_block = 4 * (64 / lanes), wanted = rows / per_block + (rows % per_block != 0);
+  const bool spread = softmax && full && rows_in_turn(rows, lanes, chunks_per_lane);
+  return std::min(wanted, spread ? max_workgroups(256) : (long long)kMaxBlocks);
+}
+
+template <typename T, int L, int R, bool SOFTMAX, bool STREAM, bool CROSSBAR>
+hipError_t launch_wavefront_as(const RowParams& p, dim3 grid, hipStream_t stream) {
   if constexpr (R == 0)
-    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, 1, SHORT, SOFTMAX, false>), dim3(blocks), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, 1, SHORT, SOFTMAX, false, false>), grid, dim3(256), 0, stream, p);
   else if (p.cols % Chunk<T>::VEC == 0)
-    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, WHOLE, SOFTMAX, STREAM>), dim3(blocks), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, WHOLE, SOFTMAX, STREAM, CROSSBAR>), grid, dim3(256), 0, stream, p);
   else if constexpr (R <= 4)  // (longer ragged rows take a workgroup)
-    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, RAGGED_END, SOFTMAX, STREAM>), dim3(blocks), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, RAGGED_END, SOFTMAX, STREAM, CROSSBAR>), grid, dim3(256), 0, stream, p);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -701,12 +730,17 @@ hipError_t launch_wavefront_as(const RowParams& p, unsigned blocks, hipStream_t 
 
 template <typename T, int L, int R, bool SOFTMAX>
 hipError_t launch_wavefront(const RowParams& p, hipStream_t stream) {
-  constexpr int G = 64 / L;
-  long long blocks = (p.rows + 4 * G - 1) / (4 * G);
-  if (blocks > kMaxBlocks) blocks = kMaxBlocks;
-  if constexpr (SOFTMAX && R > 0)
-    if (streams_output<T>(p)) return launch_wavefront_as<T, L, R, SOFTMAX, true>(p, (unsigned)blocks, stream);
-  return launch_wavefront_as<T, L, R, SOFTMAX, false>(p, (unsigned)blocks, stream);
+  const bool full = p.cols == L * Chunk<T>::VEC;
+  const dim3 grid((unsigned)wavefront_blocks(SOFTMAX, p.rows, full, L, R));
+  if constexpr (SOFTMAX && R > 0) {
+    const bool streams = streams_output<T>(p);
+    if constexpr (R == 1)
+      if (!full && rows_in_turn(p.rows, L, R))
+        return streams ? launch_wavefront_as<T, L, R, true, true, true>(p, grid, stream)
+                       : launch_wavefront_as<T, L, R, true, false, true>(p, grid, stream);
+    if (streams) return launch_wavefront_as<T, L, R, true, true, false>(p, grid, stream);
+  }
+  return launch_wavefront_as<T, L, R, SOFTMAX, false, false>(p, grid, stream);
 }
 
 template <typename T, int NT, int R, bool STREAM>
@@ -871,7 +905,9 @@ hidet_status_t hidet_row_schedule(int32_t dtype, int32_t softmax, int64_t rows, 
   const long long rows_per_workgroup = out->workgroup_size / c.threads;
   const long long limit = c.form == ROW_PER_WORKGROUP ? max_workgroups(c.threads) : kMaxBlocks;
   const long long wanted = (rows - 1) / rows_per_workgroup + 1;
-  out->workgroups = wanted < limit ? wanted : limit;
+  out->workgroups = c.form == ROWS_PER_WAVEFRONT
+                        ? wavefront_blocks(softmax != 0, rows, cols * elem_bytes(dtype) == c.threads * 16, c.threads, c.chunks)
+                        : std::min(wanted, limit);
   out->launches = c.form == ROW_PER_WORKGROUP ? (wanted - 1) / limit + 1 : 1;
   return HIDET_OK;
 }

@@ -436,3 +436,26 @@ def test_softmax_of_large_outputs_beside_and_in_place_of_the_input(dtype, rows, 
         assert torch.equal(src, dst), "in place: the same bits, and nothing written beside the rows"
         inside(dst).fill_(7.0)
         assert bool((dst == 7.0).all())
+
+
+@pytest.mark.parametrize("dtype,cols,lanes", [("f16", 8, 8), ("f32", 30, 8), ("bf16", 100, 16), ("f16", 136, 32), ("f16", 300, 64), ("f32", 256, 64),
+                                              ("f16", 128, 16), ("bf16", 392, 64)])
+def test_softmax_of_rows_that_wavefronts_take_in_turn(dtype, cols, lanes):
+    """More than eight rows (of one chunk a lane) a wavefront: those that fill their lanes get more workgroups, the lanes of others meet
+    another way, in the same order.  The same bits as from two calls of half as many rows, which are on the other side of the line, beside and
+    in place of the input."""
+    limit = 8 * 2048 * 256 // lanes
+    for rows, softmax, blocks in ((limit, 1, 2048), (limit + 1, 1, 8 * 2048 + 1 if cols * (4 if dtype == "f32" else 2) == 16 * lanes else 2048), (limit + 1, 0, 2048)):
+        s = hb.hidet_row_schedule({"f16": hb.HIDET_F16, "bf16": hb.HIDET_BF16, "f32": hb.HIDET_F32}[dtype], softmax, rows, cols)
+        assert (s["form"], s["threads_per_row"], s["chunks_per_thread"], s["workgroups"]) == (0, lanes, 1, blocks), (rows, softmax, s)
+    for rows in (limit, limit + 3):
+        x = torch.randn((rows, cols), device="cuda", generator=torch.Generator(device="cuda").manual_seed(rows)).mul_(3).to(TORCH_DTYPE[dtype])
+        y, halves = torch.empty_like(x), torch.empty_like(x)
+        hb.hidet_softmax_rows(x, y)
+        for part in (slice(0, rows // 2), slice(rows // 2, rows)):
+            hb.hidet_softmax_rows(x[part], halves[part])
+        z = x.clone()
+        hb.hidet_softmax_rows(z, z)
+        torch.cuda.synchronize()
+        assert torch.equal(y, halves) and torch.equal(z, y), rows
+        assert not torch.isnan(y).any() and float((y.float().sum(1) - 1).abs().max()) < 2e-2
