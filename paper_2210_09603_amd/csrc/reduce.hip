@@ -661,6 +661,9 @@ __global__ void __launch_bounds__(NT) long_rows_kernel(const RowParams p) {
         widen_chunk<T>(load_raw<T>(xr, c * VEC, p.cols), v);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) v[e] = __expf(v[e] - m) * inv;
+        // (always with the streaming hint: 60 rows of 140000 bf16 28.5 us without, 25.8 with, of 70001 fp32 20.6 and 18.1, one or
+        // five of 140000 fp32 28.7 and 28.4; in place there is no difference, nor to a call that reads the results then: the
+        // row itself, read twice, has driven out whatever the hint would)
         store_chunk<T, RAGGED, true>(yr, c * VEC, p.cols, v);
       }
     } else if (tid == 0) {
@@ -684,13 +687,14 @@ struct RowChoice {
 // refused).  The row-per-workgroup form runs more rows than that in several launches.
 constexpr long long max_workgroups(int threads) { return 0xffffffffLL / threads; }
 
-// Outputs of 4 MiB and more are stored with the streaming hint where they are not the input: they do not stay in the L2s, which
-// otherwise write them back behind the kernel's last store (inputs in HBM, calls one after another: 1024 x 50257 bf16 44.4 us
-// without, 41.9 with, 1024 x 33333 fp16 30.5 and 23.3, 1024 x 30000 fp32 52.3 and 46.8, 48828 x 512 fp16 20.0 and 16.6; 1024 x 1149
-// fp16, 2.3 MB, 3.7 and 4.0).  A reader that follows at once has less to find there: with a sum over the results the pair takes
-// 0.95 to 1.07 of the time (1024 x 50257 61.4 and 65.3 us, 1024 x 16384 fp16 19.1 and 18.1).  In place the lines are in the L2s
-// already, so the hint gains nothing and drives them out: with the sum, 1024 x 50257 56.6 us without, 62.3 with; attention's chain of
-// three calls, whose softmax works in place, 42 entries of 768 x 768 44.0 and 48.5 us, one of 6144 x 6144 66.6 and 76.1.
+// Outputs of 4 MiB and more, of rows that are not streamed, have the streaming hint where they are not the input: they do not
+// stay in the L2s, which otherwise write them back behind the kernel's last store (inputs in HBM, calls one after another: 1024 x
+// 50257 bf16 44.4 us without, 41.9 with, 1024 x 33333 fp16 30.5 and 23.3, 1024 x 30000 fp32 52.3 and 46.8, 48828 x 512 fp16 20.0 and
+// 16.6; 1024 x 1149 fp16, 2.3 MB, 3.7 and 4.0).  A reader that follows at once has less to find there: with a sum over the
+// results the pair takes 0.94 to 1.07 of the time (1024 x 50257 61.4 and 65.3 us, 1024 x 16384 fp16 19.1 and 18.1).  In place the
+// lines are in the L2s already, so the hint gains nothing and drives them out: with the sum, 1024 x 50257 56.6 us without, 62.3
+// with; attention's chain of three calls, whose softmax works in place, 42 entries of 768 x 768 44.0 and 48.5 us, one of 6144 x
+// 6144 66.6 and 76.1.
 template <typename T>
 bool streams_output(const RowParams& p) {
   return p.x != p.y && p.rows * (long long)p.cols >= (4LL << 20) / (long long)sizeof(T);
