@@ -420,7 +420,13 @@ struct Exponential {
       return __expf(v - c);
   }
 };
-__device__ __forceinline__ float times_power_of_2(float s, float e) { return __builtin_ldexpf(s, (int)e); }
+// The power of two for a whole e that is not positive, or infinite or no number where the row's largest value is infinite.  (A sum
+// of exponentials, at most 2^17, is 0 from 2^-167 on.)
+__host__ __device__ constexpr int power_of_2(float e) { return e > -512.0f ? (int)e : -512; }
+static_assert(power_of_2(-0.0f) == 0 && power_of_2(-511.0f) == -511 && power_of_2(-2.0f * kFar) == -512 &&
+                  power_of_2(-3.0e38f) == -512 && power_of_2(kNegInf) == -512 && power_of_2(__builtin_nanf("")) == -512,
+              "defined for every difference of two scales");
+__device__ __forceinline__ float times_power_of_2(float s, float e) { return __builtin_ldexpf(s, power_of_2(e)); }
 
 template <typename T>
 __device__ __forceinline__ u32x4 relative_to(u32x4 raw, float m) {
