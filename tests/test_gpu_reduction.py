@@ -459,3 +459,27 @@ def test_softmax_of_rows_that_wavefronts_take_in_turn(dtype, cols, lanes):
         torch.cuda.synchronize()
         assert torch.equal(y, halves) and torch.equal(z, y), rows
         assert not torch.isnan(y).any() and float((y.float().sum(1) - 1).abs().max()) < 2e-2
+
+
+@pytest.mark.parametrize("cols", [2049, 8200, 50257])
+def test_softmax_of_maxima_around_the_largest_scale(cols):
+    """A running scale serves maxima below 2^16, the difference to the maximum those beyond: bf16 rows whose maximum is next to
+    2^16 on either side, of either sign, in one place or three, with values a step below it, at the other end of the range or -inf."""
+    rows = []
+    for top, below in ((65280.0, 65024.0), (65536.0, 65280.0), (66048.0, 65536.0), (-65280.0, -65536.0), (-65536.0, -66048.0),
+                       (-66048.0, -66560.0)):
+        for rest in (below, -3.0e38, -np.inf, min(-70000.0, below)):
+            for places in ((cols - 1,), (0, cols // 2, cols - 2)):
+                x = np.full(cols, rest, dtype=np.float32)
+                x[1::3] = below
+                x[list(places)] = top
+                rows.append(x)
+    s = wl.to_storage(np.stack(rows), "bf16")
+    assert np.array_equal(wl.widen(s, "bf16")[:, 1], np.stack(rows)[:, 1])  # (all of them are bf16 values)
+    ref = red.softmax_rows(wl.widen(s, "bf16"))
+    x = to_gpu(s, "bf16")
+    y = torch.empty_like(x)
+    hb.hidet_softmax_rows(x, y)
+    torch.cuda.synchronize()
+    # (any two values differ by 256 or more: a share of the maxima is all there is)
+    assert float(np.abs(to_f64(y) - ref).max()) <= 2.0 ** -9 and not torch.isnan(y).any()
