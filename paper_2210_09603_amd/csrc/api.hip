@@ -1107,9 +1107,7 @@ bool patch_form(const Problem& conv, const SplitK& sk) {
 // each round of 256 workgroups, several that share one as much for what they are of a round; a patch a rate per stage and per
 // store of its outputs.  Fitted to 2600 random convolutions of 16 to 1024 channels and planes of 6x6 to 62x62, patches of 5x5
 // to 400 (relative): 5 % to 95 % of predictions over measurements 0.91 to 1.07 for the K-splitting tiles, 0.84 to 1.15 for the
-// others, 0.94 to 1.04 and 0.81 to 1.09 for patches of 5x5 and 3x3.  (5x5 on rows without padding columns, where a die's workgroups
-// read more weights than its L2 holds, counts as it did with one stage in flight, 2.75 us a stage: there the choice of the
-// gather is held by its test, 32 of 512x16x16, 128 channels: 83 us, from a patch 58.)
+// others, 0.94 to 1.04 and 0.81 to 1.09 for patches of 5x5 and 3x3.
 struct GatherTime {
   int bm, bn, sched;  // (0: schedules 0 and 2)
   double fixed, per_k;  // us; of 4608 values of K
@@ -1138,12 +1136,7 @@ double patch_us(const Problem& conv, int rows) {
   const bool residual = conv.p.residual != nullptr;
   if (g.KW == 3 && rows == 64) return 4.0 + std::max(1.0, (double)tiles / 256.0) * (2.3 + (residual ? 0.8 : 0.0) + 0.75 * stages);
   if (g.KW == 3) return 1.5 + whole * (5.2 + (residual ? 1.4 : 0.0) + 1.07 * stages);
-  const long long panels = tiles_m / 4;
-  const bool crosses = tiles_m > 4 && (tiles_m % 4 != 0 || (panels < 8 ? 8 % panels != 0 : panels % 8 != 0));
-  const double weights = (double)std::min<long long>(conv.p.M, crosses ? 512 : 256) * g.IC * 50.0;
-  const double die = weights + (double)conv.Nb * g.IC * g.HW * 2.0 / 8.0;  // bytes that a die's workgroups read
-  const double rate = die > 4194304.0 && g.W % 8 == 0 ? 2.75 : 1.6;
-  return 0.2 + whole * (6.1 + (residual ? 1.2 : 0.0) + rate * stages);
+  return 0.2 + whole * (6.1 + (residual ? 1.2 : 0.0) + 1.6 * stages);
 }
 // Whether they are the better choice, and on tiles of how many rows; 0: the gather is.
 // It wants 72 tiles of 64x128 (of columns with the zero columns and rows among them).  Over 130 random problems of 16 to 512
@@ -1151,17 +1144,18 @@ double patch_us(const Problem& conv, int rows) {
 // 44 to 64, where the gather's K-splitting tiles have twice the workgroups; 58 to 63 tiles of a long K, 0.75 to 0.8, are not
 // told from those.  The zeros are no more than two fifths of the outputs (images of 6x6: 1.36 times as many columns, 0.94 to
 // 1.07 of the gather's).
-// 5x5: 64 rows only, one workgroup to a compute unit, and rows of 29 at most.  From 104 tiles on (150 of more than 256 channels)
-// the predictions decide: over 400 random problems this takes 1.017 times as long as the better form of each, 3 are more than 4
-// % slower than the gather.  From 40 tiles on it would be 1.003; the limits stem from one stage in flight, and tests hold the
-// choice below them (51 of 256x14x14, 64 channels, 102 tiles: 46.6 us, from a patch 32.5).
+// 5x5: 64 rows only, one workgroup to a compute unit, and rows of 29 at most.  From 40 tiles on the predictions decide: over
+// 450 random layers of 24 to 1200 tiles this takes 1.005 times as long as the better form of each, 0.84 of the gather's time; 4 are
+// more than 4 % slower than the gather (242 of 48x16x16, 32 channels, with residual: 28.3 and 32.6 us).  From fewer tiles on a patch
+// is predicted to win only where the two are level (30 of 16x8x8, 368 channels: 7.4 us both).
 // 128 rows fetch the input half as often and win from the point where 64 rows are more than one to a compute unit (26 images
 // of 128x28x28: 14.7 us, 16.9 us on 64; at most 256 tiles of 64: 1.25 of the time of 64), unless they make a second round
 // that is less than half full (47 of 96x27x27, 80 channels, 288 tiles: 23.1 and 21.0 us; 60 of 96x30x30, 451: 26.8 and 29.0
 // us; beyond two rounds the two are level, or 64 ahead: 44 of 192x23x23, 384 channels: 57.7 and 55.7 us).
 // The counts know neither how many of the gather's columns are padding (none in rows of 8 or 16) nor which tiles it has: where
 // the predictions say that it is faster it is taken.  Of 2600 random convolutions 136 were more than 4 % slower than through it
-// by the counts alone (13 of 512x8x8, 3x3: 22 and 28 us), 16 are now, none by more than a quarter (154 of 96x8x8, 384 channels, 3x3, with residual: 20.9 and 25.8 us).
+// by the counts alone (13 of 512x8x8, 3x3: 22 and 28 us), 16 are now, none by more than a quarter (154 of 96x8x8, 384 channels,
+// 3x3, with residual: 20.9 and 25.8 us).
 int patch_rows(const Problem& conv, const SplitK& sk) {
   const ConvGeom& g = conv.p.g;
   if (!patch_form(conv, sk) || conv.p.M < 16) return 0;
@@ -1169,7 +1163,7 @@ int patch_rows(const Problem& conv, const SplitK& sk) {
   if (5 * plane > (g.KW == 3 ? 7 : 9) * (long long)g.HW) return 0;
   const long long across = (conv.Nb * plane + 127) >> 7;
   const long long of_64 = ((conv.p.M + 63LL) >> 6) * across, of_128 = ((conv.p.M + 127LL) >> 7) * across;
-  if (of_64 < (g.KW == 3 ? 72 : g.IC <= 256 ? 104 : 150)) return 0;
+  if (of_64 < (g.KW == 3 ? 72 : 40)) return 0;
   const int rows = g.KW == 3 && conv.p.M > 64 && of_64 > 256 && (of_128 <= 256 || (of_128 > 384 && of_128 <= 512)) ? 128 : 64;
   const double gather = gather_us(conv);
   return gather > 0.0 && patch_us(conv, rows) > gather * 1.05 ? 0 : rows;

@@ -15,7 +15,8 @@ from helpers import TORCH_DTYPE, assert_elementwise, conv_scale, to_f64, to_gpu
 SHAPES = [(190, 16, 6, 6, 40, True, 64, 3), (9, 32, 31, 31, 80, False, 64, 3), (3, 48, 60, 62, 33, True, 64, 3), (3, 16, 61, 61, 64, True, 64, 3),
           (37, 64, 14, 14, 130, False, 64, 3), (25, 80, 13, 15, 192, True, 64, 3), (70, 32, 14, 14, 200, True, 128, 3), (30, 48, 27, 29, 96, False, 128, 3),
           (260, 16, 7, 7, 129, False, 64, 3), (64, 16, 28, 28, 65, True, 128, 3),
-          (60, 16, 14, 14, 66, True, 64, 5), (20, 32, 29, 29, 64, False, 64, 5), (33, 48, 17, 13, 100, True, 64, 5), (150, 80, 9, 11, 40, False, 64, 5)]
+          (60, 16, 14, 14, 66, True, 64, 5), (20, 32, 29, 29, 64, False, 64, 5), (33, 48, 17, 13, 100, True, 64, 5), (150, 80, 9, 11, 40, False, 64, 5),
+          (20, 16, 14, 14, 64, True, 64, 5), (10, 32, 14, 14, 256, False, 64, 5)]
 
 
 def rows(Nb, IC, H, W, OC, dtype=hb.HIDET_F16, k=3, s=1, pad=1):
@@ -33,16 +34,19 @@ def test_the_choice_between_patch_and_gather():
     assert rows(1000, 64, 5, 5, 64) == 0 and rows(1000, 64, 6, 6, 64) == 64  # more than two fifths of zeros
     assert rows(64, 96, 14, 14, 256) == 128 and rows(74, 96, 14, 14, 256) == 64  # 226 tiles of 128 rows; 262
     assert rows(110, 96, 14, 14, 256) == 128 and rows(146, 96, 14, 14, 256) == 64  # 388; 514
-    assert rows(104, 256, 14, 14, 64, k=5, pad=2) == 64 and rows(51, 256, 14, 14, 64, k=5, pad=2) == 0  # 208 and 102 tiles
-    assert rows(60, 272, 14, 14, 64, k=5, pad=2) == 0 and rows(75, 272, 14, 14, 64, k=5, pad=2) == 64  # 120 and 150
+    assert rows(104, 256, 14, 14, 64, k=5, pad=2) == 64 and rows(51, 256, 14, 14, 64, k=5, pad=2) == 64  # 102 tiles: 44.8 us, patch 32.9
+    assert rows(60, 272, 14, 14, 64, k=5, pad=2) == 64 and rows(75, 272, 14, 14, 64, k=5, pad=2) == 64  # 120: 47.4 and 33.5 us
+    assert rows(12, 256, 14, 14, 256, k=5, pad=2) == 64 and rows(28, 512, 7, 7, 512, k=5, pad=2) == 64  # 42.8 and 31.5, 90.6 and 59.5 us
+    assert rows(19, 16, 14, 14, 64, k=5, pad=2) == 0 and rows(20, 16, 14, 14, 64, k=5, pad=2) == 64  # 38 and 40 tiles
     assert rows(40, 64, 29, 29, 64, k=5, pad=2) == 64 and rows(40, 64, 29, 30, 64, k=5, pad=2) == 0
 
 
 def test_the_gather_where_it_is_faster():
-    """Rows of 8 and 16 pixels, of which no column of the gather is padding, and weights beyond a die's L2."""
+    """Rows of 8 and 16 pixels, of which no column of the gather is padding, and patches of a second round that is nearly empty."""
     assert rows(101, 256, 8, 8, 256, k=5, pad=2) == 0 and rows(64, 128, 16, 16, 128, k=5, pad=2) == 0
     assert rows(13, 512, 8, 8, 512) == 0 and rows(128, 128, 8, 8, 32) == 0
-    assert rows(8, 1024, 15, 15, 1024, k=5, pad=2) == 0 and rows(32, 512, 16, 16, 128, k=5, pad=2) == 0
+    assert rows(8, 1024, 15, 15, 1024, k=5, pad=2) == 0 and rows(48, 512, 8, 8, 512, k=5, pad=2) == 0  # 198 us, patch 223; 99 and 119
+    assert rows(32, 512, 16, 16, 128, k=5, pad=2) == 64 and rows(40, 512, 8, 8, 512, k=5, pad=2) == 64  # 81 us, patch 58; 101 and 65
     assert rows(64, 512, 7, 7, 512) == 64 and rows(64, 256, 14, 14, 256) == 128 and rows(60, 256, 14, 14, 256, k=5, pad=2) == 64
 
 
