@@ -1,6 +1,6 @@
 """16-bit products on element-aligned rows whose wavefronts read K straight from memory (tiles of 16 rows, neither operand
 transposed): values of K around a step, a round of steps and two of them, columns of odd count and fewer than a 16-byte chunk,
-any alignment, K slices and fused input activations, against float64 within the derived bound of every element."""
+any alignment, K slices, fp32 results and fused input activations, against float64 within the derived bound of every element."""
 import numpy as np
 import pytest
 import torch
@@ -36,6 +36,9 @@ def test_against_float64(K, M, N, shift, dtype):
         hb.hidet_gemm(A, B, C, epilogue=hb.make_epilogue(relu_input=True), config=config)
         r64 = np.maximum(a64, 0)
         assert_elementwise(to_f64(C), r64 @ b64, gemm_scale(r64, b64, False, False, 1.0), dtype, K, config)
+        wide = torch.full((M, N), float("nan"), device="cuda")
+        hb.hidet_gemm(A, B, wide, config=config)
+        assert_elementwise(to_f64(wide), a64 @ b64, gemm_scale(a64, b64, False, False, 1.0), "f32", K, config)
         if K > 1:
             ws = torch.empty(3 * M * N, dtype=torch.float32, device="cuda")
             C3 = torch.full((1, M, N), float("nan"), device="cuda", dtype=a.dtype)
