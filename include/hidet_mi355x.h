@@ -187,9 +187,10 @@ typedef struct {
                                         1: ring of four stages filled by direct global -> LDS loads, wavefront ping-pong;
                                         2: as 0 with the loads of the next tile issued one iteration earlier;
                                         3: as 2 with sixteen wavefronts, 16 / (waves_m * waves_n) groups that each
-                                           multiply a share of the k steps of every K tile (sums meet in LDS); GEMMs in
-                                           16-bit types on tiles up to 64x64 run eight wavefronts instead, each of which
-                                           streams k steps of its own (the fields below describe the former) */
+                                           multiply a share of the k steps of every K tile (sums meet in LDS); GEMMs on
+                                           tiles up to 64x64 run wavefronts instead that each stream k steps of their
+                                           own: eight in 16-bit types (sixteen on some element-aligned rows), sixteen
+                                           in fp32 (the fields below describe the former, which convolutions run) */
   int32_t stages;                    /* LDS stages of block_k each */
   int32_t lds_bytes;                 /* LDS allocated by the workgroup */
   int32_t waves_k;                   /* wave groups that share every K tile (1 except with schedule 3); the workgroup

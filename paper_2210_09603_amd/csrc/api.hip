@@ -1450,7 +1450,9 @@ hidet_status_t hidet_config_info(int32_t config, hidet_config_info_t* info) {
   const int staging = info->stages * (r.bm + r.bn) * r.bk * (r.is_f32 ? 4 : 2);
   int epilogue = r.waves_m * r.mfma * (r.bn * 4 + 16 * r.waves_n);  // per-wave transposition regions
   if (r.sched == 3) epilogue += (16 / (r.waves_m * r.waves_n) - 1) * r.bm * r.bn * 4;  // partial sums of the wave groups along K
-  info->lds_bytes = staging > epilogue ? staging : epilogue;  // (GEMM form; the convolution adds a 1.3 KB mask table)
+  // (of K tiles that all wavefronts share, also for the tiles of schedule 3 whose GEMMs have wavefronts that share nothing; a
+  // convolution adds a 1.3 KB mask table)
+  info->lds_bytes = staging > epilogue ? staging : epilogue;
   return HIDET_OK;
 }
 
