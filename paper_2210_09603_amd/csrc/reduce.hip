@@ -443,10 +443,10 @@ __device__ __forceinline__ u32x4 relative_to(u32x4 raw, float m) {
 // with two long rows to a compute unit that do so in step.  So the sum of 16-bit rows is formed while the chunks arrive, each
 // thread's relative to the largest value it has seen; what is left behind the last one is a single meeting of the wavefronts,
 // and the second exponential beside the stores.  16 vector instructions an element (15 without masks), 21 (18) with the maximum,
-// the sum and the results in three passes that each widen, and exponentials of differences; vector units 81 % busy, 94 % then.  1024 x 50257 bf16, in and out of HBM:
-// 47.7 -> 44.9 us, 42.0 with streaming stores (4.9 TB/s); 512 rows of it, all resident at once, 26.8 -> 20.6; 64 x 8192
-// 3.4 -> 2.9; 6 x 19018 fp16 5.7 -> 4.5.  (One workgroup to a compute unit that requests its next row before it works on the one
-// it has: 53 us; half the wavefronts cost more than the order gives.)
+// the sum and the results in three passes that each widen, and exponentials of differences; vector units 81 % busy, 94 % then.
+// 1024 x 50257 bf16, in and out of HBM: 47.7 -> 44.9 us, 42.0 with streaming stores (4.9 TB/s); 512 rows of it, all resident at
+// once, 26.8 -> 20.6; 64 x 8192 3.4 -> 2.9; 6 x 19018 fp16 5.7 -> 4.5.  (One workgroup to a compute unit that requests its next row
+// before it works on the one it has: 53 us; half the wavefronts cost more than the order gives.)
 template <typename T, int NT, int R, bool RAGGED, bool STREAM>
 __global__ void __launch_bounds__(NT, R <= 8 ? 8 : 4) softmax_in_workgroup_kernel(const RowParams p) {
   constexpr int VEC = Chunk<T>::VEC, NW = NT / 64;

@@ -190,7 +190,8 @@ struct PartialTiles {
         if constexpr (PAIRS) {
           const f32x4 even = acc[i][j & ~1], odd = acc[i][j | 1];
           const int r = 2 * (j & 1);
-          *reinterpret_cast<f32x4*>(row + ((j & ~1) * 16 + 8 * (lane / 16) + 4 * (j & 1)) * 4) = f32x4{even[r], odd[r], even[r + 1], odd[r + 1]};
+          const int at = (j & ~1) * 16 + 8 * (lane / 16) + 4 * (j & 1);
+          *reinterpret_cast<f32x4*>(row + at * 4) = f32x4{even[r], odd[r], even[r + 1], odd[r + 1]};
         } else {
           *reinterpret_cast<f32x4*>(row + (j * 16 + 4 * (lane / 16)) * 4) = acc[i][j];
         }
