@@ -22,10 +22,12 @@
 // images of 256x14x14, 256 channels: 32.5 us pixel by pixel and at the start of a stage, 27.7 us by pairs of pixels, 26.1 us
 // between the taps.  (Four pixels a load: 26.3 us.)  45 us -> 30 us for 128x28x28, 46 -> 32 us for 512x7x7, 50 -> 37 us for
 // 64x56x56, 64 images each; 99 -> 42 us for 68 images of 192x21x21.
-// What is left is bound by the LDS: a wavefront reads 27 KB of fragments a stage, which takes 1730 of the 1970 cycles
-// that a stage lasts without loads, deposits and stores (27.4 us with all of them, 24.1 without the loads, 19.0 without any).  (The
-// barrier before the last filter row, with the fragments of the next stage read under it: 24.1 us; wave tiles of 64x64, which
-// read a third less, one to a SIMD: 30.8 us.)
+// What is left has no single bound.  For a stage the LDS reads 27 KB of fragments for each of eight wavefronts, 907 cycles (244
+// bytes a clock for these addresses), and a SIMD's 36 matrix instructions take 1152; without loads, deposits and stores a stage
+// lasts 1970, as long as one after the other, and with them 3300 (27.4 us with all of them, 24.1 without the loads, 19.0 without
+// any).  Of these the matrix cores work 35 %, the LDS 48 % (a fifth of it bank conflicts), the first-level cache 61 %; wavefronts
+// spend 32 % at wait counts and barriers and 40 % waiting to issue.  (The barrier before the last filter row, with the fragments of
+// the next stage read under it: 24.1 us; wave tiles of 64x64, which read a third less, one to a SIMD: 30.8 us.)
 // 5x5: 25 taps take 100 registers of weights and 60 more for each stage on its way, so there is one wavefront to a SIMD (64 rows
 // alone).  With one stage on its way instead of two the wavefront waited for the weights for as long as it computed: 20 of
 // 256x14x14 50.7 us, 32.0 with two; 47 of 512x7x7 94 -> 63.5 us, 15 of 128x29x29 28 -> 21.

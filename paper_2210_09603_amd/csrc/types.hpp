@@ -119,9 +119,9 @@ inline void set_block_mapping(GemmParams& p, int tiles_m, int tiles_n, int group
 // The parameters of a plain product -- row-major output, no K slices, distances between rows and batch entries below 2^32
 // elements -- in 104 bytes.  The runtime takes 3.0 us to launch a kernel with up to 112 bytes of arguments and 3.8 with 128 or
 // more, as long as the small products run: the kernels of small tiles are built for this form as well, and take it whenever it
-// holds.  They are a fifth shorter for it, without the index maps and K slices that it excludes.  Microseconds a call: 256^3
-// fp32 4.29 -> 3.96, attention of 12x128 and its three calls 12.55 -> 11.13, the two products of an MLP of 128 tokens 15.05 ->
-// 14.59.
+// holds.  They are a fifth shorter for it, without the index maps and K slices that it excludes.  Microseconds of the
+// same call with the long and the short form, queued, medians of nine in turn: 256^3 fp32 4.66 (4.57 to 5.04) and 4.13 (3.99 to
+// 4.42), fp16 128x3072x768 5.79 and 5.51, 128x768x3072 7.08 and 6.82, 8x768x3072 5.92 and 5.52.
 struct PlainParams {
   const void* A;
   const void* B;
