@@ -700,10 +700,14 @@ constexpr long long max_workgroups(int threads) { return 0xffffffffLL / threads;
 // results the pair takes 0.94 to 1.07 of the time (1024 x 50257 61.4 and 65.3 us, 1024 x 16384 fp16 19.1 and 18.1).  In place the
 // lines are in the L2s already, so the hint gains nothing and drives them out: with the sum, 1024 x 50257 56.6 us without, 62.3
 // with; attention's chain of three calls, whose softmax works in place, 42 entries of 768 x 768 44.0 and 48.5 us, one of 6144 x
-// 6144 66.6 and 76.1.
+// 6144 66.6 and 76.1.  That ends with what the caches hold: rows of more than 128 KB, one to a compute unit, have left the L2s
+// by the time they are stored (rotating buffers, without and with: 502 x 48000 fp32 46.6 and 42.4 us, 749 x 128000 fp16 87.1 and 80.9,
+// with the sum 0.98 to 1.03 of the time; 1476 x 65000 with the sum 100.9 and 111.2), and outputs of 256 MiB the last level
+// (2129 x 48000 fp32 159.4 and 134.7, with the sum 246 and 219; 4068 x 50257 fp16 150.0 and 128.5; shorter rows 0.99 to 1.03).
 template <typename T>
 bool streams_output(const RowParams& p) {
-  return p.x != p.y && p.rows * (long long)p.cols >= (4LL << 20) / (long long)sizeof(T);
+  const long long row = (long long)p.cols * (long long)sizeof(T), bytes = p.rows * row;
+  return bytes >= (p.x != p.y || row > 128 << 10 ? 4LL << 20 : 256LL << 20);
 }
 
 // A softmax whose wavefronts would work on more than eight rows of one chunk a lane in turn: with the short butterflies they go in

@@ -461,6 +461,20 @@ def test_softmax_of_rows_that_wavefronts_take_in_turn(dtype, cols, lanes):
         assert not torch.isnan(y).any() and float((y.float().sum(1) - 1).abs().max()) < 2e-2
 
 
+# outputs of 256 MiB, from where on those in place have the streaming hint as well: rows of a wavefront and of a workgroup
+@pytest.mark.parametrize("dtype,rows,cols", [("f16", 450000, 300), ("f32", 68000, 1001), ("bf16", 2100, 65003)])
+def test_softmax_in_place_of_more_than_the_last_level_cache(dtype, rows, cols):
+    x = torch.randn((rows, cols), device="cuda", generator=torch.Generator(device="cuda").manual_seed(cols)).to(TORCH_DTYPE[dtype])
+    y = torch.empty_like(x)
+    hb.hidet_softmax_rows(x, y)
+    some = torch.arange(0, rows, rows // 40, device="cuda")
+    ref = red.softmax_rows(to_f64(x[some]))
+    hb.hidet_softmax_rows(x, x)
+    torch.cuda.synchronize()
+    assert torch.equal(x, y)
+    assert within_bound(oracle.rel_frobenius(to_f64(y[some]), ref), ref, dtype)
+
+
 @pytest.mark.parametrize("cols", [2049, 8200, 50257])
 def test_softmax_of_maxima_around_the_largest_scale(cols):
     """A running scale serves maxima below 2^16, the difference to the maximum those beyond: bf16 rows whose maximum is next to
