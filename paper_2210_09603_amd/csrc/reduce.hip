@@ -185,7 +185,7 @@ __device__ __forceinline__ void meet(float v, float& a, float& b) {
 }
 template <int L, bool MAX, bool CROSSBAR = false>
 __device__ __forceinline__ float over_lanes(float v) {
-  if constexpr (CROSSBAR) {  // (see rows_in_turn; lanes meet in the same order, so the sum has the same bits)
+  if constexpr (CROSSBAR) {  // (see spreads_rows; lanes meet in the same order, so the sum has the same bits)
 #pragma unroll
     for (int o = 1; o < L; o <<= 1) {
       const float w = __shfl_xor(v, o, 64);
@@ -710,23 +710,25 @@ bool streams_output(const RowParams& p) {
   return bytes >= (p.x != p.y || row > 128 << 10 ? 4LL << 20 : 256LL << 20);
 }
 
-// A softmax whose wavefronts would work on more than eight rows of one chunk a lane in turn: with the short butterflies they go in
-// step, all of them read and then all of them write.  Rows that fill their lanes are spread out by the dispatcher, which gets a
-// workgroup for each few of them (attention's three calls on 192 entries of 512 x 512 93.9 us in turn, 91.8 this way; beside the
-// input 390625 x 128 fp16 35.9 and 32.9, 97656 x 256 fp32 35.5 and 33.0).  Others stay in turn, since a wavefront with fewer bytes is
-// worth less (130208 x 384 fp16 in place 36.8 us one by one, 35.2 in turn; 192 entries of 300 x 300 51.7 and 50.2), and combine their lanes
-// through the LDS crossbar, whose queue spreads them (166666 x 300 fp16 51.5 us with butterflies, 49.0 with the crossbar, 166666 x 150
-// fp32 43.4 and 40.7, attention on 339 of 384 x 384 105.0 and 103.6).  With fewer rows in turn neither pays: 23437 x 256 one by one 5.3
-// us, 4.9 in turn, 20000 x 150 fp32 through the crossbar 6.6, with butterflies 6.2.  Nor do they with more chunks a lane, or in
-// reductions, which write next to nothing.
-bool rows_in_turn(long long rows, int lanes, int chunks_per_lane) {
-  return chunks_per_lane == 1 && rows > 8LL * kMaxBlocks * 4 * (64 / lanes);
+// A softmax whose wavefronts would work on more than eight rows each in turn: with the short butterflies they go in step, all of
+// them read and then all of them write, and the lines that two rows share are written at different times.  A workgroup for each few
+// rows, spread out by the dispatcher, takes 0.7 to 1.0 of the time where its rows hold 2.5 KB or more (rotating buffers, beside the input,
+// in turn -> this way: 919803 x 57 fp16 66.3 -> 43.8 us, 409600 x 128 fp16 37.0 -> 34.2, 104857 x 500 fp16 47.0 -> 37.7, 322236 x 301
+// fp32 175.8 -> 133.0, 136533 x 384 fp16 39.9 -> 37.4; in place 39.2 -> 37.7, attention's three calls on 192 entries of 512 x 512
+// 93.9 -> 91.8; the worst 1.09, 1248304 x 42 fp16 in place and hot, 38.1 and 41.4).  With less the dispatcher decides
+// (4766254 x 11 fp16 130 and 155, 174762 x 300 51.1 and 54.8): these stay in turn and, 32 or more of them to a row, combine
+// their lanes through the LDS crossbar, whose queue spreads the wavefronts (646621 x 300 fp16 194.4 us with butterflies, 187.3 so,
+// 1426371 x 136 168.3 and 160.0; not 2586487 x 75 245 and 252, 12932437 x 15 497 and 515).
+// With fewer rows in turn neither pays: 23437 x 256 one by one 5.3 us, 4.9 in turn, 20000 x 150 fp32 through the crossbar 6.6,
+// with butterflies 6.2.  Nor do they in reductions, which write next to nothing.
+bool rows_in_turn(long long rows, int lanes) { return rows > 8LL * kMaxBlocks * 4 * (64 / lanes); }
+bool spreads_rows(long long rows, long long row_bytes, int lanes) {
+  return rows_in_turn(rows, lanes) && 4 * (64 / lanes) * row_bytes >= 2560;
 }
 // Workgroups of a launch whose wavefronts share a row between `lanes` lanes.
-long long wavefront_blocks(bool softmax, long long rows, bool full, int lanes, int chunks_per_lane) {
+long long wavefront_blocks(bool softmax, long long rows, long long row_bytes, int lanes) {
   const long long per_block = 4 * (64 / lanes), wanted = rows / per_block + (rows % per_block != 0);
-  const bool spread = softmax && full && rows_in_turn(rows, lanes, chunks_per_lane);
-  return std::min(wanted, spread ? max_workgroups(256) : (long long)kMaxBlocks);
+  return std::min(wanted, softmax && spreads_rows(rows, row_bytes, lanes) ? max_workgroups(256) : (long long)kMaxBlocks);
 }
 
 template <typename T, int L, int R, bool SOFTMAX, bool STREAM, bool CROSSBAR>
@@ -742,14 +744,18 @@ hipError_t launch_wavefront_as(const RowParams& p, dim3 grid, hipStream_t stream
   return hipGetLastError();
 }
 
+// (The streaming hint writes lines that two rows share in parts.  Short ragged rows have many of them: beside the input, 112347 x 57
+// fp16 13.5 us without, 15.8 with, 149796 x 42 fp32 13.6 and 14.6, 103991 x 121 fp16 13.1 and 13.0, 83886 x 150 18.1 and 17.6.  Ragged
+// rows in turn write the parts at different times: 646621 x 300 fp16 187.3 and 193.4, 1293243 x 75 fp32 192.1 and 210.2.)
 template <typename T, int L, int R, bool SOFTMAX>
 hipError_t launch_wavefront(const RowParams& p, hipStream_t stream) {
-  const bool full = p.cols == L * Chunk<T>::VEC;
-  const dim3 grid((unsigned)wavefront_blocks(SOFTMAX, p.rows, full, L, R));
+  const long long row_bytes = (long long)p.cols * (long long)sizeof(T);
+  const dim3 grid((unsigned)wavefront_blocks(SOFTMAX, p.rows, row_bytes, L));
   if constexpr (SOFTMAX && R > 0) {
-    const bool streams = streams_output<T>(p);
-    if constexpr (R == 1)
-      if (!full && rows_in_turn(p.rows, L, R))
+    const bool in_turn = rows_in_turn(p.rows, L) && !spreads_rows(p.rows, row_bytes, L);
+    const bool streams = streams_output<T>(p) && (row_bytes % 16 == 0 || (row_bytes >= 256 && !in_turn));
+    if constexpr (R == 1 && L >= 32)  // (more chunks a lane are more than 2.5 KB)
+      if (in_turn)
         return streams ? launch_wavefront_as<T, L, R, true, true, true>(p, grid, stream)
                        : launch_wavefront_as<T, L, R, true, false, true>(p, grid, stream);
     if (streams) return launch_wavefront_as<T, L, R, true, true, false>(p, grid, stream);
@@ -920,7 +926,7 @@ hidet_status_t hidet_row_schedule(int32_t dtype, int32_t softmax, int64_t rows, 
   const long long limit = c.form == ROW_PER_WORKGROUP ? max_workgroups(c.threads) : kMaxBlocks;
   const long long wanted = (rows - 1) / rows_per_workgroup + 1;
   out->workgroups = c.form == ROWS_PER_WAVEFRONT
-                        ? wavefront_blocks(softmax != 0, rows, cols * elem_bytes(dtype) == c.threads * 16, c.threads, c.chunks)
+                        ? wavefront_blocks(softmax != 0, rows, cols * elem_bytes(dtype), c.threads)
                         : std::min(wanted, limit);
   out->launches = c.form == ROW_PER_WORKGROUP ? (wanted - 1) / limit + 1 : 1;
   return HIDET_OK;

@@ -438,16 +438,19 @@ def test_softmax_of_large_outputs_beside_and_in_place_of_the_input(dtype, rows, 
         assert bool((dst == 7.0).all())
 
 
-@pytest.mark.parametrize("dtype,cols,lanes", [("f16", 8, 8), ("f32", 30, 8), ("bf16", 100, 16), ("f16", 136, 32), ("f16", 300, 64), ("f32", 256, 64),
-                                              ("f16", 128, 16), ("bf16", 392, 64)])
-def test_softmax_of_rows_that_wavefronts_take_in_turn(dtype, cols, lanes):
-    """More than eight rows (of one chunk a lane) a wavefront: those that fill their lanes get more workgroups, the lanes of others meet
+# (2.5 KB to a workgroup: 32 rows of 80 bytes, 16 of 160, 8 of 320, 4 of 640)
+@pytest.mark.parametrize("dtype,cols,lanes,spread", [("f16", 8, 8, False), ("f16", 39, 8, False), ("bf16", 40, 8, True), ("f32", 30, 8, True),
+                                                     ("bf16", 79, 16, False), ("bf16", 100, 16, True), ("f16", 128, 16, True), ("f16", 136, 32, False),
+                                                     ("f32", 80, 32, True), ("f16", 300, 64, False), ("f16", 319, 64, False), ("f32", 160, 64, True),
+                                                     ("f32", 256, 64, True), ("bf16", 392, 64, True), ("f16", 601, 64, True), ("f32", 700, 64, True)])
+def test_softmax_of_rows_that_wavefronts_take_in_turn(dtype, cols, lanes, spread):
+    """More than eight rows a wavefront: those of 2.5 KB to a workgroup get more workgroups, the lanes of others (32 and more to a row) meet
     another way, in the same order.  The same bits as from two calls of half as many rows, which are on the other side of the line, beside and
     in place of the input."""
     limit = 8 * 2048 * 256 // lanes
-    for rows, softmax, blocks in ((limit, 1, 2048), (limit + 1, 1, 8 * 2048 + 1 if cols * (4 if dtype == "f32" else 2) == 16 * lanes else 2048), (limit + 1, 0, 2048)):
+    for rows, softmax, blocks in ((limit, 1, 2048), (limit + 1, 1, 8 * 2048 + 1 if spread else 2048), (limit + 1, 0, 2048)):
         s = hb.hidet_row_schedule({"f16": hb.HIDET_F16, "bf16": hb.HIDET_BF16, "f32": hb.HIDET_F32}[dtype], softmax, rows, cols)
-        assert (s["form"], s["threads_per_row"], s["chunks_per_thread"], s["workgroups"]) == (0, lanes, 1, blocks), (rows, softmax, s)
+        assert (s["form"], s["threads_per_row"], s["workgroups"]) == (0, lanes, blocks), (rows, softmax, s)
     for rows in (limit, limit + 3):
         x = torch.randn((rows, cols), device="cuda", generator=torch.Generator(device="cuda").manual_seed(rows)).mul_(3).to(TORCH_DTYPE[dtype])
         y, halves = torch.empty_like(x), torch.empty_like(x)
