@@ -296,7 +296,7 @@ __global__ void __launch_bounds__(256) rows_in_registers_kernel(const RowParams 
         for (int r = 0; r < R; ++r)
 #pragma unroll
           for (int e = 0; e < VEC; ++e) s += v[r][e];
-        s = group_sum<L>(s);
+        s = group_sum<L, CROSSBAR>(s);
         out = p.op == HIDET_REDUCE_MEAN ? s / (float)p.cols : s;
       }
       if (sub == 0) write_scalar(p, row, out, Tag<T>::value);
@@ -720,7 +720,7 @@ bool streams_output(const RowParams& p) {
 // their lanes through the LDS crossbar, whose queue spreads the wavefronts (646621 x 300 fp16 194.4 us with butterflies, 187.3 so,
 // 1426371 x 136 168.3 and 160.0; not 2586487 x 75 245 and 252, 12932437 x 15 497 and 515).
 // With fewer rows in turn neither pays: 23437 x 256 one by one 5.3 us, 4.9 in turn, 20000 x 150 fp32 through the crossbar 6.6,
-// with butterflies 6.2.  Nor do they in reductions, which write next to nothing.
+// with butterflies 6.2.  Nor does a workgroup for each few rows in reductions, which write next to nothing.
 bool rows_in_turn(long long rows, int lanes) { return rows > 8LL * kMaxBlocks * 4 * (64 / lanes); }
 bool spreads_rows(long long rows, long long row_bytes, int lanes) {
   return rows_in_turn(rows, lanes) && 4 * (64 / lanes) * row_bytes >= 2560;
@@ -759,6 +759,15 @@ hipError_t launch_wavefront(const RowParams& p, hipStream_t stream) {
         return streams ? launch_wavefront_as<T, L, R, true, true, true>(p, grid, stream)
                        : launch_wavefront_as<T, L, R, true, false, true>(p, grid, stream);
     if (streams) return launch_wavefront_as<T, L, R, true, true, false>(p, grid, stream);
+  }
+  // Reductions of ragged 16-bit rows of up to four chunks have more vector instructions than any for a byte: in turn, their lanes
+  // meet through the LDS crossbar, beside them (7149381 x 11 fp16 sums 101 us with butterflies, 90 so, 2097152 x 17 31.4 and 28.5, 2536877
+  // x 31 36.0 and 34.4; 2383127 x 33 25.9 and 29.1, 279620 x 15, not in turn, 5.5 and 6.4; whole rows 1.1 to 1.2 of the time, fp32 too).
+  if constexpr (!SOFTMAX && R == 1 && L == 8 && sizeof(T) == 2) {
+    if (row_bytes % 16 != 0 && row_bytes < 64 && rows_in_turn(p.rows, L)) {
+      hipLaunchKernelGGL((rows_in_registers_kernel<T, L, R, RAGGED_END, false, false, true>), grid, dim3(256), 0, stream, p);
+      return hipGetLastError();
+    }
   }
   return launch_wavefront_as<T, L, R, SOFTMAX, false, false>(p, grid, stream);
 }

@@ -464,6 +464,25 @@ def test_softmax_of_rows_that_wavefronts_take_in_turn(dtype, cols, lanes, spread
         assert not torch.isnan(y).any() and float((y.float().sum(1) - 1).abs().max()) < 2e-2
 
 
+@pytest.mark.parametrize("dtype,cols", [("f16", 9), ("bf16", 15), ("f16", 17), ("bf16", 31), ("f16", 33), ("f16", 16), ("f32", 11)])
+def test_reductions_of_short_rows_that_wavefronts_take_in_turn(dtype, cols):
+    """On both sides of eight rows a wavefront, as softmax above: the same bits as from two calls of half as many rows."""
+    limit = 8 * 2048 * 32
+    for rows in (limit, limit + 3):
+        x = torch.randn((rows, cols), device="cuda", generator=torch.Generator(device="cuda").manual_seed(rows)).to(TORCH_DTYPE[dtype])
+        for op in (hb.HIDET_REDUCE_SUM, hb.HIDET_REDUCE_MAX, hb.HIDET_REDUCE_MEAN):
+            y, halves = torch.full((rows,), float("nan"), device="cuda"), torch.empty((rows,), device="cuda")
+            hb.hidet_reduce_rows(x, y, op=op)
+            for part in (slice(0, rows // 2), slice(rows // 2, rows)):
+                hb.hidet_reduce_rows(x[part], halves[part], op=op)
+            d = x.double()
+            ref = d.amax(1) if op == hb.HIDET_REDUCE_MAX else d.sum(1) if op == hb.HIDET_REDUCE_SUM else d.mean(1)
+            # (fp32 sums of `cols` terms, in any order: each of fewer than `cols` additions rounds by 2^-24 of at most the sum of magnitudes)
+            bound = cols * 2.0 ** -23 * d.abs().sum(1)
+            torch.cuda.synchronize()
+            assert torch.equal(y, halves) and bool(((y.double() - ref).abs() <= bound).all()), (rows, op)
+
+
 # outputs of 256 MiB, from where on those in place have the streaming hint as well: rows of a wavefront and of a workgroup
 @pytest.mark.parametrize("dtype,rows,cols", [("f16", 450000, 300), ("f32", 68000, 1001), ("bf16", 2100, 65003)])
 def test_softmax_in_place_of_more_than_the_last_level_cache(dtype, rows, cols):
