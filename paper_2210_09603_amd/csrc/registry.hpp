@@ -94,7 +94,8 @@ hipError_t launch_kernel(const GemmParams& p, hipStream_t stream) {
         const bool fit = direct_loads_fit<Cfg>(p);
         const bool even = (((unsigned long long)p.A / 2 | (unsigned long long)p.lda | (unsigned long long)p.strideA) & 1) == 0;
         const bool few_k = (p.k_slices > 1 ? p.k_slice_len : p.K) <= S::MAX_K;
-        if (p.N >= 2 && (even ? !fit || few_k : !fit && few_k)) {
+        const bool narrow = (p.k_slices > 1 ? p.k_slice_len : p.K) > 768LL * p.N - 512;
+        if (p.N >= 2 && (even ? !fit || few_k : !fit && few_k && !narrow)) {
           if (PlainParams c; plain_params(p, c))
             hipLaunchKernelGGL((gemm_kernel_waves_direct<T, TO, Cfg::BM, Cfg::BN, PlainParams>), grid, dim3(S::NT), 0, stream, c);
           else

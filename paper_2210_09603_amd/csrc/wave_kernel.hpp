@@ -551,8 +551,10 @@ __global__ void __launch_bounds__(S::NT) gemm_kernel_waves_f32(const Params para
 // 3072: 0.74 to 1.04; 80x45x796 4.16 -> 3.60 us; longer ones 1.02 to 1.10), 16x32 ones 0.90 up to K = 1024 (9 products; 7 longer
 // ones 0.9 to 1.24).  Where the direct loads do not fit, as with N < 8, the general schedule is what is left: 0.42 to 0.79 of its
 // time up to K = 3072 (23 products; 14x7x1264 7.8 -> 3.6 us) on any rows, 0.33 to 0.49 beyond on even ones (5x5x3768 15.5 -> 5.1),
-// but 1.04 to 1.25 beyond on odd ones, where a load of 16 bytes into registers is broken up.  Left to the loads into LDS: odd rows
-// of A (0.88 to 1.58), operands that both lie along K (the same), and whole chunks, whose lines they share better (2 to 8 %).
+// but 1.04 to 1.25 beyond on odd ones, where a load of 16 bytes into registers is broken up.  The fewer columns, the less the
+// general schedule has to do, and the earlier that is: on odd rows 1.02 to 1.09 for two columns at K = 1281 to 1409 and 1.33 at 2945
+// (300x2x2945 9.2 and 12.3 us), 0.92 to 1.03 for three up to 1793 and 1.19 at 2945, 0.82 to 1.01 for four.  Left to the loads
+// into LDS: odd rows of A (0.88 to 1.58), operands that both lie along K (the same), and whole chunks, whose lines they share better (2 to 8 %).
 template <int BM, int BN>
 struct WaveDirect {
   static constexpr int NW = 16, NT = NW * 64, STEP = 32, D = 2;
